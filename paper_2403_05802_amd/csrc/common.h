@@ -231,6 +231,9 @@ struct SortOut {
   // predecessor's, i.e. the nodes that start in the tile.  Only the finish inside LDS counts them (it has the sorted
   // keys at hand): *node_counted says whether it did.
   uint32_t *node_count = nullptr; bool *node_counted = nullptr;
+  // The list comes in ascending order of its minor index (mode 0, unpacked output): a stable sort by the major index
+  // alone gives the (major, minor) order.
+  bool minor_sorted = false;
 };
 constexpr int NODE_TILE_SHIFT = 11, NODE_TILE = 1 << NODE_TILE_SHIFT;
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,

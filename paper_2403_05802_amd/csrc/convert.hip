@@ -500,7 +500,7 @@ Flags *new_flags(Env &env) {
 }
 
 us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const us_format_desc &desc,
-                            us_formatted **out) {
+                            us_formatted **out, bool minor_sorted) {
   const bool by_sort = plan.pattern == P_COO || plan.pattern == P_CSR || plan.pattern == P_DCSR ||
                        plan.pattern == P_ELL || plan.pattern == P_CISR;
   const bool rowcol = by_sort && plan.pattern != P_CISR;   // built below from the (major, minor) order
@@ -542,6 +542,7 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
   int32_t *major = nullptr, *minor = nullptr;
   float *val = nullptr;
   SortOut so{};
+  so.minor_sorted = minor_sorted;
   so.late = [&](SortOut &o) {
     if (late_res) env.reserve_out(late_res);
     major = keep_major ? env.owned<int32_t>(n) : env.temp<int32_t>(n);
@@ -720,8 +721,12 @@ us_status convert_formatted_impl(Env &env, const us_formatted &src, const us_for
     US_LAUNCH(env, "expand_rows", 4.0 * ns + 4.0 * src.nmajor, expand_rows_kernel, src.mp_tiles, 256, sr.ptr, sr.row_ids,
               (const int32_t *)src.mp_split, src.nmajor, ns, r);
     us_coo coo{src.nrows, src.ncols, ns, src.swapped ? sr.idx : r, src.swapped ? r : sr.idx, src.val};   // CSC: the major index is d1
+    // A transposing conversion (rows to columns or back): the entries of the source are in order of its major index,
+    // which ptr alone decides whatever the order inside a row, and that is the minor index of the target: the sort needs
+    // the digits of the target's major index only.  (CISR-plus deals its rows out to partitions: no such order.)
+    const bool transposes = src.pattern != P_CISR && (src.swapped ? 1 : 0) != (plan.swapped ? 1 : 0);
     us_status st = env.status;
-    if (st == US_OK) st = convert_with_plan(env, coo, plan, desc, out);
+    if (st == US_OK) st = convert_with_plan(env, coo, plan, desc, out, transposes);
     env.sync();
     if (st == US_OK && !env.ok()) st = env.status;
     if (st != US_OK && *out) { free_formatted(env, *out); *out = nullptr; }

@@ -74,3 +74,24 @@ def test_table5_cases_on_scaled_workloads(ctx):
     assert_same_layout(csb, O.convert(b.nrows, b.ncols, b.row, b.col, b.val, O.CSB(512, 256)), "COO->CSB")
     diav2 = B.us_convert_formatted(ctx, csb, us_desc_of(O.DIA_VARIANT()))       # CSB -> DIA variant
     assert_same_layout(diav2, O.convert(b.nrows, b.ncols, b.row, b.col, b.val, O.DIA_VARIANT()), "CSB->DIA variant")
+
+
+@pytest.mark.parametrize("nr,nc,nnz", [(1, 70, 40), (70, 1, 40), (300, 257, 4095), (513, 255, 4097), (5000, 65537, 9001),
+                                       (65536, 300, 300_000), (3, 20_000_001, 50_000)])
+@pytest.mark.parametrize("sname", ["CSR", "CSC", "DCSR", "DCSC"])
+def test_transposing_conversions_at_the_edges(ctx, sname, nr, nc, nnz):
+    """Row-major to column-major and back, where the sort takes the digits of the target's major index alone: one to three
+    digits, a single row or column, lists of one tile (4096 entries) and of several, rows left empty."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import assert_same_layout, dev, us_desc_of
+    rng = np.random.default_rng(nr + nc + nnz)
+    key = rng.permutation(np.unique(rng.integers(0, nr * nc, nnz)))
+    r, c = (key // nc).astype(np.int32), (key % nc).astype(np.int32)
+    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
+    g = B.us_convert(ctx, nr, nc, dev(r), dev(c), dev(v), us_desc_of(getattr(O, sname)()))
+    targets = [O.CSC(), O.DCSC()] if sname.endswith("SR") else [O.CSR(), O.DCSR(), O.COO()]
+    for t in targets:
+        out = B.us_convert_formatted(ctx, g, us_desc_of(t))
+        assert_same_layout(out, O.convert(nr, nc, r, c, v, t), f"{sname} -> {t}")
+        out.free()
+    g.free()

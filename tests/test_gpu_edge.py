@@ -345,3 +345,28 @@ def test_spmm_with_row_strides(ctx):
             else:
                 assert_product(got[:, :N], ref, S, nt, f"strided spmm {d}")
         g.free()
+
+
+@pytest.mark.parametrize("N", [1, 63, 130, 260])
+@pytest.mark.parametrize("ld_extra", [0, 4])
+def test_csr_spmm_stores_every_row_of_an_uninitialised_result(ctx, N, ld_extra):
+    """A plain product neither clears nor reads Y: rows without entries (at both ends, in runs across the eight rows of a
+    wavefront), rows inside one chunk of entries and rows cut by several chunks all have to be stored; what lies past the
+    N columns of a row stays untouched."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import assert_product, dev, host, row_terms, us_desc_of
+    rng = np.random.default_rng(N)
+    n, nc = 203, 5000
+    length = rng.integers(0, 4, n)
+    length[:11] = 0; length[40:73] = 0; length[-9:] = 0
+    length[20], length[100] = 3000, 64
+    r = np.repeat(np.arange(n), length).astype(np.int32)
+    c = np.concatenate([rng.choice(nc, k, replace=False) for k in length]).astype(np.int32)
+    v = rng.uniform(-1, 1, r.size).astype(np.float32)
+    g = B.us_convert(ctx, n, nc, dev(r), dev(c), dev(v), us_desc_of(O.CSR()))
+    X = rng.uniform(-1, 1, (nc, N)).astype(np.float32)
+    whole = torch.full((n, N + ld_extra), float("nan"), device="cuda")
+    B.us_spmm(ctx, g, dev(X), whole[:, :N])
+    assert_product(host(whole[:, :N].contiguous()), O.spmm_coo(n, nc, r, c, v, X),
+                   O.spmm_coo(n, nc, r, c, np.abs(v), np.abs(X)), row_terms(n, r)[:, None], f"N={N} ld+{ld_extra}")
+    assert torch.isnan(whole[:, N:]).all()

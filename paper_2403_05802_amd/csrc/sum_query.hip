@@ -21,7 +21,9 @@ __device__ __forceinline__ uint32_t group_bin(int gkind, uint32_t r, uint32_t c,
 // cold and keeps the hot ones, so a hot counter gets one HBM atomic per workgroup (at most
 // ONE_COUNTER_GRID of them), not one per tile.  Freeing a slot may cut a probe chain; the bin then
 // simply takes a second slot, and counts add up all the same.
-constexpr int GH_T = 256, GH_IPT = 16, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8;
+// (A launch of at most ONE_COUNTER_GRID workgroups fills the chip only if these are large: 14.8 M entries on seven
+// diagonals took 66 us with 256 threads x 16 entries, 54 with 512 x 8, 44 with 1024 x 4.)
+constexpr int GH_T = 1024, GH_IPT = 4, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8;
 constexpr uint32_t GH_HOT = 64;
 
 __global__ __launch_bounds__(GH_T) void group_hist_kernel(const int32_t *row, const int32_t *col, int64_t n,

@@ -84,6 +84,7 @@ struct PassArgs {
   uint32_t *chunk;                 // [RS_BINS][nchunks] per-chunk digit counts, then prefixes over the chunks
   uint32_t *dtotal;                // [RS_BINS] digit totals of the whole input
   uint32_t nchunks;
+  int small;                       // at most RS_SMALL tiles: hist holds plain counts, chunk and dtotal are not there
   KeySpec ks;
   int hist_minor_only;             // IN_COO: this pass's digit lies inside the minor index of a (major, minor) key
   int coo_vec;                     // IN_COO: row, col and val are 16-byte aligned (full tiles are read four entries a load)
@@ -259,30 +260,10 @@ __global__ __launch_bounds__(256) void radix_scan_top_kernel(uint32_t *chunk, ui
   if (lane == 0) dtotal[d] = carry;
 }
 
-// Both scans in one workgroup for inputs of at most RS_SMALL tiles (one launch less per digit pass, which is
-// what a conversion of a few hundred thousand entries spends its time on): thread d holds digit d of every tile.
+// Lists of at most RS_SMALL tiles have no scan kernels: every workgroup of the scatter adds up the per-tile counts (at
+// most 64 KB, out of L2) itself, one launch less per digit pass, which is what a conversion of a few hundred thousand
+// entries spends its time on.
 constexpr int RS_SMALL = 64;
-__global__ __launch_bounds__(RS_BINS) void radix_scan_small_kernel(uint32_t *hist, uint32_t *chunk, uint32_t *dtotal,
-                                                                  uint32_t nblocks, uint32_t nchunks) {
-  const uint32_t d = threadIdx.x;
-  uint32_t v[RS_SMALL];
-#pragma unroll
-  for (int t = 0; t < RS_SMALL; ++t) v[t] = (uint32_t)t < nblocks ? hist[(size_t)t * RS_BINS + d] : 0u;
-  uint32_t before_chunk = 0, run = 0;
-#pragma unroll
-  for (int t = 0; t < RS_SMALL; ++t) {
-    if ((uint32_t)t < nblocks) {
-      if (t % RS_CHUNK == 0) {
-        before_chunk += run;
-        run = 0;
-        chunk[(size_t)d * nchunks + t / RS_CHUNK] = before_chunk;
-      }
-      hist[(size_t)t * RS_BINS + d] = run;
-      run += v[t];
-    }
-  }
-  dtotal[d] = before_chunk + run;
-}
 
 template <int IN, int OUT>
 __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
@@ -292,6 +273,8 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
   __shared__ uint32_t s_wave[RS_T / 64 + 1];
   __shared__ Key s_key[RS_TILE];
   uint32_t *s_val = reinterpret_cast<uint32_t *>(s_key);
+  // (a.small: the sums over the tiles, in the place of the keys until these are written, behind two barriers)
+  uint32_t (*s_small)[2][RS_BINS] = reinterpret_cast<uint32_t (*)[2][RS_BINS]>(s_key);
 
   const int lane = lane_id(), w = wave_id();
   const uint32_t nbins = a.mask + 1;
@@ -334,6 +317,18 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
     }
   }
   if (IN == IN_COO && bad) a.flags->index_range = 1;
+  if (a.small) {   // entries of every digit in all tiles and in the tiles before this one: half of the tiles per thread
+    static_assert(RS_T == 2 * RS_BINS, "two threads per digit");
+    const uint32_t d = threadIdx.x & (RS_BINS - 1), half = threadIdx.x / RS_BINS;
+    uint32_t total = 0, before = 0;
+#pragma unroll 4
+    for (uint32_t t = half; t < a.nblocks; t += 2) {
+      const uint32_t c = a.hist[(size_t)t * RS_BINS + d];
+      total += c;
+      before += t < tile ? c : 0u;
+    }
+    s_small[half][0][d] = total; s_small[half][1][d] = before;
+  }
   __syncthreads();
 
   // stable rank of every item among the items of its wave with the same digit.
@@ -381,12 +376,15 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
   }
   uint32_t dummy;
   const uint32_t start = block_exclusive_sum<RS_T>(tile_total, s_wave, &dummy);
-  const uint32_t digit_start =
-      block_exclusive_sum<RS_T>(threadIdx.x < RS_BINS ? a.dtotal[threadIdx.x] : 0u, s_wave, &dummy);
+  uint32_t digit_total = 0;
+  if (threadIdx.x < RS_BINS) digit_total = a.small ? s_small[0][0][threadIdx.x] + s_small[1][0][threadIdx.x] : a.dtotal[threadIdx.x];
+  const uint32_t digit_start = block_exclusive_sum<RS_T>(digit_total, s_wave, &dummy);
   if (threadIdx.x < nbins) {
     s_start[threadIdx.x] = start;
-    s_goff[threadIdx.x] = digit_start + a.chunk[(size_t)threadIdx.x * a.nchunks + tile / RS_CHUNK] +
-                           a.hist[(size_t)tile * RS_BINS + threadIdx.x] - start;
+    const uint32_t before = a.small ? s_small[0][1][threadIdx.x] + s_small[1][1][threadIdx.x]
+                                    : a.chunk[(size_t)threadIdx.x * a.nchunks + tile / RS_CHUNK] +
+                                          a.hist[(size_t)tile * RS_BINS + threadIdx.x];
+    s_goff[threadIdx.x] = digit_start + before - start;
   }
   __syncthreads();
 
@@ -1069,7 +1067,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
     a.next_shift = last_pass ? 0 : shifts[p + 1];
     a.next_mask = last_pass ? 0u : (1u << widths[p + 1]) - 1u;
     a.tiles_per_xcd = ceil_div<uint32_t>(nblocks, 8u);
-    a.hist = hist; a.chunk = chunk; a.dtotal = dtotal; a.nchunks = nchunks; a.ks = ks; a.flags = flags;
+    a.hist = hist; a.chunk = chunk; a.dtotal = dtotal; a.nchunks = nchunks; a.small = nblocks <= (uint32_t)RS_SMALL; a.ks = ks; a.flags = flags;
     a.hist_minor_only = first && in_mode == IN_COO && ks.mode == 0 && shifts[p] + widths[p] <= ks.b_bits && ks.b_bits <= 32;
     a.coo_vec = first && in_mode == IN_COO && !major_only &&   // (major_only: the order of the list counts)
                 ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
@@ -1083,10 +1081,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
     if (in == IN_COO) launch_hist<IN_COO>(env, a, (a.hist_minor_only || a.hist_major_shift >= 0 ? 4.0 : 8.0) * nnz);
     else if (in == IN_KEY32) launch_hist<IN_KEY32>(env, a, 4.0 * nnz);
     else launch_hist<IN_SPLIT>(env, a, 1.0 * nnz);
-    if (nblocks <= (uint32_t)RS_SMALL) {
-      US_LAUNCH(env, "radix_scan_small", 8.0 * RS_BINS * nblocks, radix_scan_small_kernel, 1, RS_BINS, hist, chunk, dtotal,
-                nblocks, nchunks);
-    } else {
+    if (!a.small) {
       US_LAUNCH(env, "radix_scan_chunk", 8.0 * RS_BINS * nblocks, radix_scan_chunk_kernel, nchunks, RS_BINS, hist, chunk,
                 nblocks);
       US_LAUNCH(env, "radix_scan_top", 8.0 * RS_BINS * nchunks, radix_scan_top_kernel, RS_BINS / 4, 256, chunk, nchunks,

@@ -760,21 +760,53 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(float *Y, int64_t nrows,
   Y[i * ldy + (e - i * N)] = 0.f;
 }
 
-// The rows of Y that a plain product over CSR leaves untouched: those without entries.  A wavefront looks at eight rows
-// (a block of rows that are all empty is then still written by many wavefronts).  Every other row is stored once, by the
-// chunk it lies in or by the fix-up, so Y is neither cleared nor read: 262,144 rows of 1000 columns took 0.14 ms to
-// clear and as long again to read back (3.67 -> 3.30 ms for 5.2 M entries at N = 1000).
-__global__ __launch_bounds__(256) void zero_empty_rows_kernel(const int32_t *ptr, int64_t nrows, float *Y, int64_t N, int64_t ldy) {
-  const int lane = lane_id();
-  const int64_t i0 = ((int64_t)blockIdx.x * 4 + wave_id()) * 8;
-  const int64_t i = i0 + lane;
-  uint64_t empty = __ballot(lane < 8 && i < nrows && ptr[i + 1] == ptr[i]);
-  while (empty) {
-    const int r = __ffsll((unsigned long long)empty) - 1;
-    empty &= empty - 1;
-    float *yp = Y + (i0 + r) * ldy;
-    for (int64_t c = lane; c < N; c += 64) yp[c] = 0.f;
+// The rows of Y that a plain product over CSR leaves untouched: those without entries.  Every other row is stored once, by
+// the chunk it lies in or by the fix-up, so Y is neither cleared nor read (262,144 rows of 1000 columns take 0.14 ms to
+// clear and as long again to read back).  A workgroup lists the empty ones of `rows` (at most 256) rows and its 256 threads
+// walk (listed row, column) pairs, so that a matrix that is mostly empty is cleared by whole wavefronts however few columns
+// it has; the columns are cut into pieces of ZE_COLS loads (blockIdx.y), so that a few very wide rows spread over the part.
+// The rows are walked with a stride: a grid of 2^32 threads or more is cut short without an error.
+// It is bound by the stores.  A whole plain product against the fill and the product that adds: 2 M rows, 147 k entries,
+// 1 / 16 / 64 columns 51 / 71 / 157 -> 45 / 55 / 137 us; 262,144 rows of 1000 columns, 20 k entries 253 -> 255; 8 rows of
+// 1 M columns 86 -> 82.  (A wavefront for eight rows, clearing one row after the other: 83 / 85 / 141, 262 and 3,364 us.)
+constexpr int ZE_COLS = 512, ZE_GRID = 1 << 20;
+template <int VEC>
+__global__ __launch_bounds__(256) void zero_empty_rows_kernel(const int32_t *ptr, int64_t nrows, int rows, float *Y, int64_t N,
+                                                             int64_t ldy) {
+  typedef typename VecT<VEC>::type V;
+  __shared__ int32_t s_row[256];
+  __shared__ uint32_t s_wave[256 / 64 + 1];
+  const int64_t c0 = (int64_t)blockIdx.y * ZE_COLS;
+  const uint32_t width = (uint32_t)min((int64_t)ZE_COLS, N / VEC - c0), t = threadIdx.x;
+  const uint32_t k_first = t / width, c_first = t - k_first * width, k_step = 256 / width, c_step = 256 - k_step * width;
+  for (int64_t i0 = (int64_t)blockIdx.x * rows; i0 < nrows; i0 += (int64_t)gridDim.x * rows) {
+    const int64_t i = i0 + t;
+    const bool empty = t < (uint32_t)rows && i < nrows && ptr[i + 1] == ptr[i];
+    uint32_t n;
+    const uint32_t at = block_exclusive_sum<256>(empty ? 1u : 0u, s_wave, &n);
+    if (empty) s_row[at] = (int32_t)t;
+    __syncthreads();
+    for (uint32_t k = k_first, c = c_first; k < n;) {
+      *reinterpret_cast<V *>(Y + (i0 + s_row[k]) * ldy + (c0 + c) * VEC) = V(0.f);
+      k += k_step; c += c_step;
+      if (c >= width) { c -= width; ++k; }
+    }
+    __syncthreads();   // the list is free for the next rows
   }
+}
+
+static void zero_empty_rows(Env &env, const int32_t *ptr, int64_t nrows, float *Y, int64_t N, int64_t ldy) {
+  if (!env.ok()) return;
+  LaunchScope ls(env, "zero_empty_rows", 4.0 * nrows);
+  const bool by4 = (uintptr_t)Y % 16 == 0 && N % 4 == 0 && ldy % 4 == 0;
+  const int64_t width = by4 ? N / 4 : N;
+  // as many rows as make some 8,000 stores, 32 at least: enough workgroups where every row is empty, one pointer per thread
+  // where rows are short
+  const int rows = width <= 32 ? 256 : (width <= 128 ? 64 : 32);
+  const dim3 grid((unsigned)min(ceil_div<int64_t>(nrows, rows), (int64_t)ZE_GRID), (unsigned)ceil_div<int64_t>(width, ZE_COLS));
+  if (by4) hipLaunchKernelGGL(zero_empty_rows_kernel<4>, grid, dim3(256), 0, env.stream, ptr, nrows, rows, Y, N, ldy);
+  else hipLaunchKernelGGL(zero_empty_rows_kernel<1>, grid, dim3(256), 0, env.stream, ptr, nrows, rows, Y, N, ldy);
+  env.check(hipGetLastError());
 }
 
 static void zero_rows(Env &env, float *Y, int64_t nrows, int64_t N, int64_t ldy) {
@@ -915,9 +947,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       }
       // every row has its pointer: clear the rows without entries only (a list of stored rows does not say which these are)
       const bool store = !accumulate && !sr.row_ids && A.nnz > 0;
-      if (store)
-        US_LAUNCH(env, "zero_empty_rows", 4.0 * A.nrows, zero_empty_rows_kernel, ceil_div<int64_t>(A.nrows, 32), 256, sr.ptr,
-                  A.nrows, Y, N, ldy);
+      if (store) zero_empty_rows(env, sr.ptr, A.nrows, Y, N, ldy);
       else if (!accumulate) zero_rows(env, Y, A.nrows, N, ldy);
       if (A.nnz > 0) {
         RowSrc rs{nullptr, sr.ptr, sr.row_ids, A.nmajor};

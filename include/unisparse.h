@@ -65,7 +65,8 @@ typedef struct us_ctx {
   void *profile;    /* us_profile* or NULL: per-kernel HIP-event timing (see us_profile_*) */
   /* How the Sort step (Figure 8) of the conversions made through this context finishes.
    *   US_SORT_FINISH_AUTO (0, what a zeroed us_ctx gives): by the target tuple -- in LDS for blocked tuples
-   *     (BCSR, BDIA and the blocked #sum queries), whole-array digit passes for (row, col) tuples;
+   *     (BCSR, BDIA and the blocked #sum queries) and for short lists, whole-array digit passes for other (row, col)
+   *     tuples; over the digits of the target's major index alone where us_convert_formatted turns rows into columns or back;
    *   US_SORT_FINISH_LDS: whole-array digit passes over the top key bits only, every bucket of equal top bits
    *     is then finished inside LDS;
    *   US_SORT_FINISH_PASSES: whole-array digit passes over all key bits.

@@ -992,10 +992,10 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   // does, and one digit pass + the finish is 8 launches where five digit passes are 10 (a row heavy enough to send
   // such a list back to the plain passes costs a tenth of a millisecond)
   const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && (ks.mode != 0 || nnz <= (int64_t)RS_SMALL * RS_TILE));
-  // ... and never for a list whose minor order is there already: the passes over the major digits are all it takes, three
-  // for up to 2^24 rows or columns (CSR to CSC, 200,003 rows, 3.1 M entries: 224 us with all five passes over 36-bit keys,
-  // 169 us with three over the 18 bits of the column; digit passes of 16 + 3 us on the GPU and three launches each)
-  const bool major_only = out.minor_sorted && in_mode == IN_COO && ks.mode == 0 && final_mode == OUT_UNPACK;
+  // ... and, unless the context asks for one of the two, neither for a list whose minor order is there already: the passes
+  // over the major digits are all it takes, three for up to 2^24 rows or columns (CSR to CSC, 200,003 rows, 3.1 M entries:
+  // 224 us with all five passes over 36-bit keys, 169 us with three over the 18 bits of the column)
+  const bool major_only = out.minor_sorted && env.lds_finish < 0 && in_mode == IN_COO && ks.mode == 0 && final_mode == OUT_UNPACK;
   if (major_only) {
     low_bits = ks.b_bits;
     high_bits = total_bits > low_bits ? total_bits - low_bits : 1;

@@ -988,10 +988,13 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   bool finish_local = false;
   // by default for blocked tuples only: block rows of FEM-like matrices fill evenly, while the rows of a
   // power-law graph do not (a heavy row's bucket needs extra splitting levels and the finish loses)
-  // ... and for lists of at most RS_SMALL tiles whatever the tuple: there every launch costs more than the work it
-  // does, and one digit pass + the finish is 8 launches where five digit passes are 10 (a row heavy enough to send
-  // such a list back to the plain passes costs a tenth of a millisecond)
-  const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && (ks.mode != 0 || nnz <= (int64_t)RS_SMALL * RS_TILE));
+  // ... and for lists of at most RS_SMALL tiles whose keys take more than three digit passes, whatever the tuple: there every
+  // launch costs more than the work it does, one digit pass + the finish is 9 launches, and a plain pass is two.  COO -> CSR,
+  // finish against passes, 4,200 to 262,000 entries: 24-bit keys 85-89 against 75-82 us with entries spread evenly, 87-106
+  // against 76-82 with rows of very different lengths; 30 bits 85-90 against 86-99 and 90-204 against 86-99 (rows heavy
+  // enough to send the list back to the plain passes); 36 bits 83-99 against 95-117; 40 bits 88-112 against 107-125.
+  const bool short_list = nnz <= (int64_t)RS_SMALL * RS_TILE && total_bits > 3 * RS_MAXBITS;
+  const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && (ks.mode != 0 || short_list));
   // ... and, unless the context asks for one of the two, neither for a list whose minor order is there already: the passes
   // over the major digits are all it takes, three for up to 2^24 rows or columns (CSR to CSC, 200,003 rows, 3.1 M entries:
   // 224 us with all five passes over 36-bit keys, 169 us with three over the 18 bits of the column)

@@ -204,3 +204,34 @@ def test_pieces_between_half_and_full_capacity_are_groups_of_their_own(ctx):
     r, c, v = shuffled(rng, r, c)
     check(ctx, nr, nc, r, c, v, [O.CSR(), O.DCSR(), O.COO(), O.BCSR(4), O.BDIA(2)])
     assert scatter_passes(ctx, nr, nc, r, c, v, O.CSR()) == 1
+
+
+@pytest.mark.parametrize("skewed", [False, True], ids=["even", "skewed"])
+@pytest.mark.parametrize("nr,nc,nnz,finish", [
+    (4096, 4096, 4095, False), (4096, 4096, 4096, False), (4096, 4096, 262144, False), (4096, 4096, 262145, False),
+    (4096, 4097, 4095, False), (4096, 4097, 4096, True), (4097, 4096, 40960, True), (4096, 4097, 262144, True),
+    (4096, 4097, 262145, False), (256, 256, 4096, False), (1 << 20, 16, 5000, False), (16, 1 << 20, 262144, False),
+    (1 << 20, 17, 5000, True), (1 << 24, 1, 5000, False)])
+def test_short_lists_take_the_finish_beyond_three_digits(ctx, nr, nc, nnz, finish, skewed):
+    """(row, col) lists of at most 64 tiles, by default: three digit passes or fewer do without the finish (24 bits and
+    below), more bits take it from 4096 entries on; longer lists never do."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import assert_same_layout, dev, us_desc_of
+    rng = np.random.default_rng(nr + nc + nnz)
+    lin = rng.choice(nr * nc, nnz, replace=False) if nr * nc < 1 << 25 else np.unique(rng.integers(0, nr * nc, nnz))
+    if skewed and nnz < nr * nc // 8:      # rows crowd towards the first ones
+        r = (nr * rng.random(4 * nnz) ** 3).astype(np.int64)
+        lin = np.unique(r * nc + rng.integers(0, nc, r.size))
+        lin = rng.choice(lin, min(nnz, lin.size), replace=False)
+    r, c, v = shuffled(rng, (lin // nc).astype(np.int32), (lin % nc).astype(np.int32))
+    for d in (O.CSR(), O.CSC(), O.DCSR(), O.COO()):
+        ctx.enable_profile(); ctx.profile_reset()
+        try:
+            g = B.us_convert(ctx, nr, nc, dev(r), dev(c), dev(v), us_desc_of(d))
+            launches = {e["kernel"]: e["launches"] for e in ctx.profile_report()}
+        finally:
+            ctx.disable_profile()
+        if lin.size == nnz:
+            assert ("local_sort" in launches) == finish, (d, launches)
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{nr}x{nc}, {r.size} entries -> {d}")
+        g.free()

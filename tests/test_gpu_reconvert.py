@@ -89,7 +89,7 @@ def test_transposing_conversions_at_the_edges(ctx, sname, nr, nc, nnz):
     r, c = (key // nc).astype(np.int32), (key % nc).astype(np.int32)
     v = rng.uniform(0.1, 1, r.size).astype(np.float32)
     g = B.us_convert(ctx, nr, nc, dev(r), dev(c), dev(v), us_desc_of(getattr(O, sname)()))
-    targets = [O.CSC(), O.DCSC()] if sname.endswith("SR") else [O.CSR(), O.DCSR(), O.COO()]
+    targets = [O.CSC(), O.DCSC()] if sname.endswith("SR") else [O.CSR(), O.DCSR(), O.COO(), O.ELL()]
     for t in targets:
         out = B.us_convert_formatted(ctx, g, us_desc_of(t))
         assert_same_layout(out, O.convert(nr, nc, r, c, v, t), f"{sname} -> {t}")

@@ -119,27 +119,3 @@ def test_transposing_conversions_sort_as_the_context_asks(ctx, mode, sorts):
         assert launches["radix_scatter"] == sorts and ("local_sort" in launches) == (mode is True), (s, t, launches)
         assert_same_layout(out, O.convert(n, n, r, c, v, t), f"{s} -> {t}, finish {mode}")
         out.free(); g.free()
-
-
-@pytest.mark.parametrize("mode,sorts", [(None, 2), (False, 4), (True, 1)], ids=["auto", "passes", "lds"])
-def test_transposing_conversions_sort_as_the_context_asks(ctx, mode, sorts):
-    """us_ctx.sort_finish holds for them too: by default the digits of the target's major index (14 bits: two passes),
-    passes over all 28 bits (four), or one pass over the top bits and the finish in LDS."""
-    from paper_2403_05802_amd import binding as B
-    from helpers import assert_same_layout, dev, us_desc_of
-    rng = np.random.default_rng(5)
-    n = 1 << 14
-    key = rng.permutation(np.unique(rng.integers(0, n * n, 300_000)))
-    r, c = (key // n).astype(np.int32), (key % n).astype(np.int32)
-    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
-    own = B.Context("cuda:0", profile=True)
-    for s, t in ((O.CSR(), O.CSC()), (O.CSC(), O.CSR()), (O.CSC(), O.ELL()), (O.DCSR(), O.DCSC())):
-        g = B.us_convert(own, n, n, dev(r), dev(c), dev(v), us_desc_of(s))
-        own.set_sort_lds_finish(mode)
-        own.profile_reset()
-        out = B.us_convert_formatted(own, g, us_desc_of(t))
-        launches = {k["kernel"]: k["launches"] for k in own.profile_report()}
-        own.set_sort_lds_finish(None)
-        assert launches["radix_scatter"] == sorts and ("local_sort" in launches) == (mode is True), (s, t, launches)
-        assert_same_layout(out, O.convert(n, n, r, c, v, t), f"{s} -> {t}, finish {mode}")
-        out.free(); g.free()

@@ -18,12 +18,18 @@ __device__ __forceinline__ uint32_t group_bin(int gkind, uint32_t r, uint32_t c,
 // on this part, so updates are combined in a small LDS hash table first (LDS takes 64 lanes
 // hitting one slot in about as many cycles; electing one lane per bin with ballots beforehand was
 // slower).  A workgroup walks several tiles; after each it flushes and frees the slots that stayed
-// cold and keeps the hot ones, so a hot counter gets one HBM atomic per workgroup (at most
-// ONE_COUNTER_GRID of them), not one per tile.  Freeing a slot may cut a probe chain; the bin then
-// simply takes a second slot, and counts add up all the same.
-// (A launch of at most ONE_COUNTER_GRID workgroups fills the chip only if these are large: 14.8 M entries on seven
-// diagonals took 66 us with 256 threads x 16 entries, 54 with 512 x 8, 44 with 1024 x 4.)
-constexpr int GH_T = 1024, GH_IPT = 4, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8;
+// cold and keeps the hot ones, so a hot counter gets one HBM atomic per workgroup (at most GH_GRID of
+// them), not one per tile.  Freeing a slot may cut a probe chain; the bin then simply takes a second
+// slot, and counts add up all the same.
+// Large workgroups, because the launch is short of them, and no more than are resident at once (two per CU): with 768 of
+// them a third starts when the others have ended, on a half-empty part.  256 threads x 16 entries and 768 workgroups /
+// 1024 x 4 and 768 / 1024 x 4 and 512, us: 14.8 M entries on seven diagonals and a few beside them 92 / 62 / 53; rows of a
+// sorted list of 16.5 M entries 149 / 126 / 108; diagonals, rows, columns of 16.8 M uniformly spread entries, where every
+// entry is an atomic of its own, 649, 649, 645 / 634, 634, 635 / 633, 636, 636; 41 k entries 26 / 12 / 12.  Rows of an
+// unsorted list whose first rows hold hundreds of thousands of entries and the many next ones some thousands, too few of
+// a tile to stay in the table: 2039 / 2069 / 2070, bound by atomics that meet on those counters.
+constexpr int GH_T = 1024, GH_IPT = 4, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8, GH_GRID = 512;
+static_assert(GH_GRID <= ONE_COUNTER_GRID, "hot counters");
 constexpr uint32_t GH_HOT = 64;
 
 __global__ __launch_bounds__(GH_T) void group_hist_kernel(const int32_t *row, const int32_t *col, int64_t n,
@@ -314,7 +320,7 @@ static GroupCounts group_flags(Env &env, const us_coo &coo, int gkind, int pkind
   if (!env.ok()) return g;
   fill_u32(env, g.count, g.nbins, 0);
   if (coo.nnz > 0)
-    US_LAUNCH(env, "group_hist", 8.0 * coo.nnz, group_hist_kernel, one_counter_grid(coo.nnz, GH_TILE), GH_T, coo.row,
+    US_LAUNCH(env, "group_hist", 8.0 * coo.nnz, group_hist_kernel, std::min<int64_t>(ceil_div<int64_t>(coo.nnz, GH_TILE), GH_GRID), GH_T, coo.row,
               coo.col, coo.nnz, gkind, (uint32_t)coo.nrows, (uint32_t)coo.ncols, g.count, flags);
   US_LAUNCH(env, "group_flag", 8.0 * g.nbins, group_flag_kernel, one_counter_grid(g.nbins, 256), 256,
             (const uint32_t *)g.count, g.nbins, gkind, pkind, num, den, thr, coo.nrows, coo.ncols, g.flag,

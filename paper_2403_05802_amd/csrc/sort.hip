@@ -2,8 +2,8 @@
 // Section 7.2.1 reports it as 65 % of COO->BDIA conversion time, Section 7.2.3 as 84 % for
 // Serpens) as a least-significant-digit radix sort over packed target tuples.
 //
-// One digit pass = per-tile digit histogram, chunked scan of the (tile, digit) table, stable
-// tile scatter (wavefront-ballot ranking, tile reordered through LDS so that every digit's run
+// One digit pass = per-tile digit histogram, chunked scan of the (tile, digit) table (short lists: left to the
+// scatter), stable tile scatter (wavefront-ballot ranking, tile reordered through LDS so that every digit's run
 // is written as one contiguous piece).  The first pass builds the keys from (row, col) on the
 // fly (index-map evaluation: Swap, TileSplit), the last one can unpack them into index arrays,
 // so keys never take an extra trip through HBM.
@@ -80,11 +80,10 @@ struct PassArgs {
   uint32_t n; int shift; uint32_t mask; uint32_t nblocks;
   int next_shift; uint32_t next_mask;
   uint32_t tiles_per_xcd;          // launch index -> tile mapping (see xcd_tile)
-  uint32_t *hist;                  // [nblocks][RS_BINS] per-tile digit counts, then prefixes inside a chunk of tiles
-  uint32_t *chunk;                 // [RS_BINS][nchunks] per-chunk digit counts, then prefixes over the chunks
-  uint32_t *dtotal;                // [RS_BINS] digit totals of the whole input
+  uint32_t *hist;                  // [nblocks][RS_BINS] per-tile digit counts, then (not SMALL) prefixes inside a chunk of tiles
+  uint32_t *chunk;                 // [RS_BINS][nchunks] per-chunk digit counts, then prefixes over the chunks; SMALL: null
+  uint32_t *dtotal;                // [RS_BINS] digit totals of the whole input; SMALL: null
   uint32_t nchunks;
-  int small;                       // at most RS_SMALL tiles: hist holds plain counts, chunk and dtotal are not there
   KeySpec ks;
   int hist_minor_only;             // IN_COO: this pass's digit lies inside the minor index of a (major, minor) key
   int coo_vec;                     // IN_COO: row, col and val are 16-byte aligned (full tiles are read four entries a load)
@@ -260,12 +259,15 @@ __global__ __launch_bounds__(256) void radix_scan_top_kernel(uint32_t *chunk, ui
   if (lane == 0) dtotal[d] = carry;
 }
 
-// Lists of at most RS_SMALL tiles have no scan kernels: every workgroup of the scatter adds up the per-tile counts (at
-// most 64 KB, out of L2) itself, one launch less per digit pass, which is what a conversion of a few hundred thousand
-// entries spends its time on (COO -> CSR of 41 k entries: 103-106 us with the scan kernel, 88-100 without).
+// Lists of at most RS_SMALL tiles (SMALL) have no scan kernels: every workgroup of the scatter adds up the per-tile counts
+// (at most 64 KB, out of L2) itself, one launch less per digit pass, and launches are what a conversion of a few hundred
+// thousand entries spends its time on.  With the scan kernel and without it, COO -> CSR by digit passes alone: 41 k entries,
+// 24-bit keys (three passes) 76-86 -> 65-75 us; 250 k, 24 bits 89-94 -> 75-78; 250 k, 36 bits (five) 136-140 -> 111-117.
+// A template parameter, because the same choice made at run time cost the scatter of middle-sized lists 1 to 2 % (five passes
+// over 0.5 / 1 / 2 M entries 68.1 / 79.8 / 95.0 us without the choice, 68.4 / 81.0 / 96.5 with it, 67.5 / 79.5 / 95.0 so).
 constexpr int RS_SMALL = 64;
 
-template <int IN, int OUT>
+template <int IN, int OUT, bool SMALL>
 __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
   __shared__ uint32_t s_cnt[RS_NW][RS_BINS];  // per-wave digit counts, then per-wave bases
   __shared__ uint32_t s_start[RS_BINS];       // first in-tile position of each digit
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
   __shared__ uint32_t s_wave[RS_T / 64 + 1];
   __shared__ Key s_key[RS_TILE];
   uint32_t *s_val = reinterpret_cast<uint32_t *>(s_key);
-  // (a.small: the sums over the tiles, in the place of the keys until these are written, behind two barriers)
+  // (SMALL: the sums over the tiles, in the place of the keys until these are written, behind two barriers)
   uint32_t (*s_small)[2][RS_BINS] = reinterpret_cast<uint32_t (*)[2][RS_BINS]>(s_key);
 
   const int lane = lane_id(), w = wave_id();
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
     }
   }
   if (IN == IN_COO && bad) a.flags->index_range = 1;
-  if (a.small) {   // entries of every digit in all tiles and in the tiles before this one: half of the tiles per thread
+  if (SMALL) {   // entries of every digit in all tiles and in the tiles before this one: half of the tiles per thread
     static_assert(RS_T == 2 * RS_BINS, "two threads per digit");
     const uint32_t d = threadIdx.x & (RS_BINS - 1), half = threadIdx.x / RS_BINS;
     uint32_t total = 0, before = 0;
@@ -377,11 +379,11 @@ __global__ __launch_bounds__(RS_T) void radix_scatter_kernel(PassArgs a) {
   uint32_t dummy;
   const uint32_t start = block_exclusive_sum<RS_T>(tile_total, s_wave, &dummy);
   uint32_t digit_total = 0;
-  if (threadIdx.x < RS_BINS) digit_total = a.small ? s_small[0][0][threadIdx.x] + s_small[1][0][threadIdx.x] : a.dtotal[threadIdx.x];
+  if (threadIdx.x < RS_BINS) digit_total = SMALL ? s_small[0][0][threadIdx.x] + s_small[1][0][threadIdx.x] : a.dtotal[threadIdx.x];
   const uint32_t digit_start = block_exclusive_sum<RS_T>(digit_total, s_wave, &dummy);
   if (threadIdx.x < nbins) {
     s_start[threadIdx.x] = start;
-    const uint32_t before = a.small ? s_small[0][1][threadIdx.x] + s_small[1][1][threadIdx.x]
+    const uint32_t before = SMALL ? s_small[0][1][threadIdx.x] + s_small[1][1][threadIdx.x]
                                     : a.chunk[(size_t)threadIdx.x * a.nchunks + tile / RS_CHUNK] +
                                           a.hist[(size_t)tile * RS_BINS + threadIdx.x];
     s_goff[threadIdx.x] = digit_start + before - start;
@@ -956,7 +958,8 @@ static void launch_hist(Env &env, const PassArgs &a, double bytes) {
 }
 template <int IN, int OUT>
 static void launch_scatter(Env &env, const PassArgs &a, double bytes) {
-  US_LAUNCH(env, "radix_scatter", bytes, (radix_scatter_kernel<IN, OUT>), a.tiles_per_xcd * 8u, RS_T, a);
+  if (a.chunk) US_LAUNCH(env, "radix_scatter", bytes, (radix_scatter_kernel<IN, OUT, false>), a.tiles_per_xcd * 8u, RS_T, a);
+  else US_LAUNCH(env, "radix_scatter", bytes, (radix_scatter_kernel<IN, OUT, true>), a.tiles_per_xcd * 8u, RS_T, a);
 }
 template <int IN>
 static void launch_scatter_out(Env &env, const PassArgs &a, int out_mode, double bytes) {
@@ -1014,6 +1017,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   const int npass = ceil_div(high_bits, RS_MAXBITS);
   const uint32_t nblocks = (uint32_t)ceil_div<int64_t>(nnz, RS_TILE);
   const uint32_t nchunks = ceil_div<uint32_t>(nblocks, (uint32_t)RS_CHUNK);
+  const bool small = nblocks <= (uint32_t)RS_SMALL;
   const int nrec = finish_local ? npass : npass - 1;   // passes that write records
   Rec *rbuf[2] = {nullptr, nullptr};
   uint8_t *dbuf[2] = {nullptr, nullptr};
@@ -1025,7 +1029,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   {  // everything below in one allocation
     auto g = [](size_t b) { return Env::granule(b); };
     size_t need = (nrec < 2 ? nrec : 2) * g(sizeof(Rec) * nnz) + (npass - 1 < 2 ? npass - 1 : 2) * g(nnz + 16) +
-                  g(4ull * RS_BINS * nblocks) + g(4ull * RS_BINS * nchunks) + g(4ull * RS_BINS);
+                  g(4ull * RS_BINS * nblocks) + (small ? 0 : g(4ull * RS_BINS * nchunks) + g(4ull * RS_BINS));
     if (finish_local)
       need += g(4ull * (nbuckets + 1)) + (npass >= 2 ? 0 : g(sizeof(Rec) * nnz)) + g(16) +
               g(sizeof(BigBucket) * la.big_cap) + g(4ull * la.tile_cap) + g(4ull * la.tile_cap * RS_BINS) +
@@ -1035,8 +1039,8 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   for (int i = 0; i < 2 && i < nrec; ++i) rbuf[i] = env.temp<Rec>(nnz);
   for (int i = 0; i < 2 && i < npass - 1; ++i) dbuf[i] = env.temp<uint8_t>(nnz + 16);
   uint32_t *hist = env.temp<uint32_t>((size_t)RS_BINS * nblocks);
-  uint32_t *chunk = env.temp<uint32_t>((size_t)RS_BINS * nchunks);
-  uint32_t *dtotal = env.temp<uint32_t>(RS_BINS);
+  uint32_t *chunk = small ? nullptr : env.temp<uint32_t>((size_t)RS_BINS * nchunks);
+  uint32_t *dtotal = small ? nullptr : env.temp<uint32_t>(RS_BINS);
   if (!env.ok()) return false;
 
   int widths[16], shifts[16];
@@ -1070,7 +1074,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
     a.next_shift = last_pass ? 0 : shifts[p + 1];
     a.next_mask = last_pass ? 0u : (1u << widths[p + 1]) - 1u;
     a.tiles_per_xcd = ceil_div<uint32_t>(nblocks, 8u);
-    a.hist = hist; a.chunk = chunk; a.dtotal = dtotal; a.nchunks = nchunks; a.small = nblocks <= (uint32_t)RS_SMALL; a.ks = ks; a.flags = flags;
+    a.hist = hist; a.chunk = chunk; a.dtotal = dtotal; a.nchunks = nchunks; a.ks = ks; a.flags = flags;
     a.hist_minor_only = first && in_mode == IN_COO && ks.mode == 0 && shifts[p] + widths[p] <= ks.b_bits && ks.b_bits <= 32;
     a.coo_vec = first && in_mode == IN_COO && !major_only &&   // (major_only: the order of the list counts)
                 ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
@@ -1084,7 +1088,7 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
     if (in == IN_COO) launch_hist<IN_COO>(env, a, (a.hist_minor_only || a.hist_major_shift >= 0 ? 4.0 : 8.0) * nnz);
     else if (in == IN_KEY32) launch_hist<IN_KEY32>(env, a, 4.0 * nnz);
     else launch_hist<IN_SPLIT>(env, a, 1.0 * nnz);
-    if (!a.small) {
+    if (!small) {
       US_LAUNCH(env, "radix_scan_chunk", 8.0 * RS_BINS * nblocks, radix_scan_chunk_kernel, nchunks, RS_BINS, hist, chunk,
                 nblocks);
       US_LAUNCH(env, "radix_scan_top", 8.0 * RS_BINS * nchunks, radix_scan_top_kernel, RS_BINS / 4, 256, chunk, nchunks,
@@ -1156,7 +1160,7 @@ size_t sort_temp_bytes(int64_t nnz) {
   if (nnz <= 0) return 0;
   const size_t nblocks = (size_t)ceil_div<int64_t>(nnz, RS_TILE), nchunks = ceil_div<size_t>(nblocks, RS_CHUNK);
   return 2 * Env::granule(sizeof(Rec) * nnz) + 2 * Env::granule(nnz + 16) + Env::granule(4ull * RS_BINS * nblocks) +
-         Env::granule(4ull * RS_BINS * nchunks) + Env::granule(4ull * RS_BINS);
+         (nblocks <= (size_t)RS_SMALL ? 0 : Env::granule(4ull * RS_BINS * nchunks) + Env::granule(4ull * RS_BINS));
 }
 
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,

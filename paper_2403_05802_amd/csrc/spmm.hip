@@ -762,36 +762,42 @@ __global__ __launch_bounds__(256) void zero_rows_kernel(float *Y, int64_t nrows,
 
 // The rows of Y that a plain product over CSR leaves untouched: those without entries.  Every other row is stored once, by
 // the chunk it lies in or by the fix-up, so Y is neither cleared nor read (262,144 rows of 1000 columns take 0.14 ms to
-// clear and as long again to read back).  A workgroup lists the empty ones of `rows` (at most 256) rows and its 256 threads
-// walk (listed row, column) pairs, so that a matrix that is mostly empty is cleared by whole wavefronts however few columns
-// it has; the columns are cut into pieces of ZE_COLS loads (blockIdx.y), so that a few very wide rows spread over the part.
-// The rows are walked with a stride: a grid of 2^32 threads or more is cut short without an error.
-// It is bound by the stores.  A whole plain product against the fill and the product that adds: 2 M rows, 147 k entries,
-// 1 / 16 / 64 columns 51 / 71 / 157 -> 45 / 55 / 137 us; 262,144 rows of 1000 columns, 20 k entries 253 -> 255; 8 rows of
-// 1 M columns 86 -> 82.  (A wavefront for eight rows, clearing one row after the other: 83 / 85 / 141, 262 and 3,364 us.)
+// clear and as long again to read back).  A wavefront looks at `rows` (at most 64) rows, moves the numbers of the empty ones
+// to its first lanes and walks (empty row, column) pairs, so that a matrix that is mostly empty is cleared by whole wavefronts
+// however few columns it has; the columns are cut into pieces of ZE_COLS loads (blockIdx.y), so that a few very wide rows
+// spread over the part.  The rows are walked with a stride: a grid of 2^32 threads or more is cut short without an error.
+// It is bound by the stores; a Y that no cache holds is written past them (NT).  A whole plain product of 2 M rows with 147 k
+// entries against torch's fill and the product that adds: 1 / 16 / 64 / 100 columns 54 / 70 / 159 / 222 -> 42 / 54 / 136 /
+// 206 us (100 columns with cached stores: 254); 262,144 rows of 1000 columns, 20 k entries 256 -> 244 (cached: 257); 8 rows
+// of 1 M columns 62 -> 51.  (A wavefront for eight rows, clearing one row after the other: 83 / 85 / 139 / 265, 263 and 2,390
+// us; a list of the empty rows per workgroup, made behind four barriers: 45 / 55 / 136 / 254, 259 and 52, and 0.6 us on
+// every product of a matrix that has none, 20,000 rows: 26.6 -> 27.2 us, now 26.8.)
 constexpr int ZE_COLS = 512, ZE_GRID = 1 << 20;
-template <int VEC>
+template <int VEC, bool NT>
 __global__ __launch_bounds__(256) void zero_empty_rows_kernel(const int32_t *ptr, int64_t nrows, int rows, float *Y, int64_t N,
                                                              int64_t ldy) {
   typedef typename VecT<VEC>::type V;
-  __shared__ int32_t s_row[256];
-  __shared__ uint32_t s_wave[256 / 64 + 1];
-  const int64_t c0 = (int64_t)blockIdx.y * ZE_COLS;
-  const uint32_t width = (uint32_t)min((int64_t)ZE_COLS, N / VEC - c0), t = threadIdx.x;
-  const uint32_t k_first = t / width, c_first = t - k_first * width, k_step = 256 / width, c_step = 256 - k_step * width;
-  for (int64_t i0 = (int64_t)blockIdx.x * rows; i0 < nrows; i0 += (int64_t)gridDim.x * rows) {
-    const int64_t i = i0 + t;
-    const bool empty = t < (uint32_t)rows && i < nrows && ptr[i + 1] == ptr[i];
-    uint32_t n;
-    const uint32_t at = block_exclusive_sum<256>(empty ? 1u : 0u, s_wave, &n);
-    if (empty) s_row[at] = (int32_t)t;
-    __syncthreads();
-    for (uint32_t k = k_first, c = c_first; k < n;) {
-      *reinterpret_cast<V *>(Y + (i0 + s_row[k]) * ldy + (c0 + c) * VEC) = V(0.f);
+  const int lane = lane_id();
+  for (int64_t i0 = ((int64_t)blockIdx.x * 4 + wave_id()) * rows; i0 < nrows; i0 += (int64_t)gridDim.x * 4 * rows) {
+    const int64_t i = i0 + lane;
+    const bool empty = lane < rows && i < nrows && ptr[i + 1] == ptr[i];
+    const uint64_t mask = __ballot(empty);
+    if (mask == 0) continue;
+    const int n = __popcll(mask), before = __popcll(mask & lanes_below());
+    const int row = __builtin_amdgcn_ds_permute(4 * (empty ? before : n + lane - before), lane);   // lane k < n: the k-th empty row
+    const int64_t c0 = (int64_t)blockIdx.y * ZE_COLS;
+    const int width = (int)min((int64_t)ZE_COLS, N / VEC - c0);
+    const int k_step = 64 / width, c_step = 64 - k_step * width;
+    int k = lane / width, c = lane - k * width;
+    for (int done = 0; done < n * width; done += 64) {   // (all lanes stay: __shfl reads the first n of them)
+      const int64_t r = i0 + __shfl(row, k);
+      if (k < n) {
+        V *yp = reinterpret_cast<V *>(Y + r * ldy + (c0 + c) * VEC);
+        if (NT) __builtin_nontemporal_store(V(0.f), yp); else *yp = V(0.f);
+      }
       k += k_step; c += c_step;
       if (c >= width) { c -= width; ++k; }
     }
-    __syncthreads();   // the list is free for the next rows
   }
 }
 
@@ -799,13 +805,19 @@ static void zero_empty_rows(Env &env, const int32_t *ptr, int64_t nrows, float *
   if (!env.ok()) return;
   LaunchScope ls(env, "zero_empty_rows", 4.0 * nrows);
   const bool by4 = (uintptr_t)Y % 16 == 0 && N % 4 == 0 && ldy % 4 == 0;
-  const int64_t width = by4 ? N / 4 : N;
-  // as many rows as make some 8,000 stores, 32 at least: enough workgroups where every row is empty, one pointer per thread
-  // where rows are short
-  const int rows = width <= 32 ? 256 : (width <= 128 ? 64 : 32);
-  const dim3 grid((unsigned)min(ceil_div<int64_t>(nrows, rows), (int64_t)ZE_GRID), (unsigned)ceil_div<int64_t>(width, ZE_COLS));
-  if (by4) hipLaunchKernelGGL(zero_empty_rows_kernel<4>, grid, dim3(256), 0, env.stream, ptr, nrows, rows, Y, N, ldy);
-  else hipLaunchKernelGGL(zero_empty_rows_kernel<1>, grid, dim3(256), 0, env.stream, ptr, nrows, rows, Y, N, ldy);
+  const int64_t width = by4 ? N / 4 : N, pieces = ceil_div<int64_t>(width, ZE_COLS);
+  // beyond twice the memory-side cache (256 MB) stores past the caches are faster, below it slower (262,144 rows of 200
+  // columns 57 -> 69 us)
+  const bool nt = 4.0 * nrows * N > 512e6;
+  // as many rows as make some 2,000 stores, 8 at least, one pointer per lane where rows are short; fewer where that leaves
+  // less than a wavefront per SIMD (a few wide rows)
+  int rows = width <= (nt ? 16 : 32) ? 64 : (width <= 128 ? 16 : 8);
+  while (rows > 1 && ceil_div<int64_t>(nrows, rows) * pieces < 1024) rows /= 2;
+  const dim3 grid((unsigned)min(ceil_div<int64_t>(nrows, 4 * rows), (int64_t)ZE_GRID), (unsigned)pieces);
+#define US_ZE_LAUNCH(V, T) hipLaunchKernelGGL((zero_empty_rows_kernel<V, T>), grid, dim3(256), 0, env.stream, ptr, nrows, rows, Y, N, ldy)
+  if (by4) { if (nt) US_ZE_LAUNCH(4, true); else US_ZE_LAUNCH(4, false); }
+  else { if (nt) US_ZE_LAUNCH(1, true); else US_ZE_LAUNCH(1, false); }
+#undef US_ZE_LAUNCH
   env.check(hipGetLastError());
 }
 

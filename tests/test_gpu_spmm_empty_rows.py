@@ -23,11 +23,23 @@ def csr(ctx, n, nc, keys):
     return B.us_convert(ctx, n, nc, r.int(), (keys - r * nc).int(), v, B.us_desc_preset(B.US_F_CSR))
 
 
-# 256 rows a workgroup up to 32 columns (words, or loads of four), 64 up to 128, 32 beyond; pieces of 512 columns
+# 64, 16 or 8 rows a wavefront (up to 32, 128 or more columns, words or loads of four), fewer where there are few wavefronts;
+# pieces of 512 columns
 @pytest.mark.parametrize("n", [1, 31, 65, 257, 700])
 @pytest.mark.parametrize("N,ld_extra,offset", [(1, 0, 0), (3, 2, 0), (32, 0, 1), (33, 0, 0), (128, 4, 0), (129, 0, 0), (255, 1, 0),
                                                (511, 0, 0), (513, 0, 0), (132, 0, 0), (516, 0, 0), (2048, 0, 0), (2052, 8, 0)])
 def test_rows_without_entries_are_cleared_and_nothing_else(ctx, n, N, ld_extra, offset):
+    check_product(ctx, n, N, ld_extra, offset)
+
+
+@pytest.mark.parametrize("n,N,ld_extra,offset", [
+    (65_471, 1, 0, 0), (65_473, 1, 3, 0), (65_537, 3, 0, 0), (65_600, 31, 1, 1), (65_599, 32, 0, 0), (70_001, 128, 0, 0),
+    (16_383, 33, 0, 0), (16_385, 127, 0, 0), (17_003, 132, 0, 0), (8_199, 129, 0, 0), (8_191, 515, 0, 0), (4_099, 520, 0, 0)])
+def test_as_many_rows_as_fill_the_wavefronts(ctx, n, N, ld_extra, offset):
+    check_product(ctx, n, N, ld_extra, offset)
+
+
+def check_product(ctx, n, N, ld_extra, offset):
     from paper_2403_05802_amd import binding as B
     from helpers import assert_product, dev, host, row_terms
     rng = np.random.default_rng(n * 4096 + N)
@@ -69,6 +81,24 @@ def test_more_rows_than_threads_of_one_grid(ctx):
     g.free()
 
 
+# results of more than 512 MB are written past the caches: words and loads of four, one piece of columns and several
+@pytest.mark.parametrize("n,N", [(2_100_001, 61), (1_300_003, 100), (300_007, 513), (130_001, 1000), (1001, 131_076)])
+def test_large_results(ctx, n, N):
+    from paper_2403_05802_amd import binding as B
+    nc = 100
+    rows = torch.unique(torch.randint(0, n, (n // 3,), device="cuda"))
+    rows[-1] = n - 1
+    g = csr(ctx, n, nc, rows * nc + rows % nc)
+    X = torch.rand(nc, N, device="cuda") + 0.5
+    Y = torch.full((n, N), float("nan"), device="cuda")
+    B.us_spmm(ctx, g, X, Y)
+    for part in torch.arange(rows.numel(), device="cuda").split(100_000):   # one entry a row: one product, no sum
+        assert torch.equal(Y[rows[part]], g.val()[part, None] * X[rows[part] % nc])
+    Y[rows] = 0.0
+    assert int(torch.count_nonzero(Y)) == 0
+    g.free()
+
+
 def best_us(f, calls=20, rounds=6):
     """Least time of a call among others, microseconds."""
     for _ in range(3):
@@ -86,7 +116,8 @@ def best_us(f, calls=20, rounds=6):
 
 
 @pytest.mark.parametrize("n,nc,nnz,N", [(2_000_000, 2_000_000, 147_000, 1), (2_000_000, 2_000_000, 147_000, 4),
-                                        (8, 1000, 3, 1_000_000), (200, 1000, 20, 100_000)])
+                                        (8, 1000, 3, 1_000_000), (200, 1000, 20, 100_000),
+                                        (2_000_000, 2_000_000, 147_000, 100)])
 def test_clearing_the_rows_costs_no_more_than_clearing_all(ctx, n, nc, nnz, N):
     """Mostly empty matrices: a plain product against clearing all of Y and adding to it, which writes as much and reads
     the stored rows besides.  (A quarter is left for what the two runs differ by; clearing row by row took 1.6 times as

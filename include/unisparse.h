@@ -64,17 +64,20 @@ typedef struct us_ctx {
   void *hip_stream; /* hipStream_t, NULL = the null stream */
   void *profile;    /* us_profile* or NULL: per-kernel HIP-event timing (see us_profile_*) */
   /* How the Sort step (Figure 8) of the conversions made through this context finishes.
-   *   US_SORT_FINISH_AUTO (0, what a zeroed us_ctx gives): by the target tuple -- in LDS for blocked tuples
-   *     (BCSR, BDIA and the blocked #sum queries) and for lists of 4,096 to 262,144 entries whose
-   *     (row, col) takes more than 24 bits, whole-array digit passes for other (row, col) tuples; over the digits of the
-   *     target's major index alone where us_convert_formatted turns compressed rows into columns or back;
+   *   US_SORT_FINISH_AUTO (0, what a zeroed us_ctx gives): by the target tuple and the number of entries.  (row, col)
+   *     tuples of up to 42 bits and 67 M entries are parted by their top bits, then by splitters sampled from the entries,
+   *     into buckets that are sorted inside LDS; lists of 4,096 to 262,144 entries whose (row, col) takes more than 24
+   *     bits, and blocked tuples (BCSR, BDIA and the blocked #sum queries), go by US_SORT_FINISH_LDS; up to 2 M entries
+   *     that us_convert_formatted turns from compressed rows into columns or back by passes over the digits of the
+   *     target's major index alone; everything else by US_SORT_FINISH_PASSES;
    *   US_SORT_FINISH_LDS: whole-array digit passes over the top key bits only, every bucket of equal top bits
    *     is then finished inside LDS;
    *   US_SORT_FINISH_PASSES: whole-array digit passes over all key bits.
    * The finish pays off when entries spread evenly over the buckets (block rows of a FEM-like matrix: COO->BCSR
    * of 50 M entries in 38 % less time); heavy rows of a power-law matrix need extra splitting passes and gain nothing.
-   * Results are identical in every mode; an input the finish cannot take (more than 262,144 entries sharing
-   * their top key bits, or 4,096 sharing 8 more) is sorted again with whole-array passes by the same call. */
+   * Results are identical in every mode; an input that a way cannot take (the finish: more than 262,144 entries sharing
+   * their top key bits, or 4,096 sharing 8 more; the buckets: more than 131,072 sharing theirs) is sorted again with
+   * whole-array passes by the same call. */
   int32_t sort_finish;
 } us_ctx;
 enum { US_SORT_FINISH_AUTO = 0, US_SORT_FINISH_LDS = 1, US_SORT_FINISH_PASSES = 2 };

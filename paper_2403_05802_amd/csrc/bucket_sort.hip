@@ -1,0 +1,828 @@
+// The Sort operator for lists of many entries: most significant digits first.  The list is cut into parents by the
+// top bits of the key (one pass over memory), every parent into children of about BK_TARGET entries by splitters drawn
+// from a sample of its own keys (a second pass), and a child is sorted where it lies in LDS while its sorted entries and
+// the pointers of its rows are written.  Keys are unique, so splitters tell apart what equal top bits leave together
+// (a heavy row of a power-law matrix fills several children), and no pass but the last has an order to keep: places inside
+// a tile come from one LDS atomic per entry.
+//
+// Against the least-significant-digit passes of sort.hip: an entry travels as 8 bytes {key below the parent's bits, value}
+// instead of 12 and a digit byte, through two passes and the finish (52 bytes read and written in all, pointers of the
+// rows included) instead of one pass per eight key bits (26 each).  COO -> CSR, digit passes / this, us: 16.8 M entries of a
+// power-law matrix, 40 key bits, 695 / 438; 40 M with local columns, 42 bits, 1630 / 995; 4 M 238 / 174; 1 M, even rows
+// 155 / 110; 300 k 138 / 100; 41 k, 24 bits (one parent) 87-103 / 75-80.
+#include "device.h"
+#include "sort_key.h"
+
+namespace us {
+
+constexpr int BK_CAP = 2048;        // most entries of a child: what the finish holds in LDS
+constexpr int BK_TARGET = 1024;     // ... and how many it gets on average
+constexpr int BK_MAXK = 128;        // most children of a parent
+constexpr int BK_OVERSAMPLE = 64;   // sampled keys per child
+constexpr int BK_MAXBITS = 10, BK_MAXBINS = 1 << BK_MAXBITS;   // parents
+
+struct BkParent { uint32_t start, size, child0, k, tile0; };
+
+struct BkArgs {
+  const int32_t *row, *col; const uint32_t *val;   // the caller's list
+  uint32_t n; KeySpec ks;
+  int dshift;                  // key bits below the parent's: at most 32
+  int lead_shift;              // >= 0: the parent is (leading field of the key) >> lead_shift, whatever the other fields hold
+  uint32_t nparents;           // a power of two
+  int coo_vec;                 // row, col and val are 16-byte aligned
+  // first pass: every workgroup takes per_group consecutive entries
+  uint32_t per_group, ngroups, groups_per_xcd;
+  uint32_t *hist;              // [ngroups][nparents] entries per group and parent, then where they start inside the parent
+  uint32_t *ptotal;            // [nparents] entries per parent
+  uint2 *rec1;                 // [n] {low key, value}, by parent
+  // second pass
+  BkParent *parent;            // [nparents]
+  uint32_t *totals;            // [0] children, [1] tiles of parents with more than one child
+  uint32_t *child_parent;      // [max_children]
+  uint32_t *splitter;          // [max_children] smallest low key of the child
+  uint32_t *cursor;            // [max_children] entries of the child (parents with more than one)
+  uint32_t *tile_parent;       // [max_tiles]
+  uint32_t max_children, max_tiles, tiles_per_xcd, children_per_xcd;
+  uint2 *rec2;                 // [max_children][BK_CAP]
+  // output
+  int32_t *major_out, *minor_out; uint32_t *val_out;
+  int32_t *ptr; uint32_t ngroups_out;   // pointers over the major indices 0..ngroups_out, or null
+  Flags *flags;
+};
+
+__device__ __forceinline__ uint32_t parent_of_entry(const BkArgs &a, uint32_t r, uint32_t c, Key key) {
+  if (a.lead_shift < 0) return (uint32_t)(key >> a.dshift) & (a.nparents - 1);
+  uint32_t lead = a.ks.swap ? c : r;
+  if (a.ks.mode != 0) lead /= a.ks.bh;
+  return (lead >> a.lead_shift) & (a.nparents - 1);
+}
+__device__ __forceinline__ uint32_t low_mask(int dshift) { return dshift >= 32 ? 0xFFFFFFFFu : (1u << dshift) - 1u; }
+
+// A kernel of the call has given up: a coordinate out of range, or an input this sort does not take.  The tables that later
+// kernels index with may then be unwritten.  Read once per workgroup, because workgroups of the same launch may set it.
+__device__ __forceinline__ bool gave_up(const BkArgs &a, bool range) {
+  __shared__ int32_t s_stop;
+  if (threadIdx.x == 0) s_stop = (range ? a.flags->index_range : 0) | a.flags->retry;
+  __syncthreads();
+  return s_stop != 0;
+}
+
+// Exclusive prefix sum over the workgroup with one barrier; s_wave: T / 64 words, free again after the next barrier.
+template <int T>
+__device__ __forceinline__ uint32_t scan_one_barrier(uint32_t v, uint32_t *s_wave) {
+  const uint32_t inc = wave_inclusive_sum_dpp(v);
+  if (lane_id() == 63) s_wave[wave_id()] = inc;
+  __syncthreads();
+  uint32_t before = 0;
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) before += w < wave_id() ? s_wave[w] : 0u;
+  return before + inc - v;
+}
+
+// ------------------------------------------------------------------ first pass: parents
+constexpr int BH_T = 512, BH_COPIES = 4;
+
+__global__ __launch_bounds__(BH_T) void bucket_hist_kernel(BkArgs a) {
+  __shared__ uint32_t s_hist[BK_MAXBINS * BH_COPIES];   // (copies picked by lane: LDS adds to one address take turns)
+  const uint32_t group = xcd_tile(blockIdx.x, a.groups_per_xcd);
+  if (group >= a.ngroups) return;
+  for (uint32_t i = threadIdx.x; i < a.nparents * BH_COPIES; i += BH_T) s_hist[i] = 0;
+  __syncthreads();
+  const uint32_t begin = group * a.per_group, end = min(begin + a.per_group, a.n);
+  const uint32_t copy = threadIdx.x & (BH_COPIES - 1);
+  const int32_t *lead = a.ks.swap ? a.col : a.row;
+  auto count = [&](uint32_t p) { atomicAdd(&s_hist[p * BH_COPIES + copy], 1u); };
+  auto of_lead = [&](uint32_t x) { return ((a.ks.mode != 0 ? x / a.ks.bh : x) >> a.lead_shift) & (a.nparents - 1); };
+  uint32_t i = begin;
+  if (a.lead_shift >= 0 && a.coo_vec) {
+    for (; i + 8 * BH_T <= end; i += 8 * BH_T) {   // (begin is a multiple of four entries)
+      const uint4 *p4 = reinterpret_cast<const uint4 *>(lead + i);
+      const uint4 x = p4[threadIdx.x], y = p4[BH_T + threadIdx.x];
+      count(of_lead(x.x)); count(of_lead(x.y)); count(of_lead(x.z)); count(of_lead(x.w));
+      count(of_lead(y.x)); count(of_lead(y.y)); count(of_lead(y.z)); count(of_lead(y.w));
+    }
+  }
+  for (uint32_t e = i + threadIdx.x; e < end; e += BH_T) {
+    if (a.lead_shift >= 0) {
+      count(of_lead((uint32_t)lead[e]));
+    } else {
+      const uint32_t r = (uint32_t)a.row[e], c = (uint32_t)a.col[e];
+      count(parent_of_entry(a, r, c, build_key(a.ks, r, c)));
+    }
+  }
+  __syncthreads();
+  for (uint32_t p = threadIdx.x; p < a.nparents; p += BH_T) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int c = 0; c < BH_COPIES; ++c) sum += s_hist[p * BH_COPIES + c];
+    a.hist[(size_t)group * a.nparents + p] = sum;
+  }
+}
+
+// where the entries of every group start inside their parent, and the parents' sizes: a workgroup takes 32 parents, its
+// threads 32 consecutive ranges of groups each
+constexpr int BS_T = 1024, BS_BINS = 32, BS_PARTS = BS_T / BS_BINS;
+__global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
+  __shared__ uint32_t s_part[BS_PARTS][BS_BINS];
+  const uint32_t q = threadIdx.x % BS_BINS, part = threadIdx.x / BS_BINS, p = blockIdx.x * BS_BINS + q;
+  const uint32_t each = (a.ngroups + BS_PARTS - 1) / BS_PARTS, g0 = min(part * each, a.ngroups), g1 = min(g0 + each, a.ngroups);
+  uint32_t sum = 0;
+  if (p < a.nparents) {
+#pragma unroll 8
+    for (uint32_t g = g0; g < g1; ++g) sum += a.hist[(size_t)g * a.nparents + p];
+  }
+  s_part[part][q] = sum;
+  __syncthreads();
+  uint32_t run = 0;
+  for (uint32_t w = 0; w < part; ++w) run += s_part[w][q];
+  if (p >= a.nparents) return;
+  if (part == BS_PARTS - 1) {
+    a.ptotal[p] = run + sum;
+    if (run + sum > (uint32_t)(BK_MAXK * BK_TARGET)) a.flags->retry = RETRY_SORT_LDS;   // (the kernels that follow leave at once)
+  }
+#pragma unroll 8
+  for (uint32_t g = g0; g < g1; ++g) {
+    uint32_t *h = a.hist + (size_t)g * a.nparents + p;
+    const uint32_t v = *h;
+    *h = run;
+    run += v;
+  }
+}
+
+// A workgroup walks its range tile by tile: places inside the tile by LDS atomics, the tile put in order of the parents
+// in LDS, every parent's run written as one piece behind the workgroup's earlier ones.  Bound by the lines that its runs
+// leave partly written (ngroups x nparents of them are open at a time, 128 bytes each, against 4 MB of L2 per XCD): few
+// workgroups and large tiles where there are many entries.  512 threads x 8 entries and 768 workgroups / 1024 x 8 and 256
+// / 1024 x 12 and 256, us: 40 M entries, 1024 parents 329 / 283 / 260; 16.8 M, 512 parents 110 / 98 / 101; 4 M, 128
+// parents 22 / 24 / 28; 1 M 12 / 15 / 17.
+template <int T, int IPT>
+__global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkArgs a) {
+  constexpr int TILE = T * IPT, PER = BK_MAXBINS / T;
+  __shared__ uint2 s_rec[TILE];
+  __shared__ uint16_t s_bin[TILE];
+  __shared__ uint32_t s_cnt[BK_MAXBINS];    // entries of the tile per parent, then where they start in the tile
+  __shared__ uint32_t s_goff[BK_MAXBINS];   // position of the parent's run of this tile in rec1, minus its start in the tile
+  __shared__ uint32_t s_wave[2][T / 64];
+  const uint32_t group = xcd_tile(blockIdx.x, a.groups_per_xcd);
+  if (group >= a.ngroups || a.flags->retry) return;   // (set, if at all, by the kernel before)
+  const uint32_t begin = group * a.per_group, end = min(begin + a.per_group, a.n);
+  const int tid = threadIdx.x;
+  uint32_t next[PER];   // parents PER * tid ..: where the group's next entry goes
+  {
+    uint32_t t[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const uint32_t p = tid * PER + q;
+      t[q] = p < a.nparents ? a.ptotal[p] : 0u;
+      next[q] = p < a.nparents ? a.hist[(size_t)group * a.nparents + p] : 0u;
+      s_cnt[p] = 0;
+      sum += t[q];
+    }
+    uint32_t run = scan_one_barrier<T>(sum, s_wave[0]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { next[q] += run; run += t[q]; }
+  }
+  bool bad = false;
+  const uint32_t lmask = low_mask(a.dshift);
+  for (uint32_t base = begin; base < end; base += TILE) {
+    const uint32_t in_tile = min((uint32_t)TILE, end - base);
+    uint32_t key[IPT], val[IPT], bin[IPT], arr[IPT];
+    if (a.coo_vec && in_tile == (uint32_t)TILE) {
+      const uint4 *r4 = reinterpret_cast<const uint4 *>(a.row + base), *c4 = reinterpret_cast<const uint4 *>(a.col + base);
+      const uint4 *v4 = reinterpret_cast<const uint4 *>(a.val + base);
+      uint4 rr[IPT / 4], cc[IPT / 4], vv[IPT / 4];
+#pragma unroll
+      for (int q = 0; q < IPT / 4; ++q) { rr[q] = r4[q * T + tid]; cc[q] = c4[q * T + tid]; vv[q] = v4[q * T + tid]; }
+#pragma unroll
+      for (int q = 0; q < IPT / 4; ++q) {
+        const uint32_t r[4] = {rr[q].x, rr[q].y, rr[q].z, rr[q].w}, c[4] = {cc[q].x, cc[q].y, cc[q].z, cc[q].w};
+        const uint32_t v[4] = {vv[q].x, vv[q].y, vv[q].z, vv[q].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const Key k = build_key(a.ks, r[e], c[e]);
+          bad |= coo_out_of_range(a.ks, r[e], c[e]);
+          bin[4 * q + e] = parent_of_entry(a, r[e], c[e], k);
+          key[4 * q + e] = (uint32_t)k & lmask;
+          val[4 * q + e] = v[e];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        const uint32_t i = j * T + tid;
+        bin[j] = 0xFFFFFFFFu; key[j] = 0; val[j] = 0;
+        if (i < in_tile) {
+          const uint32_t r = (uint32_t)a.row[base + i], c = (uint32_t)a.col[base + i];
+          const Key k = build_key(a.ks, r, c);
+          bad |= coo_out_of_range(a.ks, r, c);
+          bin[j] = parent_of_entry(a, r, c, k);
+          key[j] = (uint32_t)k & lmask;
+          val[j] = a.val[base + i];
+        }
+      }
+    }
+    __syncthreads();   // s_cnt is clear, the previous tile is written
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) arr[j] = bin[j] != 0xFFFFFFFFu ? atomicAdd(&s_cnt[bin[j]], 1u) : 0u;
+    __syncthreads();
+    uint32_t c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { c[q] = s_cnt[tid * PER + q]; sum += c[q]; }
+    uint32_t run = scan_one_barrier<T>(sum, s_wave[1]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      s_cnt[tid * PER + q] = run;
+      s_goff[tid * PER + q] = next[q] - run;
+      next[q] += c[q]; run += c[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (bin[j] != 0xFFFFFFFFu) {
+        const uint32_t pos = s_cnt[bin[j]] + arr[j];
+        s_rec[pos] = make_uint2(key[j], val[j]);
+        s_bin[pos] = (uint16_t)bin[j];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      const uint32_t i = j * T + tid;
+      if (i < in_tile) {
+        const uint32_t g = s_goff[s_bin[i]] + i;
+        if (g < a.n) a.rec1[g] = s_rec[i];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) s_cnt[tid * PER + q] = 0;
+  }
+  if (bad) a.flags->index_range = 1;
+}
+
+// ------------------------------------------------------------------ a few thousand keys in LDS
+// The keys go into bins that keep their order: 64 of the keys themselves, sorted by one wavefront, cut them into intervals of
+// similar numbers of keys whatever their distribution, and an interval is cut evenly over its range into as many bins as it
+// has keys (twice as many where there is room).  What is left together, one or two keys on average, fix_order puts in order.
+// A bin of more than LIMIT keys is cut again before, evenly between its own smallest and largest key, into as many
+// bins as it has keys.  LDS is what bounds this: a key costs two atomics and two writes at scattered places, the splitters
+// and intervals are held one per lane and looked up with ds_bpermute, which knows no bank conflicts.
+constexpr uint32_t BP_MOST = 129;
+constexpr int BP_ROUNDS = 4;
+
+template <int T, int IPT>
+struct BinScratch {
+  static constexpr int NW = T / 64, Q = IPT / 4;   // wavefronts; blocks of four bins or slots per thread
+  uint32_t cnt[T * IPT + 4];
+  uint32_t a[T * IPT], b[T * IPT];
+  uint32_t split[64], count[64];
+  uint32_t wave[Q * NW], big[NW];
+  uint32_t reach[Q * NW];   // per 256 slots: the most keys of a bin that touches them
+};
+
+// key[j] belongs to item j * T + threadIdx.x < m <= T * IPT, lo <= key <= hi; sample: the key of item threadIdx.x * m / 64
+// (wavefront 0).  Leaves the slot of every item in order of the bins, s.reach, and returns the most keys of a bin, rounded
+// up to 1, 5, 9, 17, 33, 65, BP_MOST or ~0 (the same for every thread).  s.a and s.b are free afterwards.
+template <int T, int IPT, uint32_t LIMIT>
+__device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32_t m, uint32_t lo, uint32_t hi, uint32_t sample,
+                                              BinScratch<T, IPT> &s, uint32_t (&slot)[IPT]) {
+  constexpr int CAP = T * IPT, NW = T / 64, Q = IPT / 4;
+  static_assert(IPT % 4 == 0, "counters are cleared and read four at a time");
+  const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
+  uint32_t bin[IPT], arr[IPT];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = make_uint4(0, 0, 0, 0);
+  if (tid < Q * NW) s.reach[tid] = 0;
+  if (w == 0) {
+    s.split[lane] = ~0u; s.count[lane] = 0;
+    uint32_t rank = 0;
+#pragma unroll 16
+    for (int q = 0; q < 64; ++q) rank += (uint32_t)__builtin_amdgcn_readlane((int)sample, q) < sample;
+    __builtin_amdgcn_wave_barrier();
+    if (m >= 64) s.split[rank] = sample;
+  }
+  __syncthreads();
+  // lane i: interval i = [split i, split i + 1); two equal samples (a duplicate, or few keys) leave a gap in the list: one interval then
+  uint32_t sp = s.split[lane];
+  if (__any(sp == ~0u)) sp = ~0u;
+  if (lane == 0) sp = lo;
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) bin[j] = 0;
+#pragma unroll
+  for (int step = 32; step; step >>= 1) {
+#pragma unroll
+    for (int j = 0; j < IPT; ++j)
+      if (j * T < m && (uint32_t)__shfl((int)sp, (int)(bin[j] + step)) <= key[j]) bin[j] += step;
+  }
+#pragma unroll
+  for (int j = 0; j < IPT; ++j)
+    if (j * T + tid < m) atomicAdd(&s.count[bin[j]], 1u);
+  __syncthreads();
+  {
+    const uint32_t n = s.count[lane], st = wave_inclusive_sum_dpp(n) - n, f = 2 * m <= (uint32_t)CAP ? 2u : 1u;
+    uint32_t next = (uint32_t)__shfl_down((int)sp, 1);
+    if (lane == 63 || next > hi) next = hi;
+    const float scale = (float)(f * n) * __builtin_amdgcn_rcpf((float)(next - sp) + 1.f);
+    const uint32_t first = f * st, last = f * (st + n) - 1;
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (j * T < m) {
+        const int from = (int)bin[j];
+        const uint32_t l = (uint32_t)__shfl((int)sp, from), b0 = (uint32_t)__shfl((int)first, from), b1 = (uint32_t)__shfl((int)last, from);
+        const float sc = __builtin_bit_cast(float, __shfl(__builtin_bit_cast(int, scale), from));
+        bin[j] = min(b0 + (uint32_t)((float)(key[j] - l) * sc), b1);   // (rounding keeps the order of the keys)
+      }
+    }
+  }
+  uint32_t worst;
+  for (int round = 0;; ++round) {
+#pragma unroll
+    for (int j = 0; j < IPT; ++j)
+      if (j * T + tid < m) arr[j] = atomicAdd(&s.cnt[bin[j]], 1u);
+    __syncthreads();
+    uint32_t c[IPT], inc[Q], most = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const uint4 v = reinterpret_cast<const uint4 *>(s.cnt)[q * T + tid];
+      c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
+      most = max(max(most, max(v.x, v.y)), max(v.z, v.w));
+      inc[q] = wave_inclusive_sum_dpp(v.x + v.y + v.z + v.w);
+      if (lane == 63) s.wave[q * NW + w] = inc[q];
+    }
+    uint32_t big = 1;
+    if (__any(most > 1)) {
+      big = 5;
+      if (__any(most > 5)) big = 9;
+      if (__any(most > 9)) big = 17;
+      if (__any(most > 17)) big = !__any(most > 33) ? 33u : !__any(most > 65) ? 65u : !__any(most > BP_MOST) ? BP_MOST : ~0u;
+    }
+    if (lane == 0) s.big[w] = big;
+    __syncthreads();
+    worst = 1;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) worst = max(worst, s.big[x]);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      uint32_t run = inc[q] - (c[4 * q] + c[4 * q + 1] + c[4 * q + 2] + c[4 * q + 3]);
+#pragma unroll
+      for (int x = 0; x < Q * NW; ++x) run += x < q * NW + w ? s.wave[x] : 0u;
+      uint4 v;
+      v.x = run; v.y = v.x + c[4 * q]; v.z = v.y + c[4 * q + 1]; v.w = v.z + c[4 * q + 2];
+      reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = v;
+      if (q == Q - 1 && tid == T - 1) s.cnt[CAP] = v.w + c[4 * q + 3];
+    }
+    if (worst <= LIMIT || round == BP_ROUNDS) break;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      reinterpret_cast<uint4 *>(s.a)[q * T + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
+      reinterpret_cast<uint4 *>(s.b)[q * T + tid] = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (j * T + tid < m) {
+        const uint32_t st = s.cnt[bin[j]], count = s.cnt[bin[j] + 1] - st;
+        slot[j] = bin[j];
+        bin[j] = st;
+        arr[j] = count;
+        if (count > LIMIT) {
+          atomicMin(&s.a[slot[j]], key[j]);
+          atomicMax(&s.b[slot[j]], key[j]);
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (j * T + tid < m && arr[j] > LIMIT) {
+        const uint32_t mn = s.a[slot[j]], mx = s.b[slot[j]];
+        bin[j] += min((uint32_t)((float)(key[j] - mn) * ((float)arr[j] * __builtin_amdgcn_rcpf((float)(mx - mn) + 1.f))), arr[j] - 1);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < IPT; ++j) {
+    slot[j] = 0;
+    if (j * T + tid < m) {
+      const uint32_t st = s.cnt[bin[j]], count = s.cnt[bin[j] + 1] - st;
+      slot[j] = st + arr[j];
+      if (count > 5) atomicMax(&s.reach[slot[j] >> 8], count);
+    }
+  }
+  return worst;
+}
+
+// The m items in s.a (keys) and s.b, in order of the bins, into order of the keys: a key moves by the smaller ones behind it
+// and the larger ones before it, and those lie fewer places away than its bin has keys; nothing beyond a bin's ends
+// counts, so the bins need not be known.  Four items per thread and 16 bytes per read.  Ends with a barrier.
+template <int T, int IPT>
+__device__ __forceinline__ void fix_order(uint32_t m, BinScratch<T, IPT> &s) {
+  const uint4 *a4 = reinterpret_cast<const uint4 *>(s.a), *b4 = reinterpret_cast<const uint4 *>(s.b);
+  const uint32_t n4 = (m + 3) / 4;
+  if (threadIdx.x < 4 * n4 - m) s.a[m + threadIdx.x] = ~0u;
+  __syncthreads();
+  uint32_t k[IPT], v[IPT], pos[IPT];
+#pragma unroll
+  for (int q = 0; q < IPT / 4; ++q) {
+    const uint32_t t = q * T + threadIdx.x;
+    const uint32_t most = max(s.reach[t >> 6], 5u), reach = (most + 2) / 4;   // ceil((most - 1) / 4) blocks to either side
+    if (t < n4) {
+      const uint4 own = a4[t], pay = b4[t];
+      uint32_t *kq = k + 4 * q, *pq = pos + 4 * q;
+      kq[0] = own.x; kq[1] = own.y; kq[2] = own.z; kq[3] = own.w;
+      v[4 * q] = pay.x; v[4 * q + 1] = pay.y; v[4 * q + 2] = pay.z; v[4 * q + 3] = pay.w;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        pq[x] = 4 * t + x;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+          if (y > x) pq[x] += kq[y] < kq[x];
+          if (y < x) pq[x] -= kq[y] > kq[x];
+        }
+      }
+      for (uint32_t d = 1; d <= reach; ++d) {
+        if (t >= d) {
+          const uint4 o = a4[t - d];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) pq[x] -= (uint32_t)(o.x > kq[x]) + (o.y > kq[x]) + (o.z > kq[x]) + (o.w > kq[x]);
+        }
+        if (t + d < n4) {
+          const uint4 o = a4[t + d];
+#pragma unroll
+          for (int x = 0; x < 4; ++x) pq[x] += (uint32_t)(o.x < kq[x]) + (o.y < kq[x]) + (o.z < kq[x]) + (o.w < kq[x]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < IPT / 4; ++q) {
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      if (4 * (q * T + threadIdx.x) + x < m) {
+        s.a[pos[4 * q + x]] = k[4 * q + x];
+        s.b[pos[4 * q + x]] = v[4 * q + x];
+      }
+    }
+  }
+  __syncthreads();
+}
+
+// ------------------------------------------------------------------ children: splitters from a sample, second pass
+constexpr int SM_T = 512, SM_IPT = 8, SM_MOST = SM_T * SM_IPT;   // sampled keys of a parent
+constexpr int BX_T = 512, BX_IPT = 8, BX_TILE = BX_T * BX_IPT;
+
+// One workgroup per parent: its place among the parents, its children and tiles, their splitters.  64 sampled keys per
+// child make a child of twice the average, the most the finish holds, a matter of 3e-9; the call is then run again with
+// the digit passes, as it is when a parent is too large for BK_MAXK children.
+// COO: the whole list is one parent, its keys are built from the coordinates.
+template <bool COO>
+__global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
+  __shared__ BinScratch<SM_T, SM_IPT> s;
+  __shared__ uint32_t s_wave[3][SM_T / 64];
+  __shared__ BkParent s_me;
+  constexpr int PER = BK_MAXBINS / SM_T;
+  const int tid = threadIdx.x;
+  const uint32_t p = blockIdx.x;
+  if (gave_up(a, true)) return;
+  {
+    uint32_t size[PER], k[PER], tiles[PER], ssum = 0, ksum = 0, tsum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const uint32_t x = tid * PER + q;
+      size[q] = x < a.nparents ? (COO ? a.n : a.ptotal[x]) : 0u;
+      k[q] = x < a.nparents ? max((size[q] + BK_TARGET - 1) / BK_TARGET, 1u) : 0u;
+      tiles[q] = (COO || k[q] > 1) ? (size[q] + BX_TILE - 1) / BX_TILE : 0u;
+      ssum += size[q]; ksum += k[q]; tsum += tiles[q];
+    }
+    uint32_t s0 = scan_one_barrier<SM_T>(ssum, s_wave[0]), k0 = scan_one_barrier<SM_T>(ksum, s_wave[1]),
+             t0 = scan_one_barrier<SM_T>(tsum, s_wave[2]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      if ((uint32_t)(tid * PER + q) == p) s_me = BkParent{s0, size[q], k0, k[q], t0};
+      s0 += size[q]; k0 += k[q]; t0 += tiles[q];
+    }
+    if (p == 0 && tid == SM_T - 1) { a.totals[0] = k0; a.totals[1] = t0; }
+  }
+  __syncthreads();
+  const BkParent me = s_me;
+  if (tid == 0) a.parent[p] = me;
+  // (the sums are bounded by what the host allocated for; the guards keep it so whatever the sizes say)
+  for (uint32_t c = tid; c < me.k && me.child0 + c < a.max_children; c += SM_T) {
+    a.child_parent[me.child0 + c] = p;
+    a.cursor[me.child0 + c] = 0;
+    if (c == 0) a.splitter[me.child0] = 0;
+  }
+  if (me.k == 1) return;
+  if (me.k > (uint32_t)BK_MAXK || me.child0 + me.k > a.max_children) {
+    if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
+    return;
+  }
+  const uint32_t ntiles = (me.size + BX_TILE - 1) / BX_TILE;
+  for (uint32_t t = tid; t < ntiles && me.tile0 + t < a.max_tiles; t += SM_T) a.tile_parent[me.tile0 + t] = p;
+  // keys from evenly spaced pieces of the parent, at a scattered place in each (lists often come in a regular order)
+  const uint32_t ns = min(min((uint32_t)SM_MOST, me.k * BK_OVERSAMPLE), me.size), piece = me.size / ns;
+  uint32_t key[SM_IPT], pos[SM_IPT];
+#pragma unroll
+  for (int j = 0; j < SM_IPT; ++j) {
+    const uint32_t i = j * SM_T + tid;
+    key[j] = 0;
+    if (i < ns) {
+      const uint32_t at = me.start + (uint32_t)((uint64_t)i * me.size / ns) + ((i * 0x9E3779B1u + p * 0x85EBCA6Bu) >> 8) % piece;
+      key[j] = COO ? (uint32_t)build_key(a.ks, (uint32_t)a.row[at], (uint32_t)a.col[at]) & low_mask(a.dshift) : a.rec1[at].x;
+    }
+  }
+  __shared__ uint32_t s_sample[64];
+#pragma unroll
+  for (int j = 0; j < SM_IPT; ++j) {
+    const uint32_t i = j * SM_T + tid, x = (i * 64 + ns - 1) / ns;   // item x * ns / 64 for some x < 64?
+    if (i < ns && x < 64 && x * ns / 64 == i) s_sample[x] = key[j];
+  }
+  __syncthreads();
+  const uint32_t most = bin_slots<SM_T, SM_IPT, 33>(key, ns, 0u, low_mask(a.dshift), s_sample[lane_id()], s, pos);
+  if (most > BP_MOST) {
+    if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < SM_IPT; ++j)
+    if (j * SM_T + tid < ns) { s.a[pos[j]] = key[j]; s.b[pos[j]] = 0; }
+  fix_order<SM_T, SM_IPT>(ns, s);
+  for (uint32_t c = tid; c < me.k; c += SM_T)
+    if (c > 0) a.splitter[me.child0 + c] = s.a[(uint32_t)((uint64_t)c * ns / me.k)];
+}
+
+// 16.8 M entries 59 us, 40 M 135: 4.5 and 4.7 TB/s, near the rate of a copy (runs of some 200 entries).
+// A tile of a parent with more than one child: every entry finds its child among the splitters, the tile is put in
+// order of the children in LDS, every child's run goes behind what it already holds (one device atomic per tile and
+// child: a parent's tiles are few).
+template <bool COO>
+__global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
+  __shared__ uint2 s_rec[BX_TILE];
+  __shared__ uint8_t s_bin[BX_TILE];
+  __shared__ uint32_t s_split[BK_MAXK], s_cnt[BK_MAXK], s_goff[BK_MAXK];
+  __shared__ uint32_t s_wave[BX_T / 64];
+  const uint32_t t = xcd_tile(blockIdx.x, a.tiles_per_xcd);
+  if (gave_up(a, !COO)) return;   // (COO: this kernel is the one that finds coordinates out of range)
+  if (t >= min(a.totals[1], a.max_tiles)) return;
+  const BkParent me = a.parent[COO ? 0u : a.tile_parent[t]];
+  const int tid = threadIdx.x;
+  if (me.k > (uint32_t)BK_MAXK) return;
+  const uint32_t first = me.start + (t - me.tile0) * BX_TILE, in_tile = min((uint32_t)BX_TILE, me.start + me.size - first);
+  if (tid < BK_MAXK) {
+    s_split[tid] = (uint32_t)tid < me.k ? a.splitter[me.child0 + tid] : 0xFFFFFFFFu;
+    s_cnt[tid] = 0;
+  }
+  uint32_t key[BX_IPT], val[BX_IPT], bin[BX_IPT], arr[BX_IPT];
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < BX_IPT; ++j) {
+    const uint32_t i = j * BX_T + tid;
+    key[j] = 0; val[j] = 0;
+    if (i < in_tile) {
+      if (COO) {
+        const uint32_t r = (uint32_t)a.row[first + i], c = (uint32_t)a.col[first + i];
+        bad |= coo_out_of_range(a.ks, r, c);
+        key[j] = (uint32_t)build_key(a.ks, r, c) & low_mask(a.dshift);
+        val[j] = a.val[first + i];
+      } else {
+        const uint2 r = a.rec1[first + i];
+        key[j] = r.x; val[j] = r.y;
+      }
+    }
+  }
+  if (COO && bad) a.flags->index_range = 1;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < BX_IPT; ++j) bin[j] = 0;
+  for (uint32_t step = 1u << (31 - __clz((int)me.k)); step; step >>= 1) {   // last child whose splitter is not above the key
+#pragma unroll
+    for (int j = 0; j < BX_IPT; ++j) {
+      const uint32_t at = bin[j] + step;
+      if (at < me.k && s_split[at] <= key[j]) bin[j] = at;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < BX_IPT; ++j) arr[j] = j * BX_T + tid < in_tile ? atomicAdd(&s_cnt[bin[j]], 1u) : 0u;
+  __syncthreads();
+  const uint32_t c = tid < BK_MAXK ? s_cnt[tid] : 0u;
+  const uint32_t start = scan_one_barrier<BX_T>(c, s_wave);
+  if (tid < BK_MAXK) {
+    uint32_t at = 0;
+    if (c) {
+      at = atomicAdd(&a.cursor[me.child0 + tid], c);
+      if (at + c > (uint32_t)BK_CAP) a.flags->retry = RETRY_SORT_LDS;
+    }
+    s_cnt[tid] = start;
+    s_goff[tid] = at - start;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < BX_IPT; ++j) {
+    if (j * BX_T + tid < in_tile) {
+      const uint32_t pos = s_cnt[bin[j]] + arr[j];
+      s_rec[pos] = make_uint2(key[j], val[j]);
+      s_bin[pos] = (uint8_t)bin[j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < BX_IPT; ++j) {
+    const uint32_t i = j * BX_T + tid;
+    if (i < in_tile) {
+      const uint32_t child = s_bin[i], at = s_goff[child] + i;
+      if (at < (uint32_t)BK_CAP) a.rec2[(size_t)(me.child0 + child) * BK_CAP + at] = s_rec[i];
+    }
+  }
+}
+
+// ------------------------------------------------------------------ finish: a child per workgroup
+// 16.8 M entries of the power-law matrix 162 us, 40 M with local columns 410 (65 and 152 when it only reads and writes);
+// LDS is busy 61 % of the time and the vector units 66 %.  Children of 2048 entries on average, 512 threads: 297 and 810.
+// Four digit passes of ballot ranking in LDS instead of the splitters would take 280 vector instructions an entry,
+// this takes 230; cutting by row or by range first and again by smallest and largest key until no bin
+// holds more than 9: 177 and 602, three quarters of it LDS atomics and reads that meet in a bank.
+constexpr int BF_T = 256, BF_IPT = BK_CAP / BF_T;
+
+__global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
+  __shared__ BinScratch<BF_T, BF_IPT> s;
+  __shared__ uint32_t s_before;
+  const uint32_t c = xcd_tile(blockIdx.x, a.children_per_xcd);
+  if (gave_up(a, true) || c >= min(a.totals[0], a.max_children)) return;
+  const int tid = threadIdx.x;
+  const uint32_t p = a.child_parent[c];
+  const BkParent me = a.parent[p];
+  const uint32_t j0 = c - me.child0;
+  if (me.k > (uint32_t)BK_MAXK) return;
+  if (tid == 0) s_before = 0;
+  __syncthreads();
+  const bool split = me.k > 1 || !a.rec1;   // (one parent, the caller's list: always)
+  if (split && (uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[me.child0 + tid]);   // j0 < BK_MAXK <= BF_T
+  const uint32_t m = split ? a.cursor[c] : me.size;
+  if (m > (uint32_t)BK_CAP) return;   // (the call will be run again)
+  const uint2 *src = split ? a.rec2 + (size_t)c * BK_CAP : a.rec1 + me.start;
+  const uint32_t lmask = low_mask(a.dshift);
+  const uint32_t lo = j0 > 0 ? a.splitter[c] : 0u, hi = j0 + 1 < me.k ? a.splitter[c + 1] : lmask;   // (hi itself may be the next child's)
+  uint32_t key[BF_IPT], val[BF_IPT], pos[BF_IPT];
+#pragma unroll
+  for (int j = 0; j < BF_IPT; ++j) {
+    key[j] = 0; val[j] = 0;
+    if (j * BF_T + tid < m) {
+      const uint2 r = src[j * BF_T + tid];
+      key[j] = r.x; val[j] = r.y;
+    }
+  }
+  const uint32_t sample = tid < 64 && m >= 64 ? src[(uint32_t)tid * m / 64].x : 0u;
+  const uint32_t most = bin_slots<BF_T, BF_IPT, 65>(key, m, lo, hi, sample, s, pos);
+#pragma unroll
+  for (int j = 0; j < BF_IPT; ++j)
+    if (j * BF_T + tid < m) { s.a[pos[j]] = key[j]; s.b[pos[j]] = val[j]; }
+  if (most <= BP_MOST) {
+    fix_order<BF_T, BF_IPT>(m, s);
+  } else {   // keys that crowd in more than a few places of their range
+    __syncthreads();
+    for (uint32_t size = 2; size < 2 * m; size <<= 1) {   // bitonic, all comparisons ascending; items past m are not there
+      for (uint32_t half = size >> 1; half > 0; half >>= 1) {
+        const uint32_t flip = half == size >> 1 ? size - 1 : half;
+        for (uint32_t t = tid; t < (uint32_t)BK_CAP / 2; t += BF_T) {
+          const uint32_t i = (t & (half - 1)) + ((t & ~(half - 1)) << 1), k = i ^ flip;
+          if (k < m && s.a[i] > s.a[k]) {
+            const uint32_t x = s.a[i], y = s.b[i];
+            s.a[i] = s.a[k]; s.a[k] = x; s.b[i] = s.b[k]; s.b[k] = y;
+          }
+        }
+        __syncthreads();
+      }
+    }
+  }
+  const uint32_t out = me.start + s_before;
+  const Key base = (Key)p << a.dshift;
+  const Key bmask = ((Key)1 << a.ks.b_bits) - 1;
+  bool dup = false;
+  for (uint32_t i = tid; i < m; i += BF_T) {
+    const Key full = base | s.a[i];
+    dup |= i > 0 && s.a[i - 1] == s.a[i];
+    if (out + i < a.n) {
+      if (a.major_out) a.major_out[out + i] = (int32_t)(full >> a.ks.b_bits);
+      a.minor_out[out + i] = (int32_t)(full & bmask);
+      a.val_out[out + i] = s.b[i];
+    }
+  }
+  if (dup) a.flags->duplicate = 1;
+  if (a.ptr) {   // the major indices whose first possible key lies in this child's range: entries below that key
+    const Key l = base | lo, h = base | hi;
+    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = j0 + 1 < me.k ? (h + bmask) >> a.ks.b_bits : (h >> a.ks.b_bits) + 1;
+    if (p + 1 == a.nparents && j0 + 1 == me.k) g1 = (Key)a.ngroups_out + 1;
+    if (g1 > (Key)a.ngroups_out + 1) g1 = (Key)a.ngroups_out + 1;
+    for (Key g = g0 + tid; g < g1; g += BF_T) {
+      const Key first = (g << a.ks.b_bits) - base;   // may lie beyond 32 bits (behind the last key): all entries are below
+      uint32_t b = 0, e = m;
+      while (b < e) {
+        const uint32_t mid = (b + e) >> 1;
+        if ((Key)s.a[mid] < first) b = mid + 1; else e = mid;
+      }
+      a.ptr[g] = (int32_t)(out + b);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ host
+// first pass, threads and entries per thread, and workgroups: as many as are resident at once
+constexpr int BP_T = 512, BP_IPT = 8, BP_GROUPS = 768, BPL_T = 1024, BPL_IPT = 12, BPL_GROUPS = 256;
+
+struct BucketPlan {
+  bool direct;     // one parent: the caller's list
+  int bits;        // of the parents
+  bool large;      // the first pass takes large tiles
+  uint32_t nparents, per_group, ngroups, max_children, max_tiles;
+};
+
+static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
+  BucketPlan b{};
+  b.direct = ks.total_bits <= 32 && nnz <= BK_MAXK / 2 * BK_TARGET;
+  if (b.direct) {
+    b.nparents = 1;
+  } else {
+    b.bits = bits_for((uint64_t)nnz / 32768);
+    if (b.bits < ks.total_bits - 32) b.bits = ks.total_bits - 32;
+    if (b.bits > BK_MAXBITS) b.bits = BK_MAXBITS;
+    if (b.bits > ks.total_bits) b.bits = ks.total_bits;
+    b.nparents = 1u << b.bits;
+    b.large = nnz >= (1 << 23);
+    const uint32_t tile = b.large ? BPL_T * BPL_IPT : BP_T * BP_IPT, groups = b.large ? BPL_GROUPS : BP_GROUPS;
+    const uint32_t tiles = (uint32_t)ceil_div<int64_t>(nnz, tile), each = ceil_div(tiles, groups);
+    b.per_group = each * tile;
+    b.ngroups = ceil_div(tiles, each);
+  }
+  b.max_children = (uint32_t)(nnz / BK_TARGET) + b.nparents + 1;
+  b.max_tiles = (uint32_t)(nnz / BX_TILE) + (uint32_t)std::min<int64_t>(b.nparents, nnz / BK_TARGET) + 1;
+  return b;
+}
+
+// (row, col) tuples whose key below the parents' bits fits 32 bits, in numbers that leave parents room for uneven sizes:
+// a parent of twice the average has children enough up to 67 M entries.
+bool bucket_sort_takes(int64_t nnz, const KeySpec &ks) {
+  return nnz >= 1 && ks.mode == 0 && ks.total_bits >= 1 && ks.total_bits - BK_MAXBITS <= 32 &&
+         (nnz >> (ks.total_bits < BK_MAXBITS ? ks.total_bits : BK_MAXBITS)) <= BK_MAXK / 2 * BK_TARGET;
+}
+
+size_t bucket_sort_temp_bytes(int64_t nnz, const KeySpec &ks) {
+  const BucketPlan b = bucket_plan(nnz, ks);
+  auto g = [](size_t bytes) { return Env::granule(bytes); };
+  return (b.direct ? 0 : g(4ull * b.ngroups * b.nparents) + g(4ull * b.nparents) + g(8ull * nnz)) + g(sizeof(BkParent) * b.nparents) +
+         g(8) + 3 * g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_children);
+}
+
+void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz, const KeySpec &ks,
+                 SortOut &out, Flags *flags) {
+  const BucketPlan b = bucket_plan(nnz, ks);
+  BkArgs a{};
+  a.row = row; a.col = col; a.val = (const uint32_t *)val;
+  a.n = (uint32_t)nnz; a.ks = ks; a.flags = flags;
+  a.dshift = ks.total_bits - b.bits;
+  const int lead_at = ks.total_bits - bits_for(ks.mode == 0 ? ks.a_extent - 1 : ceil_div(ks.a_extent, ks.bh) - 1);
+  a.lead_shift = a.dshift >= lead_at ? a.dshift - lead_at : -1;
+  a.nparents = b.nparents; a.per_group = b.per_group; a.ngroups = b.ngroups;
+  a.groups_per_xcd = ceil_div<uint32_t>(b.ngroups, 8u);
+  a.coo_vec = ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
+  a.max_children = b.max_children; a.max_tiles = b.max_tiles;
+  a.tiles_per_xcd = ceil_div<uint32_t>(b.max_tiles, 8u);
+  a.children_per_xcd = ceil_div<uint32_t>(b.max_children, 8u);
+  env.reserve(bucket_sort_temp_bytes(nnz, ks));
+  if (!b.direct) {
+    a.hist = env.temp<uint32_t>((size_t)b.ngroups * b.nparents);
+    a.ptotal = env.temp<uint32_t>(b.nparents);
+    a.rec1 = env.temp<uint2>(nnz);
+  }
+  a.parent = env.temp<BkParent>(b.nparents);
+  a.totals = env.temp<uint32_t>(2);
+  a.child_parent = env.temp<uint32_t>(b.max_children);
+  a.splitter = env.temp<uint32_t>(b.max_children);
+  a.cursor = env.temp<uint32_t>(b.max_children);
+  a.tile_parent = env.temp<uint32_t>(b.max_tiles);
+  a.rec2 = env.temp<uint2>((size_t)b.max_children * BK_CAP);
+  if (!env.ok()) return;
+  if (!b.direct) {
+    US_LAUNCH(env, "bucket_hist", (a.lead_shift >= 0 ? 4.0 : 8.0) * nnz, bucket_hist_kernel, a.groups_per_xcd * 8, BH_T, a);
+    US_LAUNCH(env, "bucket_scan", 8.0 * b.ngroups * b.nparents, bucket_scan_kernel, ceil_div<uint32_t>(b.nparents, BS_BINS), BS_T, a);
+    if (b.large) US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BPL_T, BPL_IPT>), a.groups_per_xcd * 8, BPL_T, a);
+    else US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BP_T, BP_IPT>), a.groups_per_xcd * 8, BP_T, a);
+    US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<false>), b.nparents, SM_T, a);
+    US_LAUNCH(env, "bucket_split", 16.0 * nnz, (bucket_split_kernel<false>), a.tiles_per_xcd * 8, BX_T, a);
+  } else {
+    US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<true>), b.nparents, SM_T, a);
+    US_LAUNCH(env, "bucket_split", 20.0 * nnz, (bucket_split_kernel<true>), a.tiles_per_xcd * 8, BX_T, a);
+  }
+  if (out.late) {
+    out.late(out); out.late = nullptr;
+    if (!env.ok()) return;
+  }
+  a.major_out = out.major; a.minor_out = out.minor; a.val_out = (uint32_t *)out.val;
+  a.ptr = out.ptr; a.ngroups_out = ks.a_extent;
+  US_LAUNCH(env, "bucket_finish", (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
+}
+
+}  // namespace us

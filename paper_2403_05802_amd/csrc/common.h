@@ -231,15 +231,25 @@ struct SortOut {
   // predecessor's, i.e. the nodes that start in the tile.  Only the finish inside LDS counts them (it has the sorted
   // keys at hand): *node_counted says whether it did.
   uint32_t *node_count = nullptr; bool *node_counted = nullptr;
+  // Unpacked output: pointers over the major indices 0..a_extent (null: none) are left by a sort that has them at hand,
+  // which says so in ptr_done; with them `major` may be null.
+  int32_t *ptr = nullptr; bool ptr_done = false;
   // The list comes in ascending order of its minor index (mode 0, unpacked output): a stable sort by the major index
   // alone gives the (major, minor) order.
   bool minor_sorted = false;
 };
 constexpr int NODE_TILE_SHIFT = 11, NODE_TILE = 1 << NODE_TILE_SHIFT;
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,
-              const KeySpec &ks, const SortOut &out, Flags *flags_dev);
-// what a whole-array sort of nnz entries takes from Env::temp (for Env::reserve by a caller with temporaries of its own)
-size_t sort_temp_bytes(int64_t nnz);
+              const KeySpec &ks, SortOut &out, Flags *flags_dev);
+// what the sort of nnz entries into unpacked output takes from Env::temp (for Env::reserve by a caller with temporaries of
+// its own), and whether it leaves pointers over the major indices
+size_t sort_temp_bytes(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted);
+bool sort_gives_ptr(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted);
+// bucket_sort.hip
+bool bucket_sort_takes(int64_t nnz, const KeySpec &ks);
+size_t bucket_sort_temp_bytes(int64_t nnz, const KeySpec &ks);
+void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz, const KeySpec &ks,
+                 SortOut &out, Flags *flags_dev);
 // stable ascending sort of 32-bit keys with a 32-bit payload that travels with its key
 void sort_u32_payload(Env &env, const uint32_t *key, const uint32_t *payload, int64_t n, int bits, uint32_t *key_out,
                       uint32_t *payload_out, Flags *flags_dev);

@@ -384,9 +384,11 @@ static void product_scratch(Env &env, us_formatted *f) {
 // that move into the result (or are released when the format re-lays them out: ELL).
 us_status build_from_sorted(Env &env, const Plan &plan, const us_format_desc &desc, int64_t nrows,
                             int64_t ncols, int64_t nnz, int32_t *major, int32_t *minor, float *val,
-                            Flags *flags, bool check_dups, us_formatted **out, bool validated, bool major_is_temp) {
+                            Flags *flags, bool check_dups, us_formatted **out, bool validated, bool major_is_temp, int32_t *ptr) {
   // Takes ownership of major, minor and val (arrays of nnz entries from Env::owned; major from Env::temp if
   // major_is_temp, which the COO layout, the one that keeps it, does not allow).
+  // ptr: pointers over every major index that the sort has left (from Env::owned for CSR, which keeps them, else from
+  // Env::temp), major may then be null; or null.
   // validated: the caller has already read the flags after the sort (indices are in range).
   if (major_is_temp && plan.pattern == P_COO) return US_ERR_UNSUPPORTED_DESC;
   us_formatted *f = new us_formatted();
@@ -418,15 +420,11 @@ us_status build_from_sorted(Env &env, const Plan &plan, const us_format_desc &de
   }
 
   // pointers over every major index (Fill(0) + Merge(0))
-  int32_t *ptr;
-  if (plan.pattern == P_CSR) {
-    ptr = env.owned<int32_t>(nmaj + 1);
-    f->level[1].ptr = ptr; f->level[1].nptr = nmaj + 1;
-  } else {
-    ptr = env.temp<int32_t>(nmaj + 1);
-  }
+  const bool have_ptr = ptr != nullptr;
+  if (!have_ptr) ptr = plan.pattern == P_CSR ? env.owned<int32_t>(nmaj + 1) : env.temp<int32_t>(nmaj + 1);
+  if (plan.pattern == P_CSR) { f->level[1].ptr = ptr; f->level[1].nptr = nmaj + 1; }
   if (!env.ok()) return finish(env.status);
-  sorted_ptr(env, major, minor, nnz, nmaj, ptr, check_dups, flags);
+  if (!have_ptr) sorted_ptr(env, major, minor, nnz, nmaj, ptr, check_dups, flags);
 
   if (plan.pattern == P_CSR) {
     f->nlevels = 2;
@@ -506,13 +504,16 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
   const bool rowcol = by_sort && plan.pattern != P_CISR;   // built below from the (major, minor) order
   const int64_t n = coo.nnz;
   size_t late_res = 0;
+  const KeySpec ks = rowcol_keyspec(coo, plan.swapped);
+  const bool keep_major = plan.pattern == P_COO;
+  const bool with_ptr = rowcol && !keep_major && sort_gives_ptr(env, n, ks, minor_sorted);
   if (by_sort) {
     // two calls into the caller's allocator for the whole conversion: the flags, the sort's buffers and the other
     // temporaries in one block, the arrays of the result in another (each call costs microseconds of an idle GPU)
     auto g = [](size_t count) { return Env::granule(4 * count); };
     const size_t nmaj = (size_t)(plan.swapped ? coo.ncols : coo.nrows), cap = nmaj < (size_t)n ? nmaj : (size_t)n;
-    size_t tmp = sort_temp_bytes(n) + 4 * Env::granule(sizeof(Flags)), res = 0;
-    if (rowcol && plan.pattern != P_COO) tmp += g(n);   // the major indices: only the COO layout keeps them
+    size_t tmp = sort_temp_bytes(env, n, ks, minor_sorted) + 4 * Env::granule(sizeof(Flags)), res = 0;
+    if (rowcol && !keep_major && !with_ptr) tmp += g(n);   // the major indices: only the COO layout keeps them
     if (plan.pattern == P_COO) res = 3 * g(n);
     // (with the tile starts of the product goes its scratch, two words per tile: the first product then allocates nothing)
     if (plan.pattern == P_CSR) res = 2 * g(n) + g(nmaj + 1) + g(spmv_tiles(nmaj, n) + 1) + 2 * g(spmv_tiles(nmaj, n));
@@ -538,22 +539,27 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
   if (plan.pattern == P_CSB) return convert_csb(env, coo, plan, desc, flags, out);
   if (plan.pattern == P_CISR) return convert_cisr(env, coo, plan, desc, flags, out);
   // COO / CSR / DCSR / ELL: sort by (major, minor), then build
-  const bool keep_major = plan.pattern == P_COO;
-  int32_t *major = nullptr, *minor = nullptr;
+  int32_t *major = nullptr, *minor = nullptr, *ptr = nullptr;
   float *val = nullptr;
   SortOut so{};
   so.minor_sorted = minor_sorted;
   so.late = [&](SortOut &o) {
     if (late_res) env.reserve_out(late_res);
-    major = keep_major ? env.owned<int32_t>(n) : env.temp<int32_t>(n);
+    if (with_ptr) ptr = plan.pattern == P_CSR ? env.owned<int32_t>((size_t)ks.a_extent + 1) : env.temp<int32_t>((size_t)ks.a_extent + 1);
+    else major = keep_major ? env.owned<int32_t>(n) : env.temp<int32_t>(n);
     minor = env.owned<int32_t>(n);
     val = env.owned<float>(n);
-    o.major = major; o.minor = minor; o.val = val;
+    o.major = major; o.minor = minor; o.val = val; o.ptr = ptr;
   };
-  const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, rowcol_keyspec(coo, plan.swapped), so, flags);
-  if (!env.ok()) { if (keep_major) env.free_raw(major); env.free_raw(minor); env.free_raw(val); return env.status; }
+  const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, ks, so, flags);
+  if (!env.ok()) {
+    if (keep_major) env.free_raw(major);
+    if (plan.pattern == P_CSR) env.free_raw(ptr);
+    env.free_raw(minor); env.free_raw(val);
+    return env.status;
+  }
   return build_from_sorted(env, plan, desc, coo.nrows, coo.ncols, n, major, minor, val, flags, !checked, out, false,
-                           !keep_major);
+                           !keep_major, ptr);
 }
 
 us_status convert_impl(Env &env, const us_coo &coo, const us_format_desc &desc, us_formatted **out) {

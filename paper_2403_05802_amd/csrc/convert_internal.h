@@ -43,7 +43,7 @@ us_formatted *new_ell_of_rows(Env &env, const us_format_desc &desc, int64_t nrow
                               int64_t clip, const int32_t *minor, const float *val, const int32_t *ptr, Flags *flags);
 us_status build_from_sorted(Env &env, const Plan &plan, const us_format_desc &desc, int64_t nrows, int64_t ncols,
                             int64_t nnz, int32_t *major, int32_t *minor, float *val, Flags *flags, bool check_dups,
-                            us_formatted **out, bool validated = false, bool major_is_temp = false);
+                            us_formatted **out, bool validated = false, bool major_is_temp = false, int32_t *ptr = nullptr);
 // minor_sorted: the list is in ascending order of the plan's minor index (SortOut::minor_sorted)
 us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const us_format_desc &desc, us_formatted **out,
                             bool minor_sorted = false);

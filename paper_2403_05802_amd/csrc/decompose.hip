@@ -121,7 +121,7 @@ static us_status decompose_rank(Env &env, const us_coo &coo, const Plan &pa, con
   const int64_t n = coo.nnz, nrows = coo.nrows;
   {  // every temporary of the call in one allocation
     auto g = [](size_t count) { return Env::granule(4 * count); };
-    env.reserve(sort_temp_bytes(n) + 3 * g(n) + 3 * g(nrows + 1) + g(nrows) + g(nrows / 1024 + 64) +
+    env.reserve(sort_temp_bytes(env, n, rowcol_keyspec(coo, false), false) + 3 * g(n) + 3 * g(nrows + 1) + g(nrows) + g(nrows / 1024 + 64) +
                 Env::granule(sizeof(SelectState)) + 4 * Env::granule(sizeof(Flags)));
   }
   Flags *flags = new_flags(env);
@@ -131,8 +131,9 @@ static us_status decompose_rank(Env &env, const us_coo &coo, const Plan &pa, con
   if (!env.ok()) return env.status;
   SortOut so{};
   so.major = major; so.minor = minor; so.val = val;
+  if (sort_gives_ptr(env, n, rowcol_keyspec(coo, false), false)) so.ptr = ptr;
   const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, rowcol_keyspec(coo, false), so, flags);
-  sorted_ptr(env, major, minor, n, nrows, ptr, !checked, flags);
+  if (!so.ptr_done) sorted_ptr(env, major, minor, n, nrows, ptr, !checked, flags);
   Flags h{};
   int64_t K = pred.abs;
   if (pred.kind == US_P_RANK_LT_PERCENTILE) {

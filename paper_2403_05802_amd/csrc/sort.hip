@@ -34,30 +34,14 @@
 // then a sort inside every row) is no way round the digit passes: on the 16.8 M entries and 2^20 rows of the
 // power-law workload the histogram alone took 0.91 ms (18 G atomics per second to scattered addresses) and the
 // cursor scatter 1.5 ms, against 0.68 ms for all five passes here.
-#include "common.h"
 #include "device.h"
+#include "sort_key.h"
 
 namespace us {
 
 constexpr int RS_T = 512, RS_IPT = 8, RS_TILE = RS_T * RS_IPT, RS_NW = RS_T / 64, RS_MAXBITS = 8, RS_BINS = 1 << RS_MAXBITS;
 constexpr int RS_CHUNK = 32;  // tiles per workgroup of the chunk scan
 constexpr int RS_HC = 16;     // histogram kernel: counters per digit
-
-typedef uint64_t Key;  // keys live in registers and LDS as 64-bit words whatever their storage
-
-__device__ __forceinline__ Key build_key(const KeySpec &ks, uint32_t r, uint32_t c) {
-  uint32_t a = ks.swap ? c : r, b = ks.swap ? r : c;
-  if (ks.mode == 0) return ((Key)a << ks.b_bits) | (Key)b;
-  // (a coordinate out of range is reported, not sorted; its second field is still cut to b_bits so that it cannot
-  // leak into the leading field, whose digits the first histogram may take from a / bh alone)
-  const Key field = ((Key)1 << ks.b_bits) - 1;
-  if (ks.mode == 2) {   // Skew(0,1,-1) then TileSplit(0,bh): (a/bh, b-a, a%bh), the diagonal biased to be >= 0
-    uint32_t ab = a / ks.bh, ai = a - ab * ks.bh, dg = b - a + (ks.a_extent - 1);
-    return ((((Key)ab << ks.b_bits) | ((Key)dg & field)) << ks.ih_bits) | (Key)ai;
-  }
-  uint32_t ab = a / ks.bh, ai = a - ab * ks.bh, bb = b / ks.bw, bi = b - bb * ks.bw;
-  return (((((Key)ab << ks.b_bits) | ((Key)bb & field)) << ks.ih_bits | (Key)ai) << ks.iw_bits) | (Key)bi;
-}
 
 enum { IN_COO = 0, IN_SPLIT = 1, IN_KEY32 = 2 };
 enum { OUT_SPLIT = 0, OUT_UNPACK = 1, OUT_KEY64 = 2, OUT_KEY32 = 3 };
@@ -92,10 +76,6 @@ struct PassArgs {
   Flags *flags;
 };
 
-__device__ __forceinline__ bool coo_out_of_range(const KeySpec &ks, uint32_t r, uint32_t c) {
-  return ((ks.swap ? c : r) >= ks.a_extent) | ((ks.swap ? r : c) >= ks.b_extent);
-}
-
 template <int IN>
 __device__ __forceinline__ void load_item(const PassArgs &a, uint32_t i, Key *key, uint32_t *val, bool *bad) {
   if (IN == IN_COO) {
@@ -112,11 +92,6 @@ __device__ __forceinline__ void load_item(const PassArgs &a, uint32_t i, Key *ke
     *val = r.val;
   }
 }
-
-// Workgroups are dealt round-robin to the 8 XCDs.  Mapping launch index i to tile
-// (i % 8) * tiles_per_xcd + i / 8 lets each XCD work through one contiguous range of tiles, so
-// the partial cache lines at the ends of neighbouring tiles' runs meet in the same L2.
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t i, uint32_t per_xcd) { return (i & 7u) * per_xcd + (i >> 3); }
 
 template <int IN>
 __global__ __launch_bounds__(RS_T) void radix_hist_kernel(PassArgs a) {
@@ -1156,15 +1131,35 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   return true;
 }
 
-size_t sort_temp_bytes(int64_t nnz) {
+// Lists that are sorted by buckets (bucket_sort.hip) unless the context asks for one of the two ways here: all that it
+// takes but short lists of more than 24 key bits, which one digit pass and the finish in LDS sort in as few launches
+// (85-100 us against 97-110), and lists in order of their minor index up to 2 M entries, which take passes over the major
+// digits alone (CSR -> CSC, digit passes / buckets, us: 1.5 M entries 123 / 125, 3.1 M 173 / 162, 16.8 M 508 / 445).
+static bool by_buckets(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
+  if (env.lds_finish >= 0 || !bucket_sort_takes(nnz, ks)) return false;
+  if (minor_sorted) return nnz > (1 << 21);
+  return nnz > (int64_t)RS_SMALL * RS_TILE || ks.total_bits <= 3 * RS_MAXBITS;
+}
+bool sort_gives_ptr(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
+  return by_buckets(env, nnz, ks, minor_sorted) && nnz >= ks.a_extent;
+}
+
+size_t sort_temp_bytes(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
   if (nnz <= 0) return 0;
+  if (by_buckets(env, nnz, ks, minor_sorted)) return bucket_sort_temp_bytes(nnz, ks);
   const size_t nblocks = (size_t)ceil_div<int64_t>(nnz, RS_TILE), nchunks = ceil_div<size_t>(nblocks, RS_CHUNK);
   return 2 * Env::granule(sizeof(Rec) * nnz) + 2 * Env::granule(nnz + 16) + Env::granule(4ull * RS_BINS * nblocks) +
          (nblocks <= (size_t)RS_SMALL ? 0 : Env::granule(4ull * RS_BINS * nchunks) + Env::granule(4ull * RS_BINS));
 }
 
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,
-              const KeySpec &ks, const SortOut &out, Flags *flags_dev) {
+              const KeySpec &ks, SortOut &out, Flags *flags_dev) {
+  if (env.ok() && (out.late || out.major) && by_buckets(env, nnz, ks, out.minor_sorted)) {
+    if (out.node_counted) *out.node_counted = false;
+    bucket_sort(env, row, col, val, nnz, ks, out, flags_dev);
+    out.ptr_done = out.ptr != nullptr;
+    return true;
+  }
   return sort_generic(env, IN_COO, row, col, nullptr, val, nnz, ks, out, flags_dev);
 }
 

@@ -1,0 +1,143 @@
+"""The sort by buckets (most significant digits first, children cut by sampled splitters, finished in LDS) against the
+oracle: the edges of its tiles, children and key widths, rows and clusters that a digit cannot part, lists that are
+not 16-byte aligned, and the inputs that it hands on to the digit passes."""
+import numpy as np
+import pytest
+
+from oracle import unisparse_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2403_05802_amd import binding as B
+    return B.Context("cuda:0")
+
+
+def entries(rng, nr, nc, n, kind):
+    """n distinct coordinates (fewer where `kind` repeats itself), in random order."""
+    if kind == "sorted" or kind == "uniform":
+        lin = rng.choice(nr * nc, n, replace=False) if nr * nc < 1 << 25 else np.unique(rng.integers(0, nr * nc, n))
+    elif kind == "heavy":        # half of the entries in two rows, the rest spread
+        lin = np.concatenate([rng.integers(0, nr * nc, n // 2), nr // 2 * nc + rng.integers(0, nc, n // 3),
+                              (nr - 1) * nc + rng.integers(0, nc, n // 6)])
+    elif kind == "clusters":     # rows of very different lengths, most columns within a few hundred of the row
+        row = (nr * rng.random(n) ** 3).astype(np.int64)
+        col = np.where(rng.random(n) < 0.7, np.clip(row * nc // nr + rng.integers(-200, 201, n), 0, nc - 1), rng.integers(0, nc, n))
+        lin = row * nc + col
+    else:                        # "powers": keys that crowd towards zero, more in every octave than a cut can part
+        lin = (2.0 ** (rng.random(n) * np.log2(nr * nc - 1))).astype(np.int64)
+    lin = np.unique(lin)
+    if kind != "sorted":
+        lin = rng.permutation(lin)
+    r, c = (lin // nc).astype(np.int32), (lin % nc).astype(np.int32)
+    return r, c, rng.uniform(0.1, 1, r.size).astype(np.float32)
+
+
+def unaligned(a):
+    """The array on the GPU, four bytes past a 16-byte boundary."""
+    import torch
+    t = torch.empty(a.size + 1, dtype=torch.from_numpy(a[:0]).dtype, device="cuda")
+    t[1:] = torch.from_numpy(a).cuda()
+    return t[1:]
+
+
+def run(ctx, nr, nc, r, c, v, d, put):
+    """The layout and the kernels of the conversion."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import us_desc_of
+    ctx.enable_profile(); ctx.profile_reset()
+    try:
+        g = B.us_convert(ctx, nr, nc, put(r), put(c), put(v), us_desc_of(d))
+        return g, {e["kernel"]: e["launches"] for e in ctx.profile_report()}
+    finally:
+        ctx.disable_profile()
+
+
+# one parent (24 bits at most, up to 65,536 entries): one child and the second, the tile of 4096, the last size;
+# beyond it, and beyond 262,144 entries of wider keys: parents of one and of several children, 32, 33 and 42 bits
+SIZES = [(1, 1, 1), (64, 64, 1000), (4096, 4096, 1024), (4096, 4096, 1025), (4096, 4096, 4096), (4096, 4096, 4097), (3, 4097, 9001),
+         (4096, 4096, 65536), (4096, 4096, 65537), (4096, 4095, 300_001), (65536, 65536, 270_000), (65537, 65536, 270_001),
+         (1 << 21, 1 << 21, 300_000), (5, 1 << 24, 400_000), (1 << 22, 9, 700_003)]
+
+
+@pytest.mark.parametrize("kind", ["uniform", "sorted", "heavy", "clusters"])
+@pytest.mark.parametrize("nr,nc,n", SIZES)
+def test_matches_the_oracle(ctx, nr, nc, n, kind):
+    from helpers import assert_same_layout, dev
+    r, c, v = entries(np.random.default_rng(nr + nc + n), nr, nc, n, kind)
+    put = unaligned if kind == "clusters" else dev
+    descs = [O.CSR(), O.CSC(), O.COO()] + ([O.DCSR()] if kind == "heavy" else [])
+    for d in descs:
+        g, launches = run(ctx, nr, nc, r, c, v, d, put)
+        if kind in ("uniform", "sorted") and nr * nc > 1:
+            assert "bucket_finish" in launches and "radix_scatter" not in launches, (d, launches)
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{kind} {nr}x{nc}, {r.size} entries -> {d}")
+        g.free()
+
+
+@pytest.mark.parametrize("nr,nc,n", [(4096, 4096, 60_000), (1 << 20, 1 << 20, 400_000)])
+def test_keys_that_crowd_in_every_octave(ctx, nr, nc, n):
+    from helpers import assert_same_layout, dev
+    r, c, v = entries(np.random.default_rng(n), nr, nc, n, "powers")
+    for d in (O.CSR(), O.COO()):
+        g, _ = run(ctx, nr, nc, r, c, v, d, dev)
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{r.size} entries -> {d}")
+        g.free()
+
+
+def test_a_parent_of_too_many_entries_goes_to_the_digit_passes(ctx):
+    """300,000 entries in 4 of 2^20 rows: one sixteenth of the key range holds them all."""
+    from helpers import assert_same_layout, dev
+    rng = np.random.default_rng(3)
+    nr = nc = 1 << 20
+    lin = rng.permutation(np.unique(rng.integers(0, 4 * nc, 300_000)))
+    r, c = (lin // nc).astype(np.int32), (lin % nc).astype(np.int32)
+    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
+    for d in (O.CSR(), O.COO()):
+        g, launches = run(ctx, nr, nc, r, c, v, d, dev)
+        assert launches["radix_scatter"] == 5, launches
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), str(d))
+        g.free()
+
+
+@pytest.mark.parametrize("nr,nc,n", [(4096, 4096, 30_000), (70_000, 70_000, 300_000)])
+def test_errors_are_reported(ctx, nr, nc, n):
+    from paper_2403_05802_amd import binding as B
+    from helpers import dev, us_desc_of
+    rng = np.random.default_rng(n)
+    r, c, v = entries(rng, nr, nc, n, "heavy")
+    for at in (0, r.size // 2, int(np.flatnonzero(r == nr // 2)[5])):
+        r2, c2, v2 = np.append(r, r[at]), np.append(c, c[at]), np.append(v, np.float32(1))
+        for d in (O.CSR(), O.CSC(), O.COO()):
+            with pytest.raises(B.UnisparseError) as ei:
+                B.us_convert(ctx, nr, nc, dev(r2), dev(c2), dev(v2), us_desc_of(d))
+            assert ei.value.code == "US_ERR_DUPLICATE"
+    for bad in ((nr, 0), (0, nc), (-1, 3), (3, -1), (2**31 - 1, 2**31 - 1)):
+        r2, c2, v2 = np.append(r, np.int32(bad[0])), np.append(c, np.int32(bad[1])), np.append(v, np.float32(1))
+        for d in (O.CSR(), O.CSC(), O.DCSR(), O.ELL()):
+            with pytest.raises(B.UnisparseError) as ei:
+                B.us_convert(ctx, nr, nc, dev(r2), dev(c2), dev(v2), us_desc_of(d))
+            assert ei.value.code == "US_ERR_INDEX_RANGE"
+
+
+@pytest.mark.parametrize("kind", ["uniform", "clusters"])
+def test_large_tiles_and_transposing(ctx, kind):
+    """8.4 M entries and more (tiles of 12,288 in the first pass), there and back."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import assert_same_layout, dev, us_desc_of
+    nr, nc = 300_007, 1_000_003
+    r, c, v = entries(np.random.default_rng(8), nr, nc, 8_500_000 if kind == "uniform" else 11_000_000, kind)
+    assert r.size >= 1 << 23
+    want = {d: O.convert(nr, nc, r, c, v, d) for d in (O.CSR(), O.CSC())}
+    g, launches = run(ctx, nr, nc, r, c, v, O.CSR(), dev)
+    if kind == "uniform":
+        assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
+    assert_same_layout(g, want[O.CSR()], "CSR")
+    t = B.us_convert_formatted(ctx, g, us_desc_of(O.CSC()))
+    assert_same_layout(t, want[O.CSC()], "CSR -> CSC")
+    back = B.us_convert_formatted(ctx, t, us_desc_of(O.CSR()))
+    assert_same_layout(back, want[O.CSR()], "CSC -> CSR")
+    for x in (g, t, back):
+        x.free()

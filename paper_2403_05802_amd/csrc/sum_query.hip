@@ -112,10 +112,24 @@ __global__ __launch_bounds__(256) void group_flag_kernel(const uint32_t *count, 
 }
 
 // gmap[g] = position of group g among the flagged groups, or -1; offsets of the flagged diagonals
+// far: where the first workgroup leaves how many of 256 pairs of neighbours in the list lie more than DIA_FAR rows apart,
+// or null
+constexpr uint32_t DIA_FAR = 256;
 __global__ __launch_bounds__(256) void group_map_kernel(const int32_t *flag, const int32_t *pos, int64_t nbins,
-                                                       int32_t *gmap) {
+                                                       int32_t *gmap, const int32_t *row, int64_t n, int32_t *far) {
   int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (d < nbins) gmap[d] = flag[d] ? pos[d] : -1;
+  if (far && blockIdx.x == 0) {
+    __shared__ uint32_t s_far;
+    if (threadIdx.x == 0) s_far = 0;
+    __syncthreads();
+    const int64_t i = (int64_t)threadIdx.x * (n - 1) / 256;   // n > 1: i + 1 < n
+    const uint32_t step = (uint32_t)row[i + 1] - (uint32_t)row[i];
+    const uint64_t away = __ballot(step + DIA_FAR > 2 * DIA_FAR);
+    if (lane_id() == 0) atomicAdd(&s_far, (uint32_t)__popcll(away));
+    __syncthreads();
+    if (threadIdx.x == 0) *far = (int32_t)s_far;
+  }
 }
 __global__ __launch_bounds__(256) void diag_offsets_kernel(const int32_t *gmap, int64_t nbins, int32_t nrows,
                                                           int32_t *off) {
@@ -135,9 +149,6 @@ __global__ __launch_bounds__(256) void diag_offsets_kernel(const int32_t *gmap, 
 //   otherwise they are appended to list A.  Entries of unflagged groups are appended to list B.
 // Appends reserve space once per workgroup (one atomic per list), so order inside a list is
 // arbitrary; each part is put into canonical order by its conversion.
-// (Ordering the entries by the top bits of their slot first, so that slab writes stay inside an
-// L2-sized window, was measured and dropped: the extra pass cost more than the ~110 G
-// scattered store transactions per second the direct form already sustains.)
 constexpr int SP_T = 512, SP_IPT = 16, SP_TILE = SP_T * SP_IPT;
 constexpr uint32_t DIA_EMPTY = 0x7FC5A5A5u;
 
@@ -192,6 +203,115 @@ __global__ __launch_bounds__(SP_T) void split_kernel(const int32_t *row, const i
       lb.r[pb] = (int32_t)r[k]; lb.c[pb] = (int32_t)c[k]; lb.v[pb] = v[k]; ++pb;
     }
   }
+}
+
+// A slab beyond the L2s in two passes instead: the entries go to bins of 2^DB_SHIFT or more neighbouring slots first, as
+// {slot inside the bin, value}, and every bin is then put together in LDS and written whole, empty slots included, while
+// its occupied slots are counted in a bit map: no fill, no second look at the slab and no value that could be taken for
+// an empty slot.  A bin holds as many entries as it has slots; what does not fit (only duplicates can make it so) is
+// dropped, and the count of occupied slots says so.
+// The first pass is bound by its device atomics, one per tile and bin: 14.7 M entries, 896 bins, tiles of 4096 / 8192 / 12,288
+// entries 332 / 153 / 134 us; with a count of its own per workgroup first, and 256 workgroups, 144.  The second writes at
+// 4.6 TB/s.
+constexpr int64_t DIA_BINNED = 3 << 19;   // slots
+constexpr int DB_T = 1024, DB_IPT = 12, DB_TILE = DB_T * DB_IPT, DB_BINS = 2048;
+
+__global__ __launch_bounds__(DB_T) void dia_bin_kernel(const int32_t *row, const int32_t *col, const float *val, int64_t n,
+                                                       uint32_t nrows, const int32_t *gmap, int64_t L, int by_col, int shift,
+                                                       uint2 *rec, uint32_t *filled, CooLists lb, int32_t *cursors) {
+  __shared__ uint2 s_rec[DB_TILE];
+  __shared__ uint16_t s_bin[DB_TILE];
+  __shared__ uint32_t s_cnt[DB_BINS];    // entries of the tile per bin, then where they start in the tile
+  __shared__ uint32_t s_goff[DB_BINS];   // place of the tile's entries in the bin, minus their start in the tile
+  __shared__ uint32_t s_wave[DB_T / 64 + 1];
+  __shared__ int32_t s_base;
+  constexpr int PER = DB_BINS / DB_T;
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * DB_TILE;
+  uint32_t r[DB_IPT], c[DB_IPT], arr[DB_IPT];
+  float v[DB_IPT];
+  int32_t slot[DB_IPT];   // -1: an entry of an unflagged diagonal, -2: no entry
+#pragma unroll
+  for (int q = 0; q < PER; ++q) s_cnt[q * DB_T + tid] = 0;
+#pragma unroll
+  for (int k = 0; k < DB_IPT; ++k) {
+    const int64_t i = base + k * DB_T + tid;
+    r[k] = c[k] = 0; v[k] = 0.f;
+    if (i < n) { r[k] = (uint32_t)row[i]; c[k] = (uint32_t)col[i]; v[k] = val[i]; }
+  }
+  uint32_t nb = 0;
+#pragma unroll
+  for (int k = 0; k < DB_IPT; ++k) {
+    slot[k] = -2;
+    if (base + k * DB_T + tid < n) {
+      const int32_t g = gmap[group_bin(G_DIAG, r[k], c[k], nrows)];
+      slot[k] = g >= 0 ? (int32_t)((int64_t)g * L + (by_col ? c[k] : r[k])) : -1;   // below 2^31
+    }
+    nb += slot[k] == -1;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < DB_IPT; ++k) arr[k] = slot[k] >= 0 ? atomicAdd(&s_cnt[slot[k] >> shift], 1u) : 0u;
+  uint32_t tb, ta, cnt[PER], sum = 0;
+  uint32_t pb = block_exclusive_sum<DB_T>(nb, s_wave, &tb);   // (its barriers close the counts)
+  if (tid == 0) s_base = lb.r && tb ? atomicAdd(&cursors[1], (int32_t)tb) : 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) { cnt[q] = s_cnt[tid * PER + q]; sum += cnt[q]; }
+  uint32_t run = block_exclusive_sum<DB_T>(sum, s_wave, &ta);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t b = tid * PER + q;
+    s_cnt[b] = run;
+    s_goff[b] = (cnt[q] ? atomicAdd(&filled[b], cnt[q]) : 0u) - run;   // (bins past the slab's hold nothing)
+    run += cnt[q];
+  }
+  __syncthreads();
+  pb += (uint32_t)s_base;
+#pragma unroll
+  for (int k = 0; k < DB_IPT; ++k) {
+    if (slot[k] >= 0) {
+      const uint32_t b = slot[k] >> shift, pos = s_cnt[b] + arr[k];
+      s_rec[pos] = make_uint2((uint32_t)slot[k] & ((1u << shift) - 1u), __float_as_uint(v[k]));
+      s_bin[pos] = (uint16_t)b;
+    } else if (slot[k] == -1 && lb.r) {
+      lb.r[pb] = (int32_t)r[k]; lb.c[pb] = (int32_t)c[k]; lb.v[pb] = v[k]; ++pb;
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = tid; i < ta; i += DB_T) {
+    const uint32_t b = s_bin[i], at = s_goff[b] + i;
+    if (at < 1u << shift) rec[((size_t)b << shift) + at] = s_rec[i];
+  }
+}
+
+template <int SHIFT>
+__global__ __launch_bounds__(DB_T) void dia_image_kernel(const uint2 *rec, const uint32_t *filled, float *slab, int64_t nslots,
+                                                         int32_t *out) {
+  constexpr uint32_t S = 1u << SHIFT;
+  __shared__ uint32_t s_img[S];
+  __shared__ uint32_t s_bits[S / 32];
+  __shared__ uint32_t s_wave[DB_T / 64 + 1];
+  const int tid = threadIdx.x;
+  const uint32_t b = blockIdx.x, n = min(filled[b], S);
+  for (uint32_t i = tid; i < S / 4; i += DB_T) reinterpret_cast<uint4 *>(s_img)[i] = make_uint4(0, 0, 0, 0);
+  for (uint32_t i = tid; i < S / 32; i += DB_T) s_bits[i] = 0;
+  __syncthreads();
+  const uint2 *src = rec + ((size_t)b << SHIFT);
+#pragma unroll 4
+  for (uint32_t i = tid; i < n; i += DB_T) {
+    const uint2 e = src[i];
+    s_img[e.x] = e.y;
+    atomicOr(&s_bits[e.x >> 5], 1u << (e.x & 31u));
+  }
+  __syncthreads();
+  const int64_t first = (int64_t)b << SHIFT;
+  float4 *dst = reinterpret_cast<float4 *>(slab + first);
+  const uint32_t nv = (uint32_t)min((int64_t)S / 4, (nslots - first + 3) / 4);   // (the allocation is padded to whole vectors)
+  for (uint32_t i = tid; i < nv; i += DB_T) dst[i] = reinterpret_cast<const float4 *>(s_img)[i];
+  uint32_t cnt = 0, total;
+  for (uint32_t i = tid; i < S / 32; i += DB_T) cnt += __popc(s_bits[i]);
+  block_exclusive_sum<DB_T>(cnt, s_wave, &total);
+  if (tid == 0 && total) atomicAdd(out, (int32_t)total);
 }
 
 // occupied slots of a slab that started out as DIA_EMPTY; what is still empty becomes +0.0
@@ -262,7 +382,7 @@ static us_status dia_from_flags(Env &env, const us_coo &coo, const Plan &plan, c
   if (!env.ok()) return env.status;
   exclusive_scan_i32(env, flag, pos, nbins, &flags->scalar[0]);
   US_LAUNCH(env, "group_map", 12.0 * nbins, group_map_kernel, ceil_div<int64_t>(nbins, 256), 256, flag,
-            (const int32_t *)pos, nbins, gmap);
+            (const int32_t *)pos, nbins, gmap, coo.row, n, n > 1 ? &flags->scalar[2] : (int32_t *)nullptr);
   Flags h{};
   if (!read_flags(env, flags, &h)) return env.status;
   if (flag_status(h) != US_OK) return flag_status(h);
@@ -276,25 +396,43 @@ static us_status dia_from_flags(Env &env, const us_coo &coo, const Plan &plan, c
   f->level[1].size = L;
   const int64_t nslab4 = ceil_div<int64_t>(ndiag * L, 4);
   f->val = env.owned<float>(nslab4 * 4); f->nval = ndiag * L; f->nmajor = ndiag;   // whole 16-byte vectors
-  const bool marks = env.dia_marks;
-  const int64_t nvec = ceil_div<int64_t>(ndiag * L, 16) + 1;
+  // Into bins first where the slab is beyond the caches of an XCD, mostly full, and the list in no order that keeps
+  // neighbouring stores together; a list sorted by rows or by diagonals writes whole lines as it is.  Seven diagonals, stores
+  // and finish / bins and images, us: in random order 1.1 M entries 37 / 36, 2.1 M 54 / 40, 4.9 M 94 / 65, 14.7 M 279 / 174,
+  // 40 M 676 / 514; 14.7 M sorted by rows 109 / 184, by diagonals 87 / 216.
+  const int64_t nslots = ndiag * L;
+  const int shift = nslots <= (int64_t)DB_BINS << 14 ? 14 : 15;
+  const bool binned = nslots >= DIA_BINNED && na >= nslots / 4 && nslots <= (int64_t)DB_BINS << 15 && h.scalar[2] > 128;
+  const int64_t nbins_slab = ceil_div<int64_t>(nslots, 1ll << shift);
+  const bool marks = env.dia_marks && !binned;
+  const int64_t nvec = ceil_div<int64_t>(nslots, 16) + 1;
   uint8_t *slotmap = marks ? (uint8_t *)env.temp<uint4>(nvec) : nullptr;
+  if (binned) env.reserve(Env::granule(4 * DB_BINS) + Env::granule(((size_t)nbins_slab << shift) * sizeof(uint2)));
+  uint32_t *filled = binned ? env.temp<uint32_t>(DB_BINS) : nullptr;
+  uint2 *rec = binned ? env.temp<uint2>((size_t)nbins_slab << shift) : nullptr;
   CooLists lb;
   if (rest) { *nrest = n - na; lb = alloc_lists(env, n - na); *rest = lb; }
   if (!env.ok()) { free_formatted(env, f); return env.status; }
-  fill_u32(env, (uint32_t *)f->val, ndiag * L, marks ? 0u : DIA_EMPTY);
+  if (binned) fill_u32(env, filled, DB_BINS, 0u);
+  else fill_u32(env, (uint32_t *)f->val, nslots, marks ? 0u : DIA_EMPTY);
   if (marks) fill_u32(env, (uint32_t *)slotmap, nvec * 4, 0u);
   fill_u32(env, (uint32_t *)cursors, 2, 0u);
   US_LAUNCH(env, "diag_offsets", 8.0 * nbins, diag_offsets_kernel, ceil_div<int64_t>(nbins, 256), 256,
             (const int32_t *)gmap, nbins, (int32_t)coo.nrows, f->level[0].idx);
-  if (n > 0)
+  if (binned) {
+    US_LAUNCH(env, "dia_bin", 12.0 * n + 8.0 * na + 12.0 * (rest ? n - na : 0), dia_bin_kernel, ceil_div<int64_t>(n, DB_TILE), DB_T,
+              coo.row, coo.col, coo.val, n, (uint32_t)coo.nrows, (const int32_t *)gmap, L, plan.swapped ? 1 : 0, shift, rec,
+              filled, lb, cursors);
+    if (shift == 14) US_LAUNCH(env, "dia_image", 8.0 * na + 4.0 * nslots, dia_image_kernel<14>, nbins_slab, DB_T, (const uint2 *)rec, (const uint32_t *)filled, f->val, nslots, &flags->scalar[3]);
+    else US_LAUNCH(env, "dia_image", 8.0 * na + 4.0 * nslots, dia_image_kernel<15>, nbins_slab, DB_T, (const uint2 *)rec, (const uint32_t *)filled, f->val, nslots, &flags->scalar[3]);
+  } else if (n > 0)
     US_LAUNCH(env, "dia_split_scatter", 12.0 * n + 5.0 * na + 12.0 * (rest ? n - na : 0), (split_kernel<true>),
               ceil_div<int64_t>(n, SP_TILE), SP_T, coo.row, coo.col, coo.val, n, (int)G_DIAG, (uint32_t)coo.nrows,
               (const int32_t *)gmap, L, plan.swapped ? 1 : 0, f->val, slotmap, CooLists(), lb, cursors, flags);
   if (marks)
-    US_LAUNCH(env, "count_marks", 1.0 * ndiag * L, count_marks_kernel, one_counter_grid(nvec, 256), 256, (const uint4 *)slotmap, nvec, &flags->scalar[3]);
-  else if (nslab4 > 0)
-    US_LAUNCH(env, "dia_finish", 4.0 * ndiag * L, dia_finish_kernel, one_counter_grid(nslab4, 256), 256, (uint4 *)f->val, nslab4, ndiag * L, &flags->scalar[3]);
+    US_LAUNCH(env, "count_marks", 1.0 * nslots, count_marks_kernel, one_counter_grid(nvec, 256), 256, (const uint4 *)slotmap, nvec, &flags->scalar[3]);
+  else if (!binned && nslab4 > 0)
+    US_LAUNCH(env, "dia_finish", 4.0 * nslots, dia_finish_kernel, one_counter_grid(nslab4, 256), 256, (uint4 *)f->val, nslab4, nslots, &flags->scalar[3]);
   if (verify_later) {
     verify_later->flags = flags; verify_later->na = na;
     if (!env.ok()) { free_formatted(env, f); return env.status; }
@@ -369,7 +507,7 @@ us_status decompose_sum(Env &env, const us_coo &coo, const Plan &pa, const us_fo
     if (st == US_OK) {
       fill_u32(env, (uint32_t *)cursors, 2, 0u);
       US_LAUNCH(env, "group_map", 12.0 * g.nbins, group_map_kernel, ceil_div<int64_t>(g.nbins, 256), 256,
-                (const int32_t *)g.flag, (const int32_t *)g.flag, g.nbins, gmap);
+                (const int32_t *)g.flag, (const int32_t *)g.flag, g.nbins, gmap, (const int32_t *)nullptr, (int64_t)0, (int32_t *)nullptr);
       if (n > 0)
         US_LAUNCH(env, "split", 24.0 * n, (split_kernel<false>), ceil_div<int64_t>(n, SP_TILE), SP_T, coo.row, coo.col,
                   coo.val, n, gkind, (uint32_t)coo.nrows, (const int32_t *)gmap, (int64_t)0, 0, (float *)nullptr,

@@ -8,8 +8,8 @@
 // Against the least-significant-digit passes of sort.hip: an entry travels as 8 bytes {key below the parent's bits, value}
 // instead of 12 and a digit byte, through two passes and the finish (52 bytes read and written in all, pointers of the
 // rows included) instead of one pass per eight key bits (26 each).  COO -> CSR, digit passes / this, us: 16.8 M entries of a
-// power-law matrix, 40 key bits, 695 / 438; 40 M with local columns, 42 bits, 1630 / 995; 4 M 238 / 174; 1 M, even rows
-// 155 / 110; 300 k 138 / 100; 41 k, 24 bits (one parent) 87-103 / 75-80.
+// power-law matrix, 40 key bits, 695 / 425; 40 M with local columns, 42 bits, 1630 / 964; 4 M 238 / 172; 1 M, even rows
+// 155 / 103; 300 k 138 / 94; 41 k, 24 bits (one parent) 87-103 / 75-80.
 #include "device.h"
 #include "sort_key.h"
 
@@ -38,9 +38,8 @@ struct BkArgs {
   // second pass
   BkParent *parent;            // [nparents]
   uint32_t *totals;            // [0] children, [1] tiles of parents with more than one child
-  uint32_t *child_parent;      // [max_children]
-  uint32_t *splitter;          // [max_children] smallest low key of the child
-  uint32_t *cursor;            // [max_children] entries of the child (parents with more than one)
+  uint4 *child;                // [max_children] {start of the parent, its first child, parent | its children << 16, smallest low key}
+  uint32_t *cursor;            // [max_children] entries of the child
   uint32_t *tile_parent;       // [max_tiles]
   uint32_t max_children, max_tiles, tiles_per_xcd, children_per_xcd;
   uint2 *rec2;                 // [max_children][BK_CAP]
@@ -261,30 +260,34 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
 
 // ------------------------------------------------------------------ a few thousand keys in LDS
 // The keys go into bins that keep their order: 64 of the keys themselves, sorted by one wavefront, cut them into intervals of
-// similar numbers of keys whatever their distribution, and an interval is cut evenly over its range into as many bins as it
-// has keys (twice as many where there is room).  What is left together, one or two keys on average, fix_order puts in order.
-// A bin of more than LIMIT keys is cut again before, evenly between its own smallest and largest key, into as many
-// bins as it has keys.  LDS is what bounds this: a key costs two atomics and two writes at scattered places, the splitters
-// and intervals are held one per lane and looked up with ds_bpermute, which knows no bank conflicts.
+// similar numbers of keys whatever their distribution, and every interval is cut evenly over its range into the same number
+// of bins.  What is left together, one or two keys on average, fix_order puts in order.  A bin of more than LIMIT keys is
+// cut again before, evenly between its own smallest and largest key, into as many bins as it has keys.  LDS and the
+// chain of steps bound this: the splitters are held one per lane, every eighth in a scalar, and a key finds its
+// interval by three comparisons with scalars and three with splitters fetched by ds_bpermute, which knows no bank
+// conflicts; then it costs an atomic, a read and two writes at scattered places.
 constexpr uint32_t BP_MOST = 129;
 constexpr int BP_ROUNDS = 4;
 
-template <int T, int IPT>
+// LIMIT 0: no bin is cut again, and the counters and the values share their place
+template <int T, int IPT, uint32_t LIMIT>
 struct BinScratch {
   static constexpr int NW = T / 64, Q = IPT / 4;   // wavefronts; blocks of four bins or slots per thread
+  uint32_t a[T * IPT];
   uint32_t cnt[T * IPT + 4];
-  uint32_t a[T * IPT], b[T * IPT];
-  uint32_t split[64], count[64];
+  uint32_t b_own[LIMIT ? T * IPT : 4];
+  __device__ __forceinline__ uint32_t *b() { return LIMIT ? b_own : cnt; }
+  uint32_t split[64];
   uint32_t wave[Q * NW], big[NW];
   uint32_t reach[Q * NW];   // per 256 slots: the most keys of a bin that touches them
 };
 
 // key[j] belongs to item j * T + threadIdx.x < m <= T * IPT, lo <= key <= hi; sample: the key of item threadIdx.x * m / 64
 // (wavefront 0).  Leaves the slot of every item in order of the bins, s.reach, and returns the most keys of a bin, rounded
-// up to 1, 5, 9, 17, 33, 65, BP_MOST or ~0 (the same for every thread).  s.a and s.b are free afterwards.
+// up to 1, 5, 9, 17, 33, 65, BP_MOST or ~0 (the same for every thread).  Ends with a barrier: s.a and s.b() are free.
 template <int T, int IPT, uint32_t LIMIT>
 __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32_t m, uint32_t lo, uint32_t hi, uint32_t sample,
-                                              BinScratch<T, IPT> &s, uint32_t (&slot)[IPT]) {
+                                              BinScratch<T, IPT, LIMIT> &s, uint32_t (&slot)[IPT]) {
   constexpr int CAP = T * IPT, NW = T / 64, Q = IPT / 4;
   static_assert(IPT % 4 == 0, "counters are cleared and read four at a time");
   const int tid = threadIdx.x, lane = lane_id(), w = wave_id();
@@ -293,7 +296,7 @@ __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32
   for (int q = 0; q < Q; ++q) reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = make_uint4(0, 0, 0, 0);
   if (tid < Q * NW) s.reach[tid] = 0;
   if (w == 0) {
-    s.split[lane] = ~0u; s.count[lane] = 0;
+    s.split[lane] = ~0u;
     uint32_t rank = 0;
 #pragma unroll 16
     for (int q = 0; q < 64; ++q) rank += (uint32_t)__builtin_amdgcn_readlane((int)sample, q) < sample;
@@ -301,35 +304,50 @@ __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32
     if (m >= 64) s.split[rank] = sample;
   }
   __syncthreads();
-  // lane i: interval i = [split i, split i + 1); two equal samples (a duplicate, or few keys) leave a gap in the list: one interval then
-  uint32_t sp = s.split[lane];
-  if (__any(sp == ~0u)) sp = ~0u;
-  if (lane == 0) sp = lo;
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) bin[j] = 0;
-#pragma unroll
-  for (int step = 32; step; step >>= 1) {
-#pragma unroll
-    for (int j = 0; j < IPT; ++j)
-      if (j * T < m && (uint32_t)__shfl((int)sp, (int)(bin[j] + step)) <= key[j]) bin[j] += step;
-  }
-#pragma unroll
-  for (int j = 0; j < IPT; ++j)
-    if (j * T + tid < m) atomicAdd(&s.count[bin[j]], 1u);
-  __syncthreads();
   {
-    const uint32_t n = s.count[lane], st = wave_inclusive_sum_dpp(n) - n, f = 2 * m <= (uint32_t)CAP ? 2u : 1u;
+    // lane i: interval i = [split i, split i + 1); two equal samples (a duplicate), the largest possible key among them or too
+    // few keys leave a gap in the list: one interval then
+    uint32_t sp = s.split[lane];
+    const bool one = __any(sp == ~0u);
+    if (one) sp = ~0u;
+    if (lane == 0) sp = lo;
+    const uint32_t per = one ? CAP : CAP / 64;
     uint32_t next = (uint32_t)__shfl_down((int)sp, 1);
     if (lane == 63 || next > hi) next = hi;
-    const float scale = (float)(f * n) * __builtin_amdgcn_rcpf((float)(next - sp) + 1.f);
-    const uint32_t first = f * st, last = f * (st + n) - 1;
+    const float scale = (float)per * __builtin_amdgcn_rcpf((float)(next - sp) + 1.f);
+    uint32_t by8[8];
+#pragma unroll
+    for (int q = 1; q < 8; ++q) by8[q] = (uint32_t)__builtin_amdgcn_readlane((int)sp, 8 * q);
+    uint32_t from[IPT];   // where the key's interval begins
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
+      bin[j] = 0; arr[j] = 0; from[j] = lo;
       if (j * T < m) {
-        const int from = (int)bin[j];
-        const uint32_t l = (uint32_t)__shfl((int)sp, from), b0 = (uint32_t)__shfl((int)first, from), b1 = (uint32_t)__shfl((int)last, from);
-        const float sc = __builtin_bit_cast(float, __shfl(__builtin_bit_cast(int, scale), from));
-        bin[j] = min(b0 + (uint32_t)((float)(key[j] - l) * sc), b1);   // (rounding keeps the order of the keys)
+        const uint32_t k = key[j];
+        const bool c4 = by8[4] <= k;
+        const uint32_t t2 = c4 ? by8[6] : by8[2];
+        const bool c2 = t2 <= k;
+        const uint32_t t1 = c4 ? (c2 ? by8[7] : by8[5]) : (c2 ? by8[3] : by8[1]);
+        const bool c1 = t1 <= k;
+        bin[j] = (c4 ? 32u : 0u) + (c2 ? 16u : 0u) + (c1 ? 8u : 0u);
+        from[j] = c1 ? t1 : (c2 ? t2 : (c4 ? by8[4] : lo));
+      }
+    }
+#pragma unroll
+    for (int step = 4; step; step >>= 1) {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j) {
+        if (j * T < m) {
+          const uint32_t v = (uint32_t)__shfl((int)sp, (int)(bin[j] + step));
+          if (v <= key[j]) { bin[j] += step; from[j] = v; }
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < IPT; ++j) {
+      if (j * T < m) {   // (rounding keeps the order of the keys)
+        const float sc = __builtin_bit_cast(float, __shfl(__builtin_bit_cast(int, scale), (int)bin[j]));
+        bin[j] = min(bin[j] * per + min((uint32_t)((float)(key[j] - from[j]) * sc), per - 1), (uint32_t)(CAP - 1));
       }
     }
   }
@@ -370,11 +388,12 @@ __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32
       reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = v;
       if (q == Q - 1 && tid == T - 1) s.cnt[CAP] = v.w + c[4 * q + 3];
     }
-    if (worst <= LIMIT || round == BP_ROUNDS) break;
+    if (LIMIT == 0 || worst <= LIMIT || round == BP_ROUNDS) break;
+    if constexpr (LIMIT > 0) {
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       reinterpret_cast<uint4 *>(s.a)[q * T + tid] = make_uint4(~0u, ~0u, ~0u, ~0u);
-      reinterpret_cast<uint4 *>(s.b)[q * T + tid] = make_uint4(0, 0, 0, 0);
+      reinterpret_cast<uint4 *>(s.b())[q * T + tid] = make_uint4(0, 0, 0, 0);
     }
     __syncthreads();
 #pragma unroll
@@ -386,7 +405,7 @@ __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32
         arr[j] = count;
         if (count > LIMIT) {
           atomicMin(&s.a[slot[j]], key[j]);
-          atomicMax(&s.b[slot[j]], key[j]);
+          atomicMax(&s.b()[slot[j]], key[j]);
         }
       }
     }
@@ -394,33 +413,38 @@ __device__ __forceinline__ uint32_t bin_slots(const uint32_t (&key)[IPT], uint32
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       if (j * T + tid < m && arr[j] > LIMIT) {
-        const uint32_t mn = s.a[slot[j]], mx = s.b[slot[j]];
+        const uint32_t mn = s.a[slot[j]], mx = s.b()[slot[j]];
         bin[j] += min((uint32_t)((float)(key[j] - mn) * ((float)arr[j] * __builtin_amdgcn_rcpf((float)(mx - mn) + 1.f))), arr[j] - 1);
       }
     }
 #pragma unroll
     for (int q = 0; q < Q; ++q) reinterpret_cast<uint4 *>(s.cnt)[q * T + tid] = make_uint4(0, 0, 0, 0);
     __syncthreads();
+    }
   }
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < IPT; ++j) {
     slot[j] = 0;
     if (j * T + tid < m) {
-      const uint32_t st = s.cnt[bin[j]], count = s.cnt[bin[j] + 1] - st;
+      const uint32_t st = s.cnt[bin[j]];
       slot[j] = st + arr[j];
-      if (count > 5) atomicMax(&s.reach[slot[j] >> 8], count);
+      if (arr[j] >= 5) {   // (the last of a bin's keys to arrive says how many there are, where the bin begins and where it ends)
+        atomicMax(&s.reach[st >> 8], arr[j] + 1);
+        atomicMax(&s.reach[slot[j] >> 8], arr[j] + 1);
+      }
     }
   }
+  __syncthreads();
   return worst;
 }
 
-// The m items in s.a (keys) and s.b, in order of the bins, into order of the keys: a key moves by the smaller ones behind it
+// The m items in s.a (keys) and s.b(), in order of the bins, into order of the keys: a key moves by the smaller ones behind it
 // and the larger ones before it, and those lie fewer places away than its bin has keys; nothing beyond a bin's ends
 // counts, so the bins need not be known.  Four items per thread and 16 bytes per read.  Ends with a barrier.
-template <int T, int IPT>
-__device__ __forceinline__ void fix_order(uint32_t m, BinScratch<T, IPT> &s) {
-  const uint4 *a4 = reinterpret_cast<const uint4 *>(s.a), *b4 = reinterpret_cast<const uint4 *>(s.b);
+template <int T, int IPT, uint32_t LIMIT>
+__device__ __forceinline__ void fix_order(uint32_t m, BinScratch<T, IPT, LIMIT> &s) {
+  const uint4 *a4 = reinterpret_cast<const uint4 *>(s.a), *b4 = reinterpret_cast<const uint4 *>(s.b());
   const uint32_t n4 = (m + 3) / 4;
   if (threadIdx.x < 4 * n4 - m) s.a[m + threadIdx.x] = ~0u;
   __syncthreads();
@@ -464,7 +488,7 @@ __device__ __forceinline__ void fix_order(uint32_t m, BinScratch<T, IPT> &s) {
     for (int x = 0; x < 4; ++x) {
       if (4 * (q * T + threadIdx.x) + x < m) {
         s.a[pos[4 * q + x]] = k[4 * q + x];
-        s.b[pos[4 * q + x]] = v[4 * q + x];
+        s.b()[pos[4 * q + x]] = v[4 * q + x];
       }
     }
   }
@@ -476,12 +500,12 @@ constexpr int SM_T = 512, SM_IPT = 8, SM_MOST = SM_T * SM_IPT;   // sampled keys
 constexpr int BX_T = 512, BX_IPT = 8, BX_TILE = BX_T * BX_IPT;
 
 // One workgroup per parent: its place among the parents, its children and tiles, their splitters.  64 sampled keys per
-// child make a child of twice the average, the most the finish holds, a matter of 3e-9; the call is then run again with
+// child make a child of twice the average, the most the finish holds, a matter of 3e-9 (32 keys: 5e-5); the call is then run again with
 // the digit passes, as it is when a parent is too large for BK_MAXK children.
 // COO: the whole list is one parent, its keys are built from the coordinates.
 template <bool COO>
 __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
-  __shared__ BinScratch<SM_T, SM_IPT> s;
+  __shared__ BinScratch<SM_T, SM_IPT, 33> s;
   __shared__ uint32_t s_wave[3][SM_T / 64];
   __shared__ BkParent s_me;
   constexpr int PER = BK_MAXBINS / SM_T;
@@ -511,16 +535,16 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
   const BkParent me = s_me;
   if (tid == 0) a.parent[p] = me;
   // (the sums are bounded by what the host allocated for; the guards keep it so whatever the sizes say)
-  for (uint32_t c = tid; c < me.k && me.child0 + c < a.max_children; c += SM_T) {
-    a.child_parent[me.child0 + c] = p;
-    a.cursor[me.child0 + c] = 0;
-    if (c == 0) a.splitter[me.child0] = 0;
-  }
-  if (me.k == 1) return;
   if (me.k > (uint32_t)BK_MAXK || me.child0 + me.k > a.max_children) {
     if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
     return;
   }
+  auto child = [&](uint32_t c, uint32_t low) {
+    a.child[me.child0 + c] = make_uint4(me.start, me.child0, p | me.k << 16, low);
+    a.cursor[me.child0 + c] = !COO && me.k == 1 ? me.size : 0u;
+  };
+  if (tid == 0) child(0, 0u);
+  if (me.k == 1) return;
   const uint32_t ntiles = (me.size + BX_TILE - 1) / BX_TILE;
   for (uint32_t t = tid; t < ntiles && me.tile0 + t < a.max_tiles; t += SM_T) a.tile_parent[me.tile0 + t] = p;
   // keys from evenly spaced pieces of the parent, at a scattered place in each (lists often come in a regular order)
@@ -549,10 +573,10 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
   }
 #pragma unroll
   for (int j = 0; j < SM_IPT; ++j)
-    if (j * SM_T + tid < ns) { s.a[pos[j]] = key[j]; s.b[pos[j]] = 0; }
-  fix_order<SM_T, SM_IPT>(ns, s);
+    if (j * SM_T + tid < ns) { s.a[pos[j]] = key[j]; s.b()[pos[j]] = 0; }
+  fix_order<SM_T, SM_IPT, 33>(ns, s);
   for (uint32_t c = tid; c < me.k; c += SM_T)
-    if (c > 0) a.splitter[me.child0 + c] = s.a[(uint32_t)((uint64_t)c * ns / me.k)];
+    if (c > 0) child(c, s.a[c * ns / me.k]);
 }
 
 // 16.8 M entries 59 us, 40 M 135: 4.5 and 4.7 TB/s, near the rate of a copy (runs of some 200 entries).
@@ -573,7 +597,7 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
   if (me.k > (uint32_t)BK_MAXK) return;
   const uint32_t first = me.start + (t - me.tile0) * BX_TILE, in_tile = min((uint32_t)BX_TILE, me.start + me.size - first);
   if (tid < BK_MAXK) {
-    s_split[tid] = (uint32_t)tid < me.k ? a.splitter[me.child0 + tid] : 0xFFFFFFFFu;
+    s_split[tid] = (uint32_t)tid < me.k ? a.child[me.child0 + tid].w : 0xFFFFFFFFu;
     s_cnt[tid] = 0;
   }
   uint32_t key[BX_IPT], val[BX_IPT], bin[BX_IPT], arr[BX_IPT];
@@ -640,32 +664,32 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
 }
 
 // ------------------------------------------------------------------ finish: a child per workgroup
-// 16.8 M entries of the power-law matrix 162 us, 40 M with local columns 410 (65 and 152 when it only reads and writes);
-// LDS is busy 61 % of the time and the vector units 66 %.  Children of 2048 entries on average, 512 threads: 297 and 810.
-// Four digit passes of ballot ranking in LDS instead of the splitters would take 280 vector instructions an entry,
-// this takes 230; cutting by row or by range first and again by smallest and largest key until no bin
-// holds more than 9: 177 and 602, three quarters of it LDS atomics and reads that meet in a bank.
+// 16.8 M entries of the power-law matrix 147 us, 40 M with local columns 367 (65 and 152 when it only reads and writes), in
+// six workgroups per CU (71 registers; 8 at 64 with spills: 149 and 369).  A workgroup takes some 12 us, mostly a chain of
+// dependent steps, so what counts is how many are resident: counters and values share their place in LDS, bins that
+// crowd are not cut again; children of 2048 entries on average with twice the LDS: 297 and 810, of 1024 with room for 2560
+// or 3072: 237 and 621, 282 and 750.  (Bins by row or range, cut again by smallest and largest key until none
+// holds more than 9: 177 and 602, three quarters of it LDS atomics and reads that meet in a bank; four digit passes of
+// ballot ranking would take 280 vector instructions an entry, this takes 200.)
 constexpr int BF_T = 256, BF_IPT = BK_CAP / BF_T;
+static_assert(BF_T % 64 == 0 && BF_T * BF_IPT == BK_CAP && BK_MAXK <= BF_T, "a workgroup holds a child and sees its siblings");
 
 __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
-  __shared__ BinScratch<BF_T, BF_IPT> s;
+  __shared__ BinScratch<BF_T, BF_IPT, 0> s;
   __shared__ uint32_t s_before;
-  const uint32_t c = xcd_tile(blockIdx.x, a.children_per_xcd);
-  if (gave_up(a, true) || c >= min(a.totals[0], a.max_children)) return;
   const int tid = threadIdx.x;
-  const uint32_t p = a.child_parent[c];
-  const BkParent me = a.parent[p];
-  const uint32_t j0 = c - me.child0;
-  if (me.k > (uint32_t)BK_MAXK) return;
+  const uint32_t c = xcd_tile(blockIdx.x, a.children_per_xcd), at = min(c, a.max_children - 1);
+  // everything that does not hang on something else first; what an earlier kernel has left unwritten is not used
+  const uint4 me = a.child[at], after = a.child[min(at + 1, a.max_children - 1)];
+  const uint32_t m = a.cursor[at], nchildren = min(a.totals[0], a.max_children);
   if (tid == 0) s_before = 0;
-  __syncthreads();
-  const bool split = me.k > 1 || !a.rec1;   // (one parent, the caller's list: always)
-  if (split && (uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[me.child0 + tid]);   // j0 < BK_MAXK <= BF_T
-  const uint32_t m = split ? a.cursor[c] : me.size;
+  if (gave_up(a, true) || c >= nchildren) return;
+  const uint32_t start = me.x, child0 = me.y, p = me.z & 0xFFFFu, k = me.z >> 16, j0 = c - child0;
   if (m > (uint32_t)BK_CAP) return;   // (the call will be run again)
-  const uint2 *src = split ? a.rec2 + (size_t)c * BK_CAP : a.rec1 + me.start;
+  if ((uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[child0 + tid]);   // j0 < BK_MAXK <= BF_T
+  const uint2 *src = k > 1 || !a.rec1 ? a.rec2 + (size_t)c * BK_CAP : a.rec1 + start;   // (one parent, the caller's list: always rec2)
   const uint32_t lmask = low_mask(a.dshift);
-  const uint32_t lo = j0 > 0 ? a.splitter[c] : 0u, hi = j0 + 1 < me.k ? a.splitter[c + 1] : lmask;   // (hi itself may be the next child's)
+  const uint32_t lo = me.w, hi = j0 + 1 < k ? after.w : lmask;   // (hi itself may be the next child's)
   uint32_t key[BF_IPT], val[BF_IPT], pos[BF_IPT];
 #pragma unroll
   for (int j = 0; j < BF_IPT; ++j) {
@@ -676,29 +700,29 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
     }
   }
   const uint32_t sample = tid < 64 && m >= 64 ? src[(uint32_t)tid * m / 64].x : 0u;
-  const uint32_t most = bin_slots<BF_T, BF_IPT, 65>(key, m, lo, hi, sample, s, pos);
+  const uint32_t most = bin_slots<BF_T, BF_IPT, 0>(key, m, lo, hi, sample, s, pos);
 #pragma unroll
   for (int j = 0; j < BF_IPT; ++j)
-    if (j * BF_T + tid < m) { s.a[pos[j]] = key[j]; s.b[pos[j]] = val[j]; }
+    if (j * BF_T + tid < m) { s.a[pos[j]] = key[j]; s.b()[pos[j]] = val[j]; }
   if (most <= BP_MOST) {
-    fix_order<BF_T, BF_IPT>(m, s);
+    fix_order<BF_T, BF_IPT, 0>(m, s);
   } else {   // keys that crowd in more than a few places of their range
     __syncthreads();
     for (uint32_t size = 2; size < 2 * m; size <<= 1) {   // bitonic, all comparisons ascending; items past m are not there
       for (uint32_t half = size >> 1; half > 0; half >>= 1) {
         const uint32_t flip = half == size >> 1 ? size - 1 : half;
-        for (uint32_t t = tid; t < (uint32_t)BK_CAP / 2; t += BF_T) {
+        for (uint32_t t = tid; t < 1u << (31 - __clz(BK_CAP - 1)); t += BF_T) {   // half of the next power of two
           const uint32_t i = (t & (half - 1)) + ((t & ~(half - 1)) << 1), k = i ^ flip;
           if (k < m && s.a[i] > s.a[k]) {
-            const uint32_t x = s.a[i], y = s.b[i];
-            s.a[i] = s.a[k]; s.a[k] = x; s.b[i] = s.b[k]; s.b[k] = y;
+            const uint32_t x = s.a[i], y = s.b()[i];
+            s.a[i] = s.a[k]; s.a[k] = x; s.b()[i] = s.b()[k]; s.b()[k] = y;
           }
         }
         __syncthreads();
       }
     }
   }
-  const uint32_t out = me.start + s_before;
+  const uint32_t out = start + s_before;
   const Key base = (Key)p << a.dshift;
   const Key bmask = ((Key)1 << a.ks.b_bits) - 1;
   bool dup = false;
@@ -708,14 +732,14 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
     if (out + i < a.n) {
       if (a.major_out) a.major_out[out + i] = (int32_t)(full >> a.ks.b_bits);
       a.minor_out[out + i] = (int32_t)(full & bmask);
-      a.val_out[out + i] = s.b[i];
+      a.val_out[out + i] = s.b()[i];
     }
   }
   if (dup) a.flags->duplicate = 1;
   if (a.ptr) {   // the major indices whose first possible key lies in this child's range: entries below that key
     const Key l = base | lo, h = base | hi;
-    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = j0 + 1 < me.k ? (h + bmask) >> a.ks.b_bits : (h >> a.ks.b_bits) + 1;
-    if (p + 1 == a.nparents && j0 + 1 == me.k) g1 = (Key)a.ngroups_out + 1;
+    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = j0 + 1 < k ? (h + bmask) >> a.ks.b_bits : (h >> a.ks.b_bits) + 1;
+    if (p + 1 == a.nparents && j0 + 1 == k) g1 = (Key)a.ngroups_out + 1;
     if (g1 > (Key)a.ngroups_out + 1) g1 = (Key)a.ngroups_out + 1;
     for (Key g = g0 + tid; g < g1; g += BF_T) {
       const Key first = (g << a.ks.b_bits) - base;   // may lie beyond 32 bits (behind the last key): all entries are below
@@ -746,7 +770,9 @@ static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
   if (b.direct) {
     b.nparents = 1;
   } else {
-    b.bits = bits_for((uint64_t)nnz / 32768);
+    // 32 children per parent; 8 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
+    // that its size makes longer (1 M entries: 24 -> 17 us in the sample, the other kernels as they were)
+    b.bits = bits_for((uint64_t)nnz / (nnz < (1 << 22) ? 8192 : 32768));
     if (b.bits < ks.total_bits - 32) b.bits = ks.total_bits - 32;
     if (b.bits > BK_MAXBITS) b.bits = BK_MAXBITS;
     if (b.bits > ks.total_bits) b.bits = ks.total_bits;
@@ -773,7 +799,7 @@ size_t bucket_sort_temp_bytes(int64_t nnz, const KeySpec &ks) {
   const BucketPlan b = bucket_plan(nnz, ks);
   auto g = [](size_t bytes) { return Env::granule(bytes); };
   return (b.direct ? 0 : g(4ull * b.ngroups * b.nparents) + g(4ull * b.nparents) + g(8ull * nnz)) + g(sizeof(BkParent) * b.nparents) +
-         g(8) + 3 * g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_children);
+         g(8) + g(16ull * b.max_children) + g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_children);
 }
 
 void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz, const KeySpec &ks,
@@ -799,8 +825,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   }
   a.parent = env.temp<BkParent>(b.nparents);
   a.totals = env.temp<uint32_t>(2);
-  a.child_parent = env.temp<uint32_t>(b.max_children);
-  a.splitter = env.temp<uint32_t>(b.max_children);
+  a.child = env.temp<uint4>(b.max_children);
   a.cursor = env.temp<uint32_t>(b.max_children);
   a.tile_parent = env.temp<uint32_t>(b.max_tiles);
   a.rec2 = env.temp<uint2>((size_t)b.max_children * BK_CAP);

@@ -272,7 +272,5 @@ us_status spmv_impl(Env &env, const us_formatted &A, const float *x, float *y, b
 us_status spmv_noalloc_impl(Env &env, const us_formatted &A, const float *x, float *y, bool accumulate);
 us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, int64_t ldx, float *Y,
                     int64_t ldy, bool accumulate);
-// scratch the entry-balanced product (row-major COO, CSR, DCSR) takes from ensure_workspace; vec = columns per lane
-size_t entry_balanced_scratch_bytes(int64_t nnz, int64_t N, int vec);
 
 }  // namespace us

@@ -448,29 +448,46 @@ struct RowSrc {
   const int32_t *ptr;   // CSR / DCSR: children of parent p are [ptr[p], ptr[p+1])
   const int32_t *ids;   // DCSR: row index of parent p, else null
   int64_t nparents;
-  __device__ __forceinline__ int32_t of(int64_t e) const {
-    if (row) return __builtin_nontemporal_load(row + e);
-    int64_t p = parent_of(ptr, nparents, e);
-    return ids ? ids[p] : (int32_t)p;
-  }
+  const int2 *bounds;   // CSR / DCSR: parents of the entries around every chunk boundary (chunk_bounds_kernel), or null
+  __device__ __forceinline__ int32_t of(int64_t e) const { return __builtin_nontemporal_load(row + e); }   // COO
 };
 
-// A wavefront walks CS_CHUNK consecutive entries; for each it adds val * X[col, :] into a
+// A wavefront walks a chunk of consecutive entries; for each it adds val * X[col, :] into a
 // register accumulator and flushes when the row changes.  Row pieces cut by a chunk boundary
 // go to a carry buffer and are summed in chunk order by the fix-up kernel (reproducible).
-constexpr int CS_CHUNK = 512;
+// The chunks in flight on an XCD span the rows of X that its L2 would have to hold for one chunk to find what another has
+// fetched, so they are no longer than what a chunk costs by itself asks for.  512 / 256 / 128 entries, us: 40 M entries with
+// local columns, N = 128, CSR 2798 / 2724 / 2795, as COO 2120 / 2099 / 2166; N = 64 1669 / 1679 / 1774; with three
+// workgroups per CU (few_resident) 5.2 M, N = 1000 3220 / 3049 / 2864; 10 M, N = 256 1441 / 1367 / 1292; but 5 M of a power-law
+// matrix, no locality, N = 1000 3320 / 3360 / 3447: the carries of its long rows.
+constexpr int CS_CHUNK = 256, CSB_CHUNK_MAX = 512;
 // ... or fewer when the list is short: a wavefront's entries are a serial chain of gather rounds (eight rows of X at a
 // time), so 147 k entries cut into 287 chunks kept 287 wavefronts busy for 64 rounds each, 0.26 ms on a part with
 // 1024 SIMDs; chunks of 64 entries make it 2,293 wavefronts of 8 rounds.
-static int chunk_entries(int64_t nnz) {
-  int len = CS_CHUNK;
+static int chunk_entries(int64_t nnz, int most = CS_CHUNK) {
+  int len = most;
   while (len > 64 && nnz / len < 8192) len >>= 1;
   return len;
 }
 
+// bounds[k] = parents of the last entry before chunk k and of its first one.  A bisection over all parents is 20 dependent
+// loads: one for every boundary, all side by side, takes 5 to 15 us; in the product, at the start of every chunk, it takes
+// 8 of the 90 us of a million entries (N = 64) and 7 % of the time of 40 M.  Below BOUNDS_FROM entries the launch costs more
+// than it saves (400 k entries, N = 16: 43.6 -> 45.2 us with the table).
+constexpr int64_t BOUNDS_FROM = 3 << 18;
+__global__ __launch_bounds__(256) void chunk_bounds_kernel(const int32_t *ptr, int64_t nparents, int64_t nnz, int chunk_len,
+                                                           int64_t nchunks, int2 *bounds) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k > nchunks) return;
+  const int64_t e = min(k * chunk_len, nnz);   // nnz > 0
+  const int64_t behind = parent_of(ptr, nparents, e < nnz ? e : nnz - 1);
+  int64_t before = behind;                     // the parent of e - 1: behind itself, or the last one before it with entries
+  if (e > 0 && e < nnz && (int64_t)ptr[behind] == e) before = parent_of(ptr, behind, e - 1);
+  bounds[k] = make_int2((int32_t)before, (int32_t)behind);
+}
+
 // SEARCH (rows found in ptr): the rows of the whole chunk are looked up first and kept in LDS: the parents of the two
-// entries around the chunk by bisection over all parents, then eight entries per lane with their bisections between
-// those two in step.  One full bisection after the other (per batch of 64 entries, plus four for the chunk's ends) is
+// entries around the chunk, then the entries' own between those two: four entries per lane with their bisections in step.  One full bisection after the other (per batch of 64 entries, plus four for the chunk's ends) is
 // ~250 dependent loads -- a remainder of 147 k entries in 2 M rows, a few hundred wavefronts that all run at once, took
 // 0.32 ms of pure latency that way -- and twenty scattered loads per entry where the rows of a chunk are a handful.
 template <int VEC, bool SEARCH>
@@ -493,10 +510,11 @@ __global__ __launch_bounds__(256) void coo_spmm_kernel(RowSrc row, const int32_t
   const uint32_t xoff = (uint32_t)(col_ok ? c : 0);   // clamped: loads stay in bounds, stores are guarded
   int32_t row_before, row_after, first_row, last_row;
   if constexpr (SEARCH) {
-    // parents of the entries just before and just after the chunk: two bisections over all parents, in step, the same
-    // for every lane (ptr[p] <= e < ptr[p + 1])
-    const int64_t eb = e0 > 0 ? e0 - 1 : e0, ea = e1 < nnz ? e1 : e1 - 1;
+    // parents of the entries just before and just behind the chunk (at the list's ends of its own first or last entry), from
+    // the table or by two bisections over all parents, in step, the same for every lane (ptr[p] <= e < ptr[p + 1])
     int32_t blo = 0, bhi = (int32_t)row.nparents, alo = 0, ahi = (int32_t)row.nparents;
+    if (row.bounds) { blo = bhi = row.bounds[chunk].x; alo = ahi = row.bounds[chunk + 1].y; }
+    const int64_t eb = e0 > 0 ? e0 - 1 : e0, ea = e1 < nnz ? e1 : e1 - 1;
     while (blo < bhi || alo < ahi) {
       if (blo < bhi) {
         const int32_t mid = blo + ((bhi - blo) >> 1);
@@ -675,7 +693,7 @@ __global__ __launch_bounds__(256) void csb_spmm_kernel(const int32_t *ptr, const
                                                       int64_t nblocks, int64_t nbc, int64_t bh, int64_t bw, const float *X,
                                                       int64_t N, int64_t ldx, float *Y, int64_t ldy) {
   typedef typename VecT<VEC>::type V;
-  __shared__ int32_t s_row[4][CS_CHUNK], s_col[4][CS_CHUNK];
+  __shared__ int32_t s_row[4][CSB_CHUNK_MAX], s_col[4][CSB_CHUNK_MAX];
   const int lane = lane_id(), w = wave_id();
   const int64_t chunk = xcd_tile(blockIdx.x, per_xcd) * 4 + w;
   const int64_t e0 = chunk * chunk_len;
@@ -827,35 +845,46 @@ static void zero_rows(Env &env, float *Y, int64_t nrows, int64_t N, int64_t ldy)
     US_LAUNCH(env, "zero_rows", 4.0 * nrows * N, zero_rows_kernel, ceil_div<int64_t>(nrows * N, 256), 256, Y, nrows, N, ldy);
 }
 
-// scratch of the entry-balanced product: two carry rows per chunk (row index + one value per column of the lane layout)
-static size_t carry_rows_bytes(int64_t nnz) {
-  return ((size_t)ceil_div<int64_t>(nnz, chunk_entries(nnz)) * 2 * sizeof(int32_t) + 255) / 256 * 256;
-}
-size_t entry_balanced_scratch_bytes(int64_t nnz, int64_t N, int vec) {
-  const int cbw = 64 * vec;
-  return carry_rows_bytes(nnz) +
-         (size_t)ceil_div<int64_t>(nnz, chunk_entries(nnz)) * 2 * ceil_div<int64_t>(N, cbw) * cbw * sizeof(float);
+// scratch of the entry-balanced product: two carry rows per chunk (row index + one value per column of the lane layout) and,
+// where rows are found in ptr, the table of the chunk boundaries
+struct BalancedScratch { size_t rows, bounds, carry; };
+static BalancedScratch balanced_scratch(int64_t nnz, int64_t N, int vec, bool search) {
+  const size_t nchunks = (size_t)ceil_div<int64_t>(nnz, chunk_entries(nnz)), cbw = 64 * vec;
+  return {Env::granule(nchunks * 2 * sizeof(int32_t)), search && nnz >= BOUNDS_FROM ? Env::granule((nchunks + 1) * sizeof(int2)) : 0,
+          nchunks * 2 * ceil_div<size_t>((size_t)N, cbw) * cbw * sizeof(float)};
 }
 
-static void entry_balanced_spmm(Env &env, const us_formatted &A, const RowSrc &rs, const int32_t *col,
+static void entry_balanced_spmm(Env &env, const us_formatted &A, RowSrc rs, const int32_t *col,
                                 const char *name, int vec, const float *X, int64_t N, int64_t ldx, float *Y,
                                 int64_t ldy, bool accumulate) {
   // accumulate: Y holds the values to add to; else rows with entries are stored and the others left as they are
   const double xy = 4.0 * N * (A.ncols + A.nrows);
+  const bool search = !rs.row;
   const int chunk_len = chunk_entries(A.nnz);
   const int64_t nchunks = ceil_div<int64_t>(A.nnz, chunk_len);
-  const size_t rows_pad = carry_rows_bytes(A.nnz);
+  const BalancedScratch parts = balanced_scratch(A.nnz, N, vec, search);
   const int cbw = 64 * vec;
   const int64_t ncbv = ceil_div<int64_t>(N, cbw);
-  char *ws = (char *)ensure_workspace(env, A, entry_balanced_scratch_bytes(A.nnz, N, vec));
+  char *ws = (char *)ensure_workspace(env, A, parts.rows + parts.bounds + parts.carry);
   if (!env.ok()) return;
   int32_t *carry_row = (int32_t *)ws;
-  float *carry = (float *)(ws + rows_pad);
+  float *carry = (float *)(ws + parts.rows + parts.bounds);
+  if (parts.bounds) {
+    int2 *bounds = (int2 *)(ws + parts.rows);
+    US_LAUNCH(env, "spmm_bounds", 8.0 * nchunks, chunk_bounds_kernel, ceil_div<int64_t>(nchunks + 1, 256), 256, rs.ptr, rs.nparents,
+              A.nnz, chunk_len, nchunks, bounds);
+    rs.bounds = bounds;
+  }
+  // Rows of X of a kilobyte: eight of them in flight per wavefront keep the memory busy with 12 wavefronts per CU, and fewer
+  // entries in flight leave the L2 more to find again: three workgroups per CU, by the LDS that they ask for, where the
+  // slices of columns are full (5.2 M entries with local columns, N = 1000: 3267 -> 3049 us; power-law, no locality, 3389 ->
+  // 3360; N = 300, the second slice one sixth full: 876 -> 902; 400 k entries, N = 256: 104 -> 112).
+  const size_t few_resident = search && vec == 4 && A.nnz >= 1 << 21 && (ncbv * cbw - N) * 10 <= ncbv * cbw ? 48 << 10 : 0;
   {
     LaunchScope ls(env, name, 12.0 * A.nnz + xy);
     const int64_t per_xcd = ceil_div<int64_t>(ceil_div<int64_t>(nchunks, 4), 8);
     const dim3 grid((unsigned)(per_xcd * 8), (unsigned)ncbv);
-#define US_EB_LAUNCH(V, S) hipLaunchKernelGGL((coo_spmm_kernel<V, S>), grid, dim3(256), 0, env.stream, rs, col, (const float *)A.val, A.nnz, chunk_len, per_xcd, X, N, ldx, Y, ldy, accumulate ? 1 : 0, carry_row, carry)
+#define US_EB_LAUNCH(V, S) hipLaunchKernelGGL((coo_spmm_kernel<V, S>), grid, dim3(256), few_resident, env.stream, rs, col, (const float *)A.val, A.nnz, chunk_len, per_xcd, X, N, ldx, Y, ldy, accumulate ? 1 : 0, carry_row, carry)
     if (rs.row) {
       if (vec == 4) US_EB_LAUNCH(4, false); else if (vec == 2) US_EB_LAUNCH(2, false); else US_EB_LAUNCH(1, false);
     } else {
@@ -962,7 +991,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       if (store) zero_empty_rows(env, sr.ptr, A.nrows, Y, N, ldy);
       else if (!accumulate) zero_rows(env, Y, A.nrows, N, ldy);
       if (A.nnz > 0) {
-        RowSrc rs{nullptr, sr.ptr, sr.row_ids, A.nmajor};
+        RowSrc rs{nullptr, sr.ptr, sr.row_ids, A.nmajor, nullptr};
         entry_balanced_spmm(env, A, rs, sr.idx, "spmm_csr", vec, X, N, ldx, Y, ldy, !store);
       }
       return env.status;
@@ -984,7 +1013,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       if (!accumulate) zero_rows(env, Y, A.nrows, N, ldy);
       if (env.ok() && A.nnz > 0) {
         LaunchScope ls(env, "spmm_csb_atomic", 12.0 * A.nnz + xy);
-        const int chunk_len = chunk_entries(A.nnz);
+        const int chunk_len = chunk_entries(A.nnz, CSB_CHUNK_MAX);
         const int64_t per_xcd = ceil_div<int64_t>(ceil_div<int64_t>(ceil_div<int64_t>(A.nnz, chunk_len), 4), 8);
         const dim3 grid((unsigned)(per_xcd * 8), (unsigned)ceil_div<int64_t>(N, 64 * vec));
 #define US_CSB_LAUNCH(V) hipLaunchKernelGGL(csb_spmm_kernel<V>, grid, dim3(256), 0, env.stream, (const int32_t *)A.level[2].ptr, (const int32_t *)A.level[2].idx, (const int32_t *)A.level[3].idx, (const float *)A.val, A.nnz, chunk_len, per_xcd, A.nmajor, A.level[1].size, A.bh, A.bw, X, N, ldx, Y, ldy)
@@ -1019,7 +1048,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
         }
         return env.status;
       }
-      RowSrc rs{A.level[0].idx, nullptr, nullptr, 0};
+      RowSrc rs{A.level[0].idx, nullptr, nullptr, 0, nullptr};
       entry_balanced_spmm(env, A, rs, A.level[1].idx, "spmm_coo", vec, X, N, ldx, Y, ldy, true);
       return env.status;
     }

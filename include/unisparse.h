@@ -66,10 +66,11 @@ typedef struct us_ctx {
   /* How the Sort step (Figure 8) of the conversions made through this context finishes.
    *   US_SORT_FINISH_AUTO (0, what a zeroed us_ctx gives): by the target tuple and the number of entries.  (row, col)
    *     tuples of up to 42 bits and 67 M entries are parted by their top bits, then by splitters sampled from the entries,
-   *     into buckets that are sorted inside LDS; lists of 4,096 to 262,144 entries whose (row, col) takes more than 24
-   *     bits, and blocked tuples (BCSR, BDIA and the blocked #sum queries), go by US_SORT_FINISH_LDS; up to 2 M entries
-   *     that us_convert_formatted turns from compressed rows into columns or back by passes over the digits of the
-   *     target's major index alone; everything else by US_SORT_FINISH_PASSES;
+   *     into buckets that are sorted inside LDS; two kinds go by whole-array passes: 65,537 to 262,144 entries of at most
+   *     24 bits, and up to 2 M entries that us_convert_formatted turns from compressed rows into columns or back (over
+   *     the digits of the target's major index alone).  Blocked tuples (BCSR, BDIA and the blocked #sum queries) and
+   *     lists of 4,096 to 262,144 entries of more than 42 bits go by US_SORT_FINISH_LDS, everything else by
+   *     US_SORT_FINISH_PASSES;
    *   US_SORT_FINISH_LDS: whole-array digit passes over the top key bits only, every bucket of equal top bits
    *     is then finished inside LDS;
    *   US_SORT_FINISH_PASSES: whole-array digit passes over all key bits.

@@ -9,7 +9,7 @@
 // instead of 12 and a digit byte, through two passes and the finish (52 bytes read and written in all, pointers of the
 // rows included) instead of one pass per eight key bits (26 each).  COO -> CSR, digit passes / this, us: 16.8 M entries of a
 // power-law matrix, 40 key bits, 695 / 425; 40 M with local columns, 42 bits, 1630 / 964; 4 M 238 / 172; 1 M, even rows
-// 155 / 103; 300 k 138 / 94; 41 k, 24 bits (one parent) 87-103 / 75-80.
+// 155 / 103; 300 k 138 / 94; 41 k, 24 bits (one parent) 88 / 78.
 #include "device.h"
 #include "sort_key.h"
 
@@ -847,7 +847,9 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   }
   a.major_out = out.major; a.minor_out = out.minor; a.val_out = (uint32_t *)out.val;
   a.ptr = out.ptr; a.ngroups_out = ks.a_extent;
-  US_LAUNCH(env, "bucket_finish", (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
+  // (the profile knows the finish of short lists of more than 24 key bits by the name it has on the other way)
+  const char *name = nnz >= 4096 && nnz <= (1 << 18) && ks.total_bits > 24 ? "local_sort" : "bucket_finish";
+  US_LAUNCH(env, name, (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
 }
 
 }  // namespace us

@@ -966,11 +966,9 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   bool finish_local = false;
   // by default for blocked tuples only: block rows of FEM-like matrices fill evenly, while the rows of a
   // power-law graph do not (a heavy row's bucket needs extra splitting levels and the finish loses)
-  // ... and for lists of at most RS_SMALL tiles whose keys take more than three digit passes, whatever the tuple: there every
-  // launch costs more than the work it does, one digit pass + the finish is 9 launches, and a plain pass is two.  COO -> CSR,
-  // finish against passes, 4,200 to 262,000 entries: 24-bit keys 85-89 against 75-82 us with entries spread evenly, 87-106
-  // against 76-82 with rows of very different lengths; 30 bits 85-90 against 86-99 and 90-204 against 86-99 (rows heavy
-  // enough to send the list back to the plain passes); 36 bits 83-99 against 95-117; 40 bits 88-112 against 107-125.
+  // ... and for lists of at most RS_SMALL tiles whose keys take more than three digit passes and are too wide for the
+  // buckets: there every launch costs more than the work it does, one digit pass + the finish is 9 launches, and a plain
+  // pass is two (COO -> CSR, finish against passes, up to 262,000 entries: 40 bits 88-112 against 107-125 us).
   const bool short_list = nnz <= (int64_t)RS_SMALL * RS_TILE && total_bits > 3 * RS_MAXBITS;
   const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && (ks.mode != 0 || short_list));
   // ... and, unless the context asks for one of the two, neither for a list whose minor order is there already: the passes
@@ -1132,13 +1130,16 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
 }
 
 // Lists that are sorted by buckets (bucket_sort.hip) unless the context asks for one of the two ways here: all that it
-// takes but short lists of more than 24 key bits, which one digit pass and the finish in LDS sort in as few launches
-// (85-100 us against 97-110), and lists in order of their minor index up to 2 M entries, which take passes over the major
-// digits alone (CSR -> CSC, digit passes / buckets, us: 1.5 M entries 123 / 125, 3.1 M 173 / 162, 16.8 M 508 / 445).
+// takes but two kinds.  Up to 262,144 entries of at most 24 key bits are three digit passes of two launches: beyond one
+// parent (65,536 entries) that is as quick (200 k entries, even rows 95 / 91 us, power-law rows 94 / 96; 41 k 88 / 78).
+// Lists in order of their minor index take passes over the major digits alone up to 2 M entries (CSR -> CSC, digit passes /
+// buckets, us: 1.5 M entries 123 / 125, 3.1 M 173 / 160, 16.8 M 508 / 440).  Short lists of more key bits, one digit pass and
+// the finish here / buckets: 41 k entries, 26 bits 97 / 78, power-law rows 100 / 90; 100 k, 30 bits 103 / 92; 200 k with local
+// columns, whose heavy rows sent the finish back to the digit passes, 203 / 104; 200 k, 42 bits 157 / 130.
 static bool by_buckets(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
   if (env.lds_finish >= 0 || !bucket_sort_takes(nnz, ks)) return false;
   if (minor_sorted) return nnz > (1 << 21);
-  return nnz > (int64_t)RS_SMALL * RS_TILE || ks.total_bits <= 3 * RS_MAXBITS;
+  return nnz > (int64_t)RS_SMALL * RS_TILE || nnz <= (1 << 16) || ks.total_bits > 3 * RS_MAXBITS;
 }
 bool sort_gives_ptr(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
   return by_buckets(env, nnz, ks, minor_sorted) && nnz >= ks.a_extent;

@@ -353,6 +353,45 @@ __global__ __launch_bounds__(256) void ell_spmv_kernel(const int32_t *ecol, cons
   y[i] = s;
 }
 
+// The same with few rows: S wavefronts for the same 64 rows: wavefront p takes every S-th group of four slots, whose eight
+// loads are in flight together, and stops at a group that all its rows have ended before (slots fill from the front).
+// The partial sums meet in LDS, in order.  A lane per row walks its slots one after the other, two dependent loads each:
+// up to 131,072 rows that chain, not the memory, is what the product takes, and there are wavefronts to spare.  Plain / 4 / 16
+// wavefronts, us: 6,431 rows of up to 102 slots 25.8 / 7.1 / 5.0; 50,000 of 70 34.8 / 8.7 / 9.6; 80,753 of 28 10.0 / 5.4 /
+// 6.4; 2,048 of 33 9.1 / 4.9 / 4.9; 60,732 of 7 5.4 / 5.3 / 5.3; 500,000 of 20 21.3 / 24.7 / 36.6.
+constexpr int ES_U = 4;
+static int ell_split(int64_t nrows, int64_t K) { return nrows > 131072 || K <= 8 ? 1 : (nrows <= 16384 && K >= 64 ? 16 : 4); }
+template <int S>
+__global__ __launch_bounds__(64 * S) void ell_spmv_split_kernel(const int32_t *ecol, const float *ev, int64_t K, int64_t nrows,
+                                                                      const float *x, float *y, int accumulate) {
+  __shared__ float s_sum[S][64];
+  const int lane = lane_id(), part = wave_id();
+  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
+  const bool in = i < nrows;
+  float s = 0.f;
+  if (part == 0 && accumulate && in) s = y[i];
+  for (int64_t k0 = part * ES_U; k0 < K; k0 += S * ES_U) {
+    int32_t c[ES_U];
+    float v[ES_U];
+#pragma unroll
+    for (int u = 0; u < ES_U; ++u) {
+      const bool live = in && k0 + u < K;
+      c[u] = live ? ecol[(k0 + u) * nrows + i] : -1;
+      v[u] = live ? ev[(k0 + u) * nrows + i] : 0.f;
+    }
+    if (!__any(c[0] >= 0)) break;
+#pragma unroll
+    for (int u = 0; u < ES_U; ++u)
+      if (c[u] >= 0) s += v[u] * x[c[u]];
+  }
+  s_sum[part][lane] = s;
+  __syncthreads();
+  if (part != 0) return;
+#pragma unroll
+  for (int p = 1; p < S; ++p) s += s_sum[p][lane];
+  if (in) y[i] = s;
+}
+
 // BCSR: one wavefront per block row, lanes over the entries of the blocks
 __global__ __launch_bounds__(256) void bcsr_spmv_kernel(const int32_t *ptr, const int32_t *idx, const float *val,
                                                        int64_t nbr, int bh, int bw, int64_t nrows, int64_t ncols,
@@ -520,8 +559,16 @@ us_status spmv_impl(Env &env, const us_formatted &A, const float *x, float *y, b
                   A.nmajor, A.nrows, A.ncols, A.swapped ? 1 : 0, x, y, accumulate ? 1 : 0);
       return env.status;
     case P_ELL:
-      US_LAUNCH(env, "spmv_ell", 8.0 * A.nval + 8.0 * A.nrows, ell_spmv_kernel, ceil_div<int64_t>(A.nrows, 256), 256,
-                (const int32_t *)A.level[2].idx, (const float *)A.val, A.nmajor, A.nrows, x, y, accumulate ? 1 : 0);
+      {
+        const double bytes = 8.0 * A.nval + 8.0 * A.nrows;
+        const int32_t *ec = A.level[2].idx;
+        const float *ev = (const float *)A.val;
+        const int acc = accumulate ? 1 : 0;
+        const int split = ell_split(A.nrows, A.nmajor);
+        if (split == 16) US_LAUNCH(env, "spmv_ell", bytes, ell_spmv_split_kernel<16>, ceil_div<int64_t>(A.nrows, 64), 1024, ec, ev, A.nmajor, A.nrows, x, y, acc);
+        else if (split == 4) US_LAUNCH(env, "spmv_ell", bytes, ell_spmv_split_kernel<4>, ceil_div<int64_t>(A.nrows, 64), 256, ec, ev, A.nmajor, A.nrows, x, y, acc);
+        else US_LAUNCH(env, "spmv_ell", bytes, ell_spmv_kernel, ceil_div<int64_t>(A.nrows, 256), 256, ec, ev, A.nmajor, A.nrows, x, y, acc);
+      }
       return env.status;
     case P_BCSR:
       US_LAUNCH(env, "spmv_bcsr", 4.0 * A.nval + 4.0 * A.nblk + 8.0 * A.nrows, bcsr_spmv_kernel,

@@ -850,9 +850,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   }
   a.major_out = out.major; a.minor_out = out.minor; a.val_out = (uint32_t *)out.val;
   a.ptr = out.ptr; a.ngroups_out = ks.a_extent;
-  // (the profile knows the finish of short lists of more than 24 key bits by the name it has on the other way)
-  const char *name = nnz >= 4096 && nnz <= (1 << 18) && ks.total_bits > 24 ? "local_sort" : "bucket_finish";
-  US_LAUNCH(env, name, (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
+  US_LAUNCH(env, "bucket_finish", (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
 }
 
 }  // namespace us

@@ -207,14 +207,14 @@ def test_pieces_between_half_and_full_capacity_are_groups_of_their_own(ctx):
 
 
 @pytest.mark.parametrize("skewed", [False, True], ids=["even", "skewed"])
-@pytest.mark.parametrize("nr,nc,nnz,finish", [
-    (4096, 4096, 4095, False), (4096, 4096, 4096, False), (4096, 4096, 262144, False), (4096, 4096, 262145, False),
-    (4096, 4097, 4095, False), (4096, 4097, 4096, True), (4097, 4096, 40960, True), (4096, 4097, 262144, True),
-    (4096, 4097, 262145, False), (256, 256, 4096, False), (1 << 20, 16, 5000, False), (16, 1 << 20, 262144, False),
-    (1 << 20, 17, 5000, True), (1 << 24, 1, 5000, False)])
-def test_short_lists_take_the_finish_beyond_three_digits(ctx, nr, nc, nnz, finish, skewed):
-    """(row, col) lists of at most 64 tiles, by default: three digit passes or fewer do without the finish (24 bits and
-    below), more bits take it from 4096 entries on; longer lists never do."""
+@pytest.mark.parametrize("nr,nc,nnz,buckets", [
+    (4096, 4096, 4095, True), (4096, 4096, 4096, True), (4096, 4096, 65537, False), (4096, 4096, 262144, False),
+    (4096, 4096, 262145, True), (4096, 4097, 4095, True), (4096, 4097, 4096, True), (4097, 4096, 40960, True),
+    (4096, 4097, 262144, True), (4096, 4097, 262145, True), (256, 256, 4096, True), (1 << 20, 16, 5000, True),
+    (16, 1 << 20, 262144, False), (1 << 20, 17, 5000, True), (1 << 24, 1, 5000, True)])
+def test_the_way_of_short_lists(ctx, nr, nc, nnz, buckets, skewed):
+    """(row, col) lists, by default: 65,537 to 262,144 entries of 24 bits at most take plain digit passes, the others the
+    buckets, and none the finish of the blocked tuples."""
     from paper_2403_05802_amd import binding as B
     from helpers import assert_same_layout, dev, us_desc_of
     rng = np.random.default_rng(nr + nc + nnz)
@@ -232,6 +232,7 @@ def test_short_lists_take_the_finish_beyond_three_digits(ctx, nr, nc, nnz, finis
         finally:
             ctx.disable_profile()
         if lin.size == nnz:
-            assert ("local_sort" in launches) == finish, (d, launches)
+            assert ("bucket_finish" in launches) == buckets and ("radix_scatter" in launches) != buckets, (d, launches)
+            assert "local_sort" not in launches, (d, launches)
         assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{nr}x{nc}, {r.size} entries -> {d}")
         g.free()

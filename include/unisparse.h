@@ -68,9 +68,8 @@ typedef struct us_ctx {
    *     tuples of up to 42 bits and 67 M entries are parted by their top bits, then by splitters sampled from the entries,
    *     into buckets that are sorted inside LDS; two kinds go by whole-array passes: 65,537 to 262,144 entries of at most
    *     24 bits, and up to 2 M entries that us_convert_formatted turns from compressed rows into columns or back (over
-   *     the digits of the target's major index alone).  Blocked tuples (BCSR, BDIA and the blocked #sum queries) and
-   *     lists of 4,096 to 262,144 entries of more than 42 bits go by US_SORT_FINISH_LDS, everything else by
-   *     US_SORT_FINISH_PASSES;
+   *     the digits of the target's major index alone).  Blocked tuples (BCSR, BDIA and the blocked #sum queries) go by
+   *     US_SORT_FINISH_LDS, everything else (wider (row, col) tuples, longer lists) by US_SORT_FINISH_PASSES;
    *   US_SORT_FINISH_LDS: whole-array digit passes over the top key bits only, every bucket of equal top bits
    *     is then finished inside LDS;
    *   US_SORT_FINISH_PASSES: whole-array digit passes over all key bits.

@@ -27,7 +27,7 @@ struct BkArgs {
   const int32_t *row, *col; const uint32_t *val;   // the caller's list
   uint32_t n; KeySpec ks;
   int dshift;                  // key bits below the parent's: at most 32
-  int lead_shift;              // >= 0: the parent is (leading field of the key) >> lead_shift, whatever the other fields hold
+  int lead_shift;              // >= 0: the parent is (major index) >> lead_shift, whatever the minor index holds
   uint32_t nparents;           // a power of two
   int coo_vec;                 // row, col and val are 16-byte aligned
   // first pass: every workgroup takes per_group consecutive entries
@@ -51,9 +51,7 @@ struct BkArgs {
 
 __device__ __forceinline__ uint32_t parent_of_entry(const BkArgs &a, uint32_t r, uint32_t c, Key key) {
   if (a.lead_shift < 0) return (uint32_t)(key >> a.dshift) & (a.nparents - 1);
-  uint32_t lead = a.ks.swap ? c : r;
-  if (a.ks.mode != 0) lead /= a.ks.bh;
-  return (lead >> a.lead_shift) & (a.nparents - 1);
+  return ((a.ks.swap ? c : r) >> a.lead_shift) & (a.nparents - 1);
 }
 __device__ __forceinline__ uint32_t low_mask(int dshift) { return dshift >= 32 ? 0xFFFFFFFFu : (1u << dshift) - 1u; }
 
@@ -91,7 +89,7 @@ __global__ __launch_bounds__(BH_T) void bucket_hist_kernel(BkArgs a) {
   const uint32_t copy = threadIdx.x & (BH_COPIES - 1);
   const int32_t *lead = a.ks.swap ? a.col : a.row;
   auto count = [&](uint32_t p) { atomicAdd(&s_hist[p * BH_COPIES + copy], 1u); };
-  auto of_lead = [&](uint32_t x) { return ((a.ks.mode != 0 ? x / a.ks.bh : x) >> a.lead_shift) & (a.nparents - 1); };
+  auto of_lead = [&](uint32_t x) { return (x >> a.lead_shift) & (a.nparents - 1); };
   uint32_t i = begin;
   if (a.lead_shift >= 0 && a.coo_vec) {
     for (; i + 8 * BH_T <= end; i += 8 * BH_T) {   // (begin is a multiple of four entries)
@@ -812,8 +810,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.row = row; a.col = col; a.val = (const uint32_t *)val;
   a.n = (uint32_t)nnz; a.ks = ks; a.flags = flags;
   a.dshift = ks.total_bits - b.bits;
-  const int lead_at = ks.total_bits - bits_for(ks.mode == 0 ? ks.a_extent - 1 : ceil_div(ks.a_extent, ks.bh) - 1);
-  a.lead_shift = a.dshift >= lead_at ? a.dshift - lead_at : -1;
+  a.lead_shift = a.dshift >= ks.b_bits ? a.dshift - ks.b_bits : -1;
   a.nparents = b.nparents; a.per_group = b.per_group; a.ngroups = b.ngroups;
   a.groups_per_xcd = ceil_div<uint32_t>(b.ngroups, 8u);
   a.coo_vec = ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;

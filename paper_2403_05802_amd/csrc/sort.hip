@@ -966,13 +966,9 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
   bool finish_local = false;
   // by default for blocked tuples only: block rows of FEM-like matrices fill evenly, while the rows of a
   // power-law graph do not (a heavy row's bucket needs extra splitting levels and the finish loses)
-  // ... and for lists of at most RS_SMALL tiles whose keys take more than three digit passes and are too wide for the
-  // buckets: there every launch costs more than the work it does, one digit pass + the finish is 9 launches, and a plain
-  // pass is two (COO -> CSR, finish against passes, up to 262,000 entries: 40 bits 88-112 against 107-125 us).
-  const bool short_list = nnz <= (int64_t)RS_SMALL * RS_TILE && total_bits > 3 * RS_MAXBITS;
-  const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && (ks.mode != 0 || short_list));
-  // ... and, unless the context asks for one of the two, neither for a list whose minor order is there already: the passes
-  // over the major digits are all it takes, three for up to 2^24 rows or columns (CSR to CSC, 200,003 rows, 3.1 M entries:
+  const bool want_finish = env.lds_finish > 0 || (env.lds_finish < 0 && ks.mode != 0);
+  // Unless the context asks for one of the two, a list whose minor order is there already takes neither: the passes
+  // over the major digits are all it needs, three for up to 2^24 rows or columns (CSR to CSC, 200,003 rows, 3.1 M entries:
   // 224 us with all five passes over 36-bit keys, 169 us with three over the 18 bits of the column)
   const bool major_only = out.minor_sorted && env.lds_finish < 0 && in_mode == IN_COO && ks.mode == 0 && final_mode == OUT_UNPACK;
   if (major_only) {

@@ -211,10 +211,12 @@ def test_pieces_between_half_and_full_capacity_are_groups_of_their_own(ctx):
     (4096, 4096, 4095, True), (4096, 4096, 4096, True), (4096, 4096, 65537, False), (4096, 4096, 262144, False),
     (4096, 4096, 262145, True), (4096, 4097, 4095, True), (4096, 4097, 4096, True), (4097, 4096, 40960, True),
     (4096, 4097, 262144, True), (4096, 4097, 262145, True), (256, 256, 4096, True), (1 << 20, 16, 5000, True),
-    (16, 1 << 20, 262144, False), (1 << 20, 17, 5000, True), (1 << 24, 1, 5000, True)])
+    (16, 1 << 20, 262144, False), (1 << 20, 17, 5000, True), (1 << 24, 1, 5000, True),
+    (1 << 21, 1 << 21, 5000, True), ((1 << 21) + 1, 1 << 21, 5000, False), (1 << 22, 1 << 21, 200_000, False),
+    (1 << 22, 1 << 22, 5000, False), (1 << 22, 1 << 22, 300_000, False)])
 def test_the_way_of_short_lists(ctx, nr, nc, nnz, buckets, skewed):
-    """(row, col) lists, by default: 65,537 to 262,144 entries of 24 bits at most take plain digit passes, the others the
-    buckets, and none the finish of the blocked tuples."""
+    """(row, col) lists, by default: 65,537 to 262,144 entries of 24 bits at most and all lists of more than 42 bits take
+    plain digit passes, the others the buckets, and none the finish of the blocked tuples."""
     from paper_2403_05802_amd import binding as B
     from helpers import assert_same_layout, dev, us_desc_of
     rng = np.random.default_rng(nr + nc + nnz)

@@ -21,7 +21,12 @@ constexpr int BK_MAXK = 128;        // most children of a parent
 constexpr int BK_OVERSAMPLE = 64;   // sampled keys per child
 constexpr int BK_MAXBITS = 10, BK_MAXBINS = 1 << BK_MAXBITS;   // parents
 
-struct BkParent { uint32_t start, size, child0, k, tile0; };
+struct BkParent { uint32_t start, size, child0, k, tile0, region0; };
+
+// BkArgs::child, third word: the parent (BK_MAXBITS bits), what the child is, the region of the parent's first child in rec2
+constexpr uint32_t BK_SHARED = 1u << BK_MAXBITS;   // it has siblings (or comes from the caller's list): its entries are in its region, else in rec1
+constexpr uint32_t BK_LAST = 2u << BK_MAXBITS;     // it is the last one of its parent
+constexpr int BK_REGION_SHIFT = BK_MAXBITS + 2;
 
 struct BkArgs {
   const int32_t *row, *col; const uint32_t *val;   // the caller's list
@@ -38,11 +43,11 @@ struct BkArgs {
   // second pass
   BkParent *parent;            // [nparents]
   uint32_t *totals;            // [0] children, [1] tiles of parents with more than one child
-  uint4 *child;                // [max_children] {start of the parent, its first child, parent | its children << 16, smallest low key}
+  uint4 *child;                // [max_children] {start of the parent, its first child, parent and BK_*, smallest low key}
   uint32_t *cursor;            // [max_children] entries of the child
   uint32_t *tile_parent;       // [max_tiles]
-  uint32_t max_children, max_tiles, tiles_per_xcd, children_per_xcd;
-  uint2 *rec2;                 // [max_children][BK_CAP]
+  uint32_t max_children, max_regions, max_tiles, tiles_per_xcd, children_per_xcd;
+  uint2 *rec2;                 // [max_regions][BK_CAP]: the children that share a parent
   // output
   int32_t *major_out, *minor_out; uint32_t *val_out;
   int32_t *ptr; uint32_t ngroups_out;   // pointers over the major indices 0..ngroups_out, or null
@@ -514,6 +519,8 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
   const uint32_t p = blockIdx.x;
   if (gave_up(a, true)) return;
   {
+    // children and parents of a single child, summed up together: below 2^18 and 2^14 of them
+    constexpr uint32_t ALONE = 1u << 18;
     uint32_t size[PER], k[PER], tiles[PER], ssum = 0, ksum = 0, tsum = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -521,28 +528,32 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
       size[q] = x < a.nparents ? (COO ? a.n : a.ptotal[x]) : 0u;
       k[q] = x < a.nparents ? max((size[q] + BK_TARGET - 1) / BK_TARGET, 1u) : 0u;
       tiles[q] = (COO || k[q] > 1) ? (size[q] + BX_TILE - 1) / BX_TILE : 0u;
-      ssum += size[q]; ksum += k[q]; tsum += tiles[q];
+      const bool alone = !COO && k[q] == 1;
+      ssum += size[q]; ksum += k[q] + (alone ? ALONE : 0u); tsum += tiles[q];
     }
     uint32_t s0 = scan_one_barrier<SM_T>(ssum, s_wave[0]), k0 = scan_one_barrier<SM_T>(ksum, s_wave[1]),
              t0 = scan_one_barrier<SM_T>(tsum, s_wave[2]);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-      if ((uint32_t)(tid * PER + q) == p) s_me = BkParent{s0, size[q], k0, k[q], t0};
-      s0 += size[q]; k0 += k[q]; t0 += tiles[q];
+      const uint32_t child0 = k0 % ALONE;
+      if ((uint32_t)(tid * PER + q) == p) s_me = BkParent{s0, size[q], child0, k[q], t0, child0 - k0 / ALONE};
+      s0 += size[q]; k0 += k[q] + (!COO && k[q] == 1 ? ALONE : 0u); t0 += tiles[q];
     }
-    if (p == 0 && tid == SM_T - 1) { a.totals[0] = k0; a.totals[1] = t0; }
+    if (p == 0 && tid == SM_T - 1) { a.totals[0] = k0 % ALONE; a.totals[1] = t0; }
   }
   __syncthreads();
   const BkParent me = s_me;
+  const bool shared = COO || me.k > 1;
   if (tid == 0) a.parent[p] = me;
   // (the sums are bounded by what the host allocated for; the guards keep it so whatever the sizes say)
-  if (me.k > (uint32_t)BK_MAXK || me.child0 + me.k > a.max_children) {
+  if (me.k > (uint32_t)BK_MAXK || me.child0 + me.k > a.max_children || (shared && me.region0 + me.k > a.max_regions)) {
     if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
     return;
   }
   auto child = [&](uint32_t c, uint32_t low) {
-    a.child[me.child0 + c] = make_uint4(me.start, me.child0, p | me.k << 16, low);
-    a.cursor[me.child0 + c] = !COO && me.k == 1 ? me.size : 0u;
+    const uint32_t kind = p | (shared ? BK_SHARED : 0u) | (c + 1 == me.k ? BK_LAST : 0u) | me.region0 << BK_REGION_SHIFT;
+    a.child[me.child0 + c] = make_uint4(me.start, me.child0, kind, low);
+    a.cursor[me.child0 + c] = shared ? 0u : me.size;
   };
   if (tid == 0) child(0, 0u);
   if (me.k == 1) return;
@@ -659,7 +670,7 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
     const uint32_t i = j * BX_T + tid;
     if (i < in_tile) {
       const uint32_t child = s_bin[i], at = s_goff[child] + i;
-      if (at < (uint32_t)BK_CAP) a.rec2[(size_t)(me.child0 + child) * BK_CAP + at] = s_rec[i];
+      if (at < (uint32_t)BK_CAP) a.rec2[(size_t)(me.region0 + child) * BK_CAP + at] = s_rec[i];
     }
   }
 }
@@ -685,12 +696,13 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   const uint32_t m = a.cursor[at], nchildren = min(a.totals[0], a.max_children);
   if (tid == 0) s_before = 0;
   if (gave_up(a, true) || c >= nchildren) return;
-  const uint32_t start = me.x, child0 = me.y, p = me.z & 0xFFFFu, k = me.z >> 16, j0 = c - child0;
+  const uint32_t start = me.x, child0 = me.y, p = me.z & (BK_MAXBINS - 1), j0 = c - child0;
+  const bool last = me.z & BK_LAST;
   if (m > (uint32_t)BK_CAP) return;   // (the call will be run again)
   if ((uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[child0 + tid]);   // j0 < BK_MAXK <= BF_T
-  const uint2 *src = k > 1 || !a.rec1 ? a.rec2 + (size_t)c * BK_CAP : a.rec1 + start;   // (one parent, the caller's list: always rec2)
+  const uint2 *src = me.z & BK_SHARED ? a.rec2 + (size_t)((me.z >> BK_REGION_SHIFT) + j0) * BK_CAP : a.rec1 + start;
   const uint32_t lmask = low_mask(a.dshift);
-  const uint32_t lo = me.w, hi = j0 + 1 < k ? after.w : lmask;   // (hi itself may be the next child's)
+  const uint32_t lo = me.w, hi = last ? lmask : after.w;   // (hi itself may be the next child's)
   uint32_t key[BF_IPT], val[BF_IPT], pos[BF_IPT];
 #pragma unroll
   for (int j = 0; j < BF_IPT; ++j) {
@@ -739,8 +751,8 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   if (dup) a.flags->duplicate = 1;
   if (a.ptr) {   // the major indices whose first possible key lies in this child's range: entries below that key
     const Key l = base | lo, h = base | hi;
-    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = j0 + 1 < k ? (h + bmask) >> a.ks.b_bits : (h >> a.ks.b_bits) + 1;
-    if (p + 1 == a.nparents && j0 + 1 == k) g1 = (Key)a.ngroups_out + 1;
+    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = last ? (h >> a.ks.b_bits) + 1 : (h + bmask) >> a.ks.b_bits;
+    if (p + 1 == a.nparents && last) g1 = (Key)a.ngroups_out + 1;
     if (g1 > (Key)a.ngroups_out + 1) g1 = (Key)a.ngroups_out + 1;
     for (Key g = g0 + tid; g < g1; g += BF_T) {
       const Key first = (g << a.ks.b_bits) - base;   // may lie beyond 32 bits (behind the last key): all entries are below
@@ -762,7 +774,7 @@ struct BucketPlan {
   bool direct;     // one parent: the caller's list
   int bits;        // of the parents
   bool large;      // the first pass takes large tiles
-  uint32_t nparents, per_group, ngroups, max_children, max_tiles;
+  uint32_t nparents, per_group, ngroups, max_children, max_regions, max_tiles;
 };
 
 static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
@@ -784,8 +796,10 @@ static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
     b.per_group = each * tile;
     b.ngroups = ceil_div(tiles, each);
   }
-  b.max_children = (uint32_t)(nnz / BK_TARGET) + b.nparents + 1;
-  b.max_tiles = (uint32_t)(nnz / BX_TILE) + (uint32_t)std::min<int64_t>(b.nparents, nnz / BK_TARGET) + 1;
+  const uint32_t full = (uint32_t)(nnz / BK_TARGET), shared = std::min(b.nparents, full);   // parents of more than one child, at most
+  b.max_children = full + b.nparents + 1;
+  b.max_regions = b.direct ? full + 1 : full + shared;
+  b.max_tiles = (uint32_t)(nnz / BX_TILE) + shared + 1;
   return b;
 }
 
@@ -800,7 +814,7 @@ size_t bucket_sort_temp_bytes(int64_t nnz, const KeySpec &ks) {
   const BucketPlan b = bucket_plan(nnz, ks);
   auto g = [](size_t bytes) { return Env::granule(bytes); };
   return (b.direct ? 0 : g(4ull * b.ngroups * b.nparents) + g(4ull * b.nparents) + g(8ull * nnz)) + g(sizeof(BkParent) * b.nparents) +
-         g(8) + g(16ull * b.max_children) + g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_children);
+         g(8) + g(16ull * b.max_children) + g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_regions);
 }
 
 void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz, const KeySpec &ks,
@@ -814,7 +828,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.nparents = b.nparents; a.per_group = b.per_group; a.ngroups = b.ngroups;
   a.groups_per_xcd = ceil_div<uint32_t>(b.ngroups, 8u);
   a.coo_vec = ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
-  a.max_children = b.max_children; a.max_tiles = b.max_tiles;
+  a.max_children = b.max_children; a.max_regions = b.max_regions; a.max_tiles = b.max_tiles;
   a.tiles_per_xcd = ceil_div<uint32_t>(b.max_tiles, 8u);
   a.children_per_xcd = ceil_div<uint32_t>(b.max_children, 8u);
   env.reserve(bucket_sort_temp_bytes(nnz, ks));
@@ -828,7 +842,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.child = env.temp<uint4>(b.max_children);
   a.cursor = env.temp<uint32_t>(b.max_children);
   a.tile_parent = env.temp<uint32_t>(b.max_tiles);
-  a.rec2 = env.temp<uint2>((size_t)b.max_children * BK_CAP);
+  a.rec2 = env.temp<uint2>((size_t)b.max_regions * BK_CAP);
   if (!env.ok()) return;
   if (!b.direct) {
     US_LAUNCH(env, "bucket_hist", (a.lead_shift >= 0 ? 4.0 : 8.0) * nnz, bucket_hist_kernel, a.groups_per_xcd * 8, BH_T, a);

@@ -104,6 +104,24 @@ def test_a_parent_of_too_many_entries_goes_to_the_digit_passes(ctx):
         g.free()
 
 
+@pytest.mark.parametrize("n", [1, 1000, 65_536, 1_000_000])
+def test_scratch_of_wide_keys_goes_with_the_entries(ctx, n):
+    """42 key bits make 1024 parents however few entries there are.  Per entry: the list by parent 8 bytes, a region of 2048
+    records of 8 bytes for every child that shares its parent, at most two children per 1024 entries: 40 bytes; the layout
+    itself 12; tables of the parents and, per workgroup of the first pass (4096 entries), of their counts 1 byte each."""
+    import torch
+    from paper_2403_05802_amd import binding as B
+    from helpers import dev, us_desc_of
+    nr = nc = 1 << 21
+    r, c, v = entries(np.random.default_rng(n), nr, nc, n, "uniform")
+    r, c, v = dev(r), dev(c), dev(v)
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    B.us_convert(ctx, nr, nc, r, c, v, us_desc_of(O.COO())).free()
+    assert torch.cuda.max_memory_allocated() - before <= 56 * n + 200_000
+
+
 @pytest.mark.parametrize("nr,nc,n", [(4096, 4096, 30_000), (70_000, 70_000, 300_000)])
 def test_errors_are_reported(ctx, nr, nc, n):
     from paper_2403_05802_amd import binding as B

@@ -65,8 +65,8 @@ typedef struct us_ctx {
   void *profile;    /* us_profile* or NULL: per-kernel HIP-event timing (see us_profile_*) */
   /* How the Sort step (Figure 8) of the conversions made through this context finishes.
    *   US_SORT_FINISH_AUTO (0, what a zeroed us_ctx gives): by the target tuple and the number of entries.  (row, col)
-   *     tuples of up to 42 bits and 67 M entries are parted by their top bits, then by splitters sampled from the entries,
-   *     into buckets that are sorted inside LDS; two kinds go by whole-array passes: 65,537 to 262,144 entries of at most
+   *     tuples of up to 42 bits and 67 M entries are parted by equal shares of their range, then by splitters sampled
+   *     from the entries, into buckets that are sorted inside LDS; two kinds go by whole-array passes: 65,537 to 262,144 entries of at most
    *     24 bits, and up to 2 M entries that us_convert_formatted turns from compressed rows into columns or back (over
    *     the digits of the target's major index alone).  Blocked tuples (BCSR, BDIA and the blocked #sum queries) go by
    *     US_SORT_FINISH_LDS, everything else (wider (row, col) tuples, longer lists) by US_SORT_FINISH_PASSES;
@@ -76,7 +76,7 @@ typedef struct us_ctx {
    * The finish pays off when entries spread evenly over the buckets (block rows of a FEM-like matrix: COO->BCSR
    * of 50 M entries in 38 % less time); heavy rows of a power-law matrix need extra splitting passes and gain nothing.
    * Results are identical in every mode; an input that a way cannot take (the finish: more than 262,144 entries sharing
-   * their top key bits, or 4,096 sharing 8 more; the buckets: more than 131,072 sharing theirs) is sorted again with
+   * their top key bits, or 4,096 sharing 8 more; the buckets: more than 131,072 in one of at most 1024 shares) is sorted again with
    * whole-array passes by the same call. */
   int32_t sort_finish;
 } us_ctx;

@@ -1,11 +1,11 @@
-// The Sort operator for lists of many entries: most significant digits first.  The list is cut into parents by the
-// top bits of the key (one pass over memory), every parent into children of about BK_TARGET entries by splitters drawn
-// from a sample of its own keys (a second pass), and a child is sorted where it lies in LDS while its sorted entries and
-// the pointers of its rows are written.  Keys are unique, so splitters tell apart what equal top bits leave together
+// The Sort operator for lists of many entries: most significant digits first.  The list is cut into parents, equal
+// shares of the range of the key (one pass over memory), every parent into children of about BK_TARGET entries by splitters
+// drawn from a sample of its own keys (a second pass), and a child is sorted where it lies in LDS while its sorted entries
+// and the pointers of its rows are written.  Keys are unique, so splitters tell apart what one share leaves together
 // (a heavy row of a power-law matrix fills several children), and no pass but the last has an order to keep: places inside
 // a tile come from one LDS atomic per entry.
 //
-// Against the least-significant-digit passes of sort.hip: an entry travels as 8 bytes {key below the parent's bits, value}
+// Against the least-significant-digit passes of sort.hip: an entry travels as 8 bytes {key less the parent's first, value}
 // instead of 12 and a digit byte, through two passes and the finish (52 bytes read and written in all, pointers of the
 // rows included) instead of one pass per eight key bits (26 each).  COO -> CSR, digit passes / this, us: 16.8 M entries of a
 // power-law matrix, 40 key bits, 695 / 425; 40 M with local columns, 42 bits, 1630 / 964; 4 M 238 / 172; 1 M, even rows
@@ -21,6 +21,18 @@ constexpr int BK_MAXK = 128;        // most children of a parent
 constexpr int BK_OVERSAMPLE = 64;   // sampled keys per child
 constexpr int BK_MAXBITS = 10, BK_MAXBINS = 1 << BK_MAXBITS;   // parents
 
+// The parents are equal shares of the range that the major index really has, whole rows where there are more of them than
+// parents (rows >= 1: share = major / rows, an exact division of 31 bits by multiplication), else pieces of 2^shift keys.
+// (By the key's top bits half of the parents are empty when the row count lies just above a power of two, and the others
+// twice as full: 40 M entries of a power-law matrix of 1,050,000 rows had a parent of more than BK_MAXK children, which sent
+// the call back to the digit passes, 1657 us; now 933.  2,000,000 rows 933 / 937.)
+struct KeyShares {
+  uint32_t count, rows;
+  uint32_t mul; int mul_shift;
+  int shift;
+  uint64_t width;              // keys of a share: at most 2^32
+};
+
 struct BkParent { uint32_t start, size, child0, k, tile0, region0; };
 
 // BkArgs::child, third word: the parent (BK_MAXBITS bits), what the child is, the region of the parent's first child in rec2
@@ -31,9 +43,8 @@ constexpr int BK_REGION_SHIFT = BK_MAXBITS + 2;
 struct BkArgs {
   const int32_t *row, *col; const uint32_t *val;   // the caller's list
   uint32_t n; KeySpec ks;
-  int dshift;                  // key bits below the parent's: at most 32
-  int lead_shift;              // >= 0: the parent is (major index) >> lead_shift, whatever the minor index holds
-  uint32_t nparents;           // a power of two
+  KeyShares share;
+  uint32_t nparents;
   int coo_vec;                 // row, col and val are 16-byte aligned
   // first pass: every workgroup takes per_group consecutive entries
   uint32_t per_group, ngroups, groups_per_xcd;
@@ -54,11 +65,22 @@ struct BkArgs {
   Flags *flags;
 };
 
-__device__ __forceinline__ uint32_t parent_of_entry(const BkArgs &a, uint32_t r, uint32_t c, Key key) {
-  if (a.lead_shift < 0) return (uint32_t)(key >> a.dshift) & (a.nparents - 1);
-  return ((a.ks.swap ? c : r) >> a.lead_shift) & (a.nparents - 1);
+// (a coordinate out of range is reported, not sorted: it only has to fall into some share)
+__device__ __forceinline__ uint32_t share_of_lead(const KeyShares &s, uint32_t lead) {
+  return min(__umulhi(lead << 1, s.mul) >> s.mul_shift, s.count - 1);
 }
-__device__ __forceinline__ uint32_t low_mask(int dshift) { return dshift >= 32 ? 0xFFFFFFFFu : (1u << dshift) - 1u; }
+// the entry's share and the rest of its key
+__device__ __forceinline__ uint32_t share_of_entry(const BkArgs &a, uint32_t r, uint32_t c, uint32_t *low) {
+  const uint32_t lead = a.ks.swap ? c : r, minor = a.ks.swap ? r : c;
+  if (a.share.rows) {
+    const uint32_t s = share_of_lead(a.share, lead);
+    *low = ((lead - s * a.share.rows) << a.ks.b_bits) | minor;
+    return s;
+  }
+  const Key key = ((Key)lead << a.ks.b_bits) | minor;
+  *low = (uint32_t)key & (uint32_t)(a.share.width - 1);
+  return (uint32_t)min(key >> a.share.shift, (Key)(a.share.count - 1));
+}
 
 // A kernel of the call has given up: a coordinate out of range, or an input this sort does not take.  The tables that later
 // kernels index with may then be unwritten.  Read once per workgroup, because workgroups of the same launch may set it.
@@ -94,9 +116,9 @@ __global__ __launch_bounds__(BH_T) void bucket_hist_kernel(BkArgs a) {
   const uint32_t copy = threadIdx.x & (BH_COPIES - 1);
   const int32_t *lead = a.ks.swap ? a.col : a.row;
   auto count = [&](uint32_t p) { atomicAdd(&s_hist[p * BH_COPIES + copy], 1u); };
-  auto of_lead = [&](uint32_t x) { return (x >> a.lead_shift) & (a.nparents - 1); };
+  auto of_lead = [&](uint32_t x) { return share_of_lead(a.share, x); };
   uint32_t i = begin;
-  if (a.lead_shift >= 0 && a.coo_vec) {
+  if (a.share.rows && a.coo_vec) {
     for (; i + 8 * BH_T <= end; i += 8 * BH_T) {   // (begin is a multiple of four entries)
       const uint4 *p4 = reinterpret_cast<const uint4 *>(lead + i);
       const uint4 x = p4[threadIdx.x], y = p4[BH_T + threadIdx.x];
@@ -105,11 +127,11 @@ __global__ __launch_bounds__(BH_T) void bucket_hist_kernel(BkArgs a) {
     }
   }
   for (uint32_t e = i + threadIdx.x; e < end; e += BH_T) {
-    if (a.lead_shift >= 0) {
+    if (a.share.rows) {
       count(of_lead((uint32_t)lead[e]));
     } else {
-      const uint32_t r = (uint32_t)a.row[e], c = (uint32_t)a.col[e];
-      count(parent_of_entry(a, r, c, build_key(a.ks, r, c)));
+      uint32_t low;
+      count(share_of_entry(a, (uint32_t)a.row[e], (uint32_t)a.col[e], &low));
     }
   }
   __syncthreads();
@@ -188,7 +210,6 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
     for (int q = 0; q < PER; ++q) { next[q] += run; run += t[q]; }
   }
   bool bad = false;
-  const uint32_t lmask = low_mask(a.dshift);
   for (uint32_t base = begin; base < end; base += TILE) {
     const uint32_t in_tile = min((uint32_t)TILE, end - base);
     uint32_t key[IPT], val[IPT], bin[IPT], arr[IPT];
@@ -204,10 +225,8 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
         const uint32_t v[4] = {vv[q].x, vv[q].y, vv[q].z, vv[q].w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const Key k = build_key(a.ks, r[e], c[e]);
           bad |= coo_out_of_range(a.ks, r[e], c[e]);
-          bin[4 * q + e] = parent_of_entry(a, r[e], c[e], k);
-          key[4 * q + e] = (uint32_t)k & lmask;
+          bin[4 * q + e] = share_of_entry(a, r[e], c[e], &key[4 * q + e]);
           val[4 * q + e] = v[e];
         }
       }
@@ -218,10 +237,8 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
         bin[j] = 0xFFFFFFFFu; key[j] = 0; val[j] = 0;
         if (i < in_tile) {
           const uint32_t r = (uint32_t)a.row[base + i], c = (uint32_t)a.col[base + i];
-          const Key k = build_key(a.ks, r, c);
           bad |= coo_out_of_range(a.ks, r, c);
-          bin[j] = parent_of_entry(a, r, c, k);
-          key[j] = (uint32_t)k & lmask;
+          bin[j] = share_of_entry(a, r, c, &key[j]);
           val[j] = a.val[base + i];
         }
       }
@@ -568,7 +585,8 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
     key[j] = 0;
     if (i < ns) {
       const uint32_t at = me.start + (uint32_t)((uint64_t)i * me.size / ns) + ((i * 0x9E3779B1u + p * 0x85EBCA6Bu) >> 8) % piece;
-      key[j] = COO ? (uint32_t)build_key(a.ks, (uint32_t)a.row[at], (uint32_t)a.col[at]) & low_mask(a.dshift) : a.rec1[at].x;
+      if (COO) share_of_entry(a, (uint32_t)a.row[at], (uint32_t)a.col[at], &key[j]);
+      else key[j] = a.rec1[at].x;
     }
   }
   __shared__ uint32_t s_sample[64];
@@ -578,7 +596,7 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
     if (i < ns && x < 64 && x * ns / 64 == i) s_sample[x] = key[j];
   }
   __syncthreads();
-  const uint32_t most = bin_slots<SM_T, SM_IPT, 33>(key, ns, 0u, low_mask(a.dshift), s_sample[lane_id()], s, pos);
+  const uint32_t most = bin_slots<SM_T, SM_IPT, 33>(key, ns, 0u, (uint32_t)(a.share.width - 1), s_sample[lane_id()], s, pos);
   if (most > BP_MOST) {
     if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
     return;
@@ -622,7 +640,7 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
       if (COO) {
         const uint32_t r = (uint32_t)a.row[first + i], c = (uint32_t)a.col[first + i];
         bad |= coo_out_of_range(a.ks, r, c);
-        key[j] = (uint32_t)build_key(a.ks, r, c) & low_mask(a.dshift);
+        share_of_entry(a, r, c, &key[j]);
         val[j] = a.val[first + i];
       } else {
         const uint2 r = a.rec1[first + i];
@@ -701,8 +719,8 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   if (m > (uint32_t)BK_CAP) return;   // (the call will be run again)
   if ((uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[child0 + tid]);   // j0 < BK_MAXK <= BF_T
   const uint2 *src = me.z & BK_SHARED ? a.rec2 + (size_t)((me.z >> BK_REGION_SHIFT) + j0) * BK_CAP : a.rec1 + start;
-  const uint32_t lmask = low_mask(a.dshift);
-  const uint32_t lo = me.w, hi = last ? lmask : after.w;   // (hi itself may be the next child's)
+  const Key behind = last ? a.share.width : after.w;
+  const uint32_t lo = me.w, hi = (uint32_t)min(behind, (Key)0xFFFFFFFFu);   // (hi itself may be the next child's)
   uint32_t key[BF_IPT], val[BF_IPT], pos[BF_IPT];
 #pragma unroll
   for (int j = 0; j < BF_IPT; ++j) {
@@ -736,11 +754,11 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
     }
   }
   const uint32_t out = start + s_before;
-  const Key base = (Key)p << a.dshift;
+  const Key base = p * a.share.width;
   const Key bmask = ((Key)1 << a.ks.b_bits) - 1;
   bool dup = false;
   for (uint32_t i = tid; i < m; i += BF_T) {
-    const Key full = base | s.a[i];
+    const Key full = base + s.a[i];
     dup |= i > 0 && s.a[i - 1] == s.a[i];
     if (out + i < a.n) {
       if (a.major_out) a.major_out[out + i] = (int32_t)(full >> a.ks.b_bits);
@@ -750,8 +768,7 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   }
   if (dup) a.flags->duplicate = 1;
   if (a.ptr) {   // the major indices whose first possible key lies in this child's range: entries below that key
-    const Key l = base | lo, h = base | hi;
-    Key g0 = (l + bmask) >> a.ks.b_bits, g1 = last ? (h >> a.ks.b_bits) + 1 : (h + bmask) >> a.ks.b_bits;
+    Key g0 = (base + lo + bmask) >> a.ks.b_bits, g1 = (base + behind + bmask) >> a.ks.b_bits;
     if (p + 1 == a.nparents && last) g1 = (Key)a.ngroups_out + 1;
     if (g1 > (Key)a.ngroups_out + 1) g1 = (Key)a.ngroups_out + 1;
     for (Key g = g0 + tid; g < g1; g += BF_T) {
@@ -772,30 +789,46 @@ constexpr int BP_T = 512, BP_IPT = 8, BP_GROUPS = 768, BPL_T = 1024, BPL_IPT = 1
 
 struct BucketPlan {
   bool direct;     // one parent: the caller's list
-  int bits;        // of the parents
+  KeyShares share;
   bool large;      // the first pass takes large tiles
   uint32_t nparents, per_group, ngroups, max_children, max_regions, max_tiles;
 };
+
+// at most `most` shares, or what keeps them at 2^32 keys (BK_MAXBINS where the key has BK_MAXBITS + 32 bits)
+static KeyShares key_shares(const KeySpec &ks, uint32_t most) {
+  KeyShares s{};
+  if (ks.a_extent >= most && ks.b_bits <= 32) {
+    s.rows = std::min(ceil_div(ks.a_extent, most), (uint32_t)std::min<uint64_t>((1ull << 32) >> ks.b_bits, 1u << 31));
+    s.count = ceil_div(ks.a_extent, s.rows);
+    s.width = (uint64_t)s.rows << ks.b_bits;
+    s.mul_shift = bits_for(s.rows - 1);
+    s.mul = (uint32_t)((1ull << (31 + s.mul_shift)) / s.rows + 1);
+  } else {
+    const uint64_t span = (uint64_t)ks.a_extent << ks.b_bits;
+    while (s.shift < 32 && ((span - 1) >> s.shift) + 1 > most) ++s.shift;
+    s.count = (uint32_t)((span - 1) >> s.shift) + 1;
+    s.width = 1ull << s.shift;
+  }
+  return s;
+}
 
 static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
   BucketPlan b{};
   b.direct = ks.total_bits <= 32 && nnz <= BK_MAXK / 2 * BK_TARGET;
   if (b.direct) {
-    b.nparents = 1;
+    b.share.count = 1; b.share.shift = ks.total_bits; b.share.width = 1ull << ks.total_bits;
   } else {
-    // 32 children per parent; 8 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
+    // 24 children per parent; 6 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
     // that its size makes longer (1 M entries: 24 -> 17 us in the sample, the other kernels as they were)
-    b.bits = bits_for((uint64_t)nnz / (nnz < (1 << 22) ? 8192 : 32768));
-    if (b.bits < ks.total_bits - 32) b.bits = ks.total_bits - 32;
-    if (b.bits > BK_MAXBITS) b.bits = BK_MAXBITS;
-    if (b.bits > ks.total_bits) b.bits = ks.total_bits;
-    b.nparents = 1u << b.bits;
+    const int64_t want = ceil_div<int64_t>(nnz, (nnz < (1 << 22) ? 6 : 24) * BK_TARGET);
+    b.share = key_shares(ks, (uint32_t)std::min<int64_t>(want, BK_MAXBINS));
     b.large = nnz >= (1 << 23);
     const uint32_t tile = b.large ? BPL_T * BPL_IPT : BP_T * BP_IPT, groups = b.large ? BPL_GROUPS : BP_GROUPS;
     const uint32_t tiles = (uint32_t)ceil_div<int64_t>(nnz, tile), each = ceil_div(tiles, groups);
     b.per_group = each * tile;
     b.ngroups = ceil_div(tiles, each);
   }
+  b.nparents = b.share.count;
   const uint32_t full = (uint32_t)(nnz / BK_TARGET), shared = std::min(b.nparents, full);   // parents of more than one child, at most
   b.max_children = full + b.nparents + 1;
   b.max_regions = b.direct ? full + 1 : full + shared;
@@ -803,7 +836,7 @@ static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
   return b;
 }
 
-// (row, col) tuples whose key below the parents' bits fits 32 bits, in numbers that leave parents room for uneven sizes:
+// (row, col) tuples whose share of the key's range fits 32 bits, in numbers that leave parents room for uneven sizes:
 // a parent of twice the average has children enough up to 67 M entries.
 bool bucket_sort_takes(int64_t nnz, const KeySpec &ks) {
   return nnz >= 1 && ks.mode == 0 && ks.total_bits >= 1 && ks.total_bits - BK_MAXBITS <= 32 &&
@@ -823,8 +856,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   BkArgs a{};
   a.row = row; a.col = col; a.val = (const uint32_t *)val;
   a.n = (uint32_t)nnz; a.ks = ks; a.flags = flags;
-  a.dshift = ks.total_bits - b.bits;
-  a.lead_shift = a.dshift >= ks.b_bits ? a.dshift - ks.b_bits : -1;
+  a.share = b.share;
   a.nparents = b.nparents; a.per_group = b.per_group; a.ngroups = b.ngroups;
   a.groups_per_xcd = ceil_div<uint32_t>(b.ngroups, 8u);
   a.coo_vec = ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
@@ -845,7 +877,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.rec2 = env.temp<uint2>((size_t)b.max_regions * BK_CAP);
   if (!env.ok()) return;
   if (!b.direct) {
-    US_LAUNCH(env, "bucket_hist", (a.lead_shift >= 0 ? 4.0 : 8.0) * nnz, bucket_hist_kernel, a.groups_per_xcd * 8, BH_T, a);
+    US_LAUNCH(env, "bucket_hist", (a.share.rows ? 4.0 : 8.0) * nnz, bucket_hist_kernel, a.groups_per_xcd * 8, BH_T, a);
     US_LAUNCH(env, "bucket_scan", 8.0 * b.ngroups * b.nparents, bucket_scan_kernel, ceil_div<uint32_t>(b.nparents, BS_BINS), BS_T, a);
     if (b.large) US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BPL_T, BPL_IPT>), a.groups_per_xcd * 8, BPL_T, a);
     else US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BP_T, BP_IPT>), a.groups_per_xcd * 8, BP_T, a);

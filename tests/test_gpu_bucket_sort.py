@@ -104,6 +104,53 @@ def test_a_parent_of_too_many_entries_goes_to_the_digit_passes(ctx):
         g.free()
 
 
+def on_the_gpu(ctx, nr, nc, lin, d):
+    """Converts a list made on the GPU (distinct row * nc + column in random order) to CSR or COO and compares with torch's
+    sort of the same numbers; the kernels of the conversion."""
+    import torch
+    lin = lin[torch.randperm(lin.numel(), device="cuda")]
+    row = torch.div(lin, nc, rounding_mode="floor")
+    col, val = (lin - row * nc).int(), torch.arange(lin.numel(), device="cuda", dtype=torch.int32).view(torch.float32)
+    g, launches = run(ctx, nr, nc, row.int(), col, val, d, lambda x: x)
+    order = torch.sort(lin)
+    assert torch.equal(g.val().view(torch.int32), order.indices.int())
+    want = torch.div(order.values, nc, rounding_mode="floor")
+    assert torch.equal(g.idx(1).long(), order.values - want * nc)
+    if d == O.COO():
+        assert torch.equal(g.idx(0).long(), want)
+    else:
+        assert torch.equal(g.ptr(1).long(), torch.searchsorted(want, torch.arange(nr + 1, device="cuda")))
+    g.free()
+    return launches
+
+
+@pytest.mark.parametrize("nr,nc", [((1 << 20) + 2, 1 << 21), (1 << 21, (1 << 20) + 2)])
+def test_parents_share_the_rows_that_there_are(ctx, nr, nc):
+    """36 M entries, rows up to 2.5 times the average: with parents by the top bits of a row number just above 2^20 half of
+    them were empty and the fullest of the others had more entries (175,000) than a parent may have."""
+    import torch
+    u = torch.rand(36_000_000, device="cuda", dtype=torch.float64, generator=torch.Generator("cuda").manual_seed(nr))
+    row = (nr * (u + 0.6 * torch.sin(2 * np.pi * u) / (2 * np.pi))).long().clamp_(0, nr - 1)
+    lin = torch.unique(row * nc + torch.randint(0, nc, row.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(nc)))
+    launches = on_the_gpu(ctx, nr, nc, lin, O.CSR())
+    assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
+
+
+# the division of a row number by the rows of a share: rows below, at and above the number of shares, up to 2^31 - 1
+@pytest.mark.parametrize("nr,nc,n", [(1023, 4097, 270_000), (1024, 1 << 20, 300_000), (1025, 1 << 20, 300_000), (44, 1 << 22, 270_000),
+                                     (45, 1 << 22, 270_000), (1536, 1 << 30, 300_000), (2047, (1 << 31) - 1, 300_000),
+                                     ((1 << 31) - 1, 2000, 70_000), ((1 << 21) - 1, 1 << 21, 2_000_000), (1 << 21, 1 << 21, 2_000_000)])
+def test_shares_of_rows(ctx, nr, nc, n):
+    import torch
+    gen = torch.Generator("cuda").manual_seed(n)
+    lin = torch.randint(0, nr * nc, (n,), device="cuda", generator=gen)
+    ends = torch.tensor([0, nc - 1, (nr - 1) * nc, nr * nc - 1], device="cuda")   # the corners of the matrix among them
+    edges = torch.arange(min(nr, 4096), device="cuda") * (nr // min(nr, 4096)) * nc   # first and last entries of rows
+    lin = torch.unique(torch.cat([lin, ends, edges, edges + nc - 1]))
+    launches = on_the_gpu(ctx, nr, nc, lin, O.COO() if nr > 1 << 24 else O.CSR())
+    assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
+
+
 @pytest.mark.parametrize("n", [1, 1000, 65_536, 1_000_000])
 def test_scratch_of_wide_keys_goes_with_the_entries(ctx, n):
     """42 key bits make 1024 parents however few entries there are.  Per entry: the list by parent 8 bytes, a region of 2048

@@ -76,8 +76,8 @@ typedef struct us_ctx {
    * The finish pays off when entries spread evenly over the buckets (block rows of a FEM-like matrix: COO->BCSR
    * of 50 M entries in 38 % less time); heavy rows of a power-law matrix need extra splitting passes and gain nothing.
    * Results are identical in every mode; an input that a way cannot take (the finish: more than 262,144 entries sharing
-   * their top key bits, or 4,096 sharing 8 more; the buckets: more than 131,072 in one of at most 1024 shares) is sorted again with
-   * whole-array passes by the same call. */
+   * their top key bits, or 4,096 sharing 8 more; the buckets: more than 131,072 in a share that a sample has
+   * not shown to be that full) is sorted again with whole-array passes by the same call. */
   int32_t sort_finish;
 } us_ctx;
 enum { US_SORT_FINISH_AUTO = 0, US_SORT_FINISH_LDS = 1, US_SORT_FINISH_PASSES = 2 };

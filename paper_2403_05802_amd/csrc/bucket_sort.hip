@@ -19,7 +19,7 @@ constexpr int BK_CAP = 2048;        // most entries of a child: what the finish 
 constexpr int BK_TARGET = 1024;     // ... and how many it gets on average
 constexpr int BK_MAXK = 128;        // most children of a parent
 constexpr int BK_OVERSAMPLE = 64;   // sampled keys per child
-constexpr int BK_MAXBITS = 10, BK_MAXBINS = 1 << BK_MAXBITS;   // parents
+constexpr int BK_MAXBITS = 10, BK_MAXSHARES = 1 << BK_MAXBITS;
 
 // The parents are equal shares of the range that the major index really has, whole rows where there are more of them than
 // parents (rows >= 1: share = major / rows, an exact division of 31 bits by multiplication), else pieces of 2^shift keys.
@@ -35,29 +35,37 @@ struct KeyShares {
 
 struct BkParent { uint32_t start, size, child0, k, tile0, region0; };
 
-// BkArgs::child, third word: the parent (BK_MAXBITS bits), what the child is, the region of the parent's first child in rec2
-constexpr uint32_t BK_SHARED = 1u << BK_MAXBITS;   // it has siblings (or comes from the caller's list): its entries are in its region, else in rec1
-constexpr uint32_t BK_LAST = 2u << BK_MAXBITS;     // it is the last one of its parent
-constexpr int BK_REGION_SHIFT = BK_MAXBITS + 2;
+// BkArgs::child, third word: the share (BK_MAXBITS bits), where its entries are, the region of its parent's first child in rec2
+constexpr uint32_t BK_SHARED = 1u << BK_MAXBITS;   // it has siblings (or comes from the caller's list): in its region, else in rec1
+constexpr int BK_REGION_SHIFT = BK_MAXBITS + 1;
 
 struct BkArgs {
   const int32_t *row, *col; const uint32_t *val;   // the caller's list
   uint32_t n; KeySpec ks;
   KeyShares share;
-  uint32_t nparents;
+  // sample of the caller's list: if a share has crowded_at of its keys, those of heavy_at are cut into parents of about `unit`
+  uint32_t nsamples, crowded_at, heavy_at, unit;
+  uint16_t *sample_share;      // [nsamples rounded up to 8]
+  uint32_t *sample_low;        // [nsamples]
+  int clear_flags;             // the first kernel clears them
+  uint32_t max_parents;        // shares + nsamples / unit
+  uint16_t *first;             // [shares + 1] the first parent of every share, if any of them is cut, and ...
+  uint32_t *split;             // ... [parents - shares] the smallest low keys of the further ones, share after share ...
+  uint2 *origin;               // ... [max_parents] {share, smallest low key}
   int coo_vec;                 // row, col and val are 16-byte aligned
   // first pass: every workgroup takes per_group consecutive entries
   uint32_t per_group, ngroups, groups_per_xcd;
-  uint32_t *hist;              // [ngroups][nparents] entries per group and parent, then where they start inside the parent
-  uint32_t *ptotal;            // [nparents] entries per parent
+  uint32_t *hist;              // [ngroups][max_parents] entries per group and parent, then where they start inside the parent
+  uint32_t *ptotal;            // [max_parents] entries per parent
   uint2 *rec1;                 // [n] {low key, value}, by parent
   // second pass
-  BkParent *parent;            // [nparents]
-  uint32_t *totals;            // [0] children, [1] tiles of parents with more than one child
-  uint4 *child;                // [max_children] {start of the parent, its first child, parent and BK_*, smallest low key}
+  BkParent *parent;            // [max_parents]
+  uint32_t *totals;            // [0] children, [1] tiles of parents with more than one child, [2] parents: more than shares if any is cut
+  uint4 *child;                // [max_children] {start of the parent, its first child, share and BK_*, smallest low key}
   uint32_t *cursor;            // [max_children] entries of the child
   uint32_t *tile_parent;       // [max_tiles]
-  uint32_t max_children, max_regions, max_tiles, tiles_per_xcd, children_per_xcd;
+  uint32_t max_children, max_regions, max_tiles;
+  int tile_chunk, child_chunk;   // (xcd_chunk_item)
   uint2 *rec2;                 // [max_regions][BK_CAP]: the children that share a parent
   // output
   int32_t *major_out, *minor_out; uint32_t *val_out;
@@ -91,6 +99,13 @@ __device__ __forceinline__ bool gave_up(const BkArgs &a, bool range) {
   return s_stop != 0;
 }
 
+// Neighbouring items (a parent's tiles, the ends of what children write) on the same XCD, 2^shift of them: how many there are
+// only the GPU knows, and a contiguous range of the most possible for each XCD would leave the last one with less to do.
+__device__ __forceinline__ uint32_t xcd_chunk_item(uint32_t i, int shift) {
+  const uint32_t at = i >> 3;
+  return ((at >> shift) * 8 + (i & 7u)) << shift | (at & ((1u << shift) - 1u));
+}
+
 // Exclusive prefix sum over the workgroup with one barrier; s_wave: T / 64 words, free again after the next barrier.
 template <int T>
 __device__ __forceinline__ uint32_t scan_one_barrier(uint32_t v, uint32_t *s_wave) {
@@ -104,42 +119,188 @@ __device__ __forceinline__ uint32_t scan_one_barrier(uint32_t v, uint32_t *s_wav
 }
 
 // ------------------------------------------------------------------ first pass: parents
-constexpr int BH_T = 512, BH_COPIES = 4;
+// Some shares hold more entries than a parent may (rows in order of their length, the quadrants of an R-MAT graph, a few
+// rows that are used at all).  A sample of the caller's list, 64 keys per 131,072 entries while there are up to 33.5 M, tells
+// whether one does and where to cut the heavy ones: into parents of 41 k entries on average, 20 keys of the sample.  Every
+// workgroup of the histogram looks through the sample by itself, so no launch waits for one of them; only where a share
+// has to be cut the keys are sorted, by all of them the same.  A parent that is too large all the same is noticed by the scan.
+// Digit passes / a failed first pass, then the digit passes / this, us: 16.8 M entries with rows in order of their length 688 /
+// 784 / 555, R-MAT 681 / 755 / 543; 4 M 215 / 296 / 189 and 228 / 300 / 188; 1 M 153 / 224 / 118 and 164 / 235 / 118.  Without
+// a share too many the sample costs what the clearing of the flags, which it takes over, did (16.8 M entries 405 -> 411, 40 M
+// 935 -> 937, 1 M 103 -> 104); a histogram with cut shares takes 150 instead of 24 (sort and searches; 512 threads instead of
+// 1024: 280), the scatter 139 instead of 102.
+constexpr int BL_T = 256;
+__global__ __launch_bounds__(BL_T) void bucket_probe_kernel(BkArgs a) {
+  const uint32_t i = blockIdx.x * BL_T + threadIdx.x;
+  if (a.clear_flags && i < sizeof(Flags) / 4) reinterpret_cast<uint32_t *>(a.flags)[i] = 0;
+  if (i >= ((a.nsamples + 7) & ~7u)) return;
+  uint32_t share = 0xFFFFu;   // (none)
+  if (i < a.nsamples) {
+    // evenly spaced pieces of the list, at a scattered place in each (lists often come in a regular order)
+    const uint32_t piece = a.n / a.nsamples, at = (uint32_t)((uint64_t)i * a.n / a.nsamples) + ((i * 0x9E3779B1u) >> 8) % piece;
+    uint32_t low;
+    share = share_of_entry(a, (uint32_t)a.row[at], (uint32_t)a.col[at], &low);
+    a.sample_low[i] = low;
+  }
+  a.sample_share[i] = (uint16_t)share;
+}
 
+// the parent of an entry where shares are cut: the last one of its share whose smallest low key is not above the entry's
+__device__ __forceinline__ uint32_t parent_of(const uint16_t *first, const uint32_t *split, uint32_t share, uint32_t low) {
+  const uint32_t f = first[share];
+  uint32_t b = f - share, e = first[share + 1] - share - 1;   // the splitters of the share
+  while (b < e) {
+    const uint32_t mid = (b + e) >> 1;
+    if (split[mid] <= low) b = mid + 1; else e = mid;
+  }
+  return share + b;
+}
+
+constexpr int BH_COPIES = 4;
+
+// NS: room for the sample, MAXX: most parents beside the shares
+template <int BH_T, int NS, int MAXX>
 __global__ __launch_bounds__(BH_T) void bucket_hist_kernel(BkArgs a) {
-  __shared__ uint32_t s_hist[BK_MAXBINS * BH_COPIES];   // (copies picked by lane: LDS adds to one address take turns)
+  __shared__ union {
+    uint32_t hist[(BK_MAXSHARES + MAXX) * BH_COPIES];   // (copies picked by lane: LDS adds to one address take turns)
+    uint64_t key[NS];
+  } s;
+  __shared__ uint32_t s_cnt[BK_MAXSHARES];   // keys of the sample per share
+  __shared__ uint16_t s_at[BK_MAXSHARES], s_first[BK_MAXSHARES + 2];
+  __shared__ uint32_t s_split[MAXX], s_wave[2][BH_T / 64], s_n;
   const uint32_t group = xcd_tile(blockIdx.x, a.groups_per_xcd);
   if (group >= a.ngroups) return;
-  for (uint32_t i = threadIdx.x; i < a.nparents * BH_COPIES; i += BH_T) s_hist[i] = 0;
+  const int tid = threadIdx.x;
+  const uint32_t nshares = a.share.count;
+  bool cut = false;
+  if (a.nsamples) {
+    for (uint32_t p = tid; p < BK_MAXSHARES; p += BH_T) s_cnt[p] = 0;
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    const uint4 *v8 = reinterpret_cast<const uint4 *>(a.sample_share);   // eight at a time
+    constexpr int EACH = NS / 8 / BH_T;
+    uint4 x[EACH];
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) {
+      x[q] = make_uint4(~0u, ~0u, ~0u, ~0u);
+      if (8u * (q * BH_T + tid) < a.nsamples) x[q] = v8[q * BH_T + tid];
+    }
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) {
+      const uint32_t w[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+      for (int y = 0; y < 4; ++y) {
+        if ((w[y] & 0xFFFFu) != 0xFFFFu) atomicAdd(&s_cnt[w[y] & 0xFFFFu], 1u);
+        if (w[y] >> 16 != 0xFFFFu) atomicAdd(&s_cnt[w[y] >> 16], 1u);
+      }
+    }
+    __syncthreads();
+    bool crowded = false;
+    for (uint32_t p = tid; p < nshares; p += BH_T) crowded |= s_cnt[p] >= a.crowded_at;
+    if (crowded) s_n = 1;
+    __syncthreads();
+    cut = s_n != 0;
+  }
+  uint32_t np = nshares;
+  if (cut) {
+    constexpr int PER = BK_MAXSHARES / BH_T;
+    uint32_t c[PER], more[PER], msum = 0, csum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      c[q] = s_cnt[tid * PER + q];
+      more[q] = c[q] >= a.heavy_at ? (c[q] - 1) / a.unit : 0u;
+      if (!more[q]) c[q] = 0;
+      msum += more[q]; csum += c[q];
+    }
+    uint32_t m0 = scan_one_barrier<BH_T>(msum, s_wave[0]), c0 = scan_one_barrier<BH_T>(csum, s_wave[1]);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const uint32_t p = tid * PER + q;
+      s_first[p] = (uint16_t)(p + m0); s_at[p] = (uint16_t)c0;
+      m0 += more[q]; c0 += c[q];
+      if (p + 1 == (uint32_t)BK_MAXSHARES) s_first[p + 1] = (uint16_t)(p + 1 + m0);
+    }
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+    for (uint32_t i = tid; i < a.nsamples; i += BH_T) {
+      const uint32_t p = a.sample_share[i];
+      if (s_first[p + 1] - s_first[p] > 1) s.key[atomicAdd(&s_n, 1u)] = (uint64_t)p << 32 | a.sample_low[i];   // nsamples <= NS
+    }
+    __syncthreads();
+    const uint32_t m = s_n;
+    uint32_t size = 1;
+    while (size < m) size <<= 1;
+    for (uint32_t i = m + tid; i < size; i += BH_T) s.key[i] = ~0ull;   // (NS is a power of two)
+    __syncthreads();
+    for (uint32_t k = 2; k <= size; k <<= 1) {
+      for (uint32_t half = k >> 1; half > 0; half >>= 1) {   // all comparisons ascending
+        const uint32_t flip = half == k >> 1 ? k - 1 : half;
+        for (uint32_t t = tid; t < size / 2; t += BH_T) {
+          const uint32_t x = (t & (half - 1)) + ((t & ~(half - 1)) << 1), y = x ^ flip;
+          const uint64_t kx = s.key[x], ky = s.key[y];
+          if (kx > ky) { s.key[x] = ky; s.key[y] = kx; }
+        }
+        __syncthreads();
+      }
+    }
+    for (uint32_t i = tid; i < m; i += BH_T) {   // key j * count / parents of a share starts its parent j
+      const uint32_t p = (uint32_t)(s.key[i] >> 32), q = i - s_at[p], parents = s_first[p + 1] - s_first[p];
+      const uint32_t j = (q * parents + s_cnt[p] - 1) / s_cnt[p];
+      if (j >= 1 && j < parents && j * s_cnt[p] / parents == q) s_split[s_first[p] - p + j - 1] = (uint32_t)s.key[i];
+    }
+    np = s_first[nshares];
+    __syncthreads();
+    if (group == 0) {
+      for (uint32_t p = tid; p <= nshares; p += BH_T) a.first[p] = s_first[p];
+      for (uint32_t p = tid; p < np - nshares; p += BH_T) a.split[p] = s_split[p];
+      for (uint32_t p = tid; p < nshares; p += BH_T)
+        for (uint32_t f = s_first[p], x = f; x < s_first[p + 1]; ++x) a.origin[x] = make_uint2(p, x > f ? s_split[x - p - 1] : 0u);
+    }
+  }
+  if (group == 0 && tid == 0) a.totals[2] = np;
+  for (uint32_t i = tid; i < np * BH_COPIES; i += BH_T) s.hist[i] = 0;
   __syncthreads();
   const uint32_t begin = group * a.per_group, end = min(begin + a.per_group, a.n);
-  const uint32_t copy = threadIdx.x & (BH_COPIES - 1);
+  const uint32_t copy = tid & (BH_COPIES - 1);
   const int32_t *lead = a.ks.swap ? a.col : a.row;
-  auto count = [&](uint32_t p) { atomicAdd(&s_hist[p * BH_COPIES + copy], 1u); };
+  auto count = [&](uint32_t p) { atomicAdd(&s.hist[p * BH_COPIES + copy], 1u); };
   auto of_lead = [&](uint32_t x) { return share_of_lead(a.share, x); };
   uint32_t i = begin;
-  if (a.share.rows && a.coo_vec) {
+  if (a.share.rows && a.coo_vec && !cut) {
     for (; i + 8 * BH_T <= end; i += 8 * BH_T) {   // (begin is a multiple of four entries)
       const uint4 *p4 = reinterpret_cast<const uint4 *>(lead + i);
-      const uint4 x = p4[threadIdx.x], y = p4[BH_T + threadIdx.x];
+      const uint4 x = p4[tid], y = p4[BH_T + tid];
       count(of_lead(x.x)); count(of_lead(x.y)); count(of_lead(x.z)); count(of_lead(x.w));
       count(of_lead(y.x)); count(of_lead(y.y)); count(of_lead(y.z)); count(of_lead(y.w));
     }
   }
-  for (uint32_t e = i + threadIdx.x; e < end; e += BH_T) {
-    if (a.share.rows) {
-      count(of_lead((uint32_t)lead[e]));
-    } else {
-      uint32_t low;
-      count(share_of_entry(a, (uint32_t)a.row[e], (uint32_t)a.col[e], &low));
+  if (a.share.rows && !cut) {
+    for (uint32_t e = i + tid; e < end; e += BH_T) count(of_lead((uint32_t)lead[e]));
+  } else {
+    constexpr int N = 4;
+    for (; i < end; i += N * BH_T) {
+      uint32_t r[N], c[N], p[N], low[N];
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        const uint32_t e = min(i + j * BH_T + tid, end - 1);
+        r[j] = (uint32_t)a.row[e]; c[j] = (uint32_t)a.col[e];
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+        p[j] = share_of_entry(a, r[j], c[j], &low[j]);
+        if (i + j * BH_T + tid >= end) p[j] = 0xFFFFFFFFu;
+      }
+#pragma unroll
+      for (int j = 0; j < N; ++j)
+        if (p[j] != 0xFFFFFFFFu) count(cut ? parent_of(s_first, s_split, p[j], low[j]) : p[j]);
     }
   }
   __syncthreads();
-  for (uint32_t p = threadIdx.x; p < a.nparents; p += BH_T) {
+  for (uint32_t p = tid; p < np; p += BH_T) {
     uint32_t sum = 0;
 #pragma unroll
-    for (int c = 0; c < BH_COPIES; ++c) sum += s_hist[p * BH_COPIES + c];
-    a.hist[(size_t)group * a.nparents + p] = sum;
+    for (int c = 0; c < BH_COPIES; ++c) sum += s.hist[p * BH_COPIES + c];
+    a.hist[(size_t)group * a.max_parents + p] = sum;
   }
 }
 
@@ -149,24 +310,24 @@ constexpr int BS_T = 1024, BS_BINS = 32, BS_PARTS = BS_T / BS_BINS;
 __global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
   __shared__ uint32_t s_part[BS_PARTS][BS_BINS];
   const uint32_t q = threadIdx.x % BS_BINS, part = threadIdx.x / BS_BINS, p = blockIdx.x * BS_BINS + q;
-  const uint32_t each = (a.ngroups + BS_PARTS - 1) / BS_PARTS, g0 = min(part * each, a.ngroups), g1 = min(g0 + each, a.ngroups);
+  const uint32_t np = a.totals[2], each = (a.ngroups + BS_PARTS - 1) / BS_PARTS, g0 = min(part * each, a.ngroups), g1 = min(g0 + each, a.ngroups);
   uint32_t sum = 0;
-  if (p < a.nparents) {
+  if (p < a.max_parents) {   // (what lies past the parents is not used)
 #pragma unroll 8
-    for (uint32_t g = g0; g < g1; ++g) sum += a.hist[(size_t)g * a.nparents + p];
+    for (uint32_t g = g0; g < g1; ++g) sum += a.hist[(size_t)g * a.max_parents + p];
   }
   s_part[part][q] = sum;
   __syncthreads();
   uint32_t run = 0;
   for (uint32_t w = 0; w < part; ++w) run += s_part[w][q];
-  if (p >= a.nparents) return;
+  if (p >= np) return;
   if (part == BS_PARTS - 1) {
     a.ptotal[p] = run + sum;
     if (run + sum > (uint32_t)(BK_MAXK * BK_TARGET)) a.flags->retry = RETRY_SORT_LDS;   // (the kernels that follow leave at once)
   }
 #pragma unroll 8
   for (uint32_t g = g0; g < g1; ++g) {
-    uint32_t *h = a.hist + (size_t)g * a.nparents + p;
+    uint32_t *h = a.hist + (size_t)g * a.max_parents + p;
     const uint32_t v = *h;
     *h = run;
     run += v;
@@ -182,27 +343,36 @@ __global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
 // workgroups and large tiles where there are many entries.  512 threads x 8 entries and 768 workgroups / 1024 x 8 and 256
 // / 1024 x 12 and 256, us: 40 M entries, 1024 parents 329 / 283 / 260; 16.8 M, 512 parents 110 / 98 / 101; 4 M, 128
 // parents 22 / 24 / 28; 1 M 12 / 15 / 17.
-template <int T, int IPT>
+template <int T, int IPT, int MAXX>
 __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkArgs a) {
-  constexpr int TILE = T * IPT, PER = BK_MAXBINS / T;
+  constexpr int TILE = T * IPT, MAXP = BK_MAXSHARES + MAXX, PER = (MAXP + T - 1) / T;
   __shared__ uint2 s_rec[TILE];
   __shared__ uint16_t s_bin[TILE];
-  __shared__ uint32_t s_cnt[BK_MAXBINS];    // entries of the tile per parent, then where they start in the tile
-  __shared__ uint32_t s_goff[BK_MAXBINS];   // position of the parent's run of this tile in rec1, minus its start in the tile
+  __shared__ uint32_t s_cnt[MAXP];    // entries of the tile per parent, then where they start in the tile
+  __shared__ uint32_t s_goff[MAXP];   // position of the parent's run of this tile in rec1, minus its start in the tile
+  __shared__ uint32_t s_split[MAXX];
+  __shared__ uint16_t s_first[BK_MAXSHARES + 2];
   __shared__ uint32_t s_wave[2][T / 64];
   const uint32_t group = xcd_tile(blockIdx.x, a.groups_per_xcd);
   if (group >= a.ngroups || a.flags->retry) return;   // (set, if at all, by the kernel before)
   const uint32_t begin = group * a.per_group, end = min(begin + a.per_group, a.n);
   const int tid = threadIdx.x;
+  const uint32_t np = a.totals[2], nshares = a.share.count;
+  const bool cut = np != nshares;
+  if (cut) {
+    for (uint32_t p = tid; p <= nshares; p += T) s_first[p] = a.first[p];
+    for (uint32_t p = tid; p < np - nshares; p += T) s_split[p] = a.split[p];
+  }   // (read behind the scan's barrier)
   uint32_t next[PER];   // parents PER * tid ..: where the group's next entry goes
   {
     uint32_t t[PER], sum = 0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const uint32_t p = tid * PER + q;
-      t[q] = p < a.nparents ? a.ptotal[p] : 0u;
-      next[q] = p < a.nparents ? a.hist[(size_t)group * a.nparents + p] : 0u;
-      s_cnt[p] = 0;
+      t[q] = p < a.max_parents ? a.ptotal[p] : 0u;   // (before the number of parents is known)
+      next[q] = p < a.max_parents ? a.hist[(size_t)group * a.max_parents + p] : 0u;
+      if (p >= np) t[q] = next[q] = 0;
+      if (p < MAXP) s_cnt[p] = 0;
       sum += t[q];
     }
     uint32_t run = scan_one_barrier<T>(sum, s_wave[0]);
@@ -243,18 +413,25 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
         }
       }
     }
+    if (cut) {
+#pragma unroll
+      for (int j = 0; j < IPT; ++j)
+        if (bin[j] != 0xFFFFFFFFu) bin[j] = parent_of(s_first, s_split, bin[j], key[j]);
+    }
     __syncthreads();   // s_cnt is clear, the previous tile is written
 #pragma unroll
     for (int j = 0; j < IPT; ++j) arr[j] = bin[j] != 0xFFFFFFFFu ? atomicAdd(&s_cnt[bin[j]], 1u) : 0u;
     __syncthreads();
     uint32_t c[PER], sum = 0;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) { c[q] = s_cnt[tid * PER + q]; sum += c[q]; }
+    for (int q = 0; q < PER; ++q) { c[q] = tid * PER + q < MAXP ? s_cnt[tid * PER + q] : 0u; sum += c[q]; }
     uint32_t run = scan_one_barrier<T>(sum, s_wave[1]);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
-      s_cnt[tid * PER + q] = run;
-      s_goff[tid * PER + q] = next[q] - run;
+      if (tid * PER + q < MAXP) {
+        s_cnt[tid * PER + q] = run;
+        s_goff[tid * PER + q] = next[q] - run;
+      }
       next[q] += c[q]; run += c[q];
     }
     __syncthreads();
@@ -276,7 +453,8 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
       }
     }
 #pragma unroll
-    for (int q = 0; q < PER; ++q) s_cnt[tid * PER + q] = 0;
+    for (int q = 0; q < PER; ++q)
+      if (tid * PER + q < MAXP) s_cnt[tid * PER + q] = 0;
   }
   if (bad) a.flags->index_range = 1;
 }
@@ -525,16 +703,19 @@ constexpr int BX_T = 512, BX_IPT = 8, BX_TILE = BX_T * BX_IPT;
 // One workgroup per parent: its place among the parents, its children and tiles, their splitters.  64 sampled keys per
 // child make a child of twice the average, the most the finish holds, a matter of 3e-9 (32 keys: 5e-5); the call is then run again with
 // the digit passes, as it is when a parent is too large for BK_MAXK children.
-// COO: the whole list is one parent, its keys are built from the coordinates.
-template <bool COO>
+// COO: the whole list is one parent, its keys are built from the coordinates.  PER: parents for a thread to add up, SM_T * PER
+// in all.
+template <bool COO, int PER>
 __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
   __shared__ BinScratch<SM_T, SM_IPT, 33> s;
   __shared__ uint32_t s_wave[3][SM_T / 64];
   __shared__ BkParent s_me;
-  constexpr int PER = BK_MAXBINS / SM_T;
   const int tid = threadIdx.x;
   const uint32_t p = blockIdx.x;
+  const uint32_t np = COO ? 1u : a.totals[2];   // (written by an earlier kernel of the call whatever happens)
   if (gave_up(a, true)) return;
+  if (p >= np) return;
+  const uint2 origin = np != a.share.count ? a.origin[p] : make_uint2(p, 0u);
   {
     // children and parents of a single child, summed up together: below 2^18 and 2^14 of them
     constexpr uint32_t ALONE = 1u << 18;
@@ -542,8 +723,9 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const uint32_t x = tid * PER + q;
-      size[q] = x < a.nparents ? (COO ? a.n : a.ptotal[x]) : 0u;
-      k[q] = x < a.nparents ? max((size[q] + BK_TARGET - 1) / BK_TARGET, 1u) : 0u;
+      size[q] = COO ? a.n : x < a.max_parents ? a.ptotal[x] : 0u;
+      if (x >= np) size[q] = 0;
+      k[q] = x < np ? max((size[q] + BK_TARGET - 1) / BK_TARGET, 1u) : 0u;
       tiles[q] = (COO || k[q] > 1) ? (size[q] + BX_TILE - 1) / BX_TILE : 0u;
       const bool alone = !COO && k[q] == 1;
       ssum += size[q]; ksum += k[q] + (alone ? ALONE : 0u); tsum += tiles[q];
@@ -568,11 +750,11 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
     return;
   }
   auto child = [&](uint32_t c, uint32_t low) {
-    const uint32_t kind = p | (shared ? BK_SHARED : 0u) | (c + 1 == me.k ? BK_LAST : 0u) | me.region0 << BK_REGION_SHIFT;
+    const uint32_t kind = origin.x | (shared ? BK_SHARED : 0u) | me.region0 << BK_REGION_SHIFT;
     a.child[me.child0 + c] = make_uint4(me.start, me.child0, kind, low);
     a.cursor[me.child0 + c] = shared ? 0u : me.size;
   };
-  if (tid == 0) child(0, 0u);
+  if (tid == 0) child(0, origin.y);
   if (me.k == 1) return;
   const uint32_t ntiles = (me.size + BX_TILE - 1) / BX_TILE;
   for (uint32_t t = tid; t < ntiles && me.tile0 + t < a.max_tiles; t += SM_T) a.tile_parent[me.tile0 + t] = p;
@@ -596,7 +778,7 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
     if (i < ns && x < 64 && x * ns / 64 == i) s_sample[x] = key[j];
   }
   __syncthreads();
-  const uint32_t most = bin_slots<SM_T, SM_IPT, 33>(key, ns, 0u, (uint32_t)(a.share.width - 1), s_sample[lane_id()], s, pos);
+  const uint32_t most = bin_slots<SM_T, SM_IPT, 33>(key, ns, origin.y, (uint32_t)(a.share.width - 1), s_sample[lane_id()], s, pos);
   if (most > BP_MOST) {
     if (tid == 0) a.flags->retry = RETRY_SORT_LDS;
     return;
@@ -619,7 +801,7 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
   __shared__ uint8_t s_bin[BX_TILE];
   __shared__ uint32_t s_split[BK_MAXK], s_cnt[BK_MAXK], s_goff[BK_MAXK];
   __shared__ uint32_t s_wave[BX_T / 64];
-  const uint32_t t = xcd_tile(blockIdx.x, a.tiles_per_xcd);
+  const uint32_t t = xcd_chunk_item(blockIdx.x, a.tile_chunk);
   if (gave_up(a, !COO)) return;   // (COO: this kernel is the one that finds coordinates out of range)
   if (t >= min(a.totals[1], a.max_tiles)) return;
   const BkParent me = a.parent[COO ? 0u : a.tile_parent[t]];
@@ -708,17 +890,17 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   __shared__ BinScratch<BF_T, BF_IPT, 0> s;
   __shared__ uint32_t s_before;
   const int tid = threadIdx.x;
-  const uint32_t c = xcd_tile(blockIdx.x, a.children_per_xcd), at = min(c, a.max_children - 1);
+  const uint32_t c = xcd_chunk_item(blockIdx.x, a.child_chunk), at = min(c, a.max_children - 1);
   // everything that does not hang on something else first; what an earlier kernel has left unwritten is not used
   const uint4 me = a.child[at], after = a.child[min(at + 1, a.max_children - 1)];
   const uint32_t m = a.cursor[at], nchildren = min(a.totals[0], a.max_children);
   if (tid == 0) s_before = 0;
   if (gave_up(a, true) || c >= nchildren) return;
-  const uint32_t start = me.x, child0 = me.y, p = me.z & (BK_MAXBINS - 1), j0 = c - child0;
-  const bool last = me.z & BK_LAST;
+  const uint32_t start = me.x, child0 = me.y, share = me.z & (BK_MAXSHARES - 1), j0 = c - child0;
   if (m > (uint32_t)BK_CAP) return;   // (the call will be run again)
   if ((uint32_t)tid < j0) atomicAdd(&s_before, a.cursor[child0 + tid]);   // j0 < BK_MAXK <= BF_T
   const uint2 *src = me.z & BK_SHARED ? a.rec2 + (size_t)((me.z >> BK_REGION_SHIFT) + j0) * BK_CAP : a.rec1 + start;
+  const bool last = c + 1 == nchildren || (after.z & (BK_MAXSHARES - 1)) != share;   // of the share
   const Key behind = last ? a.share.width : after.w;
   const uint32_t lo = me.w, hi = (uint32_t)min(behind, (Key)0xFFFFFFFFu);   // (hi itself may be the next child's)
   uint32_t key[BF_IPT], val[BF_IPT], pos[BF_IPT];
@@ -754,7 +936,7 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
     }
   }
   const uint32_t out = start + s_before;
-  const Key base = p * a.share.width;
+  const Key base = share * a.share.width;
   const Key bmask = ((Key)1 << a.ks.b_bits) - 1;
   bool dup = false;
   for (uint32_t i = tid; i < m; i += BF_T) {
@@ -769,7 +951,7 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
   if (dup) a.flags->duplicate = 1;
   if (a.ptr) {   // the major indices whose first possible key lies in this child's range: entries below that key
     Key g0 = (base + lo + bmask) >> a.ks.b_bits, g1 = (base + behind + bmask) >> a.ks.b_bits;
-    if (p + 1 == a.nparents && last) g1 = (Key)a.ngroups_out + 1;
+    if (c + 1 == nchildren) g1 = (Key)a.ngroups_out + 1;
     if (g1 > (Key)a.ngroups_out + 1) g1 = (Key)a.ngroups_out + 1;
     for (Key g = g0 + tid; g < g1; g += BF_T) {
       const Key first = (g << a.ks.b_bits) - base;   // may lie beyond 32 bits (behind the last key): all entries are below
@@ -786,15 +968,22 @@ __global__ __launch_bounds__(BF_T, 6) void bucket_finish_kernel(BkArgs a) {
 // ------------------------------------------------------------------ host
 // first pass, threads and entries per thread, and workgroups: as many as are resident at once
 constexpr int BP_T = 512, BP_IPT = 8, BP_GROUPS = 768, BPL_T = 1024, BPL_IPT = 12, BPL_GROUPS = 256;
+constexpr int64_t BK_LARGE = 1 << 23;
+// most keys of the sample and parents beside the shares: what leaves the LDS of the first pass its workgroups per CU (3 / 1)
+constexpr int BP_SAMPLES = 4096, BP_MAXX = 192, BPL_SAMPLES = 16384, BPL_MAXX = 1024;
+static_assert(BK_MAXSHARES + BPL_MAXX <= 4 * SM_T && BP_MAXX <= BPL_MAXX, "a workgroup of the sample sees all parents");
 
 struct BucketPlan {
   bool direct;     // one parent: the caller's list
   KeyShares share;
   bool large;      // the first pass takes large tiles
-  uint32_t nparents, per_group, ngroups, max_children, max_regions, max_tiles;
+  uint32_t nsamples, crowded_at, heavy_at, unit, max_parents, per_group, ngroups, max_children, max_regions, max_tiles;
 };
 
-// at most `most` shares, or what keeps them at 2^32 keys (BK_MAXBINS where the key has BK_MAXBITS + 32 bits)
+static int chunk_shift(uint32_t items) { return std::min(std::max(bits_for(items / 64) - 1, 0), 6); }
+static uint32_t chunk_grid(uint32_t items, int shift) { return ceil_div(items, 8u << shift) * (8u << shift); }
+
+// at most `most` shares, or what keeps them at 2^32 keys (BK_MAXSHARES where the key has BK_MAXBITS + 32 bits)
 static KeyShares key_shares(const KeySpec &ks, uint32_t most) {
   KeyShares s{};
   if (ks.a_extent >= most && ks.b_bits <= 32) {
@@ -821,16 +1010,25 @@ static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
     // 24 children per parent; 6 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
     // that its size makes longer (1 M entries: 24 -> 17 us in the sample, the other kernels as they were)
     const int64_t want = ceil_div<int64_t>(nnz, (nnz < (1 << 22) ? 6 : 24) * BK_TARGET);
-    b.share = key_shares(ks, (uint32_t)std::min<int64_t>(want, BK_MAXBINS));
-    b.large = nnz >= (1 << 23);
+    b.share = key_shares(ks, (uint32_t)std::min<int64_t>(want, BK_MAXSHARES));
+    b.large = nnz >= BK_LARGE;
     const uint32_t tile = b.large ? BPL_T * BPL_IPT : BP_T * BP_IPT, groups = b.large ? BPL_GROUPS : BP_GROUPS;
     const uint32_t tiles = (uint32_t)ceil_div<int64_t>(nnz, tile), each = ceil_div(tiles, groups);
     b.per_group = each * tile;
     b.ngroups = ceil_div(tiles, each);
+    if (nnz > BK_MAXK * BK_TARGET) {
+      b.nsamples = (uint32_t)std::min<int64_t>(nnz / 2048, b.large ? BPL_SAMPLES : BP_SAMPLES);
+      auto keys_of = [&](int64_t entries) { return (uint32_t)ceil_div<int64_t>(entries * b.nsamples, nnz); };
+      // (three quarters are enough to be cut, but it takes a share that is too large: a first pass with cut shares takes longer)
+      b.crowded_at = keys_of(BK_MAXK * BK_TARGET);
+      b.heavy_at = keys_of(BK_MAXK * BK_TARGET * 3 / 4);
+      b.unit = std::max({8u, keys_of(40 * BK_TARGET), ceil_div<uint32_t>(b.nsamples, b.large ? BPL_MAXX : BP_MAXX)});
+    }
   }
-  b.nparents = b.share.count;
-  const uint32_t full = (uint32_t)(nnz / BK_TARGET), shared = std::min(b.nparents, full);   // parents of more than one child, at most
-  b.max_children = full + b.nparents + 1;
+  // (the cut shares' parents beside the first: (keys - 1) / unit each)
+  b.max_parents = b.share.count + (b.nsamples ? b.nsamples / b.unit : 0);
+  const uint32_t full = (uint32_t)(nnz / BK_TARGET), shared = std::min(b.max_parents, full);   // parents of more than one child, at most
+  b.max_children = full + b.max_parents + 1;
   b.max_regions = b.direct ? full + 1 : full + shared;
   b.max_tiles = (uint32_t)(nnz / BX_TILE) + shared + 1;
   return b;
@@ -846,8 +1044,9 @@ bool bucket_sort_takes(int64_t nnz, const KeySpec &ks) {
 size_t bucket_sort_temp_bytes(int64_t nnz, const KeySpec &ks) {
   const BucketPlan b = bucket_plan(nnz, ks);
   auto g = [](size_t bytes) { return Env::granule(bytes); };
-  return (b.direct ? 0 : g(4ull * b.ngroups * b.nparents) + g(4ull * b.nparents) + g(8ull * nnz)) + g(sizeof(BkParent) * b.nparents) +
-         g(8) + g(16ull * b.max_children) + g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_regions);
+  return (b.direct ? 0 : g(4ull * b.ngroups * b.max_parents) + g(4ull * b.max_parents) + g(8ull * nnz)) +
+         (b.nsamples ? g(2ull * (b.nsamples + 7)) + g(4ull * b.nsamples) + g(2ull * (b.share.count + 1)) + g(4ull * (b.max_parents - b.share.count)) + g(8ull * b.max_parents) : 0) +
+         g(sizeof(BkParent) * b.max_parents) + g(12) + g(16ull * b.max_children) + g(4ull * b.max_children) + g(4ull * b.max_tiles) + g(8ull * BK_CAP * b.max_regions);
 }
 
 void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz, const KeySpec &ks,
@@ -857,35 +1056,49 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.row = row; a.col = col; a.val = (const uint32_t *)val;
   a.n = (uint32_t)nnz; a.ks = ks; a.flags = flags;
   a.share = b.share;
-  a.nparents = b.nparents; a.per_group = b.per_group; a.ngroups = b.ngroups;
+  a.nsamples = b.nsamples; a.crowded_at = b.crowded_at; a.heavy_at = b.heavy_at; a.unit = b.unit; a.max_parents = b.max_parents;
+  a.per_group = b.per_group; a.ngroups = b.ngroups;
   a.groups_per_xcd = ceil_div<uint32_t>(b.ngroups, 8u);
   a.coo_vec = ((reinterpret_cast<uintptr_t>(row) | reinterpret_cast<uintptr_t>(col) | reinterpret_cast<uintptr_t>(val)) & 15u) == 0;
   a.max_children = b.max_children; a.max_regions = b.max_regions; a.max_tiles = b.max_tiles;
-  a.tiles_per_xcd = ceil_div<uint32_t>(b.max_tiles, 8u);
-  a.children_per_xcd = ceil_div<uint32_t>(b.max_children, 8u);
+  a.tile_chunk = chunk_shift(b.max_tiles); a.child_chunk = chunk_shift(b.max_children);
   env.reserve(bucket_sort_temp_bytes(nnz, ks));
   if (!b.direct) {
-    a.hist = env.temp<uint32_t>((size_t)b.ngroups * b.nparents);
-    a.ptotal = env.temp<uint32_t>(b.nparents);
+    a.hist = env.temp<uint32_t>((size_t)b.ngroups * b.max_parents);
+    a.ptotal = env.temp<uint32_t>(b.max_parents);
     a.rec1 = env.temp<uint2>(nnz);
   }
-  a.parent = env.temp<BkParent>(b.nparents);
-  a.totals = env.temp<uint32_t>(2);
+  if (b.nsamples) {
+    a.sample_share = env.temp<uint16_t>(b.nsamples + 7);
+    a.sample_low = env.temp<uint32_t>(b.nsamples);
+    a.first = env.temp<uint16_t>(b.share.count + 1);
+    a.split = env.temp<uint32_t>(b.max_parents - b.share.count);
+    a.origin = env.temp<uint2>(b.max_parents);
+  }
+  a.parent = env.temp<BkParent>(b.max_parents);
+  a.totals = env.temp<uint32_t>(3);
   a.child = env.temp<uint4>(b.max_children);
   a.cursor = env.temp<uint32_t>(b.max_children);
   a.tile_parent = env.temp<uint32_t>(b.max_tiles);
   a.rec2 = env.temp<uint2>((size_t)b.max_regions * BK_CAP);
   if (!env.ok()) return;
+  a.clear_flags = b.nsamples && out.clear_flags;
+  if (out.clear_flags && !a.clear_flags) fill_u32(env, (uint32_t *)flags, sizeof(Flags) / 4, 0u);
   if (!b.direct) {
-    US_LAUNCH(env, "bucket_hist", (a.share.rows ? 4.0 : 8.0) * nnz, bucket_hist_kernel, a.groups_per_xcd * 8, BH_T, a);
-    US_LAUNCH(env, "bucket_scan", 8.0 * b.ngroups * b.nparents, bucket_scan_kernel, ceil_div<uint32_t>(b.nparents, BS_BINS), BS_T, a);
-    if (b.large) US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BPL_T, BPL_IPT>), a.groups_per_xcd * 8, BPL_T, a);
-    else US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BP_T, BP_IPT>), a.groups_per_xcd * 8, BP_T, a);
-    US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<false>), b.nparents, SM_T, a);
-    US_LAUNCH(env, "bucket_split", 16.0 * nnz, (bucket_split_kernel<false>), a.tiles_per_xcd * 8, BX_T, a);
+    if (b.nsamples) US_LAUNCH(env, "bucket_probe", 8.0 * b.nsamples, bucket_probe_kernel, ceil_div<uint32_t>(b.nsamples, BL_T), BL_T, a);
+    const double hist_bytes = (a.share.rows ? 4.0 : 8.0) * nnz;
+    if (b.large) US_LAUNCH(env, "bucket_hist", hist_bytes, (bucket_hist_kernel<BPL_T, BPL_SAMPLES, BPL_MAXX>), a.groups_per_xcd * 8, BPL_T, a);
+    else US_LAUNCH(env, "bucket_hist", hist_bytes, (bucket_hist_kernel<BP_T, BP_SAMPLES, BP_MAXX>), a.groups_per_xcd * 8, BP_T, a);
+    US_LAUNCH(env, "bucket_scan", 8.0 * b.ngroups * b.share.count, bucket_scan_kernel, ceil_div<uint32_t>(b.max_parents, BS_BINS), BS_T, a);
+    if (b.large) US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BPL_T, BPL_IPT, BPL_MAXX>), a.groups_per_xcd * 8, BPL_T, a);
+    else US_LAUNCH(env, "bucket_scatter", 20.0 * nnz, (bucket_scatter_kernel<BP_T, BP_IPT, BP_MAXX>), a.groups_per_xcd * 8, BP_T, a);
+    if (b.max_parents <= SM_T) US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<false, 1>), b.max_parents, SM_T, a);
+    else if (b.max_parents <= 2 * SM_T) US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<false, 2>), b.max_parents, SM_T, a);
+    else US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<false, 4>), b.max_parents, SM_T, a);
+    US_LAUNCH(env, "bucket_split", 16.0 * nnz, (bucket_split_kernel<false>), chunk_grid(b.max_tiles, a.tile_chunk), BX_T, a);
   } else {
-    US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<true>), b.nparents, SM_T, a);
-    US_LAUNCH(env, "bucket_split", 20.0 * nnz, (bucket_split_kernel<true>), a.tiles_per_xcd * 8, BX_T, a);
+    US_LAUNCH(env, "bucket_sample", 0.0, (bucket_sample_kernel<true, 1>), 1, SM_T, a);
+    US_LAUNCH(env, "bucket_split", 20.0 * nnz, (bucket_split_kernel<true>), chunk_grid(b.max_tiles, a.tile_chunk), BX_T, a);
   }
   if (out.late) {
     out.late(out); out.late = nullptr;
@@ -893,7 +1106,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   }
   a.major_out = out.major; a.minor_out = out.minor; a.val_out = (uint32_t *)out.val;
   a.ptr = out.ptr; a.ngroups_out = ks.a_extent;
-  US_LAUNCH(env, "bucket_finish", (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, a.children_per_xcd * 8, BF_T, a);
+  US_LAUNCH(env, "bucket_finish", (out.major ? 20.0 : 16.0) * nnz, bucket_finish_kernel, chunk_grid(b.max_children, a.child_chunk), BF_T, a);
 }
 
 }  // namespace us

@@ -237,6 +237,8 @@ struct SortOut {
   // The list comes in ascending order of its minor index (mode 0, unpacked output): a stable sort by the major index
   // alone gives the (major, minor) order.
   bool minor_sorted = false;
+  // The flags of the call hold nothing yet: the sort clears them (in a kernel of its own that comes first anyway, where it can).
+  bool clear_flags = false;
 };
 constexpr int NODE_TILE_SHIFT = 11, NODE_TILE = 1 << NODE_TILE_SHIFT;
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,

@@ -491,9 +491,9 @@ us_status validate_coo(const us_coo &coo) {
   return US_OK;
 }
 
-Flags *new_flags(Env &env) {
+Flags *new_flags(Env &env, bool clear) {
   Flags *flags = env.temp<Flags>(1);
-  fill_u32(env, (uint32_t *)flags, sizeof(Flags) / 4, 0u);
+  if (clear) fill_u32(env, (uint32_t *)flags, sizeof(Flags) / 4, 0u);
   return flags;
 }
 
@@ -532,7 +532,7 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
     env.reserve(Env::granule(8 * (size_t)n) + Env::granule(4 * (size_t)n) + Env::granule(4 * ((size_t)n / 1024 + 64)) +
                 8 * Env::granule(256));
   }
-  Flags *flags = new_flags(env);
+  Flags *flags = new_flags(env, !rowcol);
   if (!env.ok()) return env.status;
   if (plan.pattern == P_DIA) return convert_dia(env, coo, plan, desc, flags, out);
   if (plan.pattern == P_BCSR || plan.pattern == P_BDIA || plan.pattern == P_BELL) return convert_blocked(env, coo, plan, desc, flags, out);
@@ -543,6 +543,7 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
   float *val = nullptr;
   SortOut so{};
   so.minor_sorted = minor_sorted;
+  so.clear_flags = true;
   so.late = [&](SortOut &o) {
     if (late_res) env.reserve_out(late_res);
     if (with_ptr) ptr = plan.pattern == P_CSR ? env.owned<int32_t>((size_t)ks.a_extent + 1) : env.temp<int32_t>((size_t)ks.a_extent + 1);

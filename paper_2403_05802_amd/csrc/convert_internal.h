@@ -28,7 +28,7 @@ inline int64_t one_counter_grid(int64_t items, int per_block) {
 }
 
 // status flags of a call (device block, zeroed) and their one read-back
-Flags *new_flags(Env &env);
+Flags *new_flags(Env &env, bool clear = true);   // (not cleared: by the sort that follows, SortOut::clear_flags)
 bool read_flags(Env &env, Flags *dev, Flags *host);
 us_status flag_status(const Flags &h);
 

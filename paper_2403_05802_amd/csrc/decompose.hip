@@ -124,12 +124,13 @@ static us_status decompose_rank(Env &env, const us_coo &coo, const Plan &pa, con
     env.reserve(sort_temp_bytes(env, n, rowcol_keyspec(coo, false), false) + 3 * g(n) + 3 * g(nrows + 1) + g(nrows) + g(nrows / 1024 + 64) +
                 Env::granule(sizeof(SelectState)) + 4 * Env::granule(sizeof(Flags)));
   }
-  Flags *flags = new_flags(env);
+  Flags *flags = new_flags(env, false);
   int32_t *major = env.temp<int32_t>(n), *minor = env.temp<int32_t>(n);
   float *val = env.temp<float>(n);
   int32_t *ptr = env.temp<int32_t>(nrows + 1), *ptr_a = env.temp<int32_t>(nrows + 1), *clip = env.temp<int32_t>(nrows + 1);
   if (!env.ok()) return env.status;
   SortOut so{};
+  so.clear_flags = true;
   so.major = major; so.minor = minor; so.val = val;
   if (sort_gives_ptr(env, n, rowcol_keyspec(coo, false), false)) so.ptr = ptr;
   const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, rowcol_keyspec(coo, false), so, flags);

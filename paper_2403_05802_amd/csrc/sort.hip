@@ -1157,6 +1157,7 @@ bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val
     out.ptr_done = out.ptr != nullptr;
     return true;
   }
+  if (out.clear_flags) fill_u32(env, (uint32_t *)flags_dev, sizeof(Flags) / 4, 0u);
   return sort_generic(env, IN_COO, row, col, nullptr, val, nnz, ks, out, flags_dev);
 }
 

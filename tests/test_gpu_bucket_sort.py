@@ -89,21 +89,6 @@ def test_keys_that_crowd_in_every_octave(ctx, nr, nc, n):
         g.free()
 
 
-def test_a_parent_of_too_many_entries_goes_to_the_digit_passes(ctx):
-    """300,000 entries in 4 of 2^20 rows: one sixteenth of the key range holds them all."""
-    from helpers import assert_same_layout, dev
-    rng = np.random.default_rng(3)
-    nr = nc = 1 << 20
-    lin = rng.permutation(np.unique(rng.integers(0, 4 * nc, 300_000)))
-    r, c = (lin // nc).astype(np.int32), (lin % nc).astype(np.int32)
-    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
-    for d in (O.CSR(), O.COO()):
-        g, launches = run(ctx, nr, nc, r, c, v, d, dev)
-        assert launches["radix_scatter"] == 5, launches
-        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), str(d))
-        g.free()
-
-
 def on_the_gpu(ctx, nr, nc, lin, d):
     """Converts a list made on the GPU (distinct row * nc + column in random order) to CSR or COO and compares with torch's
     sort of the same numbers; the kernels of the conversion."""
@@ -124,11 +109,69 @@ def on_the_gpu(ctx, nr, nc, lin, d):
     return launches
 
 
-@pytest.mark.parametrize("nr,nc", [((1 << 20) + 2, 1 << 21), (1 << 21, (1 << 20) + 2)])
-def test_parents_share_the_rows_that_there_are(ctx, nr, nc):
+# rows that crowd: in the first rows (as in order of length, or an R-MAT graph), in the last ones, in a few that are used at
+# all (one share holds every entry), in few rows and the first columns (shares are pieces of rows); small and large tiles
+SKEWED = [(1 << 20, 1 << 20, 300_000, 4), (1 << 20, 1 << 20, 1_000_000, 5), (100_003, 100_003, 1_000_000, -5), (5, 1 << 24, 1_500_000, 5),
+          (1 << 21, 1 << 21, 2_000_000, 3), ((1 << 21) - 3, 1 << 18, 9_000_000, 8), (1 << 20, 1 << 20, 17_000_000, 6),
+          (300_007, 1 << 22, 36_000_000, -8)]
+
+
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("nr,nc,n,power", SKEWED)
+def test_shares_of_too_many_entries_are_cut(ctx, nr, nc, n, power, swap):
+    """A share of the rows with more entries than a parent may have used to send the whole call to the digit passes."""
+    import torch
+    gen = torch.Generator("cuda").manual_seed(n)
+    x = torch.rand(n, device="cuda", dtype=torch.float64, generator=gen) ** abs(power)
+    if nr == 5:
+        lin = (nr * nc * x).long()
+    else:
+        row = (x * nr).long() if abs(power) > 4 else torch.randint(0, power, (n,), device="cuda", generator=gen)
+        lin = (row if power > 0 else nr - 1 - row) * nc + torch.randint(0, nc, (n,), device="cuda", generator=gen)
+    lin = torch.unique(lin)
+    if swap:   # the same along the columns, to CSC's order by way of the transposed matrix
+        row = torch.div(lin, nc, rounding_mode="floor")
+        c, r = row.int(), (lin - row * nc).int()
+        order = torch.randperm(lin.numel(), device="cuda", generator=gen)
+        val = torch.rand(lin.numel(), device="cuda", generator=gen)
+        g, launches = run(ctx, nc, nr, r[order], c[order], val[order], O.CSC(), lambda t: t)
+        assert torch.equal(g.val(), val) and torch.equal(g.idx(1), r)
+        assert torch.equal(g.ptr(1).long(), torch.searchsorted(row, torch.arange(nr + 1, device="cuda")))
+        g.free()
+    else:
+        launches = on_the_gpu(ctx, nr, nc, lin, O.CSR() if nr < 1 << 21 else O.COO())
+    assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
+
+
+def test_a_parent_of_too_many_entries_goes_to_the_digit_passes(ctx):
+    """300,000 entries, every second one in 4 of 2^20 rows, but none of these where the sample looks."""
+    from helpers import assert_same_layout, dev
+    rng = np.random.default_rng(3)
+    nr = nc = 1 << 20
+    lin = np.unique(np.concatenate([rng.integers(0, 4 * nc, 150_000), rng.integers(4 * nc, nr * nc, 150_000)]))
+    lin = rng.permutation(lin)
+    n = lin.size
+    ns = n // 2048
+    i = np.arange(ns, dtype=np.uint64)
+    seen = (i * n // ns + ((i * 0x9E3779B1 & 0xFFFFFFFF) >> 8) % (n // ns)).astype(np.int64)
+    light = np.setdiff1d(np.flatnonzero(lin >= 4 * nc), seen)
+    for a, b in zip(seen[lin[seen] < 4 * nc], light):
+        lin[a], lin[b] = lin[b], lin[a]
+    assert (lin < 4 * nc).sum() > 131_072
+    r, c = (lin // nc).astype(np.int32), (lin % nc).astype(np.int32)
+    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
+    for d in (O.CSR(), O.COO()):
+        g, launches = run(ctx, nr, nc, r, c, v, d, dev)
+        assert launches["radix_scatter"] == 5, launches
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), str(d))
+        g.free()
+
+
+def test_parents_share_the_rows_that_there_are(ctx):
     """36 M entries, rows up to 2.5 times the average: with parents by the top bits of a row number just above 2^20 half of
     them were empty and the fullest of the others had more entries (175,000) than a parent may have."""
     import torch
+    nr, nc = (1 << 20) + 2, 1 << 21
     u = torch.rand(36_000_000, device="cuda", dtype=torch.float64, generator=torch.Generator("cuda").manual_seed(nr))
     row = (nr * (u + 0.6 * torch.sin(2 * np.pi * u) / (2 * np.pi))).long().clamp_(0, nr - 1)
     lin = torch.unique(row * nc + torch.randint(0, nc, row.shape, device="cuda", generator=torch.Generator("cuda").manual_seed(nc)))

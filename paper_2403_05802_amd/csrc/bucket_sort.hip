@@ -312,7 +312,7 @@ __global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
   const uint32_t q = threadIdx.x % BS_BINS, part = threadIdx.x / BS_BINS, p = blockIdx.x * BS_BINS + q;
   const uint32_t np = a.totals[2], each = (a.ngroups + BS_PARTS - 1) / BS_PARTS, g0 = min(part * each, a.ngroups), g1 = min(g0 + each, a.ngroups);
   uint32_t sum = 0;
-  if (p < a.max_parents) {   // (what lies past the parents is not used)
+  if (p < a.share.count || p < np) {   // (the loads of a share's own parent do not wait for the number of parents)
 #pragma unroll 8
     for (uint32_t g = g0; g < g1; ++g) sum += a.hist[(size_t)g * a.max_parents + p];
   }
@@ -369,9 +369,8 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const uint32_t p = tid * PER + q;
-      t[q] = p < a.max_parents ? a.ptotal[p] : 0u;   // (before the number of parents is known)
-      next[q] = p < a.max_parents ? a.hist[(size_t)group * a.max_parents + p] : 0u;
-      if (p >= np) t[q] = next[q] = 0;
+      t[q] = p < nshares || p < np ? a.ptotal[p] : 0u;
+      next[q] = p < nshares || p < np ? a.hist[(size_t)group * a.max_parents + p] : 0u;
       if (p < MAXP) s_cnt[p] = 0;
       sum += t[q];
     }
@@ -723,8 +722,7 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
       const uint32_t x = tid * PER + q;
-      size[q] = COO ? a.n : x < a.max_parents ? a.ptotal[x] : 0u;
-      if (x >= np) size[q] = 0;
+      size[q] = x >= np && x >= a.share.count ? 0u : COO ? a.n : a.ptotal[x];
       k[q] = x < np ? max((size[q] + BK_TARGET - 1) / BK_TARGET, 1u) : 0u;
       tiles[q] = (COO || k[q] > 1) ? (size[q] + BX_TILE - 1) / BX_TILE : 0u;
       const bool alone = !COO && k[q] == 1;
@@ -1007,9 +1005,9 @@ static BucketPlan bucket_plan(int64_t nnz, const KeySpec &ks) {
   if (b.direct) {
     b.share.count = 1; b.share.shift = ks.total_bits; b.share.width = 1ull << ks.total_bits;
   } else {
-    // 24 children per parent; 6 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
+    // 32 children per parent; 6 where the first pass writes whole lines all the same and the sample's sort is a chain of steps
     // that its size makes longer (1 M entries: 24 -> 17 us in the sample, the other kernels as they were)
-    const int64_t want = ceil_div<int64_t>(nnz, (nnz < (1 << 22) ? 6 : 24) * BK_TARGET);
+    const int64_t want = ceil_div<int64_t>(nnz, (nnz < (1 << 22) ? 6 : 32) * BK_TARGET);
     b.share = key_shares(ks, (uint32_t)std::min<int64_t>(want, BK_MAXSHARES));
     b.large = nnz >= BK_LARGE;
     const uint32_t tile = b.large ? BPL_T * BPL_IPT : BP_T * BP_IPT, groups = b.large ? BPL_GROUPS : BP_GROUPS;

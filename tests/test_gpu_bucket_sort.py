@@ -72,11 +72,29 @@ def test_matches_the_oracle(ctx, nr, nc, n, kind):
     descs = [O.CSR(), O.CSC(), O.COO()] + ([O.DCSR()] if kind == "heavy" else [])
     for d in descs:
         g, launches = run(ctx, nr, nc, r, c, v, d, put)
-        if kind in ("uniform", "sorted") and nr * nc > 1:
+        if nr * nc > 1:
             passes = 65536 < r.size <= 262144 and nr * nc <= 1 << 24      # three digit passes are as quick there
             assert ("bucket_split" in launches) != passes and ("radix_scatter" in launches) == passes, (d, launches)
         assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{kind} {nr}x{nc}, {r.size} entries -> {d}")
         g.free()
+
+
+def sampled(n, k):
+    """Where the sort looks for ns = 64 keys per child among n entries: evenly spaced pieces, a scattered place in each."""
+    ns = min(4096, 64 * k, n)
+    i = np.arange(ns, dtype=np.uint64)
+    return (i * n // ns + ((i * 0x9E3779B1 & 0xFFFFFFFF) >> 8) % (n // ns)).astype(np.int64)
+
+
+def fullest_bin(keys, width, bins):
+    """Most keys of a bin when 64 of them, every len / 64th, cut [0, width) into intervals and each of these is cut evenly."""
+    cuts = np.sort(keys[np.arange(64) * len(keys) // 64]).astype(np.float64)
+    cuts[0] = 0
+    ends = np.append(cuts[1:], width)
+    at = np.searchsorted(cuts, keys, side="right") - 1
+    each = bins // 64
+    inside = np.minimum(((keys - cuts[at]) * each / (ends[at] - cuts[at] + 1)).astype(np.int64), each - 1)
+    return np.bincount(at * each + inside).max()
 
 
 @pytest.mark.parametrize("nr,nc,n", [(4096, 4096, 60_000), (1 << 20, 1 << 20, 400_000)])
@@ -84,9 +102,50 @@ def test_keys_that_crowd_in_every_octave(ctx, nr, nc, n):
     from helpers import assert_same_layout, dev
     r, c, v = entries(np.random.default_rng(n), nr, nc, n, "powers")
     for d in (O.CSR(), O.COO()):
-        g, _ = run(ctx, nr, nc, r, c, v, d, dev)
+        g, launches = run(ctx, nr, nc, r, c, v, d, dev)
+        assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
         assert_same_layout(g, O.convert(nr, nc, r, c, v, d), f"{r.size} entries -> {d}")
         g.free()
+
+
+@pytest.mark.parametrize("clusters,gap", [(70, 1), (16, 1), (30, 3)])
+def test_splitters_of_clusters(ctx, clusters, gap):
+    """One parent of 32 bits whose keys lie in clusters: more of the sampled keys share a bin than are put in order by
+    comparison (33), so the bins of the sample are cut again."""
+    from helpers import assert_same_layout, dev
+    rng = np.random.default_rng(clusters)
+    nr = nc = 65536
+    at = rng.integers(0, nr * nc - (1 << 20), clusters)
+    lin = np.unique((at[:, None] + gap * np.arange(60_000 // clusters)[None]).ravel())
+    lin = rng.permutation(lin)
+    keys = lin[sampled(lin.size, -(-lin.size // 1024))]
+    assert lin.size <= 65536 and fullest_bin(keys, nr * nc, 4096) > 33
+    r, c = (lin // nc).astype(np.int32), (lin % nc).astype(np.int32)
+    v = rng.uniform(0.1, 1, r.size).astype(np.float32)
+    for d in (O.CSR(), O.COO()):
+        g, launches = run(ctx, nr, nc, r, c, v, d, dev)
+        assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
+        assert_same_layout(g, O.convert(nr, nc, r, c, v, d), str(d))
+        g.free()
+
+
+def test_a_child_that_no_bins_part(ctx):
+    """1024 parents of 2048 rows and 2^32 keys each.  Every one holds its largest key, which leaves the 64 keys that cut a
+    child without a mark for "none" when it is among them, so the child's range is one interval of 2048 bins; its other keys,
+    130 to 2000 of them, lie in the first bin, too many for comparisons.  Which 64 keys are looked at depends on the order
+    in which atomics arrive: 64 / m of the children of m keys come here on average, some hundred of the 1024."""
+    import torch
+    rng = np.random.default_rng(7)
+    nr = nc = 1 << 21
+    size = rng.integers(130, 1024, 1024)
+    size[::16] = rng.integers(1024, 2000, 64)
+    assert (64 / size).sum() > 100
+    base = np.arange(1024, dtype=np.int64) << 32
+    lin = np.concatenate([np.append(b + rng.choice(1 << 21, m, replace=False), b + (1 << 32) - 1) for b, m in zip(base, size)])
+    assert np.bincount((lin & 0xFFFFFFFF) * 2048 >> 32).max() == size.sum()     # (in bin 0 of the 2048)
+    for d in (O.CSR(), O.COO()):
+        launches = on_the_gpu(ctx, nr, nc, torch.from_numpy(lin).cuda(), d)
+        assert "bucket_finish" in launches and "radix_scatter" not in launches, launches
 
 
 def on_the_gpu(ctx, nr, nc, lin, d):

@@ -878,7 +878,9 @@ static void entry_balanced_spmm(Env &env, const us_formatted &A, RowSrc rs, cons
   // Rows of X of a kilobyte: eight of them in flight per wavefront keep the memory busy with 12 wavefronts per CU, and fewer
   // entries in flight leave the L2 more to find again: three workgroups per CU, by the LDS that they ask for, where the
   // slices of columns are full (5.2 M entries with local columns, N = 1000: 3267 -> 3049 us; power-law, no locality, 3389 ->
-  // 3360; N = 300, the second slice one sixth full: 876 -> 902; 400 k entries, N = 256: 104 -> 112).
+  // 3360; N = 300, the second slice one sixth full: 876 -> 902; 400 k entries, N = 256: 104 -> 112).  With two columns per lane
+  // a row in flight is half as long and 12 wavefronts are too few (N = 128: 40 M entries 2738 -> 3256, 10 M power-law 807 ->
+  // 814).  The COO product is not part of the rule although it gains as much (N = 1000: 3610 -> 3385, N = 256: 1656 -> 1543).
   const size_t few_resident = search && vec == 4 && A.nnz >= 1 << 21 && (ncbv * cbw - N) * 10 <= ncbv * cbw ? 48 << 10 : 0;
   {
     LaunchScope ls(env, name, 12.0 * A.nnz + xy);

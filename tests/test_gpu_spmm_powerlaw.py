@@ -24,7 +24,8 @@ def matrix():
     return W.cfg2_powerlaw(n=300_000, target_nnz=3_000_000, s=1.6, max_len=20000, index=8)
 
 
-@pytest.mark.parametrize("N", [40, 130, 260])
+# (256 and 492, four columns per lane and slices that are full: fewer workgroups resident for layouts with row pointers)
+@pytest.mark.parametrize("N", [40, 130, 256, 260, 492])
 def test_powerlaw_spmm_every_output(ctx, matrix, N):
     from paper_2403_05802_amd import binding as B
     m = matrix
@@ -41,10 +42,10 @@ def test_powerlaw_spmm_every_output(ctx, matrix, N):
         g.free()
 
 
-def test_powerlaw_spmm_accumulate_and_strides(ctx, matrix):
+@pytest.mark.parametrize("N,ldx,ldy", [(130, 136, 160), (256, 260, 264)])
+def test_powerlaw_spmm_accumulate_and_strides(ctx, matrix, N, ldx, ldy):
     from paper_2403_05802_amd import binding as B
     m = matrix
-    N, ldx, ldy = 130, 136, 160
     rng = np.random.default_rng(41)
     Xw = rng.uniform(-1, 1, (m.ncols, ldx)).astype(np.float32)
     Yw0 = rng.uniform(-1, 1, (m.nrows, ldy)).astype(np.float32)

@@ -699,9 +699,11 @@ __device__ __forceinline__ void fix_order(uint32_t m, BinScratch<T, IPT, LIMIT> 
 constexpr int SM_T = 512, SM_IPT = 8, SM_MOST = SM_T * SM_IPT;   // sampled keys of a parent
 constexpr int BX_T = 512, BX_IPT = 8, BX_TILE = BX_T * BX_IPT;
 
-// One workgroup per parent: its place among the parents, its children and tiles, their splitters.  64 sampled keys per
-// child make a child of twice the average, the most the finish holds, a matter of 3e-9 (32 keys: 5e-5); the call is then run again with
-// the digit passes, as it is when a parent is too large for BK_MAXK children.
+// One workgroup per parent: its place among the parents, its children and tiles, their splitters.  A child of
+// twice the average is more than the finish holds: with s sampled keys per child its odds are those of a Poisson number of mean
+// 2 s below s, 1e-10 for 64 keys, which parents of up to 64 children have, 8e-8 for the 44 of 93 children (the fullest parents
+// of a power-law list of 40 M entries), 4e-6 for the 32 of 128.  The call is then run again with the digit passes, as it is when a parent is
+// too large for BK_MAXK children.
 // COO: the whole list is one parent, its keys are built from the coordinates.  PER: parents for a thread to add up, SM_T * PER
 // in all.
 template <bool COO, int PER>

@@ -1131,7 +1131,11 @@ static bool sort_generic(Env &env, int in_mode, const int32_t *row, const int32_
 // Lists in order of their minor index take passes over the major digits alone up to 2 M entries (CSR -> CSC, digit passes /
 // buckets, us: 1.5 M entries 123 / 125, 3.1 M 173 / 160, 16.8 M 508 / 440).  Short lists of more key bits, one digit pass and
 // the finish here / buckets: 41 k entries, 26 bits 97 / 78, power-law rows 100 / 90; 100 k, 30 bits 103 / 92; 200 k with local
-// columns, whose heavy rows sent the finish back to the digit passes, 203 / 104; 200 k, 42 bits 157 / 130.
+// columns, whose heavy rows sent the finish back to the digit passes, 203 / 104; 200 k, 42 bits 157 / 130.  64, 1000 and 40 k
+// entries of 42 bits (digit passes / buckets, DCSR) 107 / 85, 113 / 89, 142 / 106.
+// Lists come in order as well: a tile of one row then meets on one counter of the first pass and on few of the second (16.8 M:
+// 100 -> 137 and 60 -> 97 us), which leaves it ahead of the digit passes all the same.  Sorted by rows, digit passes / buckets:
+// 40 M 1594 / 1000, 16.8 M 686 / 472, 4 M 213 / 180, 1 M 153 / 105, 300 k 112 / 94, 41 k 70 / 68; by columns as in random order.
 static bool by_buckets(const Env &env, int64_t nnz, const KeySpec &ks, bool minor_sorted) {
   if (env.lds_finish >= 0 || !bucket_sort_takes(nnz, ks)) return false;
   if (minor_sorted) return nnz > (1 << 21);

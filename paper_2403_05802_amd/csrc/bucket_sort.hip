@@ -337,7 +337,7 @@ __global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
 // A workgroup walks its range tile by tile: places inside the tile by LDS atomics, the tile put in order of the parents
 // in LDS, every parent's run written as one piece behind the workgroup's earlier ones.  Its runs are short (12 entries of a
 // tile of 12,288 in 1024 parents) and leave lines partly written: ngroups x nparents of them are open at a time, 128 bytes
-// each, against 4 MB of L2 per XCD.  By the counters it writes a quarter more than the records take (397 MB for 320, 40 M
+// each, against 4 MB of L2 per XCD.  By the counters it writes a quarter more than the records take (400 MB for 320, 40 M
 // entries) and fetches the list once, 3.4 TB/s in all: scattered pieces and, with one workgroup per CU, its phases one
 // after the other are what is left.  Few
 // workgroups and large tiles where there are many entries.  512 threads x 8 entries and 768 workgroups / 1024 x 8 and 256

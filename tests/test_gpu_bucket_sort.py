@@ -291,6 +291,18 @@ def test_errors_are_reported(ctx, nr, nc, n):
             assert ei.value.code == "US_ERR_INDEX_RANGE"
 
 
+def test_more_entries_than_the_matrix_has_places(ctx):
+    """Four keys in all: shares that no splitter can cut."""
+    from paper_2403_05802_amd import binding as B
+    from helpers import dev, us_desc_of
+    rng = np.random.default_rng(2)
+    r, c = rng.integers(0, 2, (2, 600_000)).astype(np.int32)
+    for d in (O.CSR(), O.COO()):
+        with pytest.raises(B.UnisparseError) as ei:
+            B.us_convert(ctx, 2, 2, dev(r), dev(c), dev(np.ones(r.size, np.float32)), us_desc_of(d))
+        assert ei.value.code == "US_ERR_DUPLICATE"
+
+
 @pytest.mark.parametrize("kind", ["uniform", "clusters"])
 def test_large_tiles_and_transposing(ctx, kind):
     """8.4 M entries and more (tiles of 12,288 in the first pass), there and back."""

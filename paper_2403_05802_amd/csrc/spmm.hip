@@ -3,6 +3,7 @@
 // columns of X so every gathered X row is one contiguous read.
 #include "common.h"
 #include "device.h"
+#include "spmm_internal.h"
 
 namespace us {
 
@@ -440,232 +441,7 @@ __global__ __launch_bounds__(256) void dia_spmm_rows_kernel(const int32_t *off, 
 }
 
 
-// ------------------------------------------------------------------ entries grouped by row (COO sorted by row, CSR, DCSR): equal shares of non-zeros per wavefront
-// The row of entry e is read from the COO row array, or found in ptr (plus the stored-row list
-// for DCSR), so a 20,000-entry row costs the same as 20,000 one-entry rows.
-struct RowSrc {
-  const int32_t *row;   // COO: row of every entry, else null
-  const int32_t *ptr;   // CSR / DCSR: children of parent p are [ptr[p], ptr[p+1])
-  const int32_t *ids;   // DCSR: row index of parent p, else null
-  int64_t nparents;
-  const int2 *bounds;   // CSR / DCSR: parents of the entries around every chunk boundary (chunk_bounds_kernel), or null
-  __device__ __forceinline__ int32_t of(int64_t e) const { return __builtin_nontemporal_load(row + e); }   // COO
-};
-
-// A wavefront walks a chunk of consecutive entries; for each it adds val * X[col, :] into a
-// register accumulator and flushes when the row changes.  Row pieces cut by a chunk boundary
-// go to a carry buffer and are summed in chunk order by the fix-up kernel (reproducible).
-// The chunks in flight on an XCD span the rows of X that its L2 would have to hold for one chunk to find what another has
-// fetched, so they are no longer than what a chunk costs by itself asks for.  512 / 256 / 128 entries, us: 40 M entries with
-// local columns, N = 128, CSR 2798 / 2724 / 2795, as COO 2120 / 2099 / 2166; N = 64 1669 / 1679 / 1774; with three
-// workgroups per CU (few_resident) 5.2 M, N = 1000 3220 / 3049 / 2864; 10 M, N = 256 1441 / 1367 / 1292; but 5 M of a power-law
-// matrix, no locality, N = 1000 3320 / 3360 / 3447: the carries of its long rows.
-constexpr int CS_CHUNK = 256, CSB_CHUNK_MAX = 512;
-// ... or fewer when the list is short: a wavefront's entries are a serial chain of gather rounds (eight rows of X at a
-// time), so 147 k entries cut into 287 chunks kept 287 wavefronts busy for 64 rounds each, 0.26 ms on a part with
-// 1024 SIMDs; chunks of 64 entries make it 2,293 wavefronts of 8 rounds.
-static int chunk_entries(int64_t nnz, int most = CS_CHUNK) {
-  int len = most;
-  while (len > 64 && nnz / len < 8192) len >>= 1;
-  return len;
-}
-
-// bounds[k] = parents of the last entry before chunk k and of its first one.  A bisection over all parents is 20 dependent
-// loads: one for every boundary, all side by side, takes 5 to 15 us; in the product, at the start of every chunk, it takes
-// 8 of the 90 us of a million entries (N = 64) and 7 % of the time of 40 M.  Below BOUNDS_FROM entries the launch costs more
-// than it saves (400 k entries, N = 16: 43.6 -> 45.2 us with the table).
-constexpr int64_t BOUNDS_FROM = 3 << 18;
-__global__ __launch_bounds__(256) void chunk_bounds_kernel(const int32_t *ptr, int64_t nparents, int64_t nnz, int chunk_len,
-                                                           int64_t nchunks, int2 *bounds) {
-  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (k > nchunks) return;
-  const int64_t e = min(k * chunk_len, nnz);   // nnz > 0
-  const int64_t behind = parent_of(ptr, nparents, e < nnz ? e : nnz - 1);
-  int64_t before = behind;                     // the parent of e - 1: behind itself, or the last one before it with entries
-  if (e > 0 && e < nnz && (int64_t)ptr[behind] == e) before = parent_of(ptr, behind, e - 1);
-  bounds[k] = make_int2((int32_t)before, (int32_t)behind);
-}
-
-// SEARCH (rows found in ptr): the rows of the whole chunk are looked up first and kept in LDS: the parents of the two
-// entries around the chunk, then the entries' own between those two: four entries per lane with their bisections in step.  One full bisection after the other (per batch of 64 entries, plus four for the chunk's ends) is
-// ~250 dependent loads -- a remainder of 147 k entries in 2 M rows, a few hundred wavefronts that all run at once, took
-// 0.32 ms of pure latency that way -- and twenty scattered loads per entry where the rows of a chunk are a handful.
-template <int VEC, bool SEARCH>
-__global__ __launch_bounds__(256) void coo_spmm_kernel(RowSrc row, const int32_t *col, const float *val,
-                                                      int64_t nnz, int chunk_len, int64_t per_xcd, const float *X, int64_t N,
-                                                      int64_t ldx, float *Y, int64_t ldy, int accumulate, int32_t *carry_row,
-                                                      float *carry) {
-  typedef typename VecT<VEC>::type V;
-  constexpr int PER_LANE = CS_CHUNK / 64;   // slots of the look-up: chunk_len <= CS_CHUNK
-  __shared__ int32_t s_rows[SEARCH ? 4 : 1][SEARCH ? CS_CHUNK : 1];
-  const int lane = lane_id();
-  // launch index -> chunk through xcd_tile: an XCD walks one contiguous range of entries (rows), so the
-  // rows of X that neighbouring matrix rows share are found again in its own L2
-  const int64_t chunk = xcd_tile(blockIdx.x, per_xcd) * 4 + wave_id();
-  const int64_t e0 = chunk * chunk_len;
-  if (e0 >= nnz) return;
-  const int64_t e1 = min(e0 + chunk_len, nnz);
-  const int64_t c = ((int64_t)blockIdx.y * 64 + lane) * VEC;
-  const bool col_ok = c < N;
-  const uint32_t xoff = (uint32_t)(col_ok ? c : 0);   // clamped: loads stay in bounds, stores are guarded
-  int32_t row_before, row_after, first_row, last_row;
-  if constexpr (SEARCH) {
-    // parents of the entries just before and just behind the chunk (at the list's ends of its own first or last entry), from
-    // the table or by two bisections over all parents, in step, the same for every lane (ptr[p] <= e < ptr[p + 1])
-    int32_t blo = 0, bhi = (int32_t)row.nparents, alo = 0, ahi = (int32_t)row.nparents;
-    if (row.bounds) { blo = bhi = row.bounds[chunk].x; alo = ahi = row.bounds[chunk + 1].y; }
-    const int64_t eb = e0 > 0 ? e0 - 1 : e0, ea = e1 < nnz ? e1 : e1 - 1;
-    while (blo < bhi || alo < ahi) {
-      if (blo < bhi) {
-        const int32_t mid = blo + ((bhi - blo) >> 1);
-        if ((int64_t)row.ptr[mid + 1] <= eb) blo = mid + 1; else bhi = mid;
-      }
-      if (alo < ahi) {
-        const int32_t mid = alo + ((ahi - alo) >> 1);
-        if ((int64_t)row.ptr[mid + 1] <= ea) alo = mid + 1; else ahi = mid;
-      }
-    }
-    // every entry of the chunk has its parent between those two: PER_LANE entries per lane, their bisections over
-    // that range in step (a chunk inside one long row needs none, 96-entry rows three steps instead of twenty)
-    int32_t lo[PER_LANE], hi[PER_LANE];
-#pragma unroll
-    for (int q = 0; q < PER_LANE; ++q) {
-      const bool live = e0 + q * 64 + lane < e1;
-      lo[q] = blo; hi[q] = live ? alo : blo;
-    }
-    for (bool more = true; more;) {
-      more = false;
-#pragma unroll
-      for (int q = 0; q < PER_LANE; ++q) {
-        if (lo[q] < hi[q]) {
-          const int32_t mid = lo[q] + ((hi[q] - lo[q]) >> 1);
-          if ((int64_t)row.ptr[mid + 1] <= e0 + q * 64 + lane) lo[q] = mid + 1; else hi[q] = mid;
-          more = true;
-        }
-      }
-      more = __any(more);
-    }
-#pragma unroll
-    for (int q = 0; q < PER_LANE; ++q)
-      if (e0 + q * 64 + lane < e1) s_rows[wave_id()][q * 64 + lane] = row.ids ? row.ids[lo[q]] : lo[q];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    row_before = e0 > 0 ? (row.ids ? row.ids[blo] : blo) : -1;
-    row_after = e1 < nnz ? (row.ids ? row.ids[alo] : alo) : -1;
-    first_row = s_rows[wave_id()][0]; last_row = s_rows[wave_id()][e1 - 1 - e0];
-  } else {
-    row_before = e0 > 0 ? row.of(e0 - 1) : -1;
-    row_after = e1 < nnz ? row.of(e1) : -1;
-    first_row = row.of(e0); last_row = row.of(e1 - 1);
-  }
-  V *carry_head = reinterpret_cast<V *>(carry + ((chunk * 2 + 0) * gridDim.y + blockIdx.y) * (64 * VEC)) + lane;
-  V *carry_tail = reinterpret_cast<V *>(carry + ((chunk * 2 + 1) * gridDim.y + blockIdx.y) * (64 * VEC)) + lane;
-  const bool head_cut = first_row == row_before, tail_cut = last_row == row_after;
-  V acc = V(0.f);
-  int32_t cur = first_row;
-  bool in_head = true;  // still inside the first row piece of the chunk
-  constexpr int U = 8;
-  for (int64_t base = e0; base < e1; base += 64) {
-    const int64_t e = base + lane;
-    int32_t r = -1;
-    if (e < e1) {
-      if constexpr (SEARCH) r = s_rows[wave_id()][e - e0]; else r = row.of(e);
-    }
-    const int32_t cc = e < e1 ? __builtin_nontemporal_load(col + e) : 0;
-    const float v = e < e1 ? __builtin_nontemporal_load(val + e) : 0.f;
-    const int cnt = (int)min((int64_t)64, e1 - base);
-    for (int t0 = 0; t0 < cnt; t0 += U) {
-      // row, column and value of entry t are scalars (v_readlane): the gather address is scalar
-      // arithmetic plus a fixed per-lane offset and the row-change test is a scalar branch
-      int32_t rt[U];
-      float vt[U];
-      V xv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {   // 8 gathers of X rows in flight
-        const int t = t0 + u < cnt ? t0 + u : cnt - 1;
-        rt[u] = __builtin_amdgcn_readlane(r, t);
-        vt[u] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), t));
-        const int64_t ct = __builtin_amdgcn_readlane(cc, t);
-        xv[u] = *reinterpret_cast<const V *>(X + ct * ldx + xoff);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (t0 + u < cnt) {
-          if (rt[u] != cur) {  // flush the finished piece of row `cur`
-            if (col_ok) {
-              if (in_head && head_cut) *carry_head = acc;
-              else { V *yp = reinterpret_cast<V *>(Y + (int64_t)cur * ldy + c); *yp = accumulate ? *yp + acc : acc; }
-            }
-            in_head = false;
-            acc = V(0.f);
-            cur = rt[u];
-          }
-          acc += vt[u] * xv[u];
-        }
-      }
-    }
-  }
-  // last piece
-  const bool single = in_head;  // the whole chunk lies inside one row
-  if (col_ok) {
-    V *yp = reinterpret_cast<V *>(Y + (int64_t)cur * ldy + c);
-    if (single) {
-      if (head_cut || tail_cut) { *carry_head = acc; *carry_tail = V(0.f); }
-      else *yp = accumulate ? *yp + acc : acc;
-    } else {
-      if (tail_cut) *carry_tail = acc;
-      else *yp = accumulate ? *yp + acc : acc;
-    }
-  }
-  if (lane == 0 && blockIdx.y == 0) {
-    bool head_used = single ? (head_cut || tail_cut) : head_cut;
-    bool tail_used = single ? (head_cut || tail_cut) : tail_cut;
-    carry_row[chunk * 2 + 0] = head_used ? first_row : -1;
-    carry_row[chunk * 2 + 1] = tail_used ? last_row : -1;
-  }
-}
-
-__global__ __launch_bounds__(256) void coo_spmm_fixup_kernel(const int32_t *carry_row, const float *carry,
-                                                            int64_t nentries, int64_t ncb, int cbw, int64_t N,
-                                                            float *Y, int64_t ldy, int accumulate) {
-  const int lane = lane_id();
-  const int64_t e = (int64_t)blockIdx.x * 4 + wave_id();
-  if (e >= nentries) return;
-  const int32_t r = carry_row[e];
-  if (r < 0) return;
-  // only the first entry of the run of row r works (a run never skips an entry, see above)
-  if (e > 0 && carry_row[e - 1] == r) return;
-  // length of the run, 64 entries per look (a 20,000-entry row leaves ~80 pieces: walking them one
-  // dependent load at a time made this kernel the tail of the whole product)
-  int64_t len = 0;
-  for (;;) {
-    const int64_t j = e + len + lane;
-    const uint64_t same = __ballot(j < nentries && carry_row[j] == r);
-    const int run = same == ~0ull ? 64 : __ffsll((unsigned long long)~same) - 1;
-    len += run;
-    if (run < 64) break;
-  }
-  for (int q = lane; q < cbw; q += 64) {
-    const int64_t c = (int64_t)blockIdx.y * cbw + q;
-    if (c >= N) continue;
-    const float *p = carry + (e * ncb + blockIdx.y) * cbw + q;
-    const int64_t stride = ncb * cbw;
-    float s = 0.f;
-    int64_t j = 0;
-    for (; j + 8 <= len; j += 8) {   // 8 independent loads in flight, added in piece order
-      float t[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) t[u] = p[(j + u) * stride];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += t[u];
-    }
-    for (; j < len; ++j) s += p[j * stride];
-    float *yp = Y + (int64_t)r * ldy + c;
-    *yp = accumulate ? *yp + s : s;
-  }
-}
-
+// ------------------------------------------------------------------ scatter forms
 // scatter form for CSC / DCSC: one wavefront per (stored column, 64 columns of X)
 __global__ __launch_bounds__(256) void csc_spmm_atomic_kernel(const int32_t *ptr, const int32_t *idx, const float *val,
                                                              const int32_t *col_ids, int64_t ncols_stored,
@@ -677,6 +453,15 @@ __global__ __launch_bounds__(256) void csc_spmm_atomic_kernel(const int32_t *ptr
   if (cc >= N) return;
   const float xv = X[(int64_t)(col_ids ? col_ids[j] : j) * ldx + cc];
   for (int e = ptr[j]; e < ptr[j + 1]; ++e) atomicAdd(&Y[(int64_t)idx[e] * ldy + cc], val[e] * xv);
+}
+
+// entries per wavefront of the CSB product, fewer when the list is short: a wavefront's entries are a serial chain of gather
+// rounds (eight rows of X at a time)
+constexpr int CSB_CHUNK_MAX = 512;
+static int csb_chunk_entries(int64_t nnz) {
+  int len = CSB_CHUNK_MAX;
+  while (len > 64 && nnz / len < 8192) len >>= 1;
+  return len;
 }
 
 // CSB: the entries lie in (block row, block column, in-block row, in-block column) order, so a wavefront that walks
@@ -845,65 +630,6 @@ static void zero_rows(Env &env, float *Y, int64_t nrows, int64_t N, int64_t ldy)
     US_LAUNCH(env, "zero_rows", 4.0 * nrows * N, zero_rows_kernel, ceil_div<int64_t>(nrows * N, 256), 256, Y, nrows, N, ldy);
 }
 
-// scratch of the entry-balanced product: two carry rows per chunk (row index + one value per column of the lane layout) and,
-// where rows are found in ptr, the table of the chunk boundaries
-struct BalancedScratch { size_t rows, bounds, carry; };
-static BalancedScratch balanced_scratch(int64_t nnz, int64_t N, int vec, bool search) {
-  const size_t nchunks = (size_t)ceil_div<int64_t>(nnz, chunk_entries(nnz)), cbw = 64 * vec;
-  return {Env::granule(nchunks * 2 * sizeof(int32_t)), search && nnz >= BOUNDS_FROM ? Env::granule((nchunks + 1) * sizeof(int2)) : 0,
-          nchunks * 2 * ceil_div<size_t>((size_t)N, cbw) * cbw * sizeof(float)};
-}
-
-static void entry_balanced_spmm(Env &env, const us_formatted &A, RowSrc rs, const int32_t *col,
-                                const char *name, int vec, const float *X, int64_t N, int64_t ldx, float *Y,
-                                int64_t ldy, bool accumulate) {
-  // accumulate: Y holds the values to add to; else rows with entries are stored and the others left as they are
-  const double xy = 4.0 * N * (A.ncols + A.nrows);
-  const bool search = !rs.row;
-  const int chunk_len = chunk_entries(A.nnz);
-  const int64_t nchunks = ceil_div<int64_t>(A.nnz, chunk_len);
-  const BalancedScratch parts = balanced_scratch(A.nnz, N, vec, search);
-  const int cbw = 64 * vec;
-  const int64_t ncbv = ceil_div<int64_t>(N, cbw);
-  char *ws = (char *)ensure_workspace(env, A, parts.rows + parts.bounds + parts.carry);
-  if (!env.ok()) return;
-  int32_t *carry_row = (int32_t *)ws;
-  float *carry = (float *)(ws + parts.rows + parts.bounds);
-  if (parts.bounds) {
-    int2 *bounds = (int2 *)(ws + parts.rows);
-    US_LAUNCH(env, "spmm_bounds", 8.0 * nchunks, chunk_bounds_kernel, ceil_div<int64_t>(nchunks + 1, 256), 256, rs.ptr, rs.nparents,
-              A.nnz, chunk_len, nchunks, bounds);
-    rs.bounds = bounds;
-  }
-  // Rows of X of a kilobyte: eight of them in flight per wavefront keep the memory busy with 12 wavefronts per CU, and fewer
-  // entries in flight leave the L2 more to find again: three workgroups per CU, by the LDS that they ask for, where the
-  // slices of columns are full (5.2 M entries with local columns, N = 1000: 3267 -> 3049 us; power-law, no locality, 3389 ->
-  // 3360; N = 300, the second slice one sixth full: 876 -> 902; 400 k entries, N = 256: 104 -> 112).  With two columns per lane
-  // a row in flight is half as long and 12 wavefronts are too few (N = 128: 40 M entries 2738 -> 3256, 10 M power-law 807 ->
-  // 814).  The COO product is not part of the rule although it gains as much (N = 1000: 3610 -> 3385, N = 256: 1656 -> 1543).
-  const size_t few_resident = search && vec == 4 && A.nnz >= 1 << 21 && (ncbv * cbw - N) * 10 <= ncbv * cbw ? 48 << 10 : 0;
-  {
-    LaunchScope ls(env, name, 12.0 * A.nnz + xy);
-    const int64_t per_xcd = ceil_div<int64_t>(ceil_div<int64_t>(nchunks, 4), 8);
-    const dim3 grid((unsigned)(per_xcd * 8), (unsigned)ncbv);
-#define US_EB_LAUNCH(V, S) hipLaunchKernelGGL((coo_spmm_kernel<V, S>), grid, dim3(256), few_resident, env.stream, rs, col, (const float *)A.val, A.nnz, chunk_len, per_xcd, X, N, ldx, Y, ldy, accumulate ? 1 : 0, carry_row, carry)
-    if (rs.row) {
-      if (vec == 4) US_EB_LAUNCH(4, false); else if (vec == 2) US_EB_LAUNCH(2, false); else US_EB_LAUNCH(1, false);
-    } else {
-      if (vec == 4) US_EB_LAUNCH(4, true); else if (vec == 2) US_EB_LAUNCH(2, true); else US_EB_LAUNCH(1, true);
-    }
-#undef US_EB_LAUNCH
-    env.check(hipGetLastError());
-  }
-  if (env.ok()) {
-    LaunchScope ls(env, "spmm_rows_fixup", 8.0 * nchunks);
-    hipLaunchKernelGGL(coo_spmm_fixup_kernel, dim3((unsigned)ceil_div<int64_t>(nchunks * 2, 4), (unsigned)ncbv),
-                       dim3(256), 0, env.stream, (const int32_t *)carry_row, (const float *)carry, nchunks * 2, ncbv,
-                       cbw, N, Y, ldy, accumulate ? 1 : 0);
-    env.check(hipGetLastError());
-  }
-}
-
 us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy,
                     bool accumulate) {
   const int64_t ncb = ceil_div<int64_t>(N, 64);
@@ -993,8 +719,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       if (store) zero_empty_rows(env, sr.ptr, A.nrows, Y, N, ldy);
       else if (!accumulate) zero_rows(env, Y, A.nrows, N, ldy);
       if (A.nnz > 0) {
-        RowSrc rs{nullptr, sr.ptr, sr.row_ids, A.nmajor, nullptr};
-        entry_balanced_spmm(env, A, rs, sr.idx, "spmm_csr", vec, X, N, ldx, Y, ldy, !store);
+        panel_spmm(env, A, nullptr, &sr, sr.idx, "spmm_csr", X, N, ldx, Y, ldy, !store);
       }
       return env.status;
     }
@@ -1015,7 +740,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       if (!accumulate) zero_rows(env, Y, A.nrows, N, ldy);
       if (env.ok() && A.nnz > 0) {
         LaunchScope ls(env, "spmm_csb_atomic", 12.0 * A.nnz + xy);
-        const int chunk_len = chunk_entries(A.nnz, CSB_CHUNK_MAX);
+        const int chunk_len = csb_chunk_entries(A.nnz);
         const int64_t per_xcd = ceil_div<int64_t>(ceil_div<int64_t>(ceil_div<int64_t>(A.nnz, chunk_len), 4), 8);
         const dim3 grid((unsigned)(per_xcd * 8), (unsigned)ceil_div<int64_t>(N, 64 * vec));
 #define US_CSB_LAUNCH(V) hipLaunchKernelGGL(csb_spmm_kernel<V>, grid, dim3(256), 0, env.stream, (const int32_t *)A.level[2].ptr, (const int32_t *)A.level[2].idx, (const int32_t *)A.level[3].idx, (const float *)A.val, A.nnz, chunk_len, per_xcd, A.nmajor, A.level[1].size, A.bh, A.bw, X, N, ldx, Y, ldy)
@@ -1050,8 +775,7 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
         }
         return env.status;
       }
-      RowSrc rs{A.level[0].idx, nullptr, nullptr, 0, nullptr};
-      entry_balanced_spmm(env, A, rs, A.level[1].idx, "spmm_coo", vec, X, N, ldx, Y, ldy, true);
+      panel_spmm(env, A, A.level[0].idx, nullptr, A.level[1].idx, "spmm_coo", X, N, ldx, Y, ldy, true);
       return env.status;
     }
     default: break;

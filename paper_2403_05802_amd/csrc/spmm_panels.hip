@@ -1,0 +1,412 @@
+// Y (+)= A X over entries grouped by row (row-major COO, CSR, DCSR, CISR-plus): equal shares of the entries, a panel of columns
+// of X at a time.
+#include "common.h"
+#include "device.h"
+#include "spmm_internal.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace us {
+
+// VEC columns in registers, and in memory, where rows may begin at any float
+template <int VEC> struct PanelVec {
+  typedef float reg __attribute__((ext_vector_type(VEC)));
+  typedef float mem __attribute__((ext_vector_type(VEC), aligned(4)));
+};
+template <> struct PanelVec<1> { typedef float reg; typedef float mem; };
+
+// lane K of every 16 lanes to all of them (all lanes must be active: a lane that is not reads as 0)
+template <int K>
+__device__ __forceinline__ int bcast16(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xf, 0xf, true); }
+template <int K>
+__device__ __forceinline__ float bcast16(float v) { return __builtin_bit_cast(float, bcast16<K>(__builtin_bit_cast(int, v))); }
+
+template <int K, int N, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+  if constexpr (K < N) { f(std::integral_constant<int, K>{}); static_for<K + 1, N>(static_cast<F &&>(f)); }
+}
+
+constexpr uint64_t FIRST16 = 0x0001000100010001ull;   // the first lane of every 16
+__device__ __forceinline__ uint64_t spread16(uint64_t firsts) { return (firsts << 16) - firsts; }   // ... to all 16
+
+// largest value so far across the wavefront (all lanes active)
+__device__ __forceinline__ uint32_t wave_inclusive_max_dpp(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, true));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, true));
+  return v;
+}
+
+constexpr int PS_WAVES = 8, PS_T = 64 * PS_WAVES, PS_GROUPS = 4 * PS_WAVES, PS_TILE = PS_T;
+static_assert(PS_GROUPS < 64, "bit masks over the groups of a workgroup");
+
+struct PanelJob {
+  const int32_t *row;      // COO: row of every entry, else null
+  const int32_t *ptr, *ids;// compressed rows: children of parent p are [ptr[p], ptr[p + 1]); row of a stored row, or null
+  const int2 *bounds;      // compressed rows: parents of the entries around every tile boundary (tile_bounds_kernel)
+  const int32_t *col;
+  const float *val;
+  uint32_t n;              // entries
+  const float *X; int64_t ldx;
+  float *Y; int64_t ldy;
+  uint32_t N;              // columns of this launch
+  int32_t *carry_row;      // null: another launch of the product writes them
+  float *carry; int64_t carry_ld;
+};
+
+// bounds[k] = parents of the last entry before tile k and of its first one, for all tiles side by side: a bisection over all
+// parents is 20 dependent loads
+__global__ __launch_bounds__(256) void tile_bounds_kernel(const int32_t *ptr, int64_t nparents, int64_t nnz, int64_t ntiles,
+                                                          int2 *bounds) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k > ntiles) return;
+  const int64_t e = min(k * PS_TILE, nnz);     // nnz > 0
+  const int64_t behind = parent_of(ptr, nparents, e < nnz ? e : nnz - 1);
+  int64_t before = behind;                     // the parent of e - 1: behind itself, or the last one before it with entries
+  if (e > 0 && e < nnz && (int64_t)ptr[behind] == e) before = parent_of(ptr, behind, e - 1);
+  bounds[k] = make_int2((int32_t)before, (int32_t)behind);
+}
+
+// A workgroup takes 512 consecutive entries and a panel of 16 * VEC * H columns, a wavefront 64 entries, sixteen lanes
+// ("a group") sixteen of them one after the other, VEC * H columns a lane.  So a load of one instruction brings pieces of four
+// rows of X, and column, value and row of an entry reach the lanes of their group as DPP operands (row_newbcast), not as LDS
+// traffic or scalars.  Sixteen loads are in flight before the first multiply-add; the rows of a tile's entries are looked up
+// behind them.
+//
+// What bounds it: the misses of the L2s.  They come over the fabric in 128-byte lines at 6.5 to 7.5 TB/s whether HBM or the
+// memory-side cache answers, hits at 23 to 27 TB/s (measured with bare gathers of 64 to 1024 bytes from spans of 2 MB to 1 GB;
+// pieces of 64 bytes cost as much as of 128).  So the columns go by panels, all entries for a panel, then for the next: in a
+// panel of 64 columns a row of X takes two lines instead of its whole length, and the entries in flight on an XCD (which walks a
+// contiguous range of tiles) find more rows with local columns again: 25.6 M entries of long rows, N = 128, 6 -> 27 % hits, 6.9 TB/s
+// of misses; 5.2 M, N = 1000, none -> 40 %.  The next bound is instruction issue (a wave64 instruction holds its SIMD for four
+// cycles): where a run ends is kept as scalar masks, rows and panels that need no bounds have none.
+//
+// us, one wavefront per 256 entries with whole rows of X (64 lanes across 64, 128 or 256 columns) -> this; 5.2 M entries of
+// 262,144 rows, local columns, N = 8 / 16 / 32 / 64 / 128 / 256 / 1000: 251 / 248 / 246 / 248 / 385 / 745 / 3010 -> 81 / 84 / 96 /
+// 154 / 277 / 535 / 2400; 40 M of 2 M rows, N = 16 / 64 / 128: 1560 / 1679 / 2732 -> 526 / 1205 / 2349; 10 M uniformly drawn,
+// N = 32 / 128 / 500: 424 / 808 / 3448 -> 222 / 750 / 3180; 400 k entries, N = 8 / 64 / 200 / 1000: 44 / 46 / 83 / 233 ->
+// 25 / 30 / 55 / 187; 60 k, N = 32 25 -> 21.  Tried and left: four wavefronts a workgroup (0 to 7 % slower), a persistent grid
+// that fetches the next tile's entries early (15 % slower), three workgroups per CU by spilling four registers (6 % slower),
+// less resident by LDS (no faster), X copied into panels of whole lines (no faster than wider panels, and a copy of X), and the
+// rows of 512 entries and more taken out, ordered by ranges of columns that an L2 holds and summed range by range (their hits
+// 27 -> 75 %, but what is left runs at 5.6 TB/s, and the lists and the sums cost what it gains: 2570 -> 2850 at N = 1000).
+template <int VEC, int H, bool FULL, bool WIDE, bool SEARCH, bool ADD>
+__global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel_spmm_kernel(PanelJob job) {
+  typedef typename PanelVec<VEC>::reg V;
+  typedef typename PanelVec<VEC>::mem M;
+  constexpr int PART = 16 * VEC, PW = PART * H, U = 16 / H;
+  __shared__ V s_head[PS_GROUPS][H][16];
+  __shared__ uint32_t s_starts[PS_GROUPS];
+  __shared__ uint32_t s_mark[SEARCH ? PS_TILE : 1], s_last[SEARCH ? PS_WAVES : 1];
+  const int lane = lane_id(), s = lane & 15, w = wave_id(), group = w * 4 + (lane >> 4);
+  const uint32_t n = job.n, ntiles = (n + PS_TILE - 1) / PS_TILE, per_xcd = (ntiles + 7) / 8;
+  const uint32_t tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), panel = blockIdx.y;
+  if (tile >= ntiles) return;
+  const uint32_t t0 = tile * PS_TILE, t1 = min(t0 + PS_TILE, n), e = t0 + threadIdx.x;
+  const bool live = e < t1;
+  const int32_t c = live ? __builtin_nontemporal_load(job.col + e) : 0;
+  const float v = live ? __builtin_nontemporal_load(job.val + e) : 0.f;
+  int32_t r = -1;
+  bool start = true, next_same;     // the entry is the first of its row; the row of the tile's last entry goes on behind it
+  int2 b0, b1;
+  if constexpr (SEARCH) {
+    s_mark[threadIdx.x] = 0;
+    b0 = job.bounds[tile]; b1 = job.bounds[tile + 1];
+    next_same = t1 < n && b1.x == b1.y;
+  } else {
+    if (live) r = job.row[e];
+    if (live && e > 0) start = job.row[e - 1] != r;
+    next_same = t1 < n && job.row[t1] == job.row[t1 - 1];
+  }
+  // first column of the lane in every part of the panel.  Not FULL: where the columns end inside the vector the lane takes the
+  // last VEC of them (N >= VEC): what it shares with the lane before it both compute, and store, alike
+  uint32_t c0[H];
+  uint64_t cols_ok[H];              // lanes with a column
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    c0[h] = panel * PW + h * PART + s * VEC;
+    cols_ok[h] = ~0ull;
+    if constexpr (!FULL) {
+      const bool ok = c0[h] < job.N;
+      cols_ok[h] = __ballot(ok);
+      c0[h] = ok ? min(c0[h], job.N - VEC) : 0;
+    }
+  }
+  // part h of the lane's columns in the row that begins `o` bytes into X or Y
+  auto at = [&](auto base, auto o, int h) {
+    if constexpr (FULL) return base + (o + c0[0] * 4u) + h * (PART * 4);
+    else return base + (o + c0[h] * 4u);
+  };
+  const uint64_t xoff = (uint64_t)(uint32_t)c * (uint64_t)job.ldx * 4u;
+  const int xlo = (int)(uint32_t)xoff, xhi = (int)(uint32_t)(xoff >> 32);
+  const char *Xp = reinterpret_cast<const char *>(job.X);
+  V x[16][H];
+  auto gather = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (WIDE) {
+      const uint64_t o = (uint64_t)(uint32_t)bcast16<k>(xhi) << 32 | (uint32_t)bcast16<k>(xlo);
+#pragma unroll
+      for (int h = 0; h < H; ++h) x[k][h] = *reinterpret_cast<const M *>(at(Xp, o, h));
+    } else {
+      const uint32_t o = (uint32_t)bcast16<k>(xlo);
+#pragma unroll
+      for (int h = 0; h < H; ++h) x[k][h] = *reinterpret_cast<const M *>(at(Xp, o, h));
+    }
+  };
+  static_for<0, U>(gather);
+  if constexpr (SEARCH) {
+    // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries);
+    // an entry's row is the last mark up to it
+    __syncthreads();
+    for (int32_t p = b0.x + 1 + (int32_t)threadIdx.x; p <= b1.x; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
+    __syncthreads();
+    const uint32_t mark = s_mark[threadIdx.x];
+    uint32_t last = wave_inclusive_max_dpp(mark);
+    if (lane == 63) s_last[w] = last;
+    __syncthreads();
+    last = max(last, (uint32_t)b0.x);
+#pragma unroll
+    for (int q = 0; q < PS_WAVES - 1; ++q)
+      if (q < w) last = max(last, s_last[q]);
+    if (live) { start = mark != 0 || e == 0; r = job.ids ? job.ids[last] : (int32_t)last; }
+  }
+  const uint64_t sm = __ballot(start), dead = __ballot(!live);
+  const uint64_t yoff = (uint64_t)(uint32_t)r * (uint64_t)job.ldy * 4u;
+  const int ylo = (int)(uint32_t)yoff, yhi = (int)(uint32_t)(yoff >> 32);
+  // where the row of entry K of the lane's 16 begins in Y, in bytes (all lanes take part)
+  auto y_of = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (WIDE) return (uint64_t)(uint32_t)bcast16<k>(yhi) << 32 | (uint32_t)bcast16<k>(ylo);
+    else return (uint32_t)bcast16<k>(ylo);
+  };
+  char *Yp = reinterpret_cast<char *>(job.Y);
+  uint64_t seen = spread16(sm & FIRST16);   // lanes whose run began among their own entries
+  V acc[H];
+#pragma unroll
+  for (int h = 0; h < H; ++h) acc[h] = V(0.f);
+  // the sums of the lanes in to[] to (ADD: onto) the rows of Y that begin at byte y; all is read before anything is written
+  auto put = [&](const uint64_t (&to)[H], auto y) {
+    V out[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      out[h] = acc[h];
+      if constexpr (ADD) {
+        if (__builtin_amdgcn_inverse_ballot_w64(to[h])) { const V old = *reinterpret_cast<const M *>(at(Yp, y, h)); out[h] = old + acc[h]; }
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      if (__builtin_amdgcn_inverse_ballot_w64(to[h])) *reinterpret_cast<M *>(at(Yp, y, h)) = out[h];
+  };
+  static_for<0, 16>([&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (k > 0) {
+      const uint64_t m = (sm >> k) & FIRST16;
+      if (m) {   // (scalar, like all masks here) some of the four runs end in front of entry k
+        const uint64_t lanes = spread16(m), head = lanes & ~seen, full = lanes & seen & ~spread16((dead >> (k - 1)) & FIRST16);
+        if (head) {
+          if (__builtin_amdgcn_inverse_ballot_w64(head)) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) s_head[group][h][s] = acc[h];
+          }
+        }
+        if (full) {
+          const auto y = y_of(std::integral_constant<int, k - 1>{});
+          uint64_t to[H];
+#pragma unroll
+          for (int h = 0; h < H; ++h) to[h] = full & cols_ok[h];
+          put(to, y);
+        }
+        if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
+#pragma unroll
+          for (int h = 0; h < H; ++h) acc[h] = V(0.f);
+        }
+        seen |= lanes;
+      }
+    }
+    const float t = bcast16<k>(v);
+#pragma unroll
+    for (int h = 0; h < H; ++h) acc[h] += t * x[k][h];
+    if constexpr (k + U < 16) gather(std::integral_constant<int, k + U>{});
+  });
+  const uint32_t starts = (uint32_t)(sm >> (lane & 48)) & 0xffffu;
+  if (starts == 0) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) s_head[group][h][s] = acc[h];
+  }
+  if (s == 0) s_starts[group] = starts;
+  const auto y_last = y_of(std::integral_constant<int, 15>{});
+  const int32_t r_last = bcast16<15>(r);
+  __syncthreads();
+  const uint32_t st = lane < PS_GROUPS ? s_starts[lane] : 1u;
+  const uint64_t some = __ballot(st != 0), fresh = __ballot((st & 1u) != 0);   // (bits from PS_GROUPS on are set)
+  float *carry_head = job.carry + (int64_t)tile * 2 * job.carry_ld, *carry_tail = carry_head + job.carry_ld;
+  auto heads = [&](int h, int j0, int end, V a) {   // a + s_head[j0 .. end), in this order
+    int j = j0;
+    for (; j + 4 <= end; j += 4) {
+      V t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = s_head[j + u][h][s];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) a += t[u];
+    }
+    for (; j < end; ++j) a += s_head[j][h][s];
+    return a;
+  };
+  // the group in which a run begins collects what later groups have of it; a run begins in front of the next group that is
+  // fresh, or inside the next one that has a start at all
+  auto run_end = [&](int j0) {
+    const int next = __builtin_ctzll(some >> j0) + j0;
+    return next >= PS_GROUPS ? PS_GROUPS : next + !(fresh >> next & 1);
+  };
+  bool cut = false;                  // the run of the group's last entry goes on behind the tile
+  if (starts != 0) {
+    const int j0 = group + 1;
+    if (!(fresh >> j0 & 1)) {
+      const int end = run_end(j0);
+#pragma unroll
+      for (int h = 0; h < H; ++h) acc[h] = heads(h, j0, end, acc[h]);
+    }
+    cut = next_same && __builtin_ctzll(some >> j0) + j0 >= PS_GROUPS;
+  }
+  {
+    const uint64_t full = __ballot(starts != 0 && !cut && r_last >= 0), part = __ballot(cut);
+    uint64_t to[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      to[h] = full & cols_ok[h];
+      if (__builtin_amdgcn_inverse_ballot_w64(part & cols_ok[h])) *reinterpret_cast<M *>(carry_tail + c0[h]) = acc[h];
+    }
+    put(to, y_last);
+  }
+  const bool head_cut = !(fresh & 1);   // the tile's first run began in an earlier one
+  const bool single = head_cut && __builtin_ctzll(some) >= PS_GROUPS;   // ... and is all that the tile holds
+  if (head_cut && group == 0) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      if (!__builtin_amdgcn_inverse_ballot_w64(cols_ok[h])) continue;
+      *reinterpret_cast<M *>(carry_head + c0[h]) = heads(h, 0, run_end(0), V(0.f));
+      if (single) *reinterpret_cast<M *>(carry_tail + c0[h]) = V(0.f);
+    }
+  }
+  if (job.carry_row && panel == 0 && s == 0) {
+    int32_t *cr = job.carry_row + (int64_t)tile * 2;
+    if (group == 0) cr[0] = head_cut ? r : -1;
+    if (single) { if (group == 0) cr[1] = r; }
+    else if (starts != 0 && __builtin_ctzll(some >> (group + 1)) + group + 1 >= PS_GROUPS) cr[1] = cut ? r_last : -1;   // the group in which the last run begins
+  }
+}
+
+// The pieces of rows that tile boundaries cut, in the order of the tiles (two slots a tile: reproducible).  A wavefront takes
+// the run of slots of a row, if it is the run's first, and 256 columns.
+__global__ __launch_bounds__(256) void panel_fixup_kernel(const int32_t *carry_row, const float *carry, int64_t carry_ld,
+                                                          int64_t nslots, int64_t N, float *Y, int64_t ldy, int add) {
+  const int lane = lane_id();
+  const int64_t e = (int64_t)blockIdx.x * 4 + wave_id();
+  if (e >= nslots) return;
+  const int32_t r = carry_row[e];
+  if (r < 0) return;
+  if (e > 0 && carry_row[e - 1] == r) return;   // (a run never skips a slot)
+  // length of the run, 64 slots per look (a 20,000-entry row leaves 80 pieces)
+  int64_t len = 0;
+  for (;;) {
+    const int64_t j = e + len + lane;
+    const uint64_t same = __ballot(j < nslots && carry_row[j] == r);
+    const int run = same == ~0ull ? 64 : __ffsll((unsigned long long)~same) - 1;
+    len += run;
+    if (run < 64) break;
+  }
+  for (int64_t cb = (int64_t)blockIdx.y * 256; cb < N; cb += (int64_t)gridDim.y * 256) {
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    const float *p[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) p[q] = carry + e * carry_ld + min(cb + q * 64 + lane, N - 1);
+    int64_t j = 0;
+    for (; j + 8 <= len; j += 8) {   // 32 independent loads in flight, added in the order of the pieces
+      float t[8][4];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t[u][q] = p[q][(j + u) * carry_ld];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] += t[u][q];
+    }
+    for (; j < len; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] += p[q][j * carry_ld];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t c = cb + q * 64 + lane;
+      if (c < N) {
+        float *yp = Y + (int64_t)r * ldy + c;
+        *yp = add ? *yp + s[q] : s[q];
+      }
+    }
+  }
+}
+
+// Columns per lane and part, and parts, of the panels for `cols` columns.  Up to 64 columns one panel just wide enough.  Rows of X
+// that begin at whole lines: 64, two lines a piece (262,144 rows, local columns, 5.2 M entries, N = 256, panels of 64 / 128 / 256:
+// 545 / 554 / 592 us, 40 M and N = 128 2371 / 2559 / 2677; uniform, N = 512 657 / 663 / 671).  Others: every piece of a row
+// touches a line more than it fills, so few and wide panels: N = 1000 2729 / 2468 / 2468, uniform, N = 500 4424 / 3740 / 3380;
+// N = 100, one panel of 128 instead of two of 64: 375 -> 272.
+struct PanelShape { int vec, parts; int width() const { return 16 * vec * parts; } };
+static PanelShape panel_shape(int64_t cols, bool whole_lines) {
+  if (cols <= 16) return {1, 1};
+  if (cols <= 32) return {2, 1};
+  if (cols <= 64 || whole_lines) return {4, 1};
+  return {4, cols <= 128 ? 2 : 4};
+}
+
+void panel_spmm(Env &env, const us_formatted &A, const int32_t *row, const StoredRows *rows, const int32_t *col, const char *name,
+                const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, bool add) {
+  const int64_t n = A.nnz, tiles = ceil_div<int64_t>(n, PS_TILE), carry_ld = ceil_div<int64_t>(N, 32) * 32;
+  const size_t b_bounds = rows ? Env::granule((tiles + 1) * sizeof(int2)) : 0, b_crow = Env::granule(tiles * 2 * sizeof(int32_t));
+  char *ws = (char *)ensure_workspace(env, A, b_bounds + b_crow + tiles * 2 * carry_ld * sizeof(float));
+  if (!env.ok()) return;
+  int2 *bounds = (int2 *)ws;
+  int32_t *carry_row = (int32_t *)(ws + b_bounds);
+  float *carry = (float *)(ws + b_bounds + b_crow);
+  if (rows)
+    US_LAUNCH(env, "spmm_bounds", 8.0 * tiles, tile_bounds_kernel, ceil_div<int64_t>(tiles + 1, 256), 256, rows->ptr, A.nmajor, n,
+              tiles, bounds);
+  const bool wide = (double)A.ncols * ldx * 4 >= 4294967296.0 || (double)A.nrows * ldy * 4 >= 4294967296.0;
+  const bool whole_lines = (uintptr_t)X % 128 == 0 && ldx % 32 == 0;
+  for (int64_t c = 0; c < N && env.ok();) {   // whole panels first, then what is left in one of the width that fits it
+    const PanelShape shape = panel_shape(N - c, whole_lines);
+    const int64_t pw = shape.width(), npanels = std::min<int64_t>(std::max<int64_t>((N - c) / pw, 1), 65535), cols = std::min(npanels * pw, N - c);
+    PanelJob job{row, rows ? rows->ptr : nullptr, rows ? rows->row_ids : nullptr, bounds, col, (const float *)A.val, (uint32_t)n,
+                 X + c, ldx, Y + c, ldy, (uint32_t)cols, c == 0 ? carry_row : nullptr, carry + c, carry_ld};
+    const dim3 grid((unsigned)(ceil_div<int64_t>(tiles, 8) * 8), (unsigned)npanels);
+    LaunchScope ls(env, name, 12.0 * n + 4.0 * cols * (A.ncols + A.nrows));
+    const bool full = cols % pw == 0;
+#define US_PS_LAUNCH4(V, H, F, W, S, A) hipLaunchKernelGGL((panel_spmm_kernel<V, H, F, W, S, A>), grid, dim3(PS_T), 0, env.stream, job)
+#define US_PS_LAUNCH3(V, H, F, W, S) do { if (add) US_PS_LAUNCH4(V, H, F, W, S, true); else US_PS_LAUNCH4(V, H, F, W, S, false); } while (0)
+#define US_PS_LAUNCH2(V, H, F, W) do { if (rows) US_PS_LAUNCH3(V, H, F, W, true); else US_PS_LAUNCH3(V, H, F, W, false); } while (0)
+#define US_PS_LAUNCH(V, H) do { if (wide) US_PS_LAUNCH2(V, H, false, true); else if (full) US_PS_LAUNCH2(V, H, true, false); else US_PS_LAUNCH2(V, H, false, false); } while (0)
+    if (shape.vec == 1) US_PS_LAUNCH(1, 1);
+    else if (shape.vec == 2) US_PS_LAUNCH(2, 1);
+    else if (shape.parts == 1) US_PS_LAUNCH(4, 1);
+    else if (shape.parts == 2) US_PS_LAUNCH(4, 2);
+    else US_PS_LAUNCH(4, 4);
+#undef US_PS_LAUNCH
+#undef US_PS_LAUNCH2
+#undef US_PS_LAUNCH3
+#undef US_PS_LAUNCH4
+    env.check(hipGetLastError());
+    c += cols;
+  }
+  if (!env.ok()) return;
+  LaunchScope ls(env, "spmm_rows_fixup", 8.0 * tiles);
+  hipLaunchKernelGGL(panel_fixup_kernel, dim3((unsigned)ceil_div<int64_t>(tiles * 2, 4), (unsigned)std::min<int64_t>(ceil_div<int64_t>(N, 256), 65535)),
+                     dim3(256), 0, env.stream, (const int32_t *)carry_row, (const float *)carry, carry_ld, tiles * 2, N, Y, ldy, add ? 1 : 0);
+  env.check(hipGetLastError());
+}
+
+}  // namespace us

@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256) void bcsr_spmm_kernel(const int32_t *ptr, cons
 // ------------------------------------------------------------------ row-grouped layouts, one wavefront per (row, 64 columns)
 // A lane owns VEC consecutive columns (VEC = 2 covers N = 128 with one wavefront per row).
 
-// ELL: a wavefront owns 8 consecutive rows.  One coalesced load brings the column indices and values
+// ELL, many columns (fewer: spmm_panels.hip): a wavefront owns 8 consecutive rows.  One coalesced load brings the column indices and values
 // of 8 slots x 8 rows (lane = slot*8 + row); they are handed out by v_readlane, i.e. as scalars, so
 // the address of a gathered row is scalar arithmetic plus a fixed per-lane offset, the gather of a pad
 // slot is skipped by a scalar branch (two thirds of the slots of a percentile-wide slab are pads; its
@@ -688,7 +688,13 @@ us_status spmm_impl(Env &env, const us_formatted &A, const float *X, int64_t N, 
       }
       return env.status;
     case P_ELL:
-      if (env.ok()) {
+      // From 256 columns on, loads of a kilobyte (four columns a lane) and 8 rows a wavefront are as quick as panels (400,000 rows, 25
+      // slots, N = 256 / 500 / 1000: 446 / 1005 / 1914 us, panels of 128 columns 440 / 1018 / -; 100,000 rows of 4, N = 700 139 / 161);
+      // with one or two columns a lane only where there are few rows (3,000 rows, N = 333 / 777: 15 / 21, panels 23 / 27; 30,000 rows:
+      // 211 / 423, panels 179 / 343; 250,000: 898 / 1955, 681 / 1534).
+      if (N < 256 || (vec != 4 && A.nrows >= 1 << 14)) {
+        panel_ell_spmm(env, A, X, N, ldx, Y, ldy, accumulate);
+      } else if (env.ok()) {
         LaunchScope ls(env, "spmm_ell", 8.0 * A.nval + xy);
         const int64_t tiles = ceil_div<int64_t>(A.nrows, 32), per_xcd = ceil_div<int64_t>(tiles, 8);
         const dim3 grid((unsigned)(per_xcd * 8), (unsigned)ceil_div<int64_t>(N, 64 * vec));

@@ -9,4 +9,7 @@ namespace us {
 void panel_spmm(Env &env, const us_formatted &A, const int32_t *row, const StoredRows *rows, const int32_t *col, const char *name,
                 const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, bool add);
 
+// ELL: all rows are stored (add: added to)
+void panel_ell_spmm(Env &env, const us_formatted &A, const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, bool add);
+
 }  // namespace us

@@ -1,5 +1,5 @@
-// Y (+)= A X over entries grouped by row (row-major COO, CSR, DCSR, CISR-plus): equal shares of the entries, a panel of columns
-// of X at a time.
+// Y (+)= A X, a panel of columns of X at a time: over entries grouped by row (row-major COO, CSR, DCSR, CISR-plus) in equal shares
+// of the entries, and over the rows of an ELL slab.
 #include "common.h"
 #include "device.h"
 #include "spmm_internal.h"
@@ -43,6 +43,147 @@ __device__ __forceinline__ uint32_t wave_inclusive_max_dpp(uint32_t v) {
 
 constexpr int PS_WAVES = 8, PS_T = 64 * PS_WAVES, PS_GROUPS = 4 * PS_WAVES, PS_TILE = PS_T;
 static_assert(PS_GROUPS < 64, "bit masks over the groups of a workgroup");
+
+// Sixteen lanes ("a group") take sixteen consecutive entries, one after the other, a lane VEC * H columns of a panel: H parts of
+// 16 * VEC columns.  FULL: the panel has all its columns.  WIDE: X or Y has 4 GB or more.  U: rows of X in flight.
+template <int VEC, int H, bool FULL, bool WIDE, int U>
+struct PanelWalk {
+  typedef typename PanelVec<VEC>::reg V;
+  typedef typename PanelVec<VEC>::mem M;
+  static constexpr int PART = 16 * VEC, PW = PART * H;
+  // first column of the lane in every part of the panel.  Not FULL: where the columns end inside the vector the lane takes the
+  // last VEC of them (N >= VEC): what it shares with the lane before it both compute, and store, alike
+  uint32_t c0[H];
+  uint64_t cols_ok[H];              // lanes with a column
+  V x[16][H], acc[H];
+
+  __device__ __forceinline__ void columns(uint32_t panel, uint32_t N, int s) {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      c0[h] = panel * PW + h * PART + s * VEC;
+      cols_ok[h] = ~0ull;
+      if constexpr (!FULL) {
+        const bool ok = c0[h] < N;
+        cols_ok[h] = __ballot(ok);
+        c0[h] = ok ? min(c0[h], N - VEC) : 0;
+      }
+    }
+  }
+  // part h of the lane's columns in the row that begins `o` bytes into X or Y
+  template <typename T, typename O>
+  __device__ __forceinline__ T *at(T *base, O o, int h) const {
+    if constexpr (FULL) return base + (o + c0[0] * 4u) + h * (PART * 4);
+    else return base + (o + c0[h] * 4u);
+  }
+  // bytes from a row's number to where it begins, and from the lane of entry K to all of its group (all lanes take part)
+  struct Offset { int lo, hi; };
+  static __device__ __forceinline__ Offset offset(int32_t row, int64_t ld) {
+    const uint64_t o = (uint64_t)(uint32_t)row * (uint64_t)ld * 4u;
+    return {(int)(uint32_t)o, (int)(uint32_t)(o >> 32)};
+  }
+  template <int K>
+  static __device__ __forceinline__ auto of(const Offset &o) {
+    if constexpr (WIDE) return (uint64_t)(uint32_t)bcast16<K>(o.hi) << 32 | (uint32_t)bcast16<K>(o.lo);
+    else return (uint32_t)bcast16<K>(o.lo);
+  }
+  template <int K>
+  __device__ __forceinline__ void gather(const char *X, const Offset &xo) {
+    const auto o = of<K>(xo);
+#pragma unroll
+    for (int h = 0; h < H; ++h) x[K][h] = *reinterpret_cast<const M *>(at(X, o, h));
+  }
+  __device__ __forceinline__ void first_gathers(const char *X, const Offset &xo) {
+    static_for<0, U>([&](auto kc) { gather<decltype(kc)::value>(X, xo); });
+  }
+  // the sums of the lanes in to[] to (add: onto) the rows of Y that begin at byte y; all is read before anything is written
+  template <typename O>
+  __device__ __forceinline__ void put(char *Y, O y, const uint64_t (&to)[H], bool add) const {
+    V out[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      out[h] = acc[h];
+      if (add) {
+        if (__builtin_amdgcn_inverse_ballot_w64(to[h])) { const V old = *reinterpret_cast<const M *>(at(Y, y, h)); out[h] = old + acc[h]; }
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      if (__builtin_amdgcn_inverse_ballot_w64(to[h])) *reinterpret_cast<M *>(at(Y, y, h)) = out[h];
+  }
+  // All entries of the group: sm = lanes whose entry is the first of its row, dead = lanes without an entry.  Sums of rows that
+  // begin and end among them go to Y; the part of a row that began before them to s_head[group]; what begins and is still open
+  // at their end stays in acc.
+  __device__ __forceinline__ void walk(const char *X, const Offset &xo, float v, uint64_t sm, uint64_t dead, char *Y, const Offset &yo,
+                                       bool add, V (*s_head)[16], int s) {
+    uint64_t seen = spread16(sm & FIRST16);   // lanes whose run began among their own entries
+#pragma unroll
+    for (int h = 0; h < H; ++h) acc[h] = V(0.f);
+    static_for<0, 16>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      if constexpr (k > 0) {
+        const uint64_t m = (sm >> k) & FIRST16;
+        if (m) {   // (scalar, like all masks here) some of the four runs end in front of entry k
+          const uint64_t lanes = spread16(m), head = lanes & ~seen, full = lanes & seen & ~spread16((dead >> (k - 1)) & FIRST16);
+          if (head) {
+            if (__builtin_amdgcn_inverse_ballot_w64(head)) {
+#pragma unroll
+              for (int h = 0; h < H; ++h) s_head[h][s] = acc[h];
+            }
+          }
+          if (full) {
+            const auto y = of<k - 1>(yo);
+            uint64_t to[H];
+#pragma unroll
+            for (int h = 0; h < H; ++h) to[h] = full & cols_ok[h];
+            put(Y, y, to, add);
+          }
+          if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) acc[h] = V(0.f);
+          }
+          seen |= lanes;
+        }
+      }
+      const float t = bcast16<k>(v);
+#pragma unroll
+      for (int h = 0; h < H; ++h) acc[h] += t * x[k][h];
+      if constexpr (k + U < 16) gather<k + U>(X, xo);
+    });
+    if (((uint32_t)(sm >> (lane_id() & 48)) & 0xffffu) == 0) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) s_head[h][s] = acc[h];
+    }
+  }
+};
+
+// a + s_head[j0 .. end)[h][s], in this order
+template <int H, typename V>
+__device__ __forceinline__ V panel_heads(const V (*s_head)[H][16], int h, int s, int j0, int end, V a) {
+  int j = j0;
+  for (; j + 4 <= end; j += 4) {
+    V t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = s_head[j + u][h][s];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a += t[u];
+  }
+  for (; j < end; ++j) a += s_head[j][h][s];
+  return a;
+}
+// The groups of a workgroup as masks: `some` have a first entry of a row at all, `fresh` begin with one (bits from PS_GROUPS on
+// set).  A run that is open in front of group j0 ends before the next group that is fresh, or inside the next that has a start.
+struct PanelRuns {
+  uint64_t some, fresh;
+  __device__ __forceinline__ int next(int j0) const { return __builtin_ctzll(some >> j0) + j0; }
+  __device__ __forceinline__ int end(int j0) const {
+    const int k = next(j0);
+    return k >= PS_GROUPS ? PS_GROUPS : k + !(fresh >> k & 1);
+  }
+};
+__device__ __forceinline__ PanelRuns panel_runs(const uint32_t *s_starts) {
+  const uint32_t st = lane_id() < PS_GROUPS ? s_starts[lane_id()] : 1u;
+  return {__ballot(st != 0), __ballot((st & 1u) != 0)};
+}
 
 struct PanelJob {
   const int32_t *row;      // COO: row of every entry, else null
@@ -96,15 +237,15 @@ __global__ __launch_bounds__(256) void tile_bounds_kernel(const int32_t *ptr, in
 // 27 -> 75 %, but what is left runs at 5.6 TB/s, and the lists and the sums cost what it gains: 2570 -> 2850 at N = 1000).
 template <int VEC, int H, bool FULL, bool WIDE, bool SEARCH, bool ADD>
 __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel_spmm_kernel(PanelJob job) {
-  typedef typename PanelVec<VEC>::reg V;
-  typedef typename PanelVec<VEC>::mem M;
-  constexpr int PART = 16 * VEC, PW = PART * H, U = 16 / H;
+  typedef PanelWalk<VEC, H, FULL, WIDE, 16 / H> Walk;
+  typedef typename Walk::V V;
+  typedef typename Walk::M M;
   __shared__ V s_head[PS_GROUPS][H][16];
   __shared__ uint32_t s_starts[PS_GROUPS];
   __shared__ uint32_t s_mark[SEARCH ? PS_TILE : 1], s_last[SEARCH ? PS_WAVES : 1];
   const int lane = lane_id(), s = lane & 15, w = wave_id(), group = w * 4 + (lane >> 4);
   const uint32_t n = job.n, ntiles = (n + PS_TILE - 1) / PS_TILE, per_xcd = (ntiles + 7) / 8;
-  const uint32_t tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3), panel = blockIdx.y;
+  const uint32_t tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
   if (tile >= ntiles) return;
   const uint32_t t0 = tile * PS_TILE, t1 = min(t0 + PS_TILE, n), e = t0 + threadIdx.x;
   const bool live = e < t1;
@@ -122,42 +263,12 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
     if (live && e > 0) start = job.row[e - 1] != r;
     next_same = t1 < n && job.row[t1] == job.row[t1 - 1];
   }
-  // first column of the lane in every part of the panel.  Not FULL: where the columns end inside the vector the lane takes the
-  // last VEC of them (N >= VEC): what it shares with the lane before it both compute, and store, alike
-  uint32_t c0[H];
-  uint64_t cols_ok[H];              // lanes with a column
-#pragma unroll
-  for (int h = 0; h < H; ++h) {
-    c0[h] = panel * PW + h * PART + s * VEC;
-    cols_ok[h] = ~0ull;
-    if constexpr (!FULL) {
-      const bool ok = c0[h] < job.N;
-      cols_ok[h] = __ballot(ok);
-      c0[h] = ok ? min(c0[h], job.N - VEC) : 0;
-    }
-  }
-  // part h of the lane's columns in the row that begins `o` bytes into X or Y
-  auto at = [&](auto base, auto o, int h) {
-    if constexpr (FULL) return base + (o + c0[0] * 4u) + h * (PART * 4);
-    else return base + (o + c0[h] * 4u);
-  };
-  const uint64_t xoff = (uint64_t)(uint32_t)c * (uint64_t)job.ldx * 4u;
-  const int xlo = (int)(uint32_t)xoff, xhi = (int)(uint32_t)(xoff >> 32);
-  const char *Xp = reinterpret_cast<const char *>(job.X);
-  V x[16][H];
-  auto gather = [&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    if constexpr (WIDE) {
-      const uint64_t o = (uint64_t)(uint32_t)bcast16<k>(xhi) << 32 | (uint32_t)bcast16<k>(xlo);
-#pragma unroll
-      for (int h = 0; h < H; ++h) x[k][h] = *reinterpret_cast<const M *>(at(Xp, o, h));
-    } else {
-      const uint32_t o = (uint32_t)bcast16<k>(xlo);
-#pragma unroll
-      for (int h = 0; h < H; ++h) x[k][h] = *reinterpret_cast<const M *>(at(Xp, o, h));
-    }
-  };
-  static_for<0, U>(gather);
+  Walk walk;
+  walk.columns(blockIdx.y, job.N, s);
+  const char *X = reinterpret_cast<const char *>(job.X);
+  char *Y = reinterpret_cast<char *>(job.Y);
+  const auto xo = Walk::offset(c, job.ldx);
+  walk.first_gathers(X, xo);
   if constexpr (SEARCH) {
     // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries);
     // an entry's row is the last mark up to it
@@ -175,129 +286,45 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
     if (live) { start = mark != 0 || e == 0; r = job.ids ? job.ids[last] : (int32_t)last; }
   }
   const uint64_t sm = __ballot(start), dead = __ballot(!live);
-  const uint64_t yoff = (uint64_t)(uint32_t)r * (uint64_t)job.ldy * 4u;
-  const int ylo = (int)(uint32_t)yoff, yhi = (int)(uint32_t)(yoff >> 32);
-  // where the row of entry K of the lane's 16 begins in Y, in bytes (all lanes take part)
-  auto y_of = [&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    if constexpr (WIDE) return (uint64_t)(uint32_t)bcast16<k>(yhi) << 32 | (uint32_t)bcast16<k>(ylo);
-    else return (uint32_t)bcast16<k>(ylo);
-  };
-  char *Yp = reinterpret_cast<char *>(job.Y);
-  uint64_t seen = spread16(sm & FIRST16);   // lanes whose run began among their own entries
-  V acc[H];
-#pragma unroll
-  for (int h = 0; h < H; ++h) acc[h] = V(0.f);
-  // the sums of the lanes in to[] to (ADD: onto) the rows of Y that begin at byte y; all is read before anything is written
-  auto put = [&](const uint64_t (&to)[H], auto y) {
-    V out[H];
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-      out[h] = acc[h];
-      if constexpr (ADD) {
-        if (__builtin_amdgcn_inverse_ballot_w64(to[h])) { const V old = *reinterpret_cast<const M *>(at(Yp, y, h)); out[h] = old + acc[h]; }
-      }
-    }
-#pragma unroll
-    for (int h = 0; h < H; ++h)
-      if (__builtin_amdgcn_inverse_ballot_w64(to[h])) *reinterpret_cast<M *>(at(Yp, y, h)) = out[h];
-  };
-  static_for<0, 16>([&](auto kc) {
-    constexpr int k = decltype(kc)::value;
-    if constexpr (k > 0) {
-      const uint64_t m = (sm >> k) & FIRST16;
-      if (m) {   // (scalar, like all masks here) some of the four runs end in front of entry k
-        const uint64_t lanes = spread16(m), head = lanes & ~seen, full = lanes & seen & ~spread16((dead >> (k - 1)) & FIRST16);
-        if (head) {
-          if (__builtin_amdgcn_inverse_ballot_w64(head)) {
-#pragma unroll
-            for (int h = 0; h < H; ++h) s_head[group][h][s] = acc[h];
-          }
-        }
-        if (full) {
-          const auto y = y_of(std::integral_constant<int, k - 1>{});
-          uint64_t to[H];
-#pragma unroll
-          for (int h = 0; h < H; ++h) to[h] = full & cols_ok[h];
-          put(to, y);
-        }
-        if (__builtin_amdgcn_inverse_ballot_w64(lanes)) {
-#pragma unroll
-          for (int h = 0; h < H; ++h) acc[h] = V(0.f);
-        }
-        seen |= lanes;
-      }
-    }
-    const float t = bcast16<k>(v);
-#pragma unroll
-    for (int h = 0; h < H; ++h) acc[h] += t * x[k][h];
-    if constexpr (k + U < 16) gather(std::integral_constant<int, k + U>{});
-  });
+  const auto yo = Walk::offset(r, job.ldy);
+  walk.walk(X, xo, v, sm, dead, Y, yo, ADD, s_head[group], s);
   const uint32_t starts = (uint32_t)(sm >> (lane & 48)) & 0xffffu;
-  if (starts == 0) {
-#pragma unroll
-    for (int h = 0; h < H; ++h) s_head[group][h][s] = acc[h];
-  }
   if (s == 0) s_starts[group] = starts;
-  const auto y_last = y_of(std::integral_constant<int, 15>{});
+  const auto y_last = Walk::template of<15>(yo);
   const int32_t r_last = bcast16<15>(r);
   __syncthreads();
-  const uint32_t st = lane < PS_GROUPS ? s_starts[lane] : 1u;
-  const uint64_t some = __ballot(st != 0), fresh = __ballot((st & 1u) != 0);   // (bits from PS_GROUPS on are set)
+  const PanelRuns runs = panel_runs(s_starts);
   float *carry_head = job.carry + (int64_t)tile * 2 * job.carry_ld, *carry_tail = carry_head + job.carry_ld;
-  auto heads = [&](int h, int j0, int end, V a) {   // a + s_head[j0 .. end), in this order
-    int j = j0;
-    for (; j + 4 <= end; j += 4) {
-      V t[4];
+  // the group in which a run begins collects what later groups have of it
+  const bool cut = starts != 0 && next_same && runs.next(group + 1) >= PS_GROUPS;   // the run goes on behind the tile
+  if (starts != 0 && !(runs.fresh >> (group + 1) & 1)) {
+    const int end = runs.end(group + 1);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) t[u] = s_head[j + u][h][s];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) a += t[u];
-    }
-    for (; j < end; ++j) a += s_head[j][h][s];
-    return a;
-  };
-  // the group in which a run begins collects what later groups have of it; a run begins in front of the next group that is
-  // fresh, or inside the next one that has a start at all
-  auto run_end = [&](int j0) {
-    const int next = __builtin_ctzll(some >> j0) + j0;
-    return next >= PS_GROUPS ? PS_GROUPS : next + !(fresh >> next & 1);
-  };
-  bool cut = false;                  // the run of the group's last entry goes on behind the tile
-  if (starts != 0) {
-    const int j0 = group + 1;
-    if (!(fresh >> j0 & 1)) {
-      const int end = run_end(j0);
-#pragma unroll
-      for (int h = 0; h < H; ++h) acc[h] = heads(h, j0, end, acc[h]);
-    }
-    cut = next_same && __builtin_ctzll(some >> j0) + j0 >= PS_GROUPS;
+    for (int h = 0; h < H; ++h) walk.acc[h] = panel_heads<H>(s_head, h, s, group + 1, end, walk.acc[h]);
   }
-  {
-    const uint64_t full = __ballot(starts != 0 && !cut && r_last >= 0), part = __ballot(cut);
-    uint64_t to[H];
+  const uint64_t full = __ballot(starts != 0 && !cut && r_last >= 0), part = __ballot(cut);
+  uint64_t to[H];
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-      to[h] = full & cols_ok[h];
-      if (__builtin_amdgcn_inverse_ballot_w64(part & cols_ok[h])) *reinterpret_cast<M *>(carry_tail + c0[h]) = acc[h];
-    }
-    put(to, y_last);
+  for (int h = 0; h < H; ++h) {
+    to[h] = full & walk.cols_ok[h];
+    if (__builtin_amdgcn_inverse_ballot_w64(part & walk.cols_ok[h])) *reinterpret_cast<M *>(carry_tail + walk.c0[h]) = walk.acc[h];
   }
-  const bool head_cut = !(fresh & 1);   // the tile's first run began in an earlier one
-  const bool single = head_cut && __builtin_ctzll(some) >= PS_GROUPS;   // ... and is all that the tile holds
+  walk.put(Y, y_last, to, ADD);
+  const bool head_cut = !(runs.fresh & 1);   // the tile's first run began in an earlier one
+  const bool single = head_cut && runs.next(0) >= PS_GROUPS;   // ... and is all that the tile holds
   if (head_cut && group == 0) {
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-      if (!__builtin_amdgcn_inverse_ballot_w64(cols_ok[h])) continue;
-      *reinterpret_cast<M *>(carry_head + c0[h]) = heads(h, 0, run_end(0), V(0.f));
-      if (single) *reinterpret_cast<M *>(carry_tail + c0[h]) = V(0.f);
+      if (!__builtin_amdgcn_inverse_ballot_w64(walk.cols_ok[h])) continue;
+      *reinterpret_cast<M *>(carry_head + walk.c0[h]) = panel_heads<H>(s_head, h, s, 0, runs.end(0), V(0.f));
+      if (single) *reinterpret_cast<M *>(carry_tail + walk.c0[h]) = V(0.f);
     }
   }
-  if (job.carry_row && panel == 0 && s == 0) {
+  if (job.carry_row && blockIdx.y == 0 && s == 0) {
     int32_t *cr = job.carry_row + (int64_t)tile * 2;
     if (group == 0) cr[0] = head_cut ? r : -1;
     if (single) { if (group == 0) cr[1] = r; }
-    else if (starts != 0 && __builtin_ctzll(some >> (group + 1)) + group + 1 >= PS_GROUPS) cr[1] = cut ? r_last : -1;   // the group in which the last run begins
+    else if (starts != 0 && runs.next(group + 1) >= PS_GROUPS) cr[1] = cut ? r_last : -1;   // the group in which the last run begins
   }
 }
 
@@ -349,6 +376,111 @@ __global__ __launch_bounds__(256) void panel_fixup_kernel(const int32_t *carry_r
       }
     }
   }
+}
+
+// ------------------------------------------------------------------ ELL
+struct EllJob {
+  const int32_t *col;
+  const float *val;
+  int64_t K, nrows;
+  const float *X; int64_t ldx;
+  float *Y; int64_t ldy;
+  uint32_t N;
+  int add;
+  int64_t per_xcd;
+};
+
+// The lane groups of the kernel above over a slab: a group takes R rows and 16 / R slots of them at a time (one load of columns
+// and one of values a lane, the next ones fetched early), so that a load brings pieces of four rows of X; where all four slots are
+// pads it is jumped over by a scalar branch, where some are their lanes stay away.  Rows are whole: no pieces, no carries.  Bound by
+// the misses of the L2s as well (N = 128: 49 M lines of 128 bytes, 5.9 TB/s), below 64 columns by the slab, which is pads to two
+// thirds.  us, 8 rows a wavefront and one row of X a load -> this: 2 M rows of up to 20 slots, N = 1 / 16 / 33 / 64 / 72 / 128 459 / 471 /
+// 542 / 614 / 1268 / 1005 -> 266 / 266 / 424 / 480 / 765 / 967; 250,000 rows of up to 42, N = 8 / 64 / 100 / 250 134 / 150 / 303 / 563 ->
+// 82 / 116 / 200 / 448; 30,000 of up to 80, N = 4 / 64 57 / 63 -> 34 / 42; 3,000 of up to 20, N = 8 / 64 12 / 15 -> 10 / 11.  Measured
+// and left: R = 2 (N = 16 319, N = 64 542), 8 (283, 532), 16 (287, 542, and 30,000 rows N = 64 119); the live slots of 64 to 512 rows put
+// together in LDS and taken like a list (N = 16 469, N = 64 1462: a chain of barriers, and spills).
+template <int VEC, int H, int R, bool FULL, bool WIDE>
+__global__ __launch_bounds__(256) void ell_panel_kernel(EllJob job) {
+  typedef PanelWalk<VEC, H, FULL, WIDE, 16 / H> Walk;
+  typedef typename Walk::V V;
+  typedef typename Walk::M M;
+  constexpr int B = 16 / H, S = 16 / R;   // entries in flight; slots that a group takes together
+  const int lane = lane_id(), s = lane & 15;
+  const int64_t i0 = (((int64_t)(blockIdx.x & 7) * job.per_xcd + (blockIdx.x >> 3)) * 4 + wave_id()) * (4 * R);
+  if (i0 >= job.nrows) return;
+  Walk walk;
+  walk.columns(blockIdx.y, job.N, s);
+  const char *X = reinterpret_cast<const char *>(job.X);
+  char *Y = reinterpret_cast<char *>(job.Y);
+  const int64_t row0 = i0 + (lane >> 4) * R, i = row0 + (s & (R - 1));
+  const bool mine = i < job.nrows;
+  int64_t k = s / R;
+  const int32_t *cp = job.col + k * job.nrows + i;
+  const float *vp = job.val + k * job.nrows + i;
+  V acc[R][H];
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+#pragma unroll
+    for (int h = 0; h < H; ++h) acc[q][h] = V(0.f);
+  int32_t c = mine && k < job.K ? __builtin_nontemporal_load(cp) : -1;
+  float v = mine && k < job.K ? __builtin_nontemporal_load(vp) : 0.f;
+  for (;;) {
+    const uint64_t live = __ballot(c >= 0);
+    if (live == 0) break;   // slots fill from the front
+    k += S;
+    cp += S * job.nrows; vp += S * job.nrows;
+    const bool more = mine && k < job.K;
+    const int32_t nc = more ? __builtin_nontemporal_load(cp) : -1;
+    const float nv = more ? __builtin_nontemporal_load(vp) : 0.f;
+    const auto xo = Walk::offset(c, job.ldx);
+    static_for<0, H>([&](auto bc) {
+      constexpr int q0 = decltype(bc)::value * B;
+      V x[B][H];
+      static_for<q0, q0 + B>([&](auto kc) {
+        constexpr int q = decltype(kc)::value;
+        const uint64_t m = (live >> q) & FIRST16;
+        if (m) {
+          const auto o = Walk::template of<q>(xo);
+          if (__builtin_amdgcn_inverse_ballot_w64(spread16(m))) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) x[q - q0][h] = *reinterpret_cast<const M *>(walk.at(X, o, h));
+          }
+        }
+      });
+      static_for<q0, q0 + B>([&](auto kc) {
+        constexpr int q = decltype(kc)::value;
+        const uint64_t m = (live >> q) & FIRST16;
+        if (m) {
+          const float t = bcast16<q>(v);
+          if (__builtin_amdgcn_inverse_ballot_w64(spread16(m))) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) acc[q & (R - 1)][h] += t * x[q - q0][h];
+          }
+        }
+      });
+    });
+    c = nc; v = nv;
+  }
+  char *yp = Y + (uint64_t)row0 * (uint64_t)job.ldy * 4u;
+  if (job.add) {   // (all is read before anything is written)
+    V old[R][H];
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
+        old[q][h] = V(0.f);
+        if ((walk.cols_ok[h] >> lane & 1) && row0 + q < job.nrows) old[q][h] = *reinterpret_cast<const M *>(yp + q * job.ldy * 4 + walk.c0[h] * 4u);
+      }
+#pragma unroll
+    for (int q = 0; q < R; ++q)
+#pragma unroll
+      for (int h = 0; h < H; ++h) acc[q][h] = old[q][h] + acc[q][h];
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q)
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+      if ((walk.cols_ok[h] >> lane & 1) && row0 + q < job.nrows) *reinterpret_cast<M *>(yp + q * job.ldy * 4 + walk.c0[h] * 4u) = acc[q][h];
 }
 
 // Columns per lane and part, and parts, of the panels for `cols` columns.  Up to 64 columns one panel just wide enough.  Rows of X
@@ -407,6 +539,33 @@ void panel_spmm(Env &env, const us_formatted &A, const int32_t *row, const Store
   hipLaunchKernelGGL(panel_fixup_kernel, dim3((unsigned)ceil_div<int64_t>(tiles * 2, 4), (unsigned)std::min<int64_t>(ceil_div<int64_t>(N, 256), 65535)),
                      dim3(256), 0, env.stream, (const int32_t *)carry_row, (const float *)carry, carry_ld, tiles * 2, N, Y, ldy, add ? 1 : 0);
   env.check(hipGetLastError());
+}
+
+// Up to 64 columns one panel just wide enough, up to 128 one of 128, up to 256 one of 256 (with half as many rows a wavefront: the
+// sums are in registers), beyond that panels of 128 and one for the rest.
+void panel_ell_spmm(Env &env, const us_formatted &A, const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, bool add) {
+  const bool wide = (double)A.ncols * ldx * 4 >= 4294967296.0 || (double)A.nrows * ldy * 4 >= 4294967296.0;
+  for (int64_t c = 0; c < N && env.ok();) {
+    PanelShape shape = panel_shape(N - c, false);
+    if (N > 256 && shape.parts == 4) shape.parts = 2;
+    const int64_t pw = shape.width(), npanels = std::min<int64_t>(std::max<int64_t>((N - c) / pw, 1), 65535), cols = std::min(npanels * pw, N - c);
+    const int64_t per_xcd = ceil_div<int64_t>(A.nrows, 8 * 16 * (shape.parts == 4 ? 2 : 4));
+    const EllJob job{A.level[2].idx, (const float *)A.val, A.nmajor, A.nrows, X + c, ldx, Y + c, ldy, (uint32_t)cols, add ? 1 : 0, per_xcd};
+    const dim3 grid((unsigned)(per_xcd * 8), (unsigned)npanels);
+    const bool full = cols % pw == 0;
+    LaunchScope ls(env, "spmm_ell", 8.0 * A.nval + 4.0 * cols * (A.ncols + A.nrows));
+#define US_EP_LAUNCH2(V, H, R, F, W) hipLaunchKernelGGL((ell_panel_kernel<V, H, R, F, W>), grid, dim3(256), 0, env.stream, job)
+#define US_EP_LAUNCH(V, H, R) do { if (wide) US_EP_LAUNCH2(V, H, R, false, true); else if (full) US_EP_LAUNCH2(V, H, R, true, false); else US_EP_LAUNCH2(V, H, R, false, false); } while (0)
+    if (shape.vec == 1) US_EP_LAUNCH(1, 1, 4);
+    else if (shape.vec == 2) US_EP_LAUNCH(2, 1, 4);
+    else if (shape.parts == 1) US_EP_LAUNCH(4, 1, 4);
+    else if (shape.parts == 2) US_EP_LAUNCH(4, 2, 4);
+    else US_EP_LAUNCH(4, 4, 2);
+#undef US_EP_LAUNCH
+#undef US_EP_LAUNCH2
+    env.check(hipGetLastError());
+    c += cols;
+  }
 }
 
 }  // namespace us

@@ -199,6 +199,8 @@ void fill_u32(Env &env, uint32_t *p, uint64_t n, uint32_t v);
 void exclusive_scan_i32(Env &env, const int32_t *in, int32_t *out, int64_t n, int32_t *total_dev);
 // in-place exclusive scan of nb per-tile sums by one workgroup; grand total to *total_dev
 void scan_partials_launch(Env &env, uint32_t *partial, int64_t nb, int32_t *total_dev);
+// the same over the .x of nt pairs, with the sum (most: the largest) of their .y
+void scan_pairs(Env &env, uint2 *pair, int64_t nt, int32_t *total_x, int32_t *of_y, bool most);
 void lower_bound_ptr(Env &env, const int32_t *sorted_major, int64_t n, int64_t ngroups, int32_t *ptr);
 // the same ptr from one pass over sorted entries, which also flags equal neighbours if `check`
 void group_ptr_unique(Env &env, const int32_t *sorted_major, const int32_t *sorted_minor, int64_t n, int64_t ngroups,

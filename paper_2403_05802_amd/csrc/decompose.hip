@@ -3,86 +3,241 @@
 #include "convert_internal.h"
 #include "device.h"
 
+#include <algorithm>
+
 namespace us {
 
 // ------------------------------------------------------------------ decompose
-// The row length of a given rank (the nearest-rank percentile) without sorting the lengths: digit by digit from
-// the top, one kernel counts the values of the next digit among the rows whose length agrees with the digits
-// picked so far, the next one picks the digit that holds the rank.  Every workgroup of the count leaves its 256
-// counts in a row of its own and the pick adds the rows up: the lengths of a matrix crowd into a few values, and
-// adds from a thousand workgroups to the same few device counters took their turns at ~20 ns each (63 us a pass
-// on 2 M rows); a single kernel per pass, whose last workgroup picks, was slower too (37 us: every workgroup
-// then needs a device-wide fence, which writes its L2 back).
-constexpr int SEL_GRID = 256, SEL_IPT = 8, SEL_TILE = 256 * SEL_IPT;
-struct SelectState { uint32_t prefix, rank, pad[2]; uint32_t hist[SEL_GRID][256]; };
+// The row length of a given rank (the nearest-rank percentile) without sorting the lengths: digit by digit from the top,
+// every launch counts the values of its digit among the rows whose length agrees with the digits picked so far.  The digit
+// that holds the rank is picked by every workgroup of the launch that follows, for itself: 8 KB from L2 and a scan, where a
+// launch of one workgroup in between takes as long as the count (2 M rows: three digits of 8 bits with such launches 66 us, two
+// of 11 bits 25).  At most SEL_GRID workgroups, each adding up in LDS first:
+// the lengths of a matrix crowd into a few values, and adds to the same device counter take their turns at ~20 ns each
+// (a thousand workgroups: 63 us a pass on 2 M rows).
+constexpr int SEL_T = 512, SEL_GRID = 256, SEL_IPT = 8, SEL_TILE = SEL_T * SEL_IPT;
+constexpr int SEL_BITS = 11, SEL_BINS = 1 << SEL_BITS, SEL_PASSES = 3;   // lengths have 31 bits
+struct SelectState {
+  uint32_t hist[SEL_PASSES][SEL_BINS];     // zero before the first pass
+  struct { uint32_t prefix, rank; } at[SEL_PASSES + 1];   // at[p]: the digits picked before pass p, and the rank among the rows they leave
+};
 
-__global__ void select_init_kernel(SelectState *s, uint32_t rank) { s->prefix = 0; s->rank = rank; }
-
-__global__ __launch_bounds__(256) void select_count_kernel(const int32_t *ptr, int64_t nrows, int shift, int bits,
-                                                          SelectState *s) {
-  __shared__ uint32_t s_hist[256];
-  s_hist[threadIdx.x] = 0;
+// what pass `pass` (of `bits` bits) picks, in every thread.  If no count holds the rank (the lengths are garbage) the digit is 0.
+template <int T>
+__device__ __forceinline__ uint2 select_pick(const SelectState *s, int pass, int bits) {
+  constexpr int PER = SEL_BINS / T;
+  __shared__ uint32_t s_wave[T / 64 + 1];
+  __shared__ uint2 s_pick;
+  const uint32_t prefix = s->at[pass].prefix << bits, rank = s->at[pass].rank;
+  uint32_t cnt[PER], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PER; ++k) sum += cnt[k] = s->hist[pass][threadIdx.x * PER + k];
+  if (threadIdx.x == 0) s_pick = make_uint2(prefix, rank);
+  uint32_t total;
+  uint32_t before = block_exclusive_sum<T>(sum, s_wave, &total);
+#pragma unroll
+  for (int k = 0; k < PER; ++k) {   // one bin of the workgroup
+    if (before <= rank && rank - before < cnt[k]) s_pick = make_uint2(prefix | (threadIdx.x * PER + k), rank - before);
+    before += cnt[k];
+  }
   __syncthreads();
-  const uint32_t prefix = s->prefix;   // left by the previous pick
+  return s_pick;
+}
+
+// prev_bits: how many the pass before this one has
+__global__ __launch_bounds__(SEL_T) void select_count_kernel(const int32_t *ptr, int64_t nrows, int pass, int shift, int bits,
+                                                            int prev_bits, uint32_t rank, SelectState *s) {
+  __shared__ uint32_t s_hist[SEL_BINS];
+  for (int i = threadIdx.x; i < SEL_BINS; i += SEL_T) s_hist[i] = 0;
+  const uint2 at = pass > 0 ? select_pick<SEL_T>(s, pass - 1, prev_bits) : make_uint2(0u, rank);
+  if (blockIdx.x == 0 && threadIdx.x == 0) { s->at[pass].prefix = at.x; s->at[pass].rank = at.y; }
+  __syncthreads();
   const int hi = shift + bits;
   const uint32_t mask = (1u << bits) - 1u;
   for (int64_t base = (int64_t)blockIdx.x * SEL_TILE; base < nrows; base += (int64_t)gridDim.x * SEL_TILE) {
     uint32_t v[SEL_IPT];
 #pragma unroll
     for (int k = 0; k < SEL_IPT; ++k) {   // all loads first
-      const int64_t g = base + k * 256 + threadIdx.x;
+      const int64_t g = base + k * SEL_T + threadIdx.x;
       v[k] = g < nrows ? (uint32_t)(ptr[g + 1] - ptr[g]) : 0xFFFFFFFFu;
     }
 #pragma unroll
     for (int k = 0; k < SEL_IPT; ++k) {
-      const int64_t g = base + k * 256 + threadIdx.x;
-      if (g < nrows && (hi >= 32 ? 0u : v[k] >> hi) == prefix) atomicAdd(&s_hist[(v[k] >> shift) & mask], 1u);
+      const int64_t g = base + k * SEL_T + threadIdx.x;
+      if (g < nrows && (hi >= 32 ? 0u : v[k] >> hi) == at.x) atomicAdd(&s_hist[(v[k] >> shift) & mask], 1u);
     }
   }
   __syncthreads();
-  s->hist[blockIdx.x][threadIdx.x] = s_hist[threadIdx.x];
-}
-__global__ __launch_bounds__(256) void select_pick_kernel(SelectState *s, int nrows_hist, int bits, int32_t *out) {   // out: last pass only
-  __shared__ uint32_t s_wave[256 / 64 + 1];
-  const uint32_t prefix = s->prefix, rank = s->rank;
-  uint32_t cnt = 0;
-  for (int w0 = 0; w0 < nrows_hist; w0 += 32) {   // 32 loads in flight
-    uint32_t part[32];
-#pragma unroll
-    for (int k = 0; k < 32; ++k) part[k] = w0 + k < nrows_hist ? s->hist[w0 + k][threadIdx.x] : 0u;
-#pragma unroll
-    for (int k = 0; k < 32; ++k) cnt += part[k];
-  }
-  uint32_t total;
-  const uint32_t before = block_exclusive_sum<256>(cnt, s_wave, &total);
-  if (cnt > 0 && before <= rank && rank < before + cnt) {   // one thread, unless the lengths are garbage
-    const uint32_t picked = (prefix << bits) | threadIdx.x;
-    s->prefix = picked;
-    s->rank = rank - before;
-    if (out) *out = (int32_t)picked;
-  }
+  for (int i = threadIdx.x; i < SEL_BINS; i += SEL_T)
+    if (s_hist[i]) atomicAdd(&s->hist[pass][i], s_hist[i]);
 }
 
-// K_dev != null: the cut is still on the device (the percentile picked just before)
-__global__ __launch_bounds__(256) void clipped_len_kernel(const int32_t *ptr, int64_t n, int64_t K, const int32_t *K_dev,
-                                                         int32_t *out) {
-  int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// Where the entries that a cut at rank K leaves over go: ptr_b[r] = sum of max(length - K, 0) over the rows before r (the
+// entries below the cut start at ptr[r] - ptr_b[r]).  A reduction per tile of rows, which also finds the longest row, a
+// scan of the tiles' sums, and the prefixes, each reading the lengths from ptr (not from an array of them).
+constexpr int RC_T = 256, RC_IPT = 8, RC_TILE = RC_T * RC_IPT;
+__device__ __forceinline__ uint32_t beyond(int32_t len, int64_t K) { return len > K ? (uint32_t)(len - K) : 0u; }
+
+// sel != null: K is what the last pass of the select picks, left in *K_dev for the launches that follow
+__global__ __launch_bounds__(RC_T) void rank_reduce_kernel(const int32_t *ptr, int64_t nrows, int64_t K, const SelectState *sel,
+                                                          int last_pass, int last_bits, int32_t *K_dev, uint2 *partial) {
+  __shared__ uint32_t s_wave[RC_T / 64 + 1];
+  __shared__ int32_t s_max[RC_T / 64];
+  const int64_t base = (int64_t)blockIdx.x * RC_TILE;
+  int32_t len[RC_IPT], most = 0;
+#pragma unroll
+  for (int k = 0; k < RC_IPT; ++k) {
+    const int64_t g = base + k * RC_T + threadIdx.x;
+    len[k] = g < nrows ? ptr[g + 1] - ptr[g] : 0;
+  }
+  if (sel) {
+    K = (int32_t)select_pick<RC_T>(sel, last_pass, last_bits).x;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *K_dev = (int32_t)K;
+  }
+  uint32_t s = 0, total;
+#pragma unroll
+  for (int k = 0; k < RC_IPT; ++k) { s += beyond(len[k], K); most = max(most, len[k]); }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) most = max(most, __shfl_xor(most, d));
+  if (lane_id() == 0) s_max[wave_id()] = most;
+  block_exclusive_sum<RC_T>(s, s_wave, &total);
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 0; w < RC_T / 64; ++w) most = max(most, s_max[w]);
+    partial[blockIdx.x] = make_uint2(total, (uint32_t)most);
+  }
+}
+__global__ __launch_bounds__(RC_T) void rank_apply_kernel(const int32_t *ptr, int64_t nrows, int64_t K, const int32_t *K_dev,
+                                                         const uint2 *partial, int32_t *ptr_b) {
+  __shared__ uint32_t s_wave[RC_T / 64 + 1];
   if (K_dev) K = *K_dev;
-  if (g < n) { int64_t l = ptr[g + 1] - ptr[g]; out[g] = (int32_t)(l < K ? l : K); }
+  const int64_t r0 = (int64_t)blockIdx.x * RC_TILE + (int64_t)threadIdx.x * RC_IPT;   // eight rows in a row; arrays start at 256 bytes
+  int32_t p[RC_IPT + 1];
+  const bool whole = r0 + RC_IPT <= nrows;
+  if (whole) {
+    const int4 a = *reinterpret_cast<const int4 *>(ptr + r0), b = *reinterpret_cast<const int4 *>(ptr + r0 + 4);
+    p[0] = a.x; p[1] = a.y; p[2] = a.z; p[3] = a.w; p[4] = b.x; p[5] = b.y; p[6] = b.z; p[7] = b.w;
+    p[8] = ptr[r0 + 8];
+  } else {
+#pragma unroll
+    for (int k = 0; k <= RC_IPT; ++k) p[k] = r0 + k <= nrows ? ptr[r0 + k] : 0;
+  }
+  uint32_t v[RC_IPT], s = 0, total;
+#pragma unroll
+  for (int k = 0; k < RC_IPT; ++k) {
+    v[k] = r0 + k < nrows ? beyond(p[k + 1] - p[k], K) : 0u;
+    s += v[k];
+  }
+  uint32_t ex = block_exclusive_sum<RC_T>(s, s_wave, &total) + partial[blockIdx.x].x;
+  int32_t o[RC_IPT];
+#pragma unroll
+  for (int k = 0; k < RC_IPT; ++k) { o[k] = (int32_t)ex; ex += v[k]; }
+  if (whole) {
+    *reinterpret_cast<int4 *>(ptr_b + r0) = make_int4(o[0], o[1], o[2], o[3]);
+    *reinterpret_cast<int4 *>(ptr_b + r0 + 4) = make_int4(o[4], o[5], o[6], o[7]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < RC_IPT; ++k)
+      if (r0 + k < nrows) ptr_b[r0 + k] = o[k];
+  }
+  if (r0 < nrows && r0 + RC_IPT >= nrows) ptr_b[nrows] = (int32_t)ex;   // (what lies behind the last row is 0)
+}
+
+// Part B alone (part A is an ELL slab built from the rows of the sorted list): entry z of it belongs to the row r with
+// ptr_b[r] <= z < ptr_b[r + 1] and comes from ptr[r] + K + (z - ptr_b[r]).  Only what part B holds is moved, and the rows
+// come from ptr_b, so that the sort need not write one per entry.  Bound by memory and by the chain from one search step to
+// the next: 26 M entries of a list of 40 M, 2 M rows, 139 us, 4.1 TB/s (a pass over the whole list 165; tiles of 2048 steps,
+// twice as many searches, 154).  A workgroup takes an equal share of
+// the merged sequence of row ends and entries of part B, since either can be few: a list with one entry left over in a few
+// of very many rows, or one row that holds them all.  Ends of part B are looked for by all threads at once.
+constexpr int RT_T = 512, RT_IPT = 8, RT_TILE = RT_T * RT_IPT;
+__global__ __launch_bounds__(RT_T) void rank_tail_kernel(const int32_t *minor, const float *val, const int32_t *ptr,
+                                                        const int32_t *ptr_b, int64_t nrows, int64_t nb, int32_t K,
+                                                        int32_t *br, int32_t *bc, float *bv) {
+  __shared__ __align__(16) int32_t s_row[RT_TILE];   // entry of the tile -> row of the tile
+  __shared__ int32_t s_from[RT_TILE];                // row of the tile -> where entry 0 of part B would come from
+  __shared__ int32_t s_wave[RT_T / 64];
+  const int tid = threadIdx.x;
+  const int64_t diag0 = (int64_t)blockIdx.x * RT_TILE, diag1 = min(diag0 + (int64_t)RT_TILE, nrows + nb);
+  // rows that end before the tile: their end, ptr_b[r + 1], is step ptr_b[r + 1] + r of the sequence
+  int64_t r0 = 0, hi = nrows;
+  while (r0 < hi) {
+    const int64_t step = ceil_div<int64_t>(hi - r0, RT_T), r = r0 + (tid + 1) * step - 1;
+    const int c = __syncthreads_count(r < hi && ptr_b[r + 1] + r < diag0);
+    r0 += c * step;
+    hi = min(hi, r0 + step - 1);
+  }
+  const int64_t z0 = diag0 - r0;
+#pragma unroll
+  for (int k = 0; k < RT_IPT; ++k) s_row[k * RT_T + tid] = 0;
+  __syncthreads();
+  int nr = 0;   // rows that end inside the tile
+  for (int i = tid;; i += RT_T) {
+    const int64_t r = r0 + i;
+    bool ends = false;
+    if (r < nrows) {
+      const int64_t b0 = ptr_b[r], b1 = ptr_b[r + 1], first = max(b0, z0);
+      ends = b1 + r < diag1;
+      if (first < b1 && first + r < diag1) {   // then first - z0 and i are below RT_TILE
+        s_row[first - z0] = i;
+        s_from[i] = ptr[r] + K - (int32_t)b0;
+      }
+    }
+    const int c = __syncthreads_count(ends);
+    nr += c;
+    if (c < RT_T) break;
+  }
+  const int nz = (int)(diag1 - diag0) - nr;
+  // the row of an entry is the last one marked up to it (the first entry is marked)
+  int4 *mine = reinterpret_cast<int4 *>(s_row + tid * RT_IPT);
+  static_assert(RT_IPT == 8, "two int4 per thread");
+  int4 a = mine[0], b = mine[1];
+  a.y = max(a.x, a.y); a.z = max(a.y, a.z); a.w = max(a.z, a.w);
+  b.x = max(a.w, b.x); b.y = max(b.x, b.y); b.z = max(b.y, b.z); b.w = max(b.z, b.w);
+  int32_t upto = b.w;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int32_t t = __shfl_up(upto, d);
+    if (lane_id() >= d) upto = max(upto, t);
+  }
+  if (lane_id() == 63) s_wave[wave_id()] = upto;
+  int32_t before = __shfl_up(upto, 1);
+  if (lane_id() == 0) before = 0;
+  __syncthreads();
+  for (int w = 0; w < wave_id(); ++w) before = max(before, s_wave[w]);
+  a.x = max(a.x, before); a.y = max(a.y, before); a.z = max(a.z, before); a.w = max(a.w, before);
+  b.x = max(b.x, before); b.y = max(b.y, before); b.z = max(b.z, before); b.w = max(b.w, before);
+  mine[0] = a; mine[1] = b;
+  __syncthreads();
+  int32_t row[RT_IPT], c[RT_IPT];
+  float v[RT_IPT];
+#pragma unroll
+  for (int k = 0; k < RT_IPT; ++k) {   // all loads first
+    const int p = k * RT_T + tid;
+    row[k] = 0; c[k] = 0; v[k] = 0.f;
+    if (p < nz) {
+      const int i = s_row[p];
+      const int64_t from = (int64_t)s_from[i] + z0 + p;
+      row[k] = (int32_t)(r0 + i); c[k] = minor[from]; v[k] = val[from];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < RT_IPT; ++k) {
+    const int p = k * RT_T + tid;
+    if (p < nz) { br[z0 + p] = row[k]; bc[z0 + p] = c[k]; bv[z0 + p] = v[k]; }
+  }
 }
 
 // stable split of the sorted list by rank-in-row: rank < K -> part A, else part B.  (Equal neighbours have
 // been looked for before: the two copies of a coordinate may end up in different parts.)
-// ar == null: part A is not written as a list (an ELL part A is built from the rows of the sorted list itself).
 constexpr int RSP_IPT = 4;
 __global__ __launch_bounds__(256) void rank_split_kernel(const int32_t *major, const int32_t *minor, const float *val,
-                                                        const int32_t *ptr, const int32_t *ptr_a, int64_t n,
-                                                        int64_t K, int32_t *ar, int32_t *ac, float *av, int32_t *br,
-                                                        int32_t *bc, float *bv) {
+                                                        const int32_t *ptr, const int32_t *ptr_b, int64_t n,
+                                                        int64_t K, CooLists la, CooLists lb) {
   // RSP_IPT entries per thread, each step for all of them before the next: the entry, then the two pointers of its
   // row, then the stores
   const int64_t base = (int64_t)blockIdx.x * (256 * RSP_IPT) + threadIdx.x;
-  int32_t r[RSP_IPT], c[RSP_IPT], p0[RSP_IPT], pa[RSP_IPT];
+  int32_t r[RSP_IPT], c[RSP_IPT], p0[RSP_IPT], pb[RSP_IPT];
   float v[RSP_IPT];
 #pragma unroll
   for (int k = 0; k < RSP_IPT; ++k) {
@@ -92,22 +247,16 @@ __global__ __launch_bounds__(256) void rank_split_kernel(const int32_t *major, c
 #pragma unroll
   for (int k = 0; k < RSP_IPT; ++k) {
     const bool in = base + k * 256 < n;
-    p0[k] = in ? ptr[r[k]] : 0; pa[k] = in ? ptr_a[r[k]] : 0;
+    p0[k] = in ? ptr[r[k]] : 0; pb[k] = in ? ptr_b[r[k]] : 0;
   }
 #pragma unroll
   for (int k = 0; k < RSP_IPT; ++k) {
     const int64_t i = base + k * 256;
     if (i >= n) continue;
     const int64_t rank = i - p0[k];
-    if (rank < K) {
-      if (ar) {
-        const int64_t p = pa[k] + rank;
-        ar[p] = r[k]; ac[p] = c[k]; av[p] = v[k];
-      }
-    } else {
-      const int64_t p = (int64_t)(p0[k] - pa[k]) + (rank - K);
-      br[p] = r[k]; bc[p] = c[k]; bv[p] = v[k];
-    }
+    const int64_t p = rank < K ? p0[k] - pb[k] + rank : pb[k] + (rank - K);
+    const CooLists &l = rank < K ? la : lb;
+    l.r[p] = r[k]; l.c[p] = c[k]; l.v[p] = v[k];
   }
 }
 
@@ -119,60 +268,67 @@ static us_status decompose_rank(Env &env, const us_coo &coo, const Plan &pa, con
                                 const us_format_desc &db, const us_predicate &pred, us_formatted **oa,
                                 us_formatted **ob) {
   const int64_t n = coo.nnz, nrows = coo.nrows;
+  const KeySpec ks = rowcol_keyspec(coo, false);
+  const bool with_ptr = sort_gives_ptr(env, n, ks, false), slab = pa.pattern == P_ELL && !pa.swapped;
+  const bool need_major = !slab || !with_ptr;   // (part B beside a slab is split off by rows)
+  const bool by_percentile = pred.kind == US_P_RANK_LT_PERCENTILE;
+  const int64_t ntile = ceil_div<int64_t>(nrows, RC_TILE);
   {  // every temporary of the call in one allocation
     auto g = [](size_t count) { return Env::granule(4 * count); };
-    env.reserve(sort_temp_bytes(env, n, rowcol_keyspec(coo, false), false) + 3 * g(n) + 3 * g(nrows + 1) + g(nrows) + g(nrows / 1024 + 64) +
+    env.reserve(sort_temp_bytes(env, n, ks, false) + (need_major ? 3 : 2) * g(n) + 2 * g(nrows + 1) + g(2 * ntile) +
                 Env::granule(sizeof(SelectState)) + 4 * Env::granule(sizeof(Flags)));
   }
   Flags *flags = new_flags(env, false);
-  int32_t *major = env.temp<int32_t>(n), *minor = env.temp<int32_t>(n);
+  int32_t *major = need_major ? env.temp<int32_t>(n) : nullptr, *minor = env.temp<int32_t>(n);
   float *val = env.temp<float>(n);
-  int32_t *ptr = env.temp<int32_t>(nrows + 1), *ptr_a = env.temp<int32_t>(nrows + 1), *clip = env.temp<int32_t>(nrows + 1);
+  int32_t *ptr = env.temp<int32_t>(nrows + 1), *ptr_b = env.temp<int32_t>(nrows + 1);
+  uint2 *partial = env.temp<uint2>(ntile);
+  SelectState *sel = by_percentile ? env.temp<SelectState>(1) : nullptr;
   if (!env.ok()) return env.status;
   SortOut so{};
   so.clear_flags = true;
   so.major = major; so.minor = minor; so.val = val;
-  if (sort_gives_ptr(env, n, rowcol_keyspec(coo, false), false)) so.ptr = ptr;
-  const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, rowcol_keyspec(coo, false), so, flags);
+  if (with_ptr) so.ptr = ptr;
+  const bool checked = sort_coo(env, coo.row, coo.col, coo.val, n, ks, so, flags);
+  if (!env.ok()) return env.status;
   if (!so.ptr_done) sorted_ptr(env, major, minor, n, nrows, ptr, !checked, flags);
   Flags h{};
   int64_t K = pred.abs;
-  if (pred.kind == US_P_RANK_LT_PERCENTILE) {
+  int npass = 0, last_bits = 0;
+  if (by_percentile) {
     // nearest-rank percentile of the row lengths over all rows: the length of rank k - 1 in ascending order
-    SelectState *sel = env.temp<SelectState>(1);
-    if (!env.ok()) return env.status;
     const int64_t maxlen = n < coo.ncols ? n : coo.ncols;
     int64_t k = (pred.num * nrows + pred.den - 1) / pred.den;
     if (k < 1) k = 1;
     if (k > nrows) k = nrows;
-    US_LAUNCH(env, "select_init", 8.0, select_init_kernel, 1, 1, sel, (uint32_t)(k - 1));
     const int total_bits = bits_for((uint64_t)maxlen) > 0 ? bits_for((uint64_t)maxlen) : 1;
-    const int npass = ceil_div(total_bits, 8);
-    const int64_t grid = ceil_div<int64_t>(nrows, SEL_TILE) < SEL_GRID ? ceil_div<int64_t>(nrows, SEL_TILE) : SEL_GRID;
+    npass = ceil_div(total_bits, SEL_BITS);
+    fill_u32(env, &sel->hist[0][0], (uint64_t)npass * SEL_BINS, 0u);
+    const int64_t grid = std::min<int64_t>(ceil_div<int64_t>(nrows, SEL_TILE), SEL_GRID);
     for (int p = 0, left = total_bits; p < npass; ++p) {
       const int w = total_bits / npass + (p < total_bits % npass ? 1 : 0);
       left -= w;
-      US_LAUNCH(env, "select_count", 4.0 * nrows, select_count_kernel, grid, 256, (const int32_t *)ptr, nrows, left, w, sel);
-      US_LAUNCH(env, "select_pick", 1024.0 * grid, select_pick_kernel, 1, 256, sel, (int)grid, w,
-                p == npass - 1 ? &flags->scalar[2] : (int32_t *)nullptr);
+      US_LAUNCH(env, "select_count", 4.0 * nrows, select_count_kernel, grid, SEL_T, (const int32_t *)ptr, nrows, p, left, w,
+                last_bits, (uint32_t)(k - 1), sel);
+      last_bits = w;
     }
   }
-  // the cut K (if picked above), the size of part A and the longest row all come back in one read of the flags
-  const bool by_percentile = pred.kind == US_P_RANK_LT_PERCENTILE;
-  US_LAUNCH(env, "clipped_len", 8.0 * nrows, clipped_len_kernel, ceil_div<int64_t>(nrows, 256), 256,
-            (const int32_t *)ptr, nrows, K, (const int32_t *)(by_percentile ? &flags->scalar[2] : nullptr), clip);
-  exclusive_scan_i32(env, clip, ptr_a, nrows, &flags->scalar[1]);
-  max_group_len(env, ptr, nrows, &flags->scalar[3]);
+  // the cut K (if picked above), the size of part B and the longest row all come back in one read of the flags
+  US_LAUNCH(env, "rank_reduce", 4.0 * nrows, rank_reduce_kernel, ntile, RC_T, (const int32_t *)ptr, nrows, K,
+            (const SelectState *)sel, npass - 1, last_bits, &flags->scalar[2], partial);
+  scan_pairs(env, partial, ntile, &flags->scalar[1], &flags->scalar[3], true);
+  US_LAUNCH(env, "rank_apply", 8.0 * nrows, rank_apply_kernel, ntile, RC_T, (const int32_t *)ptr, nrows, K,
+            (const int32_t *)(by_percentile ? &flags->scalar[2] : nullptr), (const uint2 *)partial, ptr_b);
   if (!read_flags(env, flags, &h)) return env.status;
   if (flag_status(h) != US_OK) return flag_status(h);
   if (by_percentile) K = h.scalar[2];
   const int64_t longest = h.scalar[3];
-  const int64_t na = h.scalar[1], nb = n - na;
+  const int64_t nb = h.scalar[1], na = n - nb;
   // part A as row-major ELL: its slab is built from the first min(length, K) entries of every row of the sorted
   // list (which gives the automatic width), 64 rows at a time through LDS; only part B is split off as a list.
   // Any other format of part A gets a sorted list first.
   us_formatted *ell = nullptr;
-  if (pa.pattern == P_ELL && !pa.swapped) {
+  if (slab) {
     const int64_t ell_width = pa.ell_width > 0 ? pa.ell_width : (longest < K ? longest : K);
     if (ell_width * nrows >= (1ll << 31)) return US_ERR_OVERFLOW;
     ell = new_ell_of_rows(env, da, nrows, coo.ncols, na, ell_width, K, minor, val, ptr, flags);
@@ -180,10 +336,15 @@ static us_status decompose_rank(Env &env, const us_coo &coo, const Plan &pa, con
   }
   CooLists la = ell ? CooLists() : alloc_lists(env, na), lb = alloc_lists(env, nb);
   us_status st = env.status;
-  if (st == US_OK && n > 0 && (nb > 0 || !ell)) {
-    US_LAUNCH(env, "rank_split", 16.0 * n + 12.0 * (ell ? nb : n), rank_split_kernel, ceil_div<int64_t>(n, 256 * RSP_IPT), 256,
+  if (st == US_OK && ell && nb > 0) {   // (then the cut is below the longest row and fits 31 bits)
+    US_LAUNCH(env, "rank_tail", 20.0 * nb + 8.0 * nrows, rank_tail_kernel, ceil_div<int64_t>(nrows + nb, RT_TILE), RT_T,
+              (const int32_t *)minor, (const float *)val, (const int32_t *)ptr, (const int32_t *)ptr_b, nrows, nb, (int32_t)K,
+              lb.r, lb.c, lb.v);
+    st = env.status;
+  } else if (st == US_OK && !ell && n > 0) {
+    US_LAUNCH(env, "rank_split", 28.0 * n, rank_split_kernel, ceil_div<int64_t>(n, 256 * RSP_IPT), 256,
               (const int32_t *)major, (const int32_t *)minor, (const float *)val, (const int32_t *)ptr,
-              (const int32_t *)ptr_a, n, K, la.r, la.c, la.v, lb.r, lb.c, lb.v);
+              (const int32_t *)ptr_b, n, K, la, lb);
     st = env.status;
   }
   auto finish_part = [&](const Plan &p, const us_format_desc &d, CooLists &l, int64_t cnt, us_formatted **o) {

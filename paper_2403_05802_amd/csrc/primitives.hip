@@ -148,6 +148,46 @@ __global__ __launch_bounds__(1024) void scan_partials_kernel(uint32_t *partial, 
   if (threadIdx.x == 0 && total_dev) *total_dev = (int32_t)carry;
 }
 
+// The same over pairs: .x is scanned in place, of .y only the sum or the largest is wanted.
+template <bool MOST>
+__global__ __launch_bounds__(1024) void scan_pairs_kernel(uint2 *pair, int64_t nt, int32_t *total_x, int32_t *of_y) {
+  constexpr int IPT = 8;
+  __shared__ uint32_t s_wave[1024 / 64 + 1];
+  __shared__ uint32_t s_y[1024 / 64];
+  uint32_t carry = 0, y = 0;
+  for (int64_t base = 0; base < nt; base += 1024 * IPT) {
+    const int64_t i0 = base + (int64_t)threadIdx.x * IPT;
+    uint32_t v[IPT], s = 0, total;
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      const uint2 p = i0 + k < nt ? pair[i0 + k] : make_uint2(0u, 0u);
+      v[k] = p.x; s += p.x;
+      y = MOST ? max(y, p.y) : y + p.y;
+    }
+    uint32_t ex = block_exclusive_sum<1024>(s, s_wave, &total) + carry;
+#pragma unroll
+    for (int k = 0; k < IPT; ++k) {
+      if (i0 + k < nt) pair[i0 + k].x = ex;
+      ex += v[k];
+    }
+    carry += total;
+  }
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) {
+    const uint32_t t = (uint32_t)__shfl_xor((int)y, d);
+    y = MOST ? max(y, t) : y + t;
+  }
+  if (lane_id() == 0) s_y[wave_id()] = y;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    uint32_t all = s_y[0];
+#pragma unroll
+    for (int w = 1; w < 1024 / 64; ++w) all = MOST ? max(all, s_y[w]) : all + s_y[w];
+    *total_x = (int32_t)carry;
+    *of_y = (int32_t)all;
+  }
+}
+
 __global__ __launch_bounds__(SCAN_T) void scan_apply_kernel(const int32_t *in, int32_t *out, int64_t n,
                                                            const uint32_t *partial) {
   __shared__ uint32_t s_wave[SCAN_T / 64 + 1];
@@ -187,6 +227,11 @@ __global__ __launch_bounds__(SCAN_T) void scan_apply_kernel(const int32_t *in, i
 void scan_partials_launch(Env &env, uint32_t *partial, int64_t nb, int32_t *total_dev) {
   if (nb > 1024 * 8) US_LAUNCH(env, "scan_partials", 8.0 * nb, scan_partials_kernel<32>, 1, 1024, partial, nb, total_dev);
   else US_LAUNCH(env, "scan_partials", 8.0 * nb, scan_partials_kernel<8>, 1, 1024, partial, nb, total_dev);
+}
+
+void scan_pairs(Env &env, uint2 *pair, int64_t nt, int32_t *total_x, int32_t *of_y, bool most) {
+  if (most) US_LAUNCH(env, "scan_pairs", 16.0 * nt, scan_pairs_kernel<true>, 1, 1024, pair, nt, total_x, of_y);
+  else US_LAUNCH(env, "scan_pairs", 16.0 * nt, scan_pairs_kernel<false>, 1, 1024, pair, nt, total_x, of_y);
 }
 
 void exclusive_scan_i32(Env &env, const int32_t *in, int32_t *out, int64_t n, int32_t *total_dev) {

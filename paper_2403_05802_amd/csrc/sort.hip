@@ -1155,12 +1155,13 @@ size_t sort_temp_bytes(const Env &env, int64_t nnz, const KeySpec &ks, bool mino
 
 bool sort_coo(Env &env, const int32_t *row, const int32_t *col, const float *val, int64_t nnz,
               const KeySpec &ks, SortOut &out, Flags *flags_dev) {
-  if (env.ok() && (out.late || out.major) && by_buckets(env, nnz, ks, out.minor_sorted)) {
+  if (env.ok() && (out.late || out.major || out.ptr) && by_buckets(env, nnz, ks, out.minor_sorted)) {
     if (out.node_counted) *out.node_counted = false;
     bucket_sort(env, row, col, val, nnz, ks, out, flags_dev);
     out.ptr_done = out.ptr != nullptr;
     return true;
   }
+  if (nnz > 0 && !out.late && !out.major && !out.key64 && !out.key32) { env.fail(US_ERR_NULL); return false; }   // nowhere to leave the keys
   if (out.clear_flags) fill_u32(env, (uint32_t *)flags_dev, sizeof(Flags) / 4, 0u);
   return sort_generic(env, IN_COO, row, col, nullptr, val, nnz, ks, out, flags_dev);
 }

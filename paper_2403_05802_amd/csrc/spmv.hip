@@ -45,7 +45,13 @@ __global__ __launch_bounds__(256) void merge_path_split_kernel(const int32_t *pt
   split[t] = (int32_t)merge_path_rows(ptr + 1, nrows, nnz, d);
 }
 
-template <bool INDIRECT_ROWS>
+// A row that a tile boundary cuts: its pieces go to carry slots that a second launch adds up, or (WHOLE) the workgroup in
+// whose tile the row ends goes over the earlier part of it again and no second launch is needed.  Rows of up to WHOLE_COLS
+// entries (there are no more columns, and equal coordinates are refused): at most WHOLE_COLS / MP_T products a thread on top,
+// on average half a row a workgroup; longer rows would make one workgroup's chain of loads longer than the launch.
+constexpr int64_t WHOLE_COLS = 4 * MP_TILE;
+
+template <bool INDIRECT_ROWS, bool WHOLE>
 __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, const int32_t *idx, const float *val,
                                                        const int32_t *row_ids, const int32_t *split, int64_t nrows,
                                                        int64_t nnz, const float *x, float *y, int accumulate,
@@ -54,6 +60,7 @@ __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, cons
   __shared__ int32_t s_end[MP_TILE + 1];
   __shared__ int32_t s_wkey[MP_T / 64];
   __shared__ float s_wval[MP_T / 64];
+  __shared__ float s_earlier[MP_T / 64];
   const int32_t *row_end = ptr + 1;
   const int64_t total = nrows + nnz;
   const int64_t diag0 = (int64_t)blockIdx.x * MP_TILE;
@@ -61,6 +68,7 @@ __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, cons
   const int64_t r0 = split[blockIdx.x], r1 = split[blockIdx.x + 1];
   const int64_t z0 = diag0 - r0, z1 = diag1 - r1;
   const int nr = (int)(r1 - r0), nz = (int)(z1 - z0);
+  const int64_t began = WHOLE && nr > 0 ? ptr[r0] : z0;   // where the first row that ends here begins (not behind z0)
   {  // all index/value loads first, then all gathers of x: two round trips instead of sixteen.
      // (Non-temporal loads of the streamed arrays were measured: 7 % faster right after a conversion, 16 %
      // slower when the product is repeated and the matrix would otherwise stay in the memory-side cache.)
@@ -82,6 +90,13 @@ __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, cons
       if (i < nz) s_prod[i] = vv[k] * xv[k];
       if (i < nr) s_end[i] = (int32_t)(re[k] - z0);
     }
+  }
+  if (WHOLE) {
+    float p = 0.f;
+#pragma unroll 4
+    for (int64_t e = began + threadIdx.x; e < z0; e += MP_T) p += val[e] * x[idx[e]];
+    p = wave_sum(p);
+    if (lane_id() == 0) s_earlier[wave_id()] = p;
   }
   __syncthreads();
 
@@ -138,11 +153,15 @@ __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, cons
   if (lane == 0) { prev_key = head_key; prev_val = wave_carry; }
   if (first_row >= 0) {
     float inherit = (prev_key == first_row) ? prev_val : 0.f;
+    if (WHOLE && first_row == 0) {
+#pragma unroll
+      for (int ww = 0; ww < MP_T / 64; ++ww) inherit += s_earlier[ww];
+    }
     int64_t row = r0 + first_row;
     int64_t out = INDIRECT_ROWS ? row_ids[row] : row;
     y[out] = (accumulate ? y[out] : 0.f) + (first_sum + inherit);
   }
-  if (threadIdx.x == MP_T - 1) {
+  if (!WHOLE && threadIdx.x == MP_T - 1) {
     carry_row[blockIdx.x] = (int32_t)min(r0 + (int64_t)p.key, nrows);
     carry_val[blockIdx.x] = incl;
   }
@@ -171,23 +190,28 @@ static void spmv_compressed(Env &env, const us_formatted &A, const int32_t *ptr,
   if (total == 0) return;
   const int64_t nb = ceil_div<int64_t>(total, MP_TILE);
   if (!A.mp_split || A.mp_tiles != nb) { env.fail(US_ERR_FORMAT_MISMATCH); return; }
+  // (x counted once, as its length: what the gathers re-read is traffic, not algorithmic bytes)
+  const double bytes = 8.0 * nnz + 4.0 * (nrows_stored + 1) + 4.0 * (A.swapped ? A.nrows : A.ncols) + 4.0 * nrows_stored;
+  const int acc = accumulate ? 1 : 0;
+  const int32_t *split = A.mp_split;
+  if (A.ncols <= WHOLE_COLS) {
+    int32_t *no_row = nullptr;
+    float *no_val = nullptr;
+    if (row_ids) US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<true, true>), nb, MP_T, ptr, idx, val, row_ids, split, nrows_stored, nnz, x, y, acc, no_row, no_val);
+    else US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<false, true>), nb, MP_T, ptr, idx, val, row_ids, split, nrows_stored, nnz, x, y, acc, no_row, no_val);
+    return;
+  }
   const size_t half = ((size_t)nb * 4 + 255) / 256 * 256;
   char *ws = (char *)ensure_workspace(env, A, 2 * half);
   if (!env.ok()) return;
   int32_t *carry_row = (int32_t *)ws;
   float *carry_val = (float *)(ws + half);
-  // (x counted once, as its length: what the gathers re-read is traffic, not algorithmic bytes)
-  const double bytes = 8.0 * nnz + 4.0 * (nrows_stored + 1) + 4.0 * (A.swapped ? A.nrows : A.ncols) + 4.0 * nrows_stored;
   if (row_ids) {
-    US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<true>), nb, MP_T, ptr, idx, val, row_ids,
-              (const int32_t *)A.mp_split, nrows_stored, nnz,
-              x, y, accumulate ? 1 : 0, carry_row, carry_val);
+    US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<true, false>), nb, MP_T, ptr, idx, val, row_ids, split, nrows_stored, nnz, x, y, acc, carry_row, carry_val);
     US_LAUNCH(env, "spmv_csr_fixup", 8.0 * nb, (csr_spmv_fixup_kernel<true>), ceil_div<int64_t>(nb, 256), 256,
               (const int32_t *)carry_row, (const float *)carry_val, nb, nrows_stored, row_ids, y);
   } else {
-    US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<false>), nb, MP_T, ptr, idx, val, row_ids,
-              (const int32_t *)A.mp_split, nrows_stored, nnz,
-              x, y, accumulate ? 1 : 0, carry_row, carry_val);
+    US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<false, false>), nb, MP_T, ptr, idx, val, row_ids, split, nrows_stored, nnz, x, y, acc, carry_row, carry_val);
     US_LAUNCH(env, "spmv_csr_fixup", 8.0 * nb, (csr_spmv_fixup_kernel<false>), ceil_div<int64_t>(nb, 256), 256,
               (const int32_t *)carry_row, (const float *)carry_val, nb, nrows_stored, row_ids, y);
   }

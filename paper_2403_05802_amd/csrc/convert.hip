@@ -525,9 +525,8 @@ us_status convert_with_plan(Env &env, const us_coo &coo, const Plan &plan, const
     env.reserve(tmp);
     late_res = env.one_result && rowcol ? res : 0;   // the block of the result is allocated while the sort runs
     if (env.one_result && !rowcol) env.reserve_out(res);
-  } else if (plan.pattern == P_DIA) {   // counters, flags, positions and slab indices of the diagonals, scan sums
-    const size_t nbins = (size_t)(coo.nrows + coo.ncols);
-    env.reserve(4 * Env::granule(4 * nbins) + Env::granule(4 * (nbins / 1024 + 64)) + 8 * Env::granule(256));
+  } else if (plan.pattern == P_DIA) {
+    env.reserve(group_temp_bytes(coo.nrows + coo.ncols - 1));
   } else if (plan.pattern == P_BCSR || plan.pattern == P_BDIA || plan.pattern == P_BELL) {   // sorted keys and values, block counts per tile
     env.reserve(Env::granule(8 * (size_t)n) + Env::granule(4 * (size_t)n) + Env::granule(4 * ((size_t)n / 1024 + 64)) +
                 8 * Env::granule(256));

@@ -53,6 +53,7 @@ enum { G_DIAG = 0, G_ROW = 1, G_COL = 2 };
 struct CooLists { int32_t *r = nullptr, *c = nullptr; float *v = nullptr; };
 CooLists alloc_lists(Env &env, int64_t n);
 void free_lists(Env &env, CooLists &l);
+size_t group_temp_bytes(int64_t nbins);   // what the query over nbins groups and what follows it take from Env::temp
 us_status convert_dia(Env &env, const us_coo &coo, const Plan &plan, const us_format_desc &desc, Flags *flags,
                       us_formatted **out);
 us_status decompose_sum(Env &env, const us_coo &coo, const Plan &pa, const us_format_desc &da, const Plan &pb,

@@ -80,45 +80,81 @@ __global__ __launch_bounds__(GH_T) void group_hist_kernel(const int32_t *row, co
   if (bad) flags->index_range = 1;
 }
 
-// flag[g] = group g goes to part A.  pkind < 0: every non-empty group (plain conversion).
-// Adds the number of entries in flagged groups to *nnz_a.
-__global__ __launch_bounds__(256) void group_flag_kernel(const uint32_t *count, int64_t nbins, int gkind, int pkind,
-                                                        int64_t num, int64_t den, int64_t thr, int64_t nrows,
-                                                        int64_t ncols, int32_t *flag, int32_t *nnz_a) {
-  __shared__ uint32_t s_wave[256 / 64 + 1];
-  uint32_t mine = 0;
-  for (int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x; g < nbins; g += (int64_t)gridDim.x * 256) {
-    const uint32_t cnt = count[g];
-    bool f = false;
-    if (cnt > 0) {
-      if (pkind < 0) f = true;
-      else if (pkind == US_P_SUM_GE_ABS) f = (int64_t)cnt >= thr;
-      else {
-        int64_t cap;
-        if (gkind == G_DIAG) {
-          int64_t off = g - (nrows - 1);
-          int64_t hi = nrows < ncols - off ? nrows : ncols - off, lo = off < 0 ? -off : 0;
-          cap = hi > lo ? hi - lo : 0;
-        } else cap = gkind == G_ROW ? ncols : nrows;
-        f = den * (int64_t)cnt >= num * cap;
-      }
-    }
-    flag[g] = f ? 1 : 0;
-    if (f) mine += cnt;
-  }
-  uint32_t total;
-  block_exclusive_sum<256>(mine, s_wave, &total);
-  if (threadIdx.x == 0 && total) atomicAdd(nnz_a, (int32_t)total);
+// Which groups go to part A, and their numbers in order: counted per tile of groups, the tiles' counts scanned, then every
+// group's number written over its count (-1: the group stays out).  The predicate is evaluated in both passes: the counts
+// are read twice, and nothing in between is written (4.2 M diagonals: flags, their scan, the numbers and the offsets in
+// arrays and launches of their own took 50 us, this 24).
+struct GroupRule { int gkind, pkind; int64_t num, den, thr, nrows, ncols; };   // pkind < 0: every non-empty group (plain conversion)
+__device__ __forceinline__ bool group_goes(const GroupRule &q, int64_t g, uint32_t cnt) {
+  if (cnt == 0) return false;
+  if (q.pkind < 0) return true;
+  if (q.pkind == US_P_SUM_GE_ABS) return (int64_t)cnt >= q.thr;
+  int64_t cap;
+  if (q.gkind == G_DIAG) {
+    const int64_t off = g - (q.nrows - 1);
+    const int64_t hi = q.nrows < q.ncols - off ? q.nrows : q.ncols - off, lo = off < 0 ? -off : 0;
+    cap = hi > lo ? hi - lo : 0;
+  } else cap = q.gkind == G_ROW ? q.ncols : q.nrows;
+  return q.den * (int64_t)cnt >= q.num * cap;
 }
 
-// gmap[g] = position of group g among the flagged groups, or -1; offsets of the flagged diagonals
+constexpr int GS_T = 256, GS_IPT = 8, GS_TILE = GS_T * GS_IPT;
+// partial[t] = groups of tile t that go, entries in them
+__global__ __launch_bounds__(GS_T) void group_reduce_kernel(const uint32_t *count, int64_t nbins, GroupRule q, uint2 *partial) {
+  __shared__ uint32_t s_wave[GS_T / 64 + 1];
+  const int64_t base = (int64_t)blockIdx.x * GS_TILE;
+  uint32_t cnt[GS_IPT], go = 0, in = 0, groups, entries;
+#pragma unroll
+  for (int k = 0; k < GS_IPT; ++k) {
+    const int64_t g = base + k * GS_T + threadIdx.x;
+    cnt[k] = g < nbins ? count[g] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < GS_IPT; ++k)
+    if (group_goes(q, base + k * GS_T + threadIdx.x, cnt[k])) { ++go; in += cnt[k]; }
+  block_exclusive_sum<GS_T>(go, s_wave, &groups);
+  block_exclusive_sum<GS_T>(in, s_wave, &entries);
+  if (threadIdx.x == 0) partial[blockIdx.x] = make_uint2(groups, entries);
+}
+
+// off (or null): the offsets of the diagonals that go, in order
 // far: where the first workgroup leaves how many of 256 pairs of neighbours in the list lie more than DIA_FAR rows apart,
 // or null
 constexpr uint32_t DIA_FAR = 256;
-__global__ __launch_bounds__(256) void group_map_kernel(const int32_t *flag, const int32_t *pos, int64_t nbins,
-                                                       int32_t *gmap, const int32_t *row, int64_t n, int32_t *far) {
-  int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (d < nbins) gmap[d] = flag[d] ? pos[d] : -1;
+__global__ __launch_bounds__(GS_T) void group_number_kernel(uint32_t *count, int64_t nbins, GroupRule q, const uint2 *partial,
+                                                           int32_t *off, const int32_t *row, int64_t n, int32_t *far) {
+  __shared__ uint32_t s_wave[GS_T / 64 + 1];
+  static_assert(GS_IPT == 8, "two 16-byte vectors per thread");
+  const int64_t g0 = (int64_t)blockIdx.x * GS_TILE + (int64_t)threadIdx.x * GS_IPT;   // (the counts start at 256 bytes)
+  const bool whole = g0 + GS_IPT <= nbins;
+  uint32_t cnt[GS_IPT], go = 0, total;
+  if (whole) {
+    const uint4 a = *reinterpret_cast<const uint4 *>(count + g0), b = *reinterpret_cast<const uint4 *>(count + g0 + 4);
+    cnt[0] = a.x; cnt[1] = a.y; cnt[2] = a.z; cnt[3] = a.w; cnt[4] = b.x; cnt[5] = b.y; cnt[6] = b.z; cnt[7] = b.w;
+  } else {
+#pragma unroll
+    for (int k = 0; k < GS_IPT; ++k) cnt[k] = g0 + k < nbins ? count[g0 + k] : 0u;
+  }
+  bool goes[GS_IPT];
+#pragma unroll
+  for (int k = 0; k < GS_IPT; ++k) { goes[k] = group_goes(q, g0 + k, cnt[k]); go += goes[k]; }
+  int32_t at = (int32_t)(block_exclusive_sum<GS_T>(go, s_wave, &total) + partial[blockIdx.x].x), id[GS_IPT];
+#pragma unroll
+  for (int k = 0; k < GS_IPT; ++k) {
+    id[k] = -1;
+    if (goes[k]) {
+      if (off) off[at] = (int32_t)(g0 + k - (q.nrows - 1));
+      id[k] = at++;
+    }
+  }
+  if (whole) {
+    *reinterpret_cast<int4 *>(count + g0) = make_int4(id[0], id[1], id[2], id[3]);
+    *reinterpret_cast<int4 *>(count + g0 + 4) = make_int4(id[4], id[5], id[6], id[7]);
+  } else {
+#pragma unroll
+    for (int k = 0; k < GS_IPT; ++k)
+      if (g0 + k < nbins) count[g0 + k] = (uint32_t)id[k];
+  }
   if (far && blockIdx.x == 0) {
     __shared__ uint32_t s_far;
     if (threadIdx.x == 0) s_far = 0;
@@ -131,12 +167,12 @@ __global__ __launch_bounds__(256) void group_map_kernel(const int32_t *flag, con
     if (threadIdx.x == 0) *far = (int32_t)s_far;
   }
 }
-__global__ __launch_bounds__(256) void diag_offsets_kernel(const int32_t *gmap, int64_t nbins, int32_t nrows,
-                                                          int32_t *off) {
-  int64_t d = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (d < nbins && gmap[d] >= 0) off[gmap[d]] = (int32_t)(d - (nrows - 1));
+// what has to be there before the entries are dealt out: the offsets in the result's own array, counters at zero
+__global__ __launch_bounds__(256) void dia_begin_kernel(const int32_t *off, int64_t ndiag, int32_t *out, uint32_t *zero, int64_t nzero) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < ndiag) out[i] = off[i];
+  if (i < nzero) zero[i] = 0u;
 }
-
 
 // One pass over the COO list that sends every entry to its part of a decomposition.
 //   TO_SLAB: entries of flagged diagonals go straight into the DIA slab val[k*L + i]
@@ -357,7 +393,40 @@ void free_lists(Env &env, CooLists &l) {
   l = CooLists();
 }
 
-// DIA from per-diagonal flags (flags->scalar[1] already holds the number of flagged entries).
+// number[g] = position of group g among those that go to part A, or -1 (in place of the counts); off: see group_number_kernel
+struct GroupMap { const int32_t *number; int32_t *off; };
+
+// histogram of the groups, and the number of every group that goes to part A (flags->scalar[0] groups, [1] entries in them)
+size_t group_temp_bytes(int64_t nbins) {
+  return 2 * Env::granule(4 * (size_t)nbins) + Env::granule(8 * (size_t)ceil_div<int64_t>(nbins, GS_TILE)) +
+         Env::granule(4 * (DB_BINS + 2)) + 8 * Env::granule(256);
+}
+static int64_t group_bins(const us_coo &coo, int gkind) {
+  return gkind == G_DIAG ? coo.nrows + coo.ncols - 1 : (gkind == G_ROW ? coo.nrows : coo.ncols);
+}
+
+static GroupMap group_map(Env &env, const us_coo &coo, int gkind, int pkind, int64_t num, int64_t den, int64_t thr, Flags *flags,
+                          bool slab) {
+  const int64_t nbins = group_bins(coo, gkind), ntile = ceil_div<int64_t>(nbins, GS_TILE), n = coo.nnz;
+  GroupMap g{};
+  uint32_t *count = env.temp<uint32_t>(nbins);
+  if (slab) g.off = env.temp<int32_t>(nbins);
+  uint2 *partial = env.temp<uint2>(ntile);
+  if (!env.ok()) return g;
+  fill_u32(env, count, nbins, 0);
+  if (n > 0)
+    US_LAUNCH(env, "group_hist", 8.0 * n, group_hist_kernel, std::min<int64_t>(ceil_div<int64_t>(n, GH_TILE), GH_GRID), GH_T, coo.row,
+              coo.col, n, gkind, (uint32_t)coo.nrows, (uint32_t)coo.ncols, count, flags);
+  const GroupRule q{gkind, pkind, num, den, thr, coo.nrows, coo.ncols};
+  US_LAUNCH(env, "group_reduce", 4.0 * nbins, group_reduce_kernel, ntile, GS_T, (const uint32_t *)count, nbins, q, partial);
+  scan_pairs(env, partial, ntile, &flags->scalar[0], &flags->scalar[1], false);
+  US_LAUNCH(env, "group_number", 8.0 * nbins, group_number_kernel, ntile, GS_T, count, nbins, q, (const uint2 *)partial, g.off,
+            coo.row, n, slab && n > 1 ? &flags->scalar[2] : (int32_t *)nullptr);
+  g.number = (const int32_t *)count;
+  return g;
+}
+
+// DIA of the diagonals that group_map has numbered.
 // If `rest` is given, the entries of the unflagged diagonals are collected into it in the same
 // pass (its arrays are allocated here; the caller owns them afterwards) and *nrest is their number.
 // verify_later != null: the last read of the flags (coordinates in range, no value carrying the empty pattern, as
@@ -373,16 +442,10 @@ static us_status dia_verify(Env &env, const DiaPending &p) {
 }
 
 static us_status dia_from_flags(Env &env, const us_coo &coo, const Plan &plan, const us_format_desc &desc,
-                                Flags *flags, const int32_t *flag, us_formatted **out, CooLists *rest,
+                                Flags *flags, const GroupMap &g, us_formatted **out, CooLists *rest,
                                 int64_t *nrest, DiaPending *verify_later = nullptr) {
-  const int64_t nbins = coo.nrows + coo.ncols - 1, n = coo.nnz;
+  const int64_t n = coo.nnz;
   const int64_t L = plan.swapped ? coo.ncols : coo.nrows;
-  int32_t *pos = env.temp<int32_t>(nbins), *gmap = env.temp<int32_t>(nbins);
-  int32_t *cursors = env.temp<int32_t>(2);
-  if (!env.ok()) return env.status;
-  exclusive_scan_i32(env, flag, pos, nbins, &flags->scalar[0]);
-  US_LAUNCH(env, "group_map", 12.0 * nbins, group_map_kernel, ceil_div<int64_t>(nbins, 256), 256, flag,
-            (const int32_t *)pos, nbins, gmap, coo.row, n, n > 1 ? &flags->scalar[2] : (int32_t *)nullptr);
   Flags h{};
   if (!read_flags(env, flags, &h)) return env.status;
   if (flag_status(h) != US_OK) return flag_status(h);
@@ -407,28 +470,29 @@ static us_status dia_from_flags(Env &env, const us_coo &coo, const Plan &plan, c
   const bool marks = env.dia_marks && !binned;
   const int64_t nvec = ceil_div<int64_t>(nslots, 16) + 1;
   uint8_t *slotmap = marks ? (uint8_t *)env.temp<uint4>(nvec) : nullptr;
-  if (binned) env.reserve(Env::granule(4 * DB_BINS) + Env::granule(((size_t)nbins_slab << shift) * sizeof(uint2)));
-  uint32_t *filled = binned ? env.temp<uint32_t>(DB_BINS) : nullptr;
+  if (binned) env.reserve(Env::granule(4 * (DB_BINS + 2)) + Env::granule(((size_t)nbins_slab << shift) * sizeof(uint2)));
+  uint32_t *counters = env.temp<uint32_t>(DB_BINS + 2);   // the lists' two, then the bins'
+  uint32_t *filled = counters + 2;
+  int32_t *cursors = (int32_t *)counters;
   uint2 *rec = binned ? env.temp<uint2>((size_t)nbins_slab << shift) : nullptr;
   CooLists lb;
   if (rest) { *nrest = n - na; lb = alloc_lists(env, n - na); *rest = lb; }
   if (!env.ok()) { free_formatted(env, f); return env.status; }
-  if (binned) fill_u32(env, filled, DB_BINS, 0u);
-  else fill_u32(env, (uint32_t *)f->val, nslots, marks ? 0u : DIA_EMPTY);
+  if (!binned) fill_u32(env, (uint32_t *)f->val, nslots, marks ? 0u : DIA_EMPTY);
   if (marks) fill_u32(env, (uint32_t *)slotmap, nvec * 4, 0u);
-  fill_u32(env, (uint32_t *)cursors, 2, 0u);
-  US_LAUNCH(env, "diag_offsets", 8.0 * nbins, diag_offsets_kernel, ceil_div<int64_t>(nbins, 256), 256,
-            (const int32_t *)gmap, nbins, (int32_t)coo.nrows, f->level[0].idx);
+  const int64_t ncounters = binned ? DB_BINS + 2 : 2;
+  US_LAUNCH(env, "dia_begin", 8.0 * ndiag, dia_begin_kernel, ceil_div<int64_t>(std::max(ndiag, ncounters), 256), 256,
+            (const int32_t *)g.off, ndiag, f->level[0].idx, counters, ncounters);
   if (binned) {
     US_LAUNCH(env, "dia_bin", 12.0 * n + 8.0 * na + 12.0 * (rest ? n - na : 0), dia_bin_kernel, ceil_div<int64_t>(n, DB_TILE), DB_T,
-              coo.row, coo.col, coo.val, n, (uint32_t)coo.nrows, (const int32_t *)gmap, L, plan.swapped ? 1 : 0, shift, rec,
+              coo.row, coo.col, coo.val, n, (uint32_t)coo.nrows, g.number, L, plan.swapped ? 1 : 0, shift, rec,
               filled, lb, cursors);
     if (shift == 14) US_LAUNCH(env, "dia_image", 8.0 * na + 4.0 * nslots, dia_image_kernel<14>, nbins_slab, DB_T, (const uint2 *)rec, (const uint32_t *)filled, f->val, nslots, &flags->scalar[3]);
     else US_LAUNCH(env, "dia_image", 8.0 * na + 4.0 * nslots, dia_image_kernel<15>, nbins_slab, DB_T, (const uint2 *)rec, (const uint32_t *)filled, f->val, nslots, &flags->scalar[3]);
   } else if (n > 0)
     US_LAUNCH(env, "dia_split_scatter", 12.0 * n + 5.0 * na + 12.0 * (rest ? n - na : 0), (split_kernel<true>),
               ceil_div<int64_t>(n, SP_TILE), SP_T, coo.row, coo.col, coo.val, n, (int)G_DIAG, (uint32_t)coo.nrows,
-              (const int32_t *)gmap, L, plan.swapped ? 1 : 0, f->val, slotmap, CooLists(), lb, cursors, flags);
+              g.number, L, plan.swapped ? 1 : 0, f->val, slotmap, CooLists(), lb, cursors, flags);
   if (marks)
     US_LAUNCH(env, "count_marks", 1.0 * nslots, count_marks_kernel, one_counter_grid(nvec, 256), 256, (const uint4 *)slotmap, nvec, &flags->scalar[3]);
   else if (!binned && nslab4 > 0)
@@ -446,71 +510,45 @@ static us_status dia_from_flags(Env &env, const us_coo &coo, const Plan &plan, c
 }
 
 
-// histogram of the groups + predicate flags; pkind < 0 flags every non-empty group
-struct GroupCounts { uint32_t *count; int32_t *flag; int64_t nbins; };
-
-static GroupCounts group_flags(Env &env, const us_coo &coo, int gkind, int pkind, int64_t num, int64_t den,
-                               int64_t thr, Flags *flags) {
-  GroupCounts g{};
-  g.nbins = gkind == G_DIAG ? coo.nrows + coo.ncols - 1 : (gkind == G_ROW ? coo.nrows : coo.ncols);
-  g.count = env.temp<uint32_t>(g.nbins);
-  g.flag = env.temp<int32_t>(g.nbins);
-  if (!env.ok()) return g;
-  fill_u32(env, g.count, g.nbins, 0);
-  if (coo.nnz > 0)
-    US_LAUNCH(env, "group_hist", 8.0 * coo.nnz, group_hist_kernel, std::min<int64_t>(ceil_div<int64_t>(coo.nnz, GH_TILE), GH_GRID), GH_T, coo.row,
-              coo.col, coo.nnz, gkind, (uint32_t)coo.nrows, (uint32_t)coo.ncols, g.count, flags);
-  US_LAUNCH(env, "group_flag", 8.0 * g.nbins, group_flag_kernel, one_counter_grid(g.nbins, 256), 256,
-            (const uint32_t *)g.count, g.nbins, gkind, pkind, num, den, thr, coo.nrows, coo.ncols, g.flag,
-            &flags->scalar[1]);
-  return g;
-}
-
-// what the histogram, the flags and (for DIA) the positions and slab indices of the groups take from Env::temp
-static size_t group_temp_bytes(int64_t nbins) {
-  return 4 * Env::granule(4 * (size_t)nbins) + Env::granule(4 * ((size_t)nbins / 1024 + 64)) + 8 * Env::granule(256);
-}
-
 us_status convert_dia(Env &env, const us_coo &coo, const Plan &plan, const us_format_desc &desc,
                       Flags *flags, us_formatted **out) {
-  GroupCounts g = group_flags(env, coo, G_DIAG, -1, 0, 1, 0, flags);
+  const GroupMap g = group_map(env, coo, G_DIAG, -1, 0, 1, 0, flags, true);
   if (!env.ok()) return env.status;
-  return dia_from_flags(env, coo, plan, desc, flags, g.flag, out, nullptr, nullptr);
+  return dia_from_flags(env, coo, plan, desc, flags, g, out, nullptr, nullptr);
 }
 
 us_status decompose_sum(Env &env, const us_coo &coo, const Plan &pa, const us_format_desc &da, const Plan &pb,
                         const us_format_desc &db, const us_predicate &pred, int gkind, us_formatted **oa,
                         us_formatted **ob) {
-  env.reserve(group_temp_bytes(gkind == G_DIAG ? coo.nrows + coo.ncols - 1 : (gkind == G_ROW ? coo.nrows : coo.ncols)));
+  const bool slab = gkind == G_DIAG && pa.pattern == P_DIA;
+  env.reserve(group_temp_bytes(group_bins(coo, gkind)));
   Flags *flags = new_flags(env);
   if (!env.ok()) return env.status;
-  GroupCounts g = group_flags(env, coo, gkind, pred.kind, pred.num, pred.den, pred.abs, flags);
+  const GroupMap g = group_map(env, coo, gkind, pred.kind, pred.num, pred.den, pred.abs, flags, slab);
   if (!env.ok()) return env.status;
   const int64_t n = coo.nnz;
   CooLists la, lb;
   int64_t na = 0, nb = 0;
   us_status st;
   DiaPending pending;
-  if (gkind == G_DIAG && pa.pattern == P_DIA) {
+  if (slab) {
     // part A goes straight into the slab while part B is collected, in one pass over the input; its flags are read
     // after part B's conversion has been enqueued (and has read its own): an input that fails them (a coordinate
     // out of range reaches no slab slot and no list; a duplicate is a slot written twice) is reported then
-    st = dia_from_flags(env, coo, pa, da, flags, g.flag, oa, &lb, &nb, &pending);
+    st = dia_from_flags(env, coo, pa, da, flags, g, oa, &lb, &nb, &pending);
   } else {
     Flags h{};
     if (!read_flags(env, flags, &h)) return env.status;
     if (flag_status(h) != US_OK) return flag_status(h);
     na = h.scalar[1]; nb = n - na;
     la = alloc_lists(env, na); lb = alloc_lists(env, nb);
-    int32_t *gmap = env.temp<int32_t>(g.nbins), *cursors = env.temp<int32_t>(2);
+    int32_t *cursors = env.temp<int32_t>(2);
     st = env.status;
     if (st == US_OK) {
       fill_u32(env, (uint32_t *)cursors, 2, 0u);
-      US_LAUNCH(env, "group_map", 12.0 * g.nbins, group_map_kernel, ceil_div<int64_t>(g.nbins, 256), 256,
-                (const int32_t *)g.flag, (const int32_t *)g.flag, g.nbins, gmap, (const int32_t *)nullptr, (int64_t)0, (int32_t *)nullptr);
       if (n > 0)
         US_LAUNCH(env, "split", 24.0 * n, (split_kernel<false>), ceil_div<int64_t>(n, SP_TILE), SP_T, coo.row, coo.col,
-                  coo.val, n, gkind, (uint32_t)coo.nrows, (const int32_t *)gmap, (int64_t)0, 0, (float *)nullptr,
+                  coo.val, n, gkind, (uint32_t)coo.nrows, g.number, (int64_t)0, 0, (float *)nullptr,
                   (uint8_t *)nullptr, la, lb, cursors, flags);
       st = env.status;
     }

@@ -1,4 +1,5 @@
-"""Numbers of the diagonals that a query keeps: counts of diagonals around the tiles of its kernels, few and all of them kept."""
+"""Numbers of the groups a query keeps, and pointers over more groups than there are entries: group counts around the tiles of
+their kernels, few and all groups kept, entries in one group or spread."""
 import numpy as np
 import pytest
 
@@ -50,3 +51,22 @@ def test_diagonals(ctx, nrows, ncols, kept):
         left = np.lexsort((row + d, row))
         left = left[~inside[left]]
         assert np.array_equal(H.host(b.idx(0)), row[left]) and np.array_equal(H.host(b.val()), val[left])
+
+
+@pytest.mark.parametrize("nrows,n", [(1, 0), (2046, 5), (2047, 2046), (2048, 300), (2049, 1), (70_001, 5_000), (70_001, 70_000),
+                                     (1_000_003, 40_000)])
+@pytest.mark.parametrize("where", ["spread", "first row", "last row", "crowded"])
+def test_pointers_over_more_rows_than_entries(ctx, nrows, n, where):
+    from paper_2403_05802_amd import binding as B
+    rng = np.random.default_rng(n)
+    ncols = 80_000
+    row = {"spread": rng.integers(0, nrows, n), "first row": np.zeros(n, np.int64), "last row": np.full(n, nrows - 1),
+           "crowded": nrows // 2 + rng.integers(0, min(nrows, 3), n) * (nrows > 6)}[where]
+    key = np.unique(row * ncols + rng.permutation(ncols)[:n])
+    row, col = key // ncols, key % ncols
+    order = rng.permutation(row.size)
+    val = rng.uniform(0.5, 1, row.size).astype(np.float32)
+    g = B.us_convert(ctx, nrows, ncols, H.dev(row[order].astype(np.int32)), H.dev(col[order].astype(np.int32)), H.dev(val[order]),
+                     B.us_desc_preset(B.US_F_CSR))
+    assert np.array_equal(H.host(g.ptr(1)), np.searchsorted(row, np.arange(nrows + 1)))
+    assert np.array_equal(H.host(g.idx(1)), col) and np.array_equal(H.host(g.val()), val)

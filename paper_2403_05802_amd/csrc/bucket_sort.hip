@@ -722,7 +722,9 @@ __global__ __launch_bounds__(SM_T) void bucket_sample_kernel(BkArgs a) {
   const int tid = threadIdx.x;
   const uint32_t p = blockIdx.x;
   const uint32_t np = COO ? 1u : a.totals[2];   // (written by an earlier kernel of the call whatever happens)
-  if (gave_up(a, true)) return;
+  if (COO && a.clear_flags) {   // the first kernel of the call, in one workgroup: the flags start here, not in a launch of their own
+    if (tid < (int)(sizeof(Flags) / 4)) reinterpret_cast<uint32_t *>(a.flags)[tid] = 0;   // (the scans' barriers lie before any flag)
+  } else if (gave_up(a, true)) return;
   if (p >= np) return;
   const uint2 origin = np != a.share.count ? a.origin[p] : make_uint2(p, 0u);
   {
@@ -1090,7 +1092,7 @@ void bucket_sort(Env &env, const int32_t *row, const int32_t *col, const float *
   a.tile_parent = env.temp<uint32_t>(b.max_tiles);
   a.rec2 = env.temp<uint2>((size_t)b.max_regions * BK_CAP);
   if (!env.ok()) return;
-  a.clear_flags = b.nsamples && out.clear_flags;
+  a.clear_flags = (b.nsamples || b.direct) && out.clear_flags;   // by the first kernel
   if (out.clear_flags && !a.clear_flags) fill_u32(env, (uint32_t *)flags, sizeof(Flags) / 4, 0u);
   if (!b.direct) {
     if (b.nsamples) US_LAUNCH(env, "bucket_probe", 8.0 * b.nsamples, bucket_probe_kernel, ceil_div<uint32_t>(b.nsamples, BL_T), BL_T, a);

@@ -310,6 +310,9 @@ __global__ __launch_bounds__(COO_T) void coo_spmv_kernel(const int32_t *row, con
 
 // ------------------------------------------------------------------ DIA: y[i] (+)= sum_k val[k*nrows+i] * x[i+off_k]
 // (the DIA variant keeps the slab indexed by column: val[k*ncols + j], j = i + off_k)
+// The loads of DIA_STEP diagonals go out together: one after the other, every diagonal is a trip to memory (seven diagonals,
+// 777,777 rows: 9.0 -> 7.2 us).
+constexpr int DIA_STEP = 8;
 __global__ __launch_bounds__(256) void dia_spmv_kernel(const int32_t *off, const float *val, int64_t ndiag,
                                                       int64_t nrows, int64_t ncols, int by_col, const float *x,
                                                       float *y, int accumulate) {
@@ -317,12 +320,22 @@ __global__ __launch_bounds__(256) void dia_spmv_kernel(const int32_t *off, const
   if (i >= nrows) return;
   float s = accumulate ? y[i] : 0.f;
   const int64_t L = by_col ? ncols : nrows;
-  for (int64_t k = 0; k < ndiag; ++k) {
-    int64_t j = i + off[k];
-    if (j >= 0 && j < ncols) s += val[k * L + (by_col ? j : i)] * x[j];
+  for (int64_t k0 = 0; k0 < ndiag; k0 += DIA_STEP) {
+    float v[DIA_STEP], xv[DIA_STEP];
+#pragma unroll
+    for (int q = 0; q < DIA_STEP; ++q) {
+      const int64_t k = k0 + q, j = i + (k < ndiag ? off[k] : 0);
+      const bool in = k < ndiag && j >= 0 && j < ncols;
+      v[q] = in ? val[k * L + (by_col ? j : i)] : 0.f;
+      xv[q] = in ? x[j] : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < DIA_STEP; ++q) s += v[q] * xv[q];
   }
   y[i] = s;
 }
+
+typedef float Float4Unaligned __attribute__((ext_vector_type(4), aligned(4)));
 
 // Row-indexed slab, nrows a multiple of 4: four rows per thread, the slab read as 16-byte vectors (the summation
 // order per row is the same as above: diagonals in ascending order of offset)
@@ -331,17 +344,32 @@ __global__ __launch_bounds__(256) void dia_spmv4_kernel(const int32_t *off, cons
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= nrows) return;
   float4 s = accumulate ? *reinterpret_cast<const float4 *>(y + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int64_t k = 0; k < ndiag; ++k) {
-    const int64_t j = i + off[k];
-    if (j + 3 < 0 || j >= ncols) continue;
-    const float4 v = *reinterpret_cast<const float4 *>(val + k * nrows + i);
-    if (j >= 0 && j + 3 < ncols) {
-      s.x += v.x * x[j]; s.y += v.y * x[j + 1]; s.z += v.z * x[j + 2]; s.w += v.w * x[j + 3];
-    } else {
-      if (j >= 0 && j < ncols) s.x += v.x * x[j];
-      if (j + 1 >= 0 && j + 1 < ncols) s.y += v.y * x[j + 1];
-      if (j + 2 >= 0 && j + 2 < ncols) s.z += v.z * x[j + 2];
-      if (j + 3 >= 0 && j + 3 < ncols) s.w += v.w * x[j + 3];
+  constexpr int STEP = DIA_STEP / 2;
+  for (int64_t k0 = 0; k0 < ndiag; k0 += STEP) {
+    float4 v[STEP];
+    Float4Unaligned xv[STEP];
+#pragma unroll
+    for (int q = 0; q < STEP; ++q) {
+      const int64_t k = k0 + q, j = i + (k < ndiag ? off[k] : 0);
+      const bool in = k < ndiag && j + 3 >= 0 && j < ncols;
+      v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+      xv[q] = Float4Unaligned{0.f, 0.f, 0.f, 0.f};
+      if (in) v[q] = *reinterpret_cast<const float4 *>(val + k * nrows + i);
+      if (in && j >= 0 && j + 3 < ncols) {
+        xv[q] = *reinterpret_cast<const Float4Unaligned *>(x + j);
+      } else if (in) {   // at an end of the row: what lies outside does not count, whatever the slab holds there
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool on = j + e >= 0 && j + e < ncols;
+          xv[q][e] = on ? x[j + e] : 0.f;
+          float *ve = e == 0 ? &v[q].x : e == 1 ? &v[q].y : e == 2 ? &v[q].z : &v[q].w;
+          *ve = on ? *ve : 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < STEP; ++q) {
+      s.x += v[q].x * xv[q][0]; s.y += v[q].y * xv[q][1]; s.z += v[q].z * xv[q][2]; s.w += v[q].w * xv[q][3];
     }
   }
   *reinterpret_cast<float4 *>(y + i) = s;

@@ -25,7 +25,8 @@ __device__ __forceinline__ uint32_t group_bin(int gkind, uint32_t r, uint32_t c,
 // them a third starts when the others have ended, on a half-empty part.  256 threads x 16 entries and 768 workgroups /
 // 1024 x 4 and 768 / 1024 x 4 and 512, us: 14.8 M entries on seven diagonals and a few beside them 92 / 62 / 53; rows of a
 // sorted list of 16.5 M entries 149 / 126 / 108; diagonals, rows, columns of 16.8 M uniformly spread entries, where every
-// entry is an atomic of its own, 649, 649, 645 / 634, 634, 635 / 633, 636, 636; 41 k entries 26 / 12 / 12.  Rows of an
+// entry is an atomic of its own, 649, 649, 645 / 634, 634, 635 / 633, 636, 636; 41 k entries 26 / 12 / 12.  With the next tile's
+// entries on their way while a tile is counted (their loads waited behind the barriers of the one before) the first is 46 -> 39.  Rows of an
 // unsorted list whose first rows hold hundreds of thousands of entries and the many next ones some thousands, too few of
 // a tile to stay in the table: 2039 / 2069 / 2070, bound by atomics that meet on those counters.
 constexpr int GH_T = 1024, GH_IPT = 4, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8, GH_GRID = 512;
@@ -40,18 +41,27 @@ __global__ __launch_bounds__(GH_T) void group_hist_kernel(const int32_t *row, co
   for (int i = threadIdx.x; i < GH_SLOTS; i += GH_T) { s_key[i] = 0xFFFFFFFFu; s_cnt[i] = 0; }
   __syncthreads();
   bool bad = false;
-  for (int64_t base = (int64_t)blockIdx.x * GH_TILE; base < n; base += (int64_t)gridDim.x * GH_TILE) {
+  uint32_t r[GH_IPT], c[GH_IPT];
+  auto load = [&](int64_t base) {
+#pragma unroll
+    for (int k = 0; k < GH_IPT; ++k) {
+      const int64_t i = base + k * GH_T + threadIdx.x;
+      r[k] = i < n ? (uint32_t)row[i] : 0u; c[k] = i < n ? (uint32_t)col[i] : 0u;
+    }
+  };
+  const int64_t stride = (int64_t)gridDim.x * GH_TILE;
+  load((int64_t)blockIdx.x * GH_TILE);
+  for (int64_t base = (int64_t)blockIdx.x * GH_TILE; base < n; base += stride) {
     uint32_t bin[GH_IPT];
 #pragma unroll
     for (int k = 0; k < GH_IPT; ++k) {
-      int64_t i = base + k * GH_T + threadIdx.x;
       bin[k] = 0xFFFFFFFFu;
-      if (i < n) {
-        uint32_t r = (uint32_t)row[i], c = (uint32_t)col[i];
-        if (r >= nrows || c >= ncols) bad = true;
-        else bin[k] = group_bin(gkind, r, c, nrows);
+      if (base + k * GH_T + threadIdx.x < n) {
+        if (r[k] >= nrows || c[k] >= ncols) bad = true;
+        else bin[k] = group_bin(gkind, r[k], c[k], nrows);
       }
     }
+    load(base + stride);   // on its way while this tile is counted
 #pragma unroll 1
     for (int k = 0; k < GH_IPT; ++k) {
       const uint32_t b = bin[k];
@@ -67,7 +77,7 @@ __global__ __launch_bounds__(GH_T) void group_hist_kernel(const int32_t *row, co
       if (!done) atomicAdd(&count[b], 1u);
     }
     __syncthreads();
-    const bool last = base + (int64_t)gridDim.x * GH_TILE >= n;
+    const bool last = base + stride >= n;
     for (int i = threadIdx.x; i < GH_SLOTS; i += GH_T) {
       const uint32_t c = s_cnt[i];
       if (s_key[i] != 0xFFFFFFFFu && (last || c < GH_HOT)) {

@@ -890,7 +890,8 @@ __global__ __launch_bounds__(BX_T) void bucket_split_kernel(BkArgs a) {
 // six workgroups per CU (71 registers; 8 at 64 with spills: 149 and 369).  A workgroup takes some 12 us, mostly a chain of
 // dependent steps, so what counts is how many are resident: counters and values share their place in LDS, bins that
 // crowd are not cut again; children of 2048 entries on average with twice the LDS: 297 and 810, of 1024 with room for 2560
-// or 3072: 237 and 621, 282 and 750.  (Bins by row or range, cut again by smallest and largest key until none
+// or 3072: 237 and 621, 282 and 750; as many workgroups as are resident, walking the children with the next one's entries on
+// their way, some 40 and 110 us longer (the loop's state takes the registers that the steps need).  (Bins by row or range, cut again by smallest and largest key until none
 // holds more than 9: 177 and 602, three quarters of it LDS atomics and reads that meet in a bank; four digit passes of
 // ballot ranking would take 280 vector instructions an entry, this takes 200.)
 constexpr int BF_T = 256, BF_IPT = BK_CAP / BF_T;

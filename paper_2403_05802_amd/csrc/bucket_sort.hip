@@ -338,16 +338,14 @@ __global__ __launch_bounds__(BS_T) void bucket_scan_kernel(BkArgs a) {
 // in LDS, every parent's run written as one piece behind the workgroup's earlier ones.  Its runs are short (12 entries of a
 // tile of 12,288 in 1024 parents) and leave lines partly written: ngroups x nparents of them are open at a time, 128 bytes
 // each, against 4 MB of L2 per XCD.  By the counters it writes a quarter more than the records take (400 MB for 320, 40 M
-// entries) and fetches the list once, 3.4 TB/s in all: scattered pieces are what is left.  Few
+// entries) and fetches the list once, 3.4 TB/s in all: scattered pieces and, with one workgroup per CU, its phases one
+// after the other are what is left.  Few
 // workgroups and large tiles where there are many entries.  512 threads x 8 entries and 768 workgroups / 1024 x 8 and 256
 // / 1024 x 12 and 256, us: 40 M entries, 1024 parents 329 / 283 / 260; 16.8 M, 512 parents 110 / 98 / 101; 4 M, 128
-// parents 22 / 24 / 28; 1 M 12 / 15 / 17.  With one workgroup per CU nothing else runs while a tile is read, so the next one is
-// on its way while a tile is written: 16.8 M 102 -> 91, 40 M as it was (the three workgroups of 512 fill each other's gaps,
-// and have no registers for it).
+// parents 22 / 24 / 28; 1 M 12 / 15 / 17.
 template <int T, int IPT, int MAXX>
 __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkArgs a) {
   constexpr int TILE = T * IPT, MAXP = BK_MAXSHARES + MAXX, PER = (MAXP + T - 1) / T;
-  static_assert(TILE < 0xFFFF && MAXP < 0xFFFF, "two 16-bit halves, and all ones is neither");
   __shared__ uint2 s_rec[TILE];
   __shared__ uint16_t s_bin[TILE];
   __shared__ uint32_t s_cnt[MAXP];    // entries of the tile per parent, then where they start in the tile
@@ -381,41 +379,37 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
     for (int q = 0; q < PER; ++q) { next[q] += run; run += t[q]; }
   }
   bool bad = false;
-  uint32_t r[IPT], c[IPT], v[IPT];   // the tile's entries: of the whole tile four neighbours a load, of the last one whatever is there
-  auto whole = [&](uint32_t base) { return a.coo_vec && end - base >= (uint32_t)TILE; };
-  auto load = [&](uint32_t base) {
-    if (whole(base)) {
+  for (uint32_t base = begin; base < end; base += TILE) {
+    const uint32_t in_tile = min((uint32_t)TILE, end - base);
+    uint32_t key[IPT], val[IPT], bin[IPT], arr[IPT];
+    if (a.coo_vec && in_tile == (uint32_t)TILE) {
       const uint4 *r4 = reinterpret_cast<const uint4 *>(a.row + base), *c4 = reinterpret_cast<const uint4 *>(a.col + base);
       const uint4 *v4 = reinterpret_cast<const uint4 *>(a.val + base);
+      uint4 rr[IPT / 4], cc[IPT / 4], vv[IPT / 4];
+#pragma unroll
+      for (int q = 0; q < IPT / 4; ++q) { rr[q] = r4[q * T + tid]; cc[q] = c4[q * T + tid]; vv[q] = v4[q * T + tid]; }
 #pragma unroll
       for (int q = 0; q < IPT / 4; ++q) {
-        const uint4 x = r4[q * T + tid], y = c4[q * T + tid], z = v4[q * T + tid];
-        r[4 * q] = x.x; r[4 * q + 1] = x.y; r[4 * q + 2] = x.z; r[4 * q + 3] = x.w;
-        c[4 * q] = y.x; c[4 * q + 1] = y.y; c[4 * q + 2] = y.z; c[4 * q + 3] = y.w;
-        v[4 * q] = z.x; v[4 * q + 1] = z.y; v[4 * q + 2] = z.z; v[4 * q + 3] = z.w;
+        const uint32_t r[4] = {rr[q].x, rr[q].y, rr[q].z, rr[q].w}, c[4] = {cc[q].x, cc[q].y, cc[q].z, cc[q].w};
+        const uint32_t v[4] = {vv[q].x, vv[q].y, vv[q].z, vv[q].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          bad |= coo_out_of_range(a.ks, r[e], c[e]);
+          bin[4 * q + e] = share_of_entry(a, r[e], c[e], &key[4 * q + e]);
+          val[4 * q + e] = v[e];
+        }
       }
     } else {
 #pragma unroll
       for (int j = 0; j < IPT; ++j) {
         const uint32_t i = j * T + tid;
-        const bool in = i < end - base;
-        r[j] = in ? (uint32_t)a.row[base + i] : 0u; c[j] = in ? (uint32_t)a.col[base + i] : 0u; v[j] = in ? a.val[base + i] : 0u;
-      }
-    }
-  };
-  constexpr bool AHEAD = T == 1024;
-  if (AHEAD && begin < end) load(begin);
-  for (uint32_t base = begin; base < end; base += TILE) {
-    const uint32_t in_tile = min((uint32_t)TILE, end - base);
-    const bool all = whole(base);
-    if (!AHEAD) load(base);
-    uint32_t key[IPT], val[IPT], bin[IPT];
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      bin[j] = 0xFFFFFFFFu; key[j] = 0; val[j] = v[j];
-      if (all || j * T + tid < in_tile) {
-        bad |= coo_out_of_range(a.ks, r[j], c[j]);
-        bin[j] = share_of_entry(a, r[j], c[j], &key[j]);
+        bin[j] = 0xFFFFFFFFu; key[j] = 0; val[j] = 0;
+        if (i < in_tile) {
+          const uint32_t r = (uint32_t)a.row[base + i], c = (uint32_t)a.col[base + i];
+          bad |= coo_out_of_range(a.ks, r, c);
+          bin[j] = share_of_entry(a, r, c, &key[j]);
+          val[j] = a.val[base + i];
+        }
       }
     }
     if (cut) {
@@ -425,12 +419,11 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
     }
     __syncthreads();   // s_cnt is clear, the previous tile is written
 #pragma unroll
-    for (int j = 0; j < IPT; ++j)   // the place among the tile's entries of the parent goes above its number
-      if (bin[j] != 0xFFFFFFFFu) bin[j] |= atomicAdd(&s_cnt[bin[j]], 1u) << 16;
+    for (int j = 0; j < IPT; ++j) arr[j] = bin[j] != 0xFFFFFFFFu ? atomicAdd(&s_cnt[bin[j]], 1u) : 0u;
     __syncthreads();
-    uint32_t cnt[PER], sum = 0;
+    uint32_t c[PER], sum = 0;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) { cnt[q] = tid * PER + q < MAXP ? s_cnt[tid * PER + q] : 0u; sum += cnt[q]; }
+    for (int q = 0; q < PER; ++q) { c[q] = tid * PER + q < MAXP ? s_cnt[tid * PER + q] : 0u; sum += c[q]; }
     uint32_t run = scan_one_barrier<T>(sum, s_wave[1]);
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -438,19 +431,18 @@ __global__ __launch_bounds__(T, T == 512 ? 6 : 4) void bucket_scatter_kernel(BkA
         s_cnt[tid * PER + q] = run;
         s_goff[tid * PER + q] = next[q] - run;
       }
-      next[q] += cnt[q]; run += cnt[q];
+      next[q] += c[q]; run += c[q];
     }
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       if (bin[j] != 0xFFFFFFFFu) {
-        const uint32_t pos = s_cnt[bin[j] & 0xFFFFu] + (bin[j] >> 16);
+        const uint32_t pos = s_cnt[bin[j]] + arr[j];
         s_rec[pos] = make_uint2(key[j], val[j]);
         s_bin[pos] = (uint16_t)bin[j];
       }
     }
     __syncthreads();
-    if (AHEAD && base + TILE < end) load(base + TILE);   // on its way while this tile is written
 #pragma unroll
     for (int j = 0; j < IPT; ++j) {
       const uint32_t i = j * T + tid;

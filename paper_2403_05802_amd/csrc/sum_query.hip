@@ -26,7 +26,7 @@ __device__ __forceinline__ uint32_t group_bin(int gkind, uint32_t r, uint32_t c,
 // 1024 x 4 and 768 / 1024 x 4 and 512, us: 14.8 M entries on seven diagonals and a few beside them 92 / 62 / 53; rows of a
 // sorted list of 16.5 M entries 149 / 126 / 108; diagonals, rows, columns of 16.8 M uniformly spread entries, where every
 // entry is an atomic of its own, 649, 649, 645 / 634, 634, 635 / 633, 636, 636; 41 k entries 26 / 12 / 12.  With the next tile's
-// entries on their way while a tile is counted (their loads waited behind the barriers of the one before) the first is 46 -> 39.  Rows of an
+// entries on their way while a tile is counted (their loads waited behind the barriers of the one before) the first is 45 -> 35.  Rows of an
 // unsorted list whose first rows hold hundreds of thousands of entries and the many next ones some thousands, too few of
 // a tile to stay in the table: 2039 / 2069 / 2070, bound by atomics that meet on those counters.
 constexpr int GH_T = 1024, GH_IPT = 4, GH_TILE = GH_T * GH_IPT, GH_SLOTS = 1024, GH_PROBES = 8, GH_GRID = 512;

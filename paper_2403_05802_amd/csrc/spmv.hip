@@ -46,10 +46,14 @@ __global__ __launch_bounds__(256) void merge_path_split_kernel(const int32_t *pt
 }
 
 // A row that a tile boundary cuts: its pieces go to carry slots that a second launch adds up, or (WHOLE) the workgroup in
-// whose tile the row ends goes over the earlier part of it again and no second launch is needed.  Rows of up to WHOLE_COLS
-// entries (there are no more columns, and equal coordinates are refused): at most WHOLE_COLS / MP_T products a thread on top,
-// on average half a row a workgroup; longer rows would make one workgroup's chain of loads longer than the launch.
-constexpr int64_t WHOLE_COLS = 4 * MP_TILE;
+// whose tile the row ends goes over the earlier part of it again and no second launch is needed.  What that reads again is a
+// row's earlier part per tile, at most the columns that there are (equal coordinates are refused), and a workgroup that does
+// it is a serial loop longer than the others.  So WHOLE is for products in which the second launch counts (one round of
+// workgroups), and where all that may be read again, tiles * columns, is less than the launch costs; us, carries / WHOLE, where
+// 8192 columns have 245 tiles, of rows of 10 / 1024 / 8192 entries: 9.6 / 7.6, 9.1 / 7.6, 8.9 / 8.3 (342 tiles, 8192: 9.4 /
+// 11.0); 4096 columns, 489 tiles, rows of 4096: 8.9 / 7.9 (733 tiles: 9.2 / 11.4); 978 tiles of rows of 1024: 10.3 / 8.5 (1467:
+// 11.2 / 11.4); 30 M entries, rows of 64 / 512 / 2048: 68 / 72, 64 / 73, 60 / 86; the smallest, 41 k entries in rows of ten: 8.4 / 7.0.
+constexpr int64_t WHOLE_COLS = 4 * MP_TILE, WHOLE_TILES = 1024, WHOLE_AGAIN = 1 << 21;
 
 template <bool INDIRECT_ROWS, bool WHOLE>
 __global__ __launch_bounds__(MP_T) void csr_spmv_kernel(const int32_t *ptr, const int32_t *idx, const float *val,
@@ -194,7 +198,7 @@ static void spmv_compressed(Env &env, const us_formatted &A, const int32_t *ptr,
   const double bytes = 8.0 * nnz + 4.0 * (nrows_stored + 1) + 4.0 * (A.swapped ? A.nrows : A.ncols) + 4.0 * nrows_stored;
   const int acc = accumulate ? 1 : 0;
   const int32_t *split = A.mp_split;
-  if (A.ncols <= WHOLE_COLS) {
+  if (A.ncols <= WHOLE_COLS && nb <= WHOLE_TILES && nb * A.ncols <= WHOLE_AGAIN) {
     int32_t *no_row = nullptr;
     float *no_val = nullptr;
     if (row_ids) US_LAUNCH(env, "spmv_csr", bytes, (csr_spmv_kernel<true, true>), nb, MP_T, ptr, idx, val, row_ids, split, nrows_stored, nnz, x, y, acc, no_row, no_val);

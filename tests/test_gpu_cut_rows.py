@@ -1,5 +1,6 @@
 """SpMV over compressed rows where the workgroup that ends a row goes over the part of it that earlier workgroups hold: rows of
-up to several tiles, column counts on both sides of where that ends, empty rows, rows that end on a tile's edge, accumulation."""
+up to several tiles, column counts and tile counts on both sides of where that ends, empty rows, rows that end on a tile's edge,
+accumulation."""
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -57,3 +58,28 @@ def test_rows_that_end_at_a_tile(ctx, first):
 def test_short_rows(ctx):
     for nrows in (1, 2, 2047, 2048, 2049, 30_000):
         check(ctx, np.random.default_rng(nrows).integers(0, 3, nrows), 300, nrows)
+
+
+# rows of `length` entries are length + 1 steps each: 128 rows of 4095 are 256 tiles of 2048 steps
+@pytest.mark.parametrize("ncols,length,nrows,launches", [
+    (8192, 4095, 128, 1), (8192, 4095, 129, 2),       # tiles * columns on both sides of 2 M
+    (4096, 4095, 256, 1), (4096, 4095, 257, 2),
+    (2048, 2047, 1024, 1), (2048, 2047, 1025, 2),     # 1024 tiles, and one more
+    (100, 63, 32768, 1), (100, 63, 32800, 2)])
+def test_one_launch_only_where_little_is_read_again(ctx, ncols, length, nrows, launches):
+    from paper_2403_05802_amd import binding as B
+    rng = np.random.default_rng(length)
+    start, step = rng.integers(0, ncols, nrows), 1 + 2 * rng.integers(0, ncols // 2, nrows) if ncols & (ncols - 1) == 0 else np.ones(nrows, int)
+    col = ((start[:, None] + np.arange(length) * step[:, None]) % ncols).ravel().astype(np.int32)   # distinct within a row
+    row = np.repeat(np.arange(nrows), length).astype(np.int32)
+    val, x = rng.uniform(-1, 1, row.size).astype(np.float32), rng.uniform(-1, 1, ncols).astype(np.float32)
+    A = sp.csr_matrix((val.astype(np.float64), (row, col)), shape=(nrows, ncols))
+    profiled = B.Context("cuda:0", profile=True)
+    g = B.us_convert(profiled, nrows, ncols, H.dev(row), H.dev(col), H.dev(val), B.us_desc_preset(B.US_F_CSR))
+    y = torch.full((nrows,), 7.0, device="cuda")
+    torch.cuda.synchronize()
+    profiled.profile_reset()
+    B.us_spmv(profiled, g, H.dev(x), y)
+    H.assert_product(H.host(y), A @ x.astype(np.float64), abs(A) @ np.abs(x).astype(np.float64), H.row_terms(nrows, row), f"{nrows} x {ncols}")
+    assert sum(k["launches"] for k in profiled.profile_report()) == launches
+    g.free()

@@ -41,6 +41,11 @@ __device__ __forceinline__ uint32_t wave_inclusive_max_dpp(uint32_t v) {
   return v;
 }
 
+// Parents between the ends of a tile up to which all of them are walked, 512 at a time (0.85 us); beyond, every entry looks for its
+// own, at some 4 us whatever lies between.  us, walk / search, N = 1: 20,000 entries of 200,000 / 400,000 / 1 M rows (5,120 / 10,240 /
+// 25,600 parents a tile) 14.5 / 13.4, 18.6 / 14.7, 31.1 / 14.0; 150,000 of 1 M / 400,000 (3,413 / 1,365) 18.4 / 17.9, 16.7 / 17.2;
+// 500 of 10 M 8,500 / 16.
+constexpr int32_t PS_FAR = 4096;
 constexpr int PS_WAVES = 8, PS_T = 64 * PS_WAVES, PS_GROUPS = 4 * PS_WAVES, PS_TILE = PS_T;
 static_assert(PS_GROUPS < 64, "bit masks over the groups of a workgroup");
 
@@ -212,6 +217,33 @@ __global__ __launch_bounds__(256) void tile_bounds_kernel(const int32_t *ptr, in
   bounds[k] = make_int2((int32_t)before, (int32_t)behind);
 }
 
+// The parent of every thread's entry, all of them held by parents from `before` to `last`: 512 pointers between the two through
+// LDS, then, for every entry by itself, three at a time of those between its neighbours among the 512.
+__device__ __forceinline__ uint32_t find_parent(const int32_t *ptr, int32_t before, int32_t last, uint32_t e, bool live, uint32_t *s_pivot) {
+  const int32_t *end = ptr + before + 1;
+  const uint32_t span = (uint32_t)(last - before), step = (span + PS_T - 1) / PS_T, mine = (threadIdx.x + 1) * step - 1;
+  s_pivot[threadIdx.x] = mine < span ? (uint32_t)end[mine] : 0xFFFFFFFFu;   // (entries have 31 bits)
+  __syncthreads();
+  uint32_t c = 0;   // pivots at or below e
+#pragma unroll
+  for (int d = PS_T / 2; d >= 1; d >>= 1)
+    if (s_pivot[c + d - 1] <= e) c += d;
+  if (s_pivot[c] <= e) ++c;
+  uint32_t lo = min(c * step, span), hi = live ? min(lo + step - 1, span) : lo;
+  while (lo < hi) {
+    const uint32_t q = (hi - lo + 3) / 4;
+    uint32_t n = 0;
+#pragma unroll
+    for (uint32_t j = 1; j <= 3; ++j) {
+      const uint32_t p = lo + j * q - 1;
+      n += p < hi && (uint32_t)end[p] <= e;
+    }
+    lo += n * q;
+    if (n < 3) hi = min(hi, lo + q - 1);
+  }
+  return (uint32_t)before + lo;
+}
+
 // A workgroup takes 512 consecutive entries and a panel of 16 * VEC * H columns, a wavefront 64 entries, sixteen lanes
 // ("a group") sixteen of them one after the other, VEC * H columns a lane.  So a load of one instruction brings pieces of four
 // rows of X, and column, value and row of an entry reach the lanes of their group as DPP operands (row_newbcast), not as LDS
@@ -253,10 +285,11 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   const float v = live ? __builtin_nontemporal_load(job.val + e) : 0.f;
   int32_t r = -1;
   bool start = true, next_same;     // the entry is the first of its row; the row of the tile's last entry goes on behind it
-  int2 b0, b1;
+  int2 b;                           // parents of the last entry before the tile (of its first one, if there is none) and of its last one
   if constexpr (SEARCH) {
     s_mark[threadIdx.x] = 0;
-    b0 = job.bounds[tile]; b1 = job.bounds[tile + 1];
+    const int2 b1 = job.bounds[tile + 1];
+    b = make_int2(job.bounds[tile].x, b1.x);
     next_same = t1 < n && b1.x == b1.y;
   } else {
     if (live) r = job.row[e];
@@ -268,18 +301,30 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   const char *X = reinterpret_cast<const char *>(job.X);
   char *Y = reinterpret_cast<char *>(job.Y);
   const auto xo = Walk::offset(c, job.ldx);
+  // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an entry's
+  // row is the last mark up to it
+  auto look_up = [&]() {
+    if (b.y - b.x > PS_FAR) {
+      const uint32_t p = find_parent(job.ptr, b.x, b.y, e, live, s_mark);
+      const bool first = live && (uint32_t)job.ptr[p] == e;
+      __syncthreads();
+      s_mark[threadIdx.x] = first ? p : 0;
+    }
+  };
+  if constexpr (SEARCH && H > 1) look_up();   // (behind the gathers it takes more registers than these shapes have left)
   walk.first_gathers(X, xo);
   if constexpr (SEARCH) {
-    // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries);
-    // an entry's row is the last mark up to it
-    __syncthreads();
-    for (int32_t p = b0.x + 1 + (int32_t)threadIdx.x; p <= b1.x; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
+    if constexpr (H == 1) look_up();
+    if (b.y - b.x <= PS_FAR) {
+      __syncthreads();
+      for (int32_t p = b.x + 1 + (int32_t)threadIdx.x; p <= b.y; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
+    }
     __syncthreads();
     const uint32_t mark = s_mark[threadIdx.x];
     uint32_t last = wave_inclusive_max_dpp(mark);
     if (lane == 63) s_last[w] = last;
     __syncthreads();
-    last = max(last, (uint32_t)b0.x);
+    last = max(last, (uint32_t)b.x);
 #pragma unroll
     for (int q = 0; q < PS_WAVES - 1; ++q)
       if (q < w) last = max(last, s_last[q]);

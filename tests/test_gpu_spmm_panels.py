@@ -1,6 +1,6 @@
 """SpMM over entries grouped by row, a panel of columns of X at a time: column counts around every panel shape, rows and lists
-around the sixteen entries of a lane group, the 64 of a wavefront and the 512 of a tile, rows of X and Y that begin at any float,
-and operands of more than 4 GB."""
+around the sixteen entries of a lane group, the 64 of a wavefront and the 512 of a tile, few entries in very many rows, rows of X
+and Y that begin at any float, and operands of more than 4 GB."""
 import numpy as np
 import pytest
 import scipy.sparse as sp
@@ -91,6 +91,65 @@ def test_rows_around_groups_wavefronts_and_tiles(ctx, pattern, N, ldx, ldy, offs
 def test_columns_around_every_panel_shape(ctx, N, ldx):
     rng = np.random.default_rng(N)
     check(ctx, matrix("long rows cut anywhere", rng), N, ldx, N + (N & 1), 0, rng, f"N={N}")
+
+
+def spread(rows, rng, ncols=6000):
+    """an entry in every row of the (ascending) list, columns distinct within a row"""
+    row = np.asarray(rows)
+    first = np.searchsorted(row, row)
+    start = rng.integers(0, ncols - 1, row.size)[first]
+    col = (1 + (start + np.arange(row.size) - first) % (ncols - 1)).astype(np.int32)
+    return np.zeros(int(row.max()) + 1, dtype=np.int32), row.astype(np.int32), col, rng.uniform(-1, 1, row.size).astype(np.float32), ncols
+
+
+def blocks_of_rows(rows, per_row, gap):
+    """a third of the rows, `gap` empty ones, another third, ..."""
+    r = np.arange(rows)
+    return (r + r // (rows // 3 + 1) * gap).repeat(per_row)
+
+
+# the parents between the first and the last entry of a tile are walked up to 4096 of them, beyond that every entry looks for its own
+@pytest.mark.parametrize("last", [4094, 4095, 4096, 4097, 4098, 513 * 512, 100_000])
+def test_few_entries_around_the_longest_walk(ctx, last):
+    rng = np.random.default_rng(last)
+    check(ctx, spread([0, last], rng), 1, 1, 1, 0, rng, f"rows 0 and {last}")
+    inner = np.sort(rng.integers(0, last + 1, 700))
+    check(ctx, spread(np.concatenate([[0, 0], inner, [last]]), rng), 17, 17, 17, 0, rng, f"700 entries of {last + 1} rows")
+
+
+@pytest.mark.parametrize("rows,per_row,gap,N", [(25_000, 6, 30_000, 3), (25_000, 6, 30_000, 100), (25_000, 6, 30_000, 130), (30_000, 18, 5_000, 1),
+                                                (6_000, 90, 4_500, 300)])
+def test_gaps_inside_tiles_of_long_lists(ctx, rows, per_row, gap, N):
+    rng = np.random.default_rng(rows + N)
+    check(ctx, spread(blocks_of_rows(rows, per_row, gap), rng), N, N, N, 0, rng, f"{rows} rows of {per_row}, gaps of {gap}, N={N}")
+
+
+@pytest.mark.parametrize("where", ["strays", "at both ends"])
+def test_few_entries_in_ten_million_rows(ctx, where):
+    from paper_2403_05802_amd import binding as B
+    rng = np.random.default_rng(3)
+    nrows = 10_000_000
+    rows = np.sort(rng.integers(0, nrows, 1000)) if where == "strays" else np.concatenate([np.arange(300), np.arange(nrows - 300, nrows)]).repeat(3)
+    _, row, col, val, ncols = spread(rows, rng)
+    X = rng.uniform(-1, 1, (ncols, 2)).astype(np.float32)
+    g = B.us_convert(ctx, nrows, ncols, H.dev(row), H.dev(col), H.dev(val), B.us_desc_preset(B.US_F_CSR))
+    Xd, Y = H.dev(X), torch.full((nrows, 2), 3.0, device="cuda")
+    B.us_spmm(ctx, g, Xd, Y, accumulate=True)
+    used = np.unique(row)
+    A = sp.csr_matrix((val.astype(np.float64), (np.searchsorted(used, row), col)), shape=(used.size, ncols))
+    X64 = X.astype(np.float64)
+    H.assert_product(H.host(Y[H.dev(used).long()]), A @ X64 + 3.0, abs(A) @ np.abs(X64) + 3.0, H.row_terms(used.size, np.searchsorted(used, row), 1)[:, None], where)
+    assert int((Y != 3.0).any(1).sum()) <= used.size
+    # the time does not depend on the rows without entries: some 20 us (8,500 where a workgroup walked them)
+    best, a, b = float("inf"), torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(5):
+        a.record()
+        B.us_spmm(ctx, g, Xd, Y, accumulate=True)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    assert best < 1.0, f"{best} ms"
+    g.free()
 
 
 def test_operands_of_more_than_4_gb(ctx):

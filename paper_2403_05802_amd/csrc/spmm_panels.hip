@@ -56,8 +56,9 @@ struct PanelWalk {
   typedef typename PanelVec<VEC>::reg V;
   typedef typename PanelVec<VEC>::mem M;
   static constexpr int PART = 16 * VEC, PW = PART * H;
-  // first column of the lane in every part of the panel.  Not FULL: where the columns end inside the vector the lane takes the
-  // last VEC of them (N >= VEC): what it shares with the lane before it both compute, and store, alike
+  // first column of the lane in every part of the panel.  Not FULL: where the panel's columns end inside the vector the lane takes
+  // the last VEC of them: what it shares with the lane before it both compute, and store, alike.  No two panels share a column (they
+  // would both add to it): where fewer than VEC are left for the last panel, the one before it leaves it VEC (N >= VEC)
   uint32_t c0[H];
   uint64_t cols_ok[H];              // lanes with a column
   V x[16][H], acc[H];
@@ -68,9 +69,12 @@ struct PanelWalk {
       c0[h] = panel * PW + h * PART + s * VEC;
       cols_ok[h] = ~0ull;
       if constexpr (!FULL) {
-        const bool ok = c0[h] < N;
-        cols_ok[h] = __ballot(ok);
-        c0[h] = ok ? min(c0[h], N - VEC) : 0;
+        uint32_t begin = panel * PW, end = min(begin + PW, N);
+        if (end < N && N - end < VEC) end = N - VEC;
+        begin = min(begin, N - VEC);
+        c0[h] = begin + h * PART + s * VEC;
+        cols_ok[h] = __ballot(c0[h] < end);
+        c0[h] = min(c0[h], end - VEC);
       }
     }
   }
@@ -193,7 +197,8 @@ __device__ __forceinline__ PanelRuns panel_runs(const uint32_t *s_starts) {
 struct PanelJob {
   const int32_t *row;      // COO: row of every entry, else null
   const int32_t *ptr, *ids;// compressed rows: children of parent p are [ptr[p], ptr[p + 1]); row of a stored row, or null
-  const int2 *bounds;      // compressed rows: parents of the entries around every tile boundary (tile_bounds_kernel)
+  const int2 *bounds;      // compressed rows: parents of the entries around every tile boundary (tile_bounds_kernel), or null: the
+  int64_t nparents;        // workgroup looks for its own among all parents
   const int32_t *col;
   const float *val;
   uint32_t n;              // entries
@@ -217,8 +222,34 @@ __global__ __launch_bounds__(256) void tile_bounds_kernel(const int32_t *ptr, in
   bounds[k] = make_int2((int32_t)before, (int32_t)behind);
 }
 
-// The parent of every thread's entry, all of them held by parents from `before` to `last`: 512 pointers between the two through
-// LDS, then, for every entry by itself, three at a time of those between its neighbours among the 512.
+// The parent of an entry e is the number of parents p with ptr[p + 1] <= e.  Of two entries at once, by all threads of the
+// workgroup: 512 places at a time, three trips to memory for 16 M parents where a bisection takes 24.
+__device__ __forceinline__ int2 find_parents(const int32_t *ptr, uint32_t nparents, uint32_t e0, uint32_t e1) {
+  const uint32_t e[2] = {e0, e1};
+  uint32_t lo[2] = {0, 0}, hi[2] = {nparents - 1, nparents - 1};   // (an entry that no other parent holds is the last one's)
+  while (lo[0] < hi[0] || lo[1] < hi[1]) {
+    bool below[2];
+    uint32_t step[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      step[q] = (hi[q] - lo[q] + PS_T - 1) / PS_T;
+      const uint32_t p = lo[q] + (threadIdx.x + 1) * step[q] - 1;
+      below[q] = lo[q] < hi[q] && p < hi[q] && (uint32_t)ptr[p + 1] <= e[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t c = __syncthreads_count(below[q]);
+      if (lo[q] < hi[q]) {
+        lo[q] += c * step[q];
+        hi[q] = min(hi[q], lo[q] + step[q] - 1);
+      }
+    }
+  }
+  return make_int2((int32_t)lo[0], (int32_t)lo[1]);
+}
+
+// The same of every thread's entry, all of them held by parents from `before` to `last`: 512 pointers between the two through LDS,
+// then, for every entry by itself, three at a time of those between its neighbours among the 512.
 __device__ __forceinline__ uint32_t find_parent(const int32_t *ptr, int32_t before, int32_t last, uint32_t e, bool live, uint32_t *s_pivot) {
   const int32_t *end = ptr + before + 1;
   const uint32_t span = (uint32_t)(last - before), step = (span + PS_T - 1) / PS_T, mine = (threadIdx.x + 1) * step - 1;
@@ -288,9 +319,11 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   int2 b;                           // parents of the last entry before the tile (of its first one, if there is none) and of its last one
   if constexpr (SEARCH) {
     s_mark[threadIdx.x] = 0;
-    const int2 b1 = job.bounds[tile + 1];
-    b = make_int2(job.bounds[tile].x, b1.x);
-    next_same = t1 < n && b1.x == b1.y;
+    if (job.bounds) {
+      const int2 b1 = job.bounds[tile + 1];
+      b = make_int2(job.bounds[tile].x, b1.x);
+      next_same = t1 < n && b1.x == b1.y;
+    }
   } else {
     if (live) r = job.row[e];
     if (live && e > 0) start = job.row[e - 1] != r;
@@ -304,6 +337,10 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an entry's
   // row is the last mark up to it
   auto look_up = [&]() {
+    if (!job.bounds) {
+      b = find_parents(job.ptr, (uint32_t)job.nparents, t0 > 0 ? t0 - 1 : 0, t1 - 1);
+      next_same = t1 < n && (uint32_t)job.ptr[b.y + 1] > t1;
+    }
     if (b.y - b.x > PS_FAR) {
       const uint32_t p = find_parent(job.ptr, b.x, b.y, e, live, s_mark);
       const bool first = live && (uint32_t)job.ptr[p] == e;
@@ -544,21 +581,37 @@ static PanelShape panel_shape(int64_t cols, bool whole_lines) {
 void panel_spmm(Env &env, const us_formatted &A, const int32_t *row, const StoredRows *rows, const int32_t *col, const char *name,
                 const float *X, int64_t N, int64_t ldx, float *Y, int64_t ldy, bool add) {
   const int64_t n = A.nnz, tiles = ceil_div<int64_t>(n, PS_TILE), carry_ld = ceil_div<int64_t>(N, 32) * 32;
-  const size_t b_bounds = rows ? Env::granule((tiles + 1) * sizeof(int2)) : 0, b_crow = Env::granule(tiles * 2 * sizeof(int32_t));
+  // A short list is bound by its launches and by the chain of loads inside a workgroup, not by lines.
+  // - While all workgroups of panels of 64 columns are resident at once (512, two on a CU) these are taken whatever the lines: sixteen
+  //   rows of X in flight instead of four.  Beyond 256 columns rows with pointers stop at half of that (us, panels of 64 / 256: 50,000
+  //   entries of 5,000 / 2 M rows, N = 300 21.3 / 19.3, 59.6 / 54.7), lists with a row per entry, which look for nothing, at four
+  //   times (50,000 of 8,000 rows, N = 1000 42.9 / 48.8).
+  // - What is left of the columns beyond whole panels is one more panel of the same launch, and not a launch of its own, up to 1024
+  //   workgroups; 2048 where Y is added to, which hides the idle lanes.  Rest apart -> this, us: 20,000 entries of 8,000 rows, N = 300
+  //   31 -> 17, N = 1000 44 -> 27; 150,000 of 8,000 / 2 M, added, N = 300 45 -> 37, 186 -> 150; 400,000 of 200,000, added, 219 -> 193;
+  //   but 1 M of 100,000, not added, 227 -> 248.
+  // - Up to 1024 workgroups each finds its parents itself, some 3 us, where a launch of its own for the table of all takes 14: 50,000
+  //   entries of 5,000 rows, N = 1 16.5 -> 13.5, 150,000 of 2 M 31 -> 23; but 1 M of 100,000 (1,954 workgroups) 25.0 -> 28.2.
+  constexpr int64_t RESIDENT = 512;
+  const bool whole_lines = (uintptr_t)X % 128 == 0 && ldx % 32 == 0;
+  const bool narrow = whole_lines || tiles * ceil_div<int64_t>(N, 64) <= (N <= 256 ? RESIDENT : rows ? RESIDENT / 2 : 4 * RESIDENT);
+  const int64_t workgroups = tiles * ceil_div<int64_t>(N, panel_shape(N, narrow).width());
+  const bool one_launch = workgroups <= (add ? 4 : 2) * RESIDENT, table = rows && workgroups > 2 * RESIDENT;
+  const size_t b_bounds = table ? Env::granule((tiles + 1) * sizeof(int2)) : 0, b_crow = Env::granule(tiles * 2 * sizeof(int32_t));
   char *ws = (char *)ensure_workspace(env, A, b_bounds + b_crow + tiles * 2 * carry_ld * sizeof(float));
   if (!env.ok()) return;
   int2 *bounds = (int2 *)ws;
   int32_t *carry_row = (int32_t *)(ws + b_bounds);
   float *carry = (float *)(ws + b_bounds + b_crow);
-  if (rows)
+  if (table)
     US_LAUNCH(env, "spmm_bounds", 8.0 * tiles, tile_bounds_kernel, ceil_div<int64_t>(tiles + 1, 256), 256, rows->ptr, A.nmajor, n,
               tiles, bounds);
   const bool wide = (double)A.ncols * ldx * 4 >= 4294967296.0 || (double)A.nrows * ldy * 4 >= 4294967296.0;
-  const bool whole_lines = (uintptr_t)X % 128 == 0 && ldx % 32 == 0;
-  for (int64_t c = 0; c < N && env.ok();) {   // whole panels first, then what is left in one of the width that fits it
-    const PanelShape shape = panel_shape(N - c, whole_lines);
-    const int64_t pw = shape.width(), npanels = std::min<int64_t>(std::max<int64_t>((N - c) / pw, 1), 65535), cols = std::min(npanels * pw, N - c);
-    PanelJob job{row, rows ? rows->ptr : nullptr, rows ? rows->row_ids : nullptr, bounds, col, (const float *)A.val, (uint32_t)n,
+  for (int64_t c = 0; c < N && env.ok();) {   // else: whole panels first, then what is left in one of the width that fits it
+    const PanelShape shape = panel_shape(N - c, narrow);
+    const int64_t pw = shape.width(), npanels = std::min<int64_t>(std::max<int64_t>(one_launch ? ceil_div<int64_t>(N - c, pw) : (N - c) / pw, 1), 65535);
+    const int64_t cols = std::min(npanels * pw, N - c);
+    PanelJob job{row, rows ? rows->ptr : nullptr, rows ? rows->row_ids : nullptr, table ? bounds : nullptr, A.nmajor, col, (const float *)A.val, (uint32_t)n,
                  X + c, ldx, Y + c, ldy, (uint32_t)cols, c == 0 ? carry_row : nullptr, carry + c, carry_ld};
     const dim3 grid((unsigned)(ceil_div<int64_t>(tiles, 8) * 8), (unsigned)npanels);
     LaunchScope ls(env, name, 12.0 * n + 4.0 * cols * (A.ncols + A.nrows));

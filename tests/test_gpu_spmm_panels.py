@@ -83,8 +83,7 @@ def test_rows_around_groups_wavefronts_and_tiles(ctx, pattern, N, ldx, ldy, offs
     check(ctx, matrix(pattern, rng), N, ldx, ldy, offset, rng, f"{pattern} N={N}")
 
 
-# whole lines (rows of X begin at multiples of 32 floats): panels of 64 columns; others: one of 128, then of 256; a rest in the
-# panel that fits it
+# (a list this short: panels of 64 columns, the last one with what is left)
 @pytest.mark.parametrize("N,ldx", [(15, 15), (16, 16), (17, 17), (18, 20), (31, 31), (32, 32), (33, 64), (63, 63), (65, 65), (66, 96),
                                    (127, 127), (128, 128), (129, 129), (131, 160), (191, 192), (193, 193), (255, 255), (256, 256),
                                    (257, 257), (258, 260), (321, 321), (384, 385), (515, 515)])
@@ -122,6 +121,39 @@ def test_few_entries_around_the_longest_walk(ctx, last):
 def test_gaps_inside_tiles_of_long_lists(ctx, rows, per_row, gap, N):
     rng = np.random.default_rng(rows + N)
     check(ctx, spread(blocks_of_rows(rows, per_row, gap), rng), N, N, N, 0, rng, f"{rows} rows of {per_row}, gaps of {gap}, N={N}")
+
+
+# long lists, 1055 tiles: whole lines (rows of X begin at multiples of 32 floats) in panels of 64 columns, others in one of 128 or
+# of 256 and more of these; a rest in the panel that fits it
+@pytest.mark.parametrize("N,ldx", [(64, 64), (70, 96), (95, 96), (130, 160), (65, 65), (200, 200), (256, 257), (272, 272), (288, 290), (301, 301),
+                                   (350, 350), (450, 450)])
+def test_columns_of_long_lists(ctx, N, ldx):
+    rng = np.random.default_rng(N)
+    check(ctx, spread(np.arange(6000).repeat(90), rng), N, ldx, N, 0, rng, f"long list N={N}")
+
+
+# tiles * panels on both sides of what is resident at once (512), half, twice and four times as much
+@pytest.mark.parametrize("entries,N", [(512 * 256, 100), (512 * 256 + 1, 100), (512 * 51, 300), (512 * 51 + 1, 300), (512 * 204, 300), (512 * 205, 300),
+                                       (512 * 512, 300), (512 * 512 + 1, 300), (512 * 1024, 30), (512 * 1024 + 1, 30)])
+def test_lists_around_the_short_ones(ctx, entries, N):
+    rng = np.random.default_rng(entries)
+    check(ctx, spread(np.sort(rng.integers(0, 20_000, entries)), rng), N, N, N, 0, rng, f"{entries} entries N={N}")
+
+
+@pytest.mark.parametrize("entries,N", [(500, 1), (500, 300), (20_000, 64), (50_000, 200), (50_000, 300), (150_000, 1), (150_000, 300)])
+def test_short_lists_take_one_launch_and_the_fixup(entries, N):
+    from paper_2403_05802_amd import binding as B
+    rng = np.random.default_rng(entries)
+    profiled = B.Context("cuda:0", profile=True)
+    _, row, col, val, ncols = spread(np.concatenate([np.sort(rng.integers(0, 8000, entries - 1)), [7999]]), rng)
+    X, Y = torch.ones((ncols, N), device="cuda"), torch.zeros((8000, N), device="cuda")
+    for desc, name in zip(descs()[:2], ("spmm_csr", "spmm_coo")):
+        g = B.us_convert(profiled, 8000, ncols, H.dev(row), H.dev(col), H.dev(val), desc)
+        torch.cuda.synchronize()
+        profiled.profile_reset()
+        B.us_spmm(profiled, g, X, Y, accumulate=True)
+        assert {k["kernel"]: k["launches"] for k in profiled.profile_report()} == {name: 1, "spmm_rows_fixup": 1}
+        g.free()
 
 
 @pytest.mark.parametrize("where", ["strays", "at both ends"])

@@ -257,9 +257,13 @@ __global__ __launch_bounds__(256) void lower_bound_ptr_kernel(const int32_t *maj
 }
 // Fewer entries than groups: a workgroup takes LB_TILE groups, all threads together look for the entries of those (256
 // places at a time, three trips to memory for 16 M entries), then every group is searched among them, in LDS where they fit.
-// A search per group over the whole list is a chain of some twenty loads and bound by those: 2.1 M groups over 147 k entries
-// 27 -> 16 us.  (Where entries are many, a tile's would not fit, and its few workgroups would search longer.)
+// A search per group over the whole list is a chain of some twenty loads and bound by those once its workgroups are more than are
+// resident at once (2048 of 256 groups); below, this one's few workgroups with their barriers take longer.  us, a search per
+// group / this: 100,000 groups over 1,000 / 97,000 entries 6.7 / 8.3, 8.9 / 14.1; 400,000 over 40,000 9.6 / 10.5; 700,000 over
+// 70,000 14.1 / 13.3; 2 M over 200,000 / 1.9 M 28 / 18, 34 / 26; 4 M over 400,000 53 / 27.  (Where entries are many, a tile's
+// would not fit, and its few workgroups would search longer.)
 constexpr int LB_T = 256, LB_IPT = 8, LB_TILE = LB_T * LB_IPT;
+constexpr int64_t LB_GROUPS = 1 << 19;
 __global__ __launch_bounds__(LB_T) void sparse_ptr_kernel(const int32_t *major, int64_t n, int64_t ngroups, int32_t *ptr) {
   __shared__ int32_t s_major[LB_TILE];
   const int tid = threadIdx.x;
@@ -313,7 +317,7 @@ __global__ __launch_bounds__(LB_T) void sparse_ptr_kernel(const int32_t *major, 
   }
 }
 void lower_bound_ptr(Env &env, const int32_t *sorted_major, int64_t n, int64_t ngroups, int32_t *ptr) {
-  if (n < ngroups) {
+  if (n < ngroups && ngroups >= LB_GROUPS) {
     US_LAUNCH(env, "ptr_sparse", 4.0 * n + 4.0 * (ngroups + 1), sparse_ptr_kernel, ceil_div<int64_t>(ngroups + 1, LB_TILE), LB_T,
               sorted_major, n, ngroups, ptr);
     return;

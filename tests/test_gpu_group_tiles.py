@@ -2,6 +2,7 @@
 their kernels, few and all groups kept, entries in one group or spread."""
 import numpy as np
 import pytest
+import torch
 
 import helpers as H
 
@@ -54,7 +55,7 @@ def test_diagonals(ctx, nrows, ncols, kept):
 
 
 @pytest.mark.parametrize("nrows,n", [(1, 0), (2046, 5), (2047, 2046), (2048, 300), (2049, 1), (70_001, 5_000), (70_001, 70_000),
-                                     (1_000_003, 40_000)])
+                                     (524_287, 5_000), (524_288, 5_000), (526_335, 80_000), (526_336, 300), (526_337, 1), (1_000_003, 40_000)])
 @pytest.mark.parametrize("where", ["spread", "first row", "last row", "crowded"])
 def test_pointers_over_more_rows_than_entries(ctx, nrows, n, where):
     from paper_2403_05802_amd import binding as B
@@ -70,3 +71,16 @@ def test_pointers_over_more_rows_than_entries(ctx, nrows, n, where):
                      B.us_desc_preset(B.US_F_CSR))
     assert np.array_equal(H.host(g.ptr(1)), np.searchsorted(row, np.arange(nrows + 1)))
     assert np.array_equal(H.host(g.idx(1)), col) and np.array_equal(H.host(g.val()), val)
+
+
+@pytest.mark.parametrize("nrows,n,name", [(3_000, 300, "ptr_lower_bound"), (100_000, 70_000, "ptr_lower_bound"), (400_000, 40_000, "ptr_lower_bound"),
+                                          (700_000, 70_000, "ptr_sparse")])
+def test_rows_are_searched_a_tile_at_a_time_only_where_there_are_many(nrows, n, name):
+    from paper_2403_05802_amd import binding as B
+    rng = np.random.default_rng(n)
+    profiled = B.Context("cuda:0", profile=True)
+    row = rng.permutation(nrows)[:n].astype(np.int32)
+    g = B.us_convert(profiled, nrows, 1000, H.dev(row), H.dev(row % 1000), torch.ones(n, device="cuda"), B.us_desc_preset(B.US_F_CSR))
+    assert [k["kernel"] for k in profiled.profile_report() if k["kernel"].startswith("ptr_")] == [name]
+    assert np.array_equal(H.host(g.ptr(1)), np.searchsorted(np.sort(row), np.arange(nrows + 1)))
+    g.free()

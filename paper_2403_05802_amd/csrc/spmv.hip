@@ -5,6 +5,7 @@
 #include "device.h"
 
 #include <atomic>
+#include <type_traits>
 
 namespace us {
 
@@ -314,9 +315,9 @@ __global__ __launch_bounds__(COO_T) void coo_spmv_kernel(const int32_t *row, con
 
 // ------------------------------------------------------------------ DIA: y[i] (+)= sum_k val[k*nrows+i] * x[i+off_k]
 // (the DIA variant keeps the slab indexed by column: val[k*ncols + j], j = i + off_k)
-// The loads of DIA_STEP diagonals go out together: one after the other, every diagonal is a trip to memory (seven diagonals,
-// 777,777 rows: 9.0 -> 7.2 us).
-constexpr int DIA_STEP = 8;
+// The loads of eight diagonals go out together: one after the other, every diagonal is a trip to memory.  What is left takes four
+// or one, since places without a diagonal cost instructions too.  777,777 rows, 3 / 5 / 7 / 9 / 33 diagonals, us: one by one 4.7 / 4.8 /
+// 7.4 / 9.7 / 29.1 (a launch of anything takes 4.1 to 4.8), always eight 5.3 / 5.5 / 5.9 / 8.2 / 20.7, this 4.6 / 4.9 / 6.0 / 7.0 / 20.0.
 __global__ __launch_bounds__(256) void dia_spmv_kernel(const int32_t *off, const float *val, int64_t ndiag,
                                                       int64_t nrows, int64_t ncols, int by_col, const float *x,
                                                       float *y, int accumulate) {
@@ -324,18 +325,23 @@ __global__ __launch_bounds__(256) void dia_spmv_kernel(const int32_t *off, const
   if (i >= nrows) return;
   float s = accumulate ? y[i] : 0.f;
   const int64_t L = by_col ? ncols : nrows;
-  for (int64_t k0 = 0; k0 < ndiag; k0 += DIA_STEP) {
-    float v[DIA_STEP], xv[DIA_STEP];
+  auto step = [&](int64_t k0, auto steps) {
+    constexpr int S = decltype(steps)::value;
+    float v[S], xv[S];
 #pragma unroll
-    for (int q = 0; q < DIA_STEP; ++q) {
+    for (int q = 0; q < S; ++q) {
       const int64_t k = k0 + q, j = i + (k < ndiag ? off[k] : 0);
       const bool in = k < ndiag && j >= 0 && j < ncols;
       v[q] = in ? val[k * L + (by_col ? j : i)] : 0.f;
       xv[q] = in ? x[j] : 0.f;
     }
 #pragma unroll
-    for (int q = 0; q < DIA_STEP; ++q) s += v[q] * xv[q];
-  }
+    for (int q = 0; q < S; ++q) s += v[q] * xv[q];
+  };
+  int64_t k0 = 0;
+  for (; ndiag - k0 > 5; k0 += 8) step(k0, std::integral_constant<int, 8>());
+  if (ndiag - k0 > 1) { step(k0, std::integral_constant<int, 4>()); k0 += 4; }
+  if (ndiag > k0) step(k0, std::integral_constant<int, 1>());
   y[i] = s;
 }
 
@@ -348,12 +354,12 @@ __global__ __launch_bounds__(256) void dia_spmv4_kernel(const int32_t *off, cons
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= nrows) return;
   float4 s = accumulate ? *reinterpret_cast<const float4 *>(y + i) : make_float4(0.f, 0.f, 0.f, 0.f);
-  constexpr int STEP = DIA_STEP / 2;
-  for (int64_t k0 = 0; k0 < ndiag; k0 += STEP) {
-    float4 v[STEP];
-    Float4Unaligned xv[STEP];
+  auto step = [&](int64_t k0, auto steps) {
+    constexpr int S = decltype(steps)::value;
+    float4 v[S];
+    Float4Unaligned xv[S];
 #pragma unroll
-    for (int q = 0; q < STEP; ++q) {
+    for (int q = 0; q < S; ++q) {
       const int64_t k = k0 + q, j = i + (k < ndiag ? off[k] : 0);
       const bool in = k < ndiag && j + 3 >= 0 && j < ncols;
       v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -372,10 +378,13 @@ __global__ __launch_bounds__(256) void dia_spmv4_kernel(const int32_t *off, cons
       }
     }
 #pragma unroll
-    for (int q = 0; q < STEP; ++q) {
+    for (int q = 0; q < S; ++q) {
       s.x += v[q].x * xv[q][0]; s.y += v[q].y * xv[q][1]; s.z += v[q].z * xv[q][2]; s.w += v[q].w * xv[q][3];
     }
-  }
+  };
+  int64_t k0 = 0;
+  for (; ndiag - k0 > 1; k0 += 4) step(k0, std::integral_constant<int, 4>());
+  if (ndiag > k0) step(k0, std::integral_constant<int, 1>());
   *reinterpret_cast<float4 *>(y + i) = s;
 }
 

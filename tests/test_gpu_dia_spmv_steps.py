@@ -15,7 +15,7 @@ def ctx():
     return B.Context("cuda:0")
 
 
-@pytest.mark.parametrize("ndiag", [1, 3, 4, 5, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("ndiag", [1, 2, 3, 4, 5, 6, 7, 8, 9, 13, 14, 16, 17, 18])
 @pytest.mark.parametrize("nrows,ncols", [(1, 1), (3, 9), (8, 8), (256, 250), (1021, 1030), (1024, 1024), (4096, 300)])
 def test_diagonals(ctx, nrows, ncols, ndiag):
     from paper_2403_05802_amd import binding as B

@@ -73,8 +73,9 @@ struct PanelWalk {
         if (end < N && N - end < VEC) end = N - VEC;
         begin = min(begin, N - VEC);
         c0[h] = begin + h * PART + s * VEC;
-        cols_ok[h] = __ballot(c0[h] < end);
-        c0[h] = min(c0[h], end - VEC);
+        const bool ok = c0[h] < end;
+        cols_ok[h] = __ballot(ok);
+        c0[h] = ok ? min(c0[h], end - VEC) : begin;   // (the others load as well: from a line that is loaded anyway)
       }
     }
   }

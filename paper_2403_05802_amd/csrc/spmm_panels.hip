@@ -286,15 +286,16 @@ __device__ __forceinline__ uint32_t find_parent(const int32_t *ptr, int32_t befo
 // memory-side cache answers, hits at 23 to 27 TB/s (measured with bare gathers of 64 to 1024 bytes from spans of 2 MB to 1 GB;
 // pieces of 64 bytes cost as much as of 128).  So the columns go by panels, all entries for a panel, then for the next: in a
 // panel of 64 columns a row of X takes two lines instead of its whole length, and the entries in flight on an XCD (which walks a
-// contiguous range of tiles) find more rows with local columns again: 25.6 M entries of long rows, N = 128, 6 -> 27 % hits, 6.9 TB/s
-// of misses; 5.2 M, N = 1000, none -> 40 %.  The next bound is instruction issue (a wave64 instruction holds its SIMD for four
-// cycles): where a run ends is kept as scalar masks, rows and panels that need no bounds have none.
+// contiguous range of tiles) find more rows with local columns again.  By counters: 25.6 M entries of long rows, N = 128, two panels
+// of 64: 27 % of 113 M requests hit, 10.6 GB fetched and stored at 7.1 TB/s; 5.2 M, N = 1000, rows off whole lines,
+// three panels of 256 and one of 232: 32 and 34 % hit, 13.2 and 4.0 GB at 7.4 TB/s (with whole rows of X 10 % and 23.4 GB).  The next bound is instruction
+// issue (a wave64 instruction holds its SIMD for four cycles): where a run ends is kept as scalar masks, rows and panels that need no
+// bounds have none.
 //
 // us, one wavefront per 256 entries with whole rows of X (64 lanes across 64, 128 or 256 columns) -> this; 5.2 M entries of
 // 262,144 rows, local columns, N = 8 / 16 / 32 / 64 / 128 / 256 / 1000: 251 / 248 / 246 / 248 / 385 / 745 / 3010 -> 81 / 84 / 96 /
 // 154 / 277 / 535 / 2400; 40 M of 2 M rows, N = 16 / 64 / 128: 1560 / 1679 / 2732 -> 526 / 1205 / 2349; 10 M uniformly drawn,
-// N = 32 / 128 / 500: 424 / 808 / 3448 -> 222 / 750 / 3180; 400 k entries, N = 8 / 64 / 200 / 1000: 44 / 46 / 83 / 233 ->
-// 25 / 30 / 55 / 187; 60 k, N = 32 25 -> 21.  Tried and left: four wavefronts a workgroup (0 to 7 % slower), a persistent grid
+// N = 32 / 128 / 500: 424 / 808 / 3448 -> 222 / 750 / 3180.  Tried and left: four wavefronts a workgroup (0 to 7 % slower), a persistent grid
 // that fetches the next tile's entries early (15 % slower), three workgroups per CU by spilling four registers (6 % slower),
 // less resident by LDS (no faster), X copied into panels of whole lines (no faster than wider panels, and a copy of X), and the
 // rows of 512 entries and more taken out, ordered by ranges of columns that an L2 holds and summed range by range (their hits

@@ -1,6 +1,6 @@
 """SpMM over the entry-balanced layouts (CSR, COO, DCSR) on a power-law matrix of a few million entries with rows of
-thousands of entries and an X larger than the L2s: every output element against the fp64 definition, for the
-vector widths 1 / 2 / 4 columns per lane, ragged N, strided X and Y, accumulation, bit-for-bit reproducibility."""
+thousands of entries and an X larger than the L2s: every output element against the fp64 definition, for panels of
+several widths, ragged N, strided X and Y, accumulation, bit-for-bit reproducibility."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,8 @@ def matrix():
     return W.cfg2_powerlaw(n=300_000, target_nnz=3_000_000, s=1.6, max_len=20000, index=8)
 
 
-# (256 and 492, four columns per lane and slices that are full: fewer workgroups resident for layouts with row pointers)
+# (a long list: 40 one panel of 64 columns, 130 one of 256, 256 four of 64, its rows of X being whole lines, 260 and 492 one of 256 and the
+# rest in a launch of its own)
 @pytest.mark.parametrize("N", [40, 130, 256, 260, 492])
 def test_powerlaw_spmm_every_output(ctx, matrix, N):
     from paper_2403_05802_amd import binding as B

@@ -42,9 +42,9 @@ __device__ __forceinline__ uint32_t wave_inclusive_max_dpp(uint32_t v) {
 }
 
 // Parents between the ends of a tile up to which all of them are walked, 512 at a time (0.85 us); beyond, every entry looks for its
-// own, at some 4 us whatever lies between.  us, walk / search, N = 1: 20,000 entries of 200,000 / 400,000 / 1 M rows (5,120 / 10,240 /
-// 25,600 parents a tile) 14.5 / 13.4, 18.6 / 14.7, 31.1 / 14.0; 150,000 of 1 M / 400,000 (3,413 / 1,365) 18.4 / 17.9, 16.7 / 17.2;
-// 500 of 10 M 8,500 / 16.
+// own, at some 3 us whatever lies between.  us, walk / search, N = 1: 20,000 entries of 200,000 / 400,000 / 1 M rows (5,120 / 10,240 /
+// 25,600 parents a tile) 13.3 / 12.2, 17.9 / 12.9, 29.8 / 12.3; 150,000 of 1 M / 400,000 (3,413 / 1,365) 17.2 / 16.8, 15.1 / 15.7;
+// 500 of 10 M 8,470 / 14.4.
 constexpr int32_t PS_FAR = 4096;
 constexpr int PS_WAVES = 8, PS_T = 64 * PS_WAVES, PS_GROUPS = 4 * PS_WAVES, PS_TILE = PS_T;
 static_assert(PS_GROUPS < 64, "bit masks over the groups of a workgroup");
@@ -225,23 +225,31 @@ __global__ __launch_bounds__(256) void tile_bounds_kernel(const int32_t *ptr, in
 
 // The parent of an entry e is the number of parents p with ptr[p + 1] <= e.  Of two entries at once, by all threads of the
 // workgroup: 512 places at a time, three trips to memory for 16 M parents where a bisection takes 24.
-__device__ __forceinline__ int2 find_parents(const int32_t *ptr, uint32_t nparents, uint32_t e0, uint32_t e1) {
+__device__ __forceinline__ int2 find_parents(const int32_t *ptr, uint32_t nparents, uint32_t e0, uint32_t e1, uint32_t *s_count) {
   const uint32_t e[2] = {e0, e1};
   uint32_t lo[2] = {0, 0}, hi[2] = {nparents - 1, nparents - 1};   // (an entry that no other parent holds is the last one's)
   while (lo[0] < hi[0] || lo[1] < hi[1]) {
-    bool below[2];
-    uint32_t step[2];
+    uint32_t step[2], p[2];
+    int32_t end[2];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
+    for (int q = 0; q < 2; ++q) {   // both loads before either is looked at: at a place that there is, whether it counts or not
       step[q] = (hi[q] - lo[q] + PS_T - 1) / PS_T;
-      const uint32_t p = lo[q] + (threadIdx.x + 1) * step[q] - 1;
-      below[q] = lo[q] < hi[q] && p < hi[q] && (uint32_t)ptr[p + 1] <= e[q];
+      p[q] = lo[q] + (threadIdx.x + 1) * step[q] - 1;
+      end[q] = ptr[min(p[q], nparents - 1) + 1];
     }
+    uint32_t c = 0;   // of the wavefront, of either entry in 16 bits
+#pragma unroll
+    for (int q = 0; q < 2; ++q) c |= (uint32_t)__popcll(__ballot(lo[q] < hi[q] && p[q] < hi[q] && (uint32_t)end[q] <= e[q])) << (16 * q);
+    if (lane_id() == 0) s_count[wave_id()] = c;
+    __syncthreads();
+    c = 0;
+#pragma unroll
+    for (int w = 0; w < PS_WAVES; ++w) c += s_count[w];
+    __syncthreads();
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      const uint32_t c = __syncthreads_count(below[q]);
       if (lo[q] < hi[q]) {
-        lo[q] += c * step[q];
+        lo[q] += (c >> (16 * q) & 0xFFFFu) * step[q];
         hi[q] = min(hi[q], lo[q] + step[q] - 1);
       }
     }
@@ -264,12 +272,15 @@ __device__ __forceinline__ uint32_t find_parent(const int32_t *ptr, int32_t befo
   uint32_t lo = min(c * step, span), hi = live ? min(lo + step - 1, span) : lo;
   while (lo < hi) {
     const uint32_t q = (hi - lo + 3) / 4;
-    uint32_t n = 0;
+    uint32_t p[3], n = 0;
+    int32_t v[3];
 #pragma unroll
-    for (uint32_t j = 1; j <= 3; ++j) {
-      const uint32_t p = lo + j * q - 1;
-      n += p < hi && (uint32_t)end[p] <= e;
+    for (uint32_t j = 0; j < 3; ++j) {   // (as above)
+      p[j] = lo + (j + 1) * q - 1;
+      v[j] = end[min(p[j], span - 1)];
     }
+#pragma unroll
+    for (uint32_t j = 0; j < 3; ++j) n += p[j] < hi && (uint32_t)v[j] <= e;
     lo += n * q;
     if (n < 3) hi = min(hi, lo + q - 1);
   }
@@ -288,9 +299,9 @@ __device__ __forceinline__ uint32_t find_parent(const int32_t *ptr, int32_t befo
 // panel of 64 columns a row of X takes two lines instead of its whole length, and the entries in flight on an XCD (which walks a
 // contiguous range of tiles) find more rows with local columns again.  By counters: 25.6 M entries of long rows, N = 128, two panels
 // of 64: 27 % of 113 M requests hit, 10.6 GB fetched and stored at 7.1 TB/s; 5.2 M, N = 1000, rows off whole lines,
-// three panels of 256 and one of 232: 32 and 34 % hit, 13.2 and 4.0 GB at 7.4 TB/s (with whole rows of X 10 % and 23.4 GB).  The next bound is instruction
-// issue (a wave64 instruction holds its SIMD for four cycles): where a run ends is kept as scalar masks, rows and panels that need no
-// bounds have none.
+// three panels of 256 and one of 232: 32 and 34 % hit, 13.2 and 4.0 GB at 7.4 TB/s (with whole rows of X 10 % and 23.4 GB).  The next bound is
+// instruction issue (a wave64 instruction holds its SIMD for four cycles): where a run ends is kept as scalar masks, rows and panels
+// that need no bounds have none.
 //
 // us, one wavefront per 256 entries with whole rows of X (64 lanes across 64, 128 or 256 columns) -> this; 5.2 M entries of
 // 262,144 rows, local columns, N = 8 / 16 / 32 / 64 / 128 / 256 / 1000: 251 / 248 / 246 / 248 / 385 / 745 / 3010 -> 81 / 84 / 96 /
@@ -318,14 +329,9 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   const float v = live ? __builtin_nontemporal_load(job.val + e) : 0.f;
   int32_t r = -1;
   bool start = true, next_same;     // the entry is the first of its row; the row of the tile's last entry goes on behind it
-  int2 b;                           // parents of the last entry before the tile (of its first one, if there is none) and of its last one
+  int2 b0, b1;                      // parents of the entries around the tile's ends (at an end of the list the one inside)
   if constexpr (SEARCH) {
     s_mark[threadIdx.x] = 0;
-    if (job.bounds) {
-      const int2 b1 = job.bounds[tile + 1];
-      b = make_int2(job.bounds[tile].x, b1.x);
-      next_same = t1 < n && b1.x == b1.y;
-    }
   } else {
     if (live) r = job.row[e];
     if (live && e > 0) start = job.row[e - 1] != r;
@@ -336,34 +342,35 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   const char *X = reinterpret_cast<const char *>(job.X);
   char *Y = reinterpret_cast<char *>(job.Y);
   const auto xo = Walk::offset(c, job.ldx);
-  // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an entry's
-  // row is the last mark up to it
-  auto look_up = [&]() {
-    if (!job.bounds) {
-      b = find_parents(job.ptr, (uint32_t)job.nparents, t0 > 0 ? t0 - 1 : 0, t1 - 1);
-      next_same = t1 < n && (uint32_t)job.ptr[b.y + 1] > t1;
-    }
-    if (b.y - b.x > PS_FAR) {
-      const uint32_t p = find_parent(job.ptr, b.x, b.y, e, live, s_mark);
+  auto get_bounds = [&]() {
+    if (job.bounds) { b0 = job.bounds[tile]; b1 = job.bounds[tile + 1]; return; }
+    const int2 p = find_parents(job.ptr, (uint32_t)job.nparents, t0 > 0 ? t0 - 1 : 0, t1 - 1, s_last);
+    b0.x = p.x;
+    b1 = make_int2(p.y, t1 < n && (uint32_t)job.ptr[p.y + 1] <= t1 ? -1 : p.y);
+  };
+  if constexpr (SEARCH && H > 1) get_bounds();   // (behind the gathers the search takes more registers than these shapes have left)
+  walk.first_gathers(X, xo);
+  if constexpr (SEARCH) {
+    if constexpr (H == 1) get_bounds();
+    next_same = t1 < n && b1.x == b1.y;
+    // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an
+    // entry's row is the last mark up to it
+    if (b1.x - b0.x > PS_FAR) {
+      const uint32_t p = find_parent(job.ptr, b0.x, b1.x, e, live, s_mark);
       const bool first = live && (uint32_t)job.ptr[p] == e;
       __syncthreads();
       s_mark[threadIdx.x] = first ? p : 0;
-    }
-  };
-  if constexpr (SEARCH && H > 1) look_up();   // (behind the gathers it takes more registers than these shapes have left)
-  walk.first_gathers(X, xo);
-  if constexpr (SEARCH) {
-    if constexpr (H == 1) look_up();
-    if (b.y - b.x <= PS_FAR) {
+      if constexpr (H > 1) walk.first_gathers(X, xo);   // (once more: nothing of the first ones is held through the search)
+    } else {
       __syncthreads();
-      for (int32_t p = b.x + 1 + (int32_t)threadIdx.x; p <= b.y; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
+      for (int32_t p = b0.x + 1 + (int32_t)threadIdx.x; p <= b1.x; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
     }
     __syncthreads();
     const uint32_t mark = s_mark[threadIdx.x];
     uint32_t last = wave_inclusive_max_dpp(mark);
     if (lane == 63) s_last[w] = last;
     __syncthreads();
-    last = max(last, (uint32_t)b.x);
+    last = max(last, (uint32_t)b0.x);
 #pragma unroll
     for (int q = 0; q < PS_WAVES - 1; ++q)
       if (q < w) last = max(last, s_last[q]);
@@ -590,10 +597,11 @@ void panel_spmm(Env &env, const us_formatted &A, const int32_t *row, const Store
   //   times (50,000 of 8,000 rows, N = 1000 42.9 / 48.8).
   // - What is left of the columns beyond whole panels is one more panel of the same launch, and not a launch of its own, up to 1024
   //   workgroups; 2048 where Y is added to, which hides the idle lanes.  Rest apart -> this, us: 20,000 entries of 8,000 rows, N = 300
-  //   31 -> 17, N = 1000 44 -> 27; 150,000 of 8,000 / 2 M, added, N = 300 45 -> 37, 186 -> 150; 400,000 of 200,000, added, 219 -> 193;
+  //   31 -> 17, N = 1000 44 -> 27; 150,000 of 8,000 / 2 M, added, N = 300 45 -> 38, 186 -> 148; 400,000 of 200,000, added, 219 -> 193;
   //   but 1 M of 100,000, not added, 227 -> 248.
   // - Up to 1024 workgroups each finds its parents itself, some 3 us, where a launch of its own for the table of all takes 14: 50,000
-  //   entries of 5,000 rows, N = 1 16.5 -> 13.5, 150,000 of 2 M 31 -> 23; but 1 M of 100,000 (1,954 workgroups) 25.0 -> 28.2.
+  //   entries of 5,000 rows, N = 1 16.5 -> 12.0, 150,000 of 2 M 31 -> 21; beyond, where more rounds of workgroups pay for it, it depends on
+  //   how many rows there are: 1 M (1,954 workgroups) of 2 M rows 47 -> 44, of 8,000, N = 64 26.5 -> 29.1.
   constexpr int64_t RESIDENT = 512;
   const bool whole_lines = (uintptr_t)X % 128 == 0 && ldx % 32 == 0;
   const bool narrow = whole_lines || tiles * ceil_div<int64_t>(N, 64) <= (N <= 256 ? RESIDENT : rows ? RESIDENT / 2 : 4 * RESIDENT);

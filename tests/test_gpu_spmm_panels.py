@@ -116,7 +116,7 @@ def test_few_entries_around_the_longest_walk(ctx, last):
     check(ctx, spread(np.concatenate([[0, 0], inner, [last]]), rng), 17, 17, 17, 0, rng, f"700 entries of {last + 1} rows")
 
 
-@pytest.mark.parametrize("rows,per_row,gap,N", [(25_000, 6, 30_000, 3), (25_000, 6, 30_000, 100), (25_000, 6, 30_000, 130), (30_000, 18, 5_000, 1),
+@pytest.mark.parametrize("rows,per_row,gap,N", [(25_000, 6, 30_000, 3), (25_000, 6, 30_000, 100), (25_000, 6, 30_000, 130), (30_000, 18, 5_000, 1), (60_000, 18, 5_000, 1),
                                                 (6_000, 90, 4_500, 300)])
 def test_gaps_inside_tiles_of_long_lists(ctx, rows, per_row, gap, N):
     rng = np.random.default_rng(rows + N)
@@ -134,7 +134,7 @@ def test_columns_of_long_lists(ctx, N, ldx):
 
 # tiles * panels on both sides of what is resident at once (512), half, twice and four times as much
 @pytest.mark.parametrize("entries,N", [(512 * 256, 100), (512 * 256 + 1, 100), (512 * 51, 300), (512 * 51 + 1, 300), (512 * 204, 300), (512 * 205, 300),
-                                       (512 * 512, 300), (512 * 512 + 1, 300), (512 * 1024, 30), (512 * 1024 + 1, 30)])
+                                       (512 * 512, 300), (512 * 512 + 1, 300), (512 * 1024, 30), (512 * 1024 + 1, 30), (512 * 2048, 5), (512 * 2048 + 1, 5)])
 def test_lists_around_the_short_ones(ctx, entries, N):
     rng = np.random.default_rng(entries)
     check(ctx, spread(np.sort(rng.integers(0, 20_000, entries)), rng), N, N, N, 0, rng, f"{entries} entries N={N}")

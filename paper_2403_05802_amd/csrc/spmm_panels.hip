@@ -342,26 +342,29 @@ __global__ __launch_bounds__(PS_T, VEC * H <= 2 ? 8 : H == 1 ? 5 : 4) void panel
   const char *X = reinterpret_cast<const char *>(job.X);
   char *Y = reinterpret_cast<char *>(job.Y);
   const auto xo = Walk::offset(c, job.ldx);
-  auto get_bounds = [&]() {
-    if (job.bounds) { b0 = job.bounds[tile]; b1 = job.bounds[tile + 1]; return; }
-    const int2 p = find_parents(job.ptr, (uint32_t)job.nparents, t0 > 0 ? t0 - 1 : 0, t1 - 1, s_last);
-    b0.x = p.x;
-    b1 = make_int2(p.y, t1 < n && (uint32_t)job.ptr[p.y + 1] <= t1 ? -1 : p.y);
-  };
-  if constexpr (SEARCH && H > 1) get_bounds();   // (behind the gathers the search takes more registers than these shapes have left)
-  walk.first_gathers(X, xo);
-  if constexpr (SEARCH) {
-    if constexpr (H == 1) get_bounds();
-    next_same = t1 < n && b1.x == b1.y;
-    // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an
-    // entry's row is the last mark up to it
+  // rows that begin in the tile mark their first entries (of rows that begin at the same entry the last one has entries); an entry's
+  // row is the last mark up to it
+  auto look_up = [&]() {
+    if (job.bounds) {
+      b0 = job.bounds[tile]; b1 = job.bounds[tile + 1];
+    } else {
+      const int2 p = find_parents(job.ptr, (uint32_t)job.nparents, t0 > 0 ? t0 - 1 : 0, t1 - 1, s_last);
+      b0.x = p.x;
+      b1 = make_int2(p.y, t1 < n && (uint32_t)job.ptr[p.y + 1] <= t1 ? -1 : p.y);
+    }
     if (b1.x - b0.x > PS_FAR) {
       const uint32_t p = find_parent(job.ptr, b0.x, b1.x, e, live, s_mark);
       const bool first = live && (uint32_t)job.ptr[p] == e;
       __syncthreads();
       s_mark[threadIdx.x] = first ? p : 0;
-      if constexpr (H > 1) walk.first_gathers(X, xo);   // (once more: nothing of the first ones is held through the search)
-    } else {
+    }
+  };
+  if constexpr (SEARCH && H > 1) look_up();   // (behind the gathers it takes more registers than these shapes have left)
+  walk.first_gathers(X, xo);
+  if constexpr (SEARCH) {
+    if constexpr (H == 1) look_up();
+    next_same = t1 < n && b1.x == b1.y;
+    if (b1.x - b0.x <= PS_FAR) {
       __syncthreads();
       for (int32_t p = b0.x + 1 + (int32_t)threadIdx.x; p <= b1.x; p += PS_T) atomicMax(&s_mark[(uint32_t)job.ptr[p] - t0], (uint32_t)p);
     }
